@@ -141,7 +141,7 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                the block boundaries; even, >= 2 (default 1000 when 0);
  *   strip_rows   rows per wavefront strip of the sweep, also of the
  *                two-step sweep below (0: tuned default; the two-step
- *                default fills whole rounds of resident strips). While
+ *                default fills whole rounds of resident strips; not used by the boxes of steps_per_sweep). While
  *                the active channels make fewer one-step strips than the
  *                GPU has SIMDs, their heights are divided alike (down to
  *                4 rows, or a narrow kernel's row group) to spread them
@@ -188,11 +188,17 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                steps per pass over the state (a
  *                strip's rows of step t are kept on chip for step t+1);
  *                without the viscoelastic option the narrow channels (width
- *                1, 2, 4, ..., 64) without pressure_gradient do too;
- *                other channels, other handles and steps outside whole
- *                blocks run one step per pass. Each node update is the
- *                arithmetic of the one-step pass; states agree with it to
- *                round-off; 1: one step per pass always.
+ *                1, 2, 4, ..., 64) without pressure_gradient do too.
+ *                Handles whose channels of a width class hold few nodes
+ *                (about a million and less, any K; not with stress_force or
+ *                pressure_gradient) advance them more steps per pass
+ *                instead, in boxes of nodes whose state stays on chip for a
+ *                divisor of K / 2 steps, also in the steps outside whole
+ *                blocks when every active channel does. Other channels,
+ *                other handles and steps outside whole blocks run one step
+ *                per pass. Each node update is the arithmetic of the
+ *                one-step pass; states agree with it to round-off; 1: one
+ *                step per pass always.
  */
 typedef struct {
   int32_t precision;

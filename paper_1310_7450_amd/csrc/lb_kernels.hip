@@ -263,6 +263,20 @@ __device__ __forceinline__ double group_sum(double v) {
   return v;
 }
 
+// a * b, never contracted with what uses it.
+template <typename T>
+__device__ __forceinline__ T rounded_product(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+// a * b + c rounded once.
+template <typename T>
+__device__ __forceinline__ T fused(T a, T b, T c) {
+  if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
+  return __builtin_fma(a, b, c);
+}
+
 // Channel constants in the arithmetic type.
 template <typename T>
 struct Coef {
@@ -340,15 +354,17 @@ __device__ __forceinline__ void node_update(const T f[9], T sd, T mx, T my, T Pc
     // relaxation implicit, sigma' = [sigma + kappa sigma + sigma kappa^T +
     // G D] / (1 + 1/tau_M), written as sigma plus its increment so that FP32
     // rounds only the increment.
+    // (explicit fused operations: sums of two products, which the compiler
+    // may contract either way, round alike in every kernel)
     const T II = T(0.5) * (Dxx * Dxx + T(2) * Dxy * Dxy + Dyy * Dyy);
     const T rate = q.inv_tau + root(II) * q.inv_gc;  // 1 / tau_M
     const T d = recip<T>(T(1) + rate);
-    const T cxx = T(2) * (kxx * sp[0] + kxy * sp[1]);
-    const T cxy = kxx * sp[1] + kxy * sp[2] + kyx * sp[0] + kyy * sp[1];
-    const T cyy = T(2) * (kyx * sp[1] + kyy * sp[2]);
-    sxx = sp[0] + (cxx + q.G * Dxx - rate * sp[0]) * d;
-    sxy = sp[1] + (cxy + q.G * Dxy - rate * sp[1]) * d;
-    syy = sp[2] + (cyy + q.G * Dyy - rate * sp[2]) * d;
+    const T cxx = fused(kxx, sp[0], rounded_product(kxy, sp[1]));
+    const T cyy = fused(kyx, sp[1], rounded_product(kyy, sp[2]));
+    const T cxy = fused(kxx, sp[1], fused(kxy, sp[2], fused(kyx, sp[0], rounded_product(kyy, sp[1]))));
+    sxx = fused(fused(-rate, sp[0], fused(q.G, Dxx, rounded_product(T(2), cxx))), d, sp[0]);
+    sxy = fused(fused(-rate, sp[1], fused(q.G, Dxy, cxy)), d, sp[1]);
+    syy = fused(fused(-rate, sp[2], fused(q.G, Dyy, rounded_product(T(2), cyy))), d, sp[2]);
     sn[0] = sxx;
     sn[1] = sxy;
     sn[2] = syy;
@@ -415,7 +431,9 @@ __device__ __forceinline__ void node_update(const T f[9], T sd, T mx, T my, T Pc
     }
     const T E4 = SHIFT ? T(4.5) * q.om : T(0);  // (c.du)(c.(u+ur)), even
     const T B3 = SHIFT ? T(3) * q.om : T(0);    // c.du, odd
-    const T Ccf = T(3) * q.kf * fx;             // 3 kf (c.f) for c_x = 1, odd
+    // rounded by itself, also where it is not constant over a kernel's loop (a
+    // node's result does not depend on the kernel it falls to)
+    const T Ccf = rounded_product(T(3) * q.kf, fx);  // 3 kf (c.f) for c_x = 1, odd
     const T Dcf = T(9) * q.kf * fx;             // 9 kf (c.u)(c.f) for c_x = 1, even
     const T spS = q.sp * Sxx, spT = T(2) * q.sp * Txy;
     const T usx = ux + ur;                      // (u + ur)_x (ur = 0 without SHIFT)
@@ -890,6 +908,172 @@ __global__ void __launch_bounds__(128) sweep_narrow2_kernel(SweepArgs a) {
       if (bnext < nB && j == jB(bnext)) group(bnext++);
     }
     __syncthreads();
+  }
+}
+
+// Many steps per launch for small lattices: one workgroup takes a box of
+// nodes [x0, x1) x [y0, y1) of one channel through S steps with the state in
+// LDS. It loads the box and a halo of 2 S nodes around it (clipped at the
+// walls; a box of the channel's whole width needs no columns beyond it), one
+// node per thread, and each step consumes two nodes of the halo: a step's
+// u~ needs the populations one node further out, and its stencil u~ another.
+// Per step a node's thread pulls its nine populations from LDS, forms u~ into
+// LDS, and after a barrier takes its four stencil velocities, updates the node
+// and writes its populations back in place (every pull of the step is done
+// by then); a second barrier ends the step. The trace, the stress of the
+// viscoelastic model, the pull addresses and the row references' shifts are
+// node-local and stay in registers for the whole launch. The last step
+// stores the box. Per node the arithmetic is that of the one-step sweeps.
+//
+// Small lattices are bound by latency: a launch of one or two steps costs
+// 4 to 10 us whatever it computes. Here a step costs its chain of two LDS
+// exchanges and the node update, about 0.9 us at one wavefront per SIMD and
+// 1.05 at two (FP64 1.0 and 1.4): one 8 x 64 channel 1.05 us per step against
+// 4.7 at two steps per launch. With every CU full (256 ragged channels, 80
+// VGPRs, six wavefronts per SIMD in FP32) it issues VALU work about two
+// thirds of the time: 5.3 us per step against 13.2.
+template <typename T, bool VE, int TH>
+__global__ void __launch_bounds__(TH, sizeof(T) == 4 ? 6 : 4) sweep_block_kernel(SweepArgs a, int S) {
+  constexpr bool SHIFT = sizeof(T) == 4;
+  // planes of TH values: the populations at P(i), u~ at U and V, placed so
+  // that the pull addresses of populations 2 and 4 also address u~ of the
+  // rows below and above (a wall row's read another plane and are not used)
+  __shared__ T l[11 * TH];
+  constexpr int U = 2 * TH, V = 3 * TH;
+  auto P = [](int i) __attribute__((always_inline)) { return (i < 2 ? i : (i == 2 ? 4 : (i == 4 ? 5 : (i == 3 ? 6 : i + 2)))) * TH; };
+  const Strip st = a.strips[xcd_item(blockIdx.x, a.n_wg)];
+  const ChanDev c = a.ch[st.ch];
+  const int nx = c.nx, ny = c.ny, halo = 2 * S;
+  const Coef<T> q(c);
+  // the region: the box and its halo
+  const bool whole = st.x1 - st.x0 >= nx;
+  const int cx0 = whole ? 0 : st.x0 - halo, cw = whole ? nx : st.x1 - st.x0 + 2 * halo;
+  const int ry0 = st.y0 - halo < 0 ? 0 : st.y0 - halo, ry1 = st.y1 + halo > ny ? ny : st.y1 + halo;
+  const int rows = ry1 - ry0;
+  const bool in = (int)threadIdx.x < rows * cw;  // (the host keeps rows * cw <= TH)
+  const int n = in ? threadIdx.x : 0;
+  // nodes row by row, or column by column where only columns are cut: the
+  // halo is then at both ends of the node order, and whole wavefronts drop
+  // out of the later steps
+  const bool by_col = !whole && rows == ny;
+  const int sx = by_col ? rows : 1, sy = by_col ? 1 : cw;
+  const int major = n / (by_col ? rows : cw), minor = n - major * (by_col ? rows : cw);
+  const int r = by_col ? minor : major, cc = by_col ? major : minor, y = ry0 + r;
+  int x = cx0 + cc;
+  if (!whole) {
+    x %= nx;
+    x += x < 0 ? nx : 0;
+  }
+  const bool bot = y == 0, top = y == ny - 1;
+  // neighbours inside the region (at its cut edges the node itself: what
+  // they lead to is outside the part of the region still valid)
+  const int il = cc > 0 ? n - sx : (whole ? n + cw - 1 : n), ir = cc < cw - 1 ? n + sx : (whole ? n - (cw - 1) : n);
+  const int od = r > 0 ? -sy : 0, ou = r < rows - 1 ? sy : 0;
+  const int i2 = bot ? P(4) + n : P(2) + n + od, i4 = top ? P(2) + n : P(4) + n + ou;
+  const int i5 = bot ? P(7) + n : P(5) + il + od, i6 = bot ? P(8) + n : P(6) + ir + od;
+  const int i7 = top ? P(5) + n : P(7) + ir + ou, i8 = top ? P(6) + n : P(8) + il + ou;
+  // the channel's own slots, 32-bit (the host keeps nx * ny small enough)
+  const unsigned o = (unsigned)y * nx + x;
+  const unsigned o0 = lslot(0, o), oS = ((o >> 6) * kStressPlanes) * kTile + (o & (kTile - 1));
+  const T *__restrict__ A = static_cast<const T *>(a.A) + c.off * kPlanes + o0;
+  T Pc = T(0), sg[3] = {T(0), T(0), T(0)};
+  if (in) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) l[P(i) + n] = A[i * kTile];
+    Pc = A[9 * kTile];
+    if constexpr (VE) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) sg[p] = static_cast<const T *>(a.SA)[c.off * kStressPlanes + oS + p * kTile];
+    }
+  }
+  // FP32: the row's reference and what to_row_reference adds to each pulled
+  // population
+  T urc = T(0), urd = T(0), uru = T(0), sh[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+  if constexpr (SHIFT) {
+    const float *ur = a.uref + c.row_off;
+    urc = ur[y];
+    urd = ur[bot ? y : y - 1];
+    uru = ur[top ? y : y + 1];
+    to_row_reference(sh, urd, urc, uru, bot, top);
+    if (bot) urd = -urc;
+  }
+  // position in the box, for the part of the region a step still updates
+  const int ylo = st.y0 - y, yhi = y - (st.y1 - 1);              // > 0 outside the box
+  const int xlo = whole ? 0 : halo - cc, xhi = whole ? 0 : cc - (cw - 1 - halo);
+  const int out_by = max(max(ylo, yhi), max(xlo, xhi));          // distance outside the box (<= 0: inside)
+  __syncthreads();
+#pragma unroll 1
+  for (int s = 0; s < S; ++s) {
+    const long long t = c.t + a.k + s;
+    const T fx = (t < c.t_startup) ? T(c.g) : T(0);
+    const T uwg = (t < c.t_startup) ? T(c.uw) : T(0);
+    const T uw6 = (!c.zh && t >= 1 && t - 1 < c.t_startup) ? T(c.uw / 6.0) : T(0);
+    const int reach = 2 * (S - 1 - s);  // this step updates the box and `reach` nodes around it
+    T f[9], sd, mx, my;
+    U2<T> uc;
+    if (in && out_by <= reach + 1) {
+      f[0] = l[P(0) + n];
+      f[1] = l[P(1) + il];
+      f[3] = l[P(3) + ir];
+      f[2] = l[i2];
+      f[5] = l[i5];
+      f[6] = l[i6];
+      f[4] = l[i4];
+      f[7] = l[i7] - (top ? uw6 : T(0));
+      f[8] = l[i8] + (top ? uw6 : T(0));
+      if constexpr (SHIFT) {
+#pragma clang fp contract(off)
+        f[2] += sh[2];
+        f[5] += sh[5];
+        f[6] += sh[6];
+        f[4] += sh[4];
+        f[7] += sh[7];
+        f[8] += sh[8];
+      }
+      if (c.zh && top) zou_he_top<T, SHIFT>(f, uwg, urc, fx);
+      moments<T>(f, sd, mx, my);
+      uc = u_tilde<T, SHIFT>(sd, mx, my, fx, urc);
+      l[U + n] = uc.x;
+      l[V + n] = uc.y;
+    }
+    __syncthreads();
+    if (in && out_by <= reach) {
+      const U2<T> lf{l[U + il], l[V + il]}, rt{l[U + ir], l[V + ir]};
+      U2<T> dn{l[U - P(2) + i2], l[V - P(2) + i2]}, up{l[U - P(4) + i4], l[V - P(4) + i4]};
+      if (bot) dn = U2<T>{-uc.x, -uc.y};
+      T kref = T(0);
+      if (top) {
+        const U2<T> m = c.zh ? dn : uc;
+        up = U2<T>{(SHIFT ? T(0) : T(2) * uwg) - m.x, -m.y};
+      }
+      if constexpr (SHIFT) {
+        const T urt = top ? T(2) * uwg - (c.zh ? urd : urc) : uru;
+        kref = T(0.5) * (urt - urd);
+      }
+      T out[9], trT, sn[3];
+      double obs[OF_COUNT];
+      node_update<T, SHIFT, false, VE>(f, sd, mx, my, Pc, fx, lf, rt, dn, up, urc, kref, q, c.nnp, sg, sn, out, trT,
+                                       obs);
+      Pc = trT;
+      if constexpr (VE) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) sg[p] = sn[p];
+      }
+      if (s < S - 1) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) l[P(i) + n] = out[i];
+      } else {
+        T *__restrict__ B = static_cast<T *>(a.B) + c.off * kPlanes + o0;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) B[i * kTile] = out[i];
+        B[9 * kTile] = trT;
+        if constexpr (VE) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) static_cast<T *>(a.SB)[c.off * kStressPlanes + oS + p * kTile] = sn[p];
+        }
+      }
+    }
+    if (s < S - 1) __syncthreads();
   }
 }
 
@@ -2827,6 +3011,25 @@ hipError_t launch_tiles(const SweepArgs &a, hipStream_t s) {
     else hipLaunchKernelGGL((sweep_tile_kernel<false, false>), grid, block, 0, s, a);
   }
   return hipGetLastError();
+}
+
+template <typename T, bool VE>
+hipError_t launch_block_t(int threads, const SweepArgs &a, int S, hipStream_t s) {
+  const dim3 grid(a.n_wg), block(threads);
+  switch (threads) {
+    case 256: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 256>), grid, block, 0, s, a, S); break;
+    case 512: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 512>), grid, block, 0, s, a, S); break;
+    case 1024: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 1024>), grid, block, 0, s, a, S); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_blocks(bool fp32, int threads, const SweepArgs &a, int S, hipStream_t s) {
+  if (a.n_strips == 0) return hipSuccess;
+  if (a.ve && (!a.SA || !a.SB)) return hipErrorInvalidValue;
+  if (fp32) return a.ve ? launch_block_t<float, true>(threads, a, S, s) : launch_block_t<float, false>(threads, a, S, s);
+  return a.ve ? launch_block_t<double, true>(threads, a, S, s) : launch_block_t<double, false>(threads, a, S, s);
 }
 
 hipError_t launch_reduce(const ChanDev *ch, int n_ch, const double *part, double *prof,

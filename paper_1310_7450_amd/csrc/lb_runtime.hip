@@ -57,9 +57,11 @@ struct Layout {
   // two steps per launch: strips of the other channels for captured blocks
   // (and their reverse), and the two-step strips
   size_t off_bstrips = 0, off_brstrips = 0, off_tstrips = 0;
+  size_t off_blk = 0;     // boxes of the channels that run many steps per launch
   size_t off_btiles = 0;  // tiles of the tiled channels without two-step strips
   int strip_cap = 0;      // entries of each one-step strip list
   int max_two = 0;
+  long long max_boxes = 0;
   std::vector<ChanDev> ch;
 };
 
@@ -220,6 +222,45 @@ bool two_step_channel(const lb_channel &c, int esize) {
 bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize) {
   return !o->viscoelastic && !is_strip_class(width_class(c.nx, esize)) && c.pressure_gradient == 0;
 }
+// Channels whose steps run in boxes, many per launch (sweep_block_kernel):
+// without the pressure drive, with either stress model and any top wall,
+// while the handle's channels of the same kind hold few enough nodes. A small
+// lattice is bound by the latency of its launches, which boxes take once for
+// several steps; a large one by instruction issue, of which the boxes' halos
+// cost more than the halos of strips. Measured, us per step, boxes against
+// the path they replace:
+//  * aligned widths (vector class; two steps per launch): FP32 512 x 512 7.3
+//    against 20.2, 1024 x 1024 21.3 / 27.0, 2048 x 1024 41.1 / 34.4; FP64
+//    1536 x 512 27.2 / 31.7, 1024 x 1024 34.2 / 32.1; FP64 time-integrated
+//    1024 x 512 19.4 / 23.7, 1536 x 512 29.3 / 24.1;
+//  * other widths above 64: FP32 (one step per launch) 200 x 20 1.9 / 14.3,
+//    1000 x 300 8.8 / 21.3, 4000 x 2000 180 / 210; FP64 (tiles) 200 x 20
+//    1.9 / 6.2, 1000 x 300 11.4 / 12.2, 1000 x 500 18.0 / 16.6, but
+//    time-integrated 4000 x 2000 278 / 309;
+//  * narrow widths, whose boxes need no columns beside them: 8 x 64 1.1 / 4.7
+//    (FP64 1.4 / 3.9), 256 ragged channels of 8 columns 5.3 / 13.2 (8.5 /
+//    22.1), 8 x 262144 27.7 / 48.1; from 32 columns on a box holds few rows:
+//    64 x 8192 12.8 / 15.7 (FP64 17.3 / 15.2), 64 x 65536 92 / 80.
+std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize) {
+  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, KINDS };
+  const bool fp32 = esize == 4, ve = o->viscoelastic;
+  const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
+  const long long limit[KINDS] = {fp32 ? M + M / 4 : (ve ? 5 * M / 8 : 3 * M / 4), (fp32 || ve) ? 8 * M : 3 * M / 10,
+                                  always, ve ? always : (fp32 ? M : M / 4)};
+  std::vector<int> kind(n, -1);
+  long long nodes[KINDS] = {};
+  for (int i = 0; i < n; ++i) {
+    if (o->steps_per_sweep == 1 || o->stress_force || c[i].pressure_gradient != 0) continue;
+    const size_t N = (size_t)c[i].nx * c[i].ny;
+    if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
+    const int cls = width_class(c[i].nx, esize);
+    kind[i] = cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
+    nodes[kind[i]] += (long long)N;
+  }
+  std::vector<char> ok(n, 0);
+  for (int i = 0; i < n; ++i) ok[i] = kind[i] >= 0 && nodes[kind[i]] <= limit[kind[i]];
+  return ok;
+}
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
 // Stored columns of the two-step strips of a width at npl nodes per lane:
 // at most two_step_cols(npl) (248 at four, 124 at two), in multiples of
@@ -295,6 +336,111 @@ int narrow_two_step_rows(const std::vector<lb_channel> &chans, long long slots, 
     last_fit = R;
   }
   return last_fit > 0 ? last_fit : 1 << 30;
+}
+// Many steps per launch on boxes (sweep_block_kernel): the box shape of one
+// channel and the launch's steps and threads.
+struct BoxShape {
+  int ow, oh;  // box width and height
+};
+struct BoxPlan {
+  int S = 0, threads = 0;  // S = 0: no plan
+  std::vector<BoxShape> shape;
+};
+// Largest boxes whose region (box and a halo of 2 S nodes, clipped at the
+// walls; none across a box of the whole width) holds at most cap nodes: the
+// whole width if that fits, all rows, or cut both ways, whichever repeats the
+// fewest halo nodes. False if not even one node fits.
+bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
+  const int h = 4 * S;  // halo nodes in one direction, both sides
+  double eff = 0;
+  auto even = [](int n, int w) { return (n + (n + w - 1) / w - 1) / ((n + w - 1) / w); };
+  auto offer = [&](int ow, int oh) {
+    if (ow < 1 || oh < 1) return;
+    ow = even(c.nx, std::min(ow, c.nx));
+    oh = even(c.ny, std::min(oh, c.ny));
+    const long long cw = ow >= c.nx ? c.nx : ow + h, rh = oh >= c.ny ? c.ny : std::min(oh + h, c.ny);
+    if (cw * rh > cap) return;
+    const double e = (double)ow * oh / (double)(cw * rh);
+    if (e > eff) {
+      eff = e;
+      best = BoxShape{ow, oh};
+    }
+  };
+  if (c.nx <= cap) {
+    if ((long long)c.nx * c.ny <= cap) offer(c.nx, c.ny);
+    offer(c.nx, cap / c.nx - h);
+  }
+  if (c.nx <= 64) return eff > 0;  // cutting such a row only adds halo
+  if (c.ny <= cap) offer(cap / c.ny - h, c.ny);
+  for (int ow = 4; ow + h <= cap; ow += (ow < 32 ? 4 : 16)) offer(ow, cap / (ow + h) - h);
+  return eff > 0;
+}
+// wavefronts of a region at work in step s of S (see the kernel's node order)
+int box_waves(const lb_channel &c, BoxShape b, int S, int s) {
+  const int reach = 2 * (S - 1 - s) + 1;
+  const bool whole = b.ow >= c.nx;
+  const int cw = whole ? c.nx : b.ow + 4 * S;
+  const int rows = std::min(b.oh + 2 * reach, c.ny);
+  if (!whole && std::min(b.oh + 4 * S, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
+  return (rows * cw + 63) / 64;
+}
+void add_boxes(int ci, const lb_channel &c, BoxShape b, std::vector<Strip> &out) {
+  for (int y0 = 0; y0 < c.ny; y0 += b.oh)
+    for (int x0 = 0; x0 < c.nx; x0 += b.ow)
+      out.push_back(Strip{ci, x0, y0, std::min(y0 + b.oh, c.ny), 0, std::min(x0 + b.ow, c.nx)});
+}
+long long box_count(const lb_channel &c, BoxShape b) {
+  return (long long)((c.nx + b.ow - 1) / b.ow) * ((c.ny + b.oh - 1) / b.oh);
+}
+// The plan of least estimated time per step. A launch takes, in us,
+// launch + rounds (start + S (step + wave v m)) + (S busy V + load R) / CUs
+// for its rounds of resident workgroups, v wavefronts per SIMD of the largest
+// box at work, m boxes sharing a CU, V wavefronts at work and R wavefronts of
+// the regions in all; part/8 of the threads hold the largest region. The constants are fitted to 700 launches (one 8 x 64
+// channel to 1024 x 512 nodes and 256 ragged 8-wide channels, S 1 to 20;
+// mean error 12% FP32, 9% FP64): the plan picked was within 6% of the best
+// measured one in every case. S divides K / 2, so that a captured block is
+// an even number of launches and leaves the state in its buffer.
+BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int cus, long long room) {
+  BoxPlan best;
+  double best_us = 1e300;
+  const double launch = fp32 ? 2.7 : 2.0, start = fp32 ? 0.13 : 0.63, step = fp32 ? 0.38 : 0.59,
+               wave = fp32 ? 0.29 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
+  for (int S = 1; S <= K / 2 && S <= 64; ++S) {  // (beyond 64 a launch's own time no longer counts)
+    if ((K / 2) % S) continue;
+    for (int th = 256; th <= 1024; th *= 2) {
+      const int resident = (fp32 ? 24 : 16) * 64 / th;  // workgroups of a CU, by registers
+      for (int part : {8, 6, 4, 3, 2}) {
+        BoxPlan p;
+        p.S = S;
+        p.threads = th;
+        double W = 0, R = 0, V = 0, vmax = 0;
+        bool ok = true;
+        for (const lb_channel &c : chans) {
+          BoxShape b;
+          if (!(ok = box_shape(c, S, th * part / 8, b))) break;
+          p.shape.push_back(b);
+          const double w = (double)box_count(c, b);
+          const int v0 = box_waves(c, b, S, 0);
+          const double v = 0.5 * (v0 + box_waves(c, b, S, S - 1));
+          W += w;
+          R += w * v0;
+          V += w * v;
+          vmax = std::max(vmax, v);
+        }
+        if (!ok || W > (double)room) continue;
+        const double slots = (double)resident * cus, rounds = std::ceil(W / slots);
+        const double m = W <= slots ? std::ceil(W / cus) : 1.3;
+        const double us =
+            (launch + rounds * (start + S * (step + wave * m * vmax / 4)) + (S * busy * V + load * R) / cus) / S;
+        if (us < best_us) {
+          best_us = us;
+          best = p;
+        }
+      }
+    }
+  }
+  return best;
 }
 void add_two_step_strips(int ci, const lb_channel &c, int npl, int H, std::vector<Strip> &out) {
   const std::vector<int> x = two_step_cuts(c.nx, npl);
@@ -404,6 +550,9 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
     if (two_step_channel(c[i], L.esize))
       L.max_two += (int)(two_step_cuts(c[i].nx, npl).size() - 1) * ((c[i].ny + min_rows - 1) / min_rows);
   L.off_btiles = take(sizeof(Strip) * std::max(L.n_tiles, 1));
+  // boxes of 64 nodes, or 4096 boxes and two per channel
+  L.max_boxes = std::max<long long>(4096 + 2ll * n, L.plane / 64);
+  L.off_blk = take(sizeof(Strip) * L.max_boxes);
   L.off_tstrips = take(sizeof(Strip) * std::max(L.max_two, 1));
   L.bytes = at;
   return L;
@@ -434,6 +583,12 @@ struct lb_handle {
   Strip *dbact = nullptr, *dbact_rev = nullptr;  // captured blocks: active channels without two-step strips
   Strip *dtwo = nullptr;                        // two-step strips of the active channels
   int bact_begin[kClasses] = {0}, bact_count[kClasses] = {0};
+  // captured blocks: the boxes of the channels that run blk_S steps per launch
+  Strip *dblk = nullptr;
+  int n_blk = 0, blk_S = 0, blk_threads = 0;
+  bool blk_only = false;       // every active channel runs in boxes
+  std::vector<char> blk_ok;    // channels whose captured steps run in boxes
+  int cus = 256;
   // captured blocks: the narrow two-step strips of each width, after the
   // others in dbact
   int n2_begin[kClasses] = {0}, n2_count[kClasses] = {0};
@@ -558,13 +713,41 @@ lb_status upload_strips(lb_handle *h, bool all) {
     }
     // captured blocks: two-step strips for the eligible active channels, the
     // one-step strips of the others
-    std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped;
+    std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped, boxes;
     bool wall = false;
-    if (h->two_step) {
+    h->blk_S = h->n_blk = 0;
+    h->blk_only = false;
+    {
+      std::vector<lb_channel> chans;
+      std::vector<int> ids;
+      bool others = false;
+      for (int i = 0; i < h->n_ch; ++i) {
+        if (!h->active[i]) continue;
+        if (h->blk_ok[i]) {
+          chans.push_back(h->in[i]);
+          ids.push_back(i);
+        } else {
+          others = true;
+        }
+      }
+      if (!ids.empty()) {
+        BoxPlan p = plan_boxes(chans, h->K, h->L.esize == 4, h->cus, h->L.max_boxes);
+        if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
+        for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], boxes);
+        if ((long long)boxes.size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
+        h->blk_S = p.S;
+        h->blk_threads = p.threads;
+        h->n_blk = (int)boxes.size();
+        h->blk_only = !others;
+        HIPCHECK(h, hipMemcpyAsync(h->dblk, boxes.data(), boxes.size() * sizeof(Strip), hipMemcpyHostToDevice,
+                                   h->stream));
+      }
+    }
+    if (h->two_step || h->blk_S) {
       const int es = h->L.esize;
       std::vector<lb_channel> elig, nelig;
       for (int i = 0; i < h->n_ch; ++i) {
-        if (!h->active[i]) continue;
+        if (!h->active[i] || h->blk_ok[i] || !h->two_step) continue;
         if (two_step_channel(h->in[i], es)) elig.push_back(h->in[i]);
         else if (narrow_two_step_channel(&h->opt, h->in[i], es)) nelig.push_back(h->in[i]);
       }
@@ -572,11 +755,11 @@ lb_status upload_strips(lb_handle *h, bool all) {
       const int H = h->opt.strip_rows > 0 ? std::min(h->opt.strip_rows, kTwoStepMaxRows)
                                           : two_step_rows(elig, npl, h->slots);
       for (int i = 0; i < h->n_ch; ++i) {
-        if (!h->active[i]) continue;
-        if (two_step_channel(h->in[i], es)) {
+        if (!h->active[i] || h->blk_ok[i]) continue;
+        if (h->two_step && two_step_channel(h->in[i], es)) {
           add_two_step_strips(i, h->in[i], npl, H, two);
           wall = wall || two_step_wall(h->in[i]);
-        } else if (!narrow_two_step_channel(&h->opt, h->in[i], es) && !tiled(&h->opt, h->in[i])) {
+        } else if (!(h->two_step && narrow_two_step_channel(&h->opt, h->in[i], es)) && !tiled(&h->opt, h->in[i])) {
           add_strips(i, h->L.ch[i], es, rows_of(i), stack, braw);
         }
       }
@@ -585,7 +768,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
         const int R2 = narrow_two_step_rows(nelig, h->n2slots, h->opt.strip_rows,
                                             h->L.strip_cap - (long long)braw.size());
         for (int i = 0; i < h->n_ch; ++i)
-          if (h->active[i] && narrow_two_step_channel(&h->opt, h->in[i], es))
+          if (h->active[i] && !h->blk_ok[i] && narrow_two_step_channel(&h->opt, h->in[i], es))
             add_strips(i, h->L.ch[i], es, narrow_rows(R2, h->in[i].nx), stack, n2raw);
       }
     }
@@ -670,6 +853,15 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
   return LB_OK;
 }
 
+// Enqueues S steps of every channel that runs in boxes (from buffer src, step
+// offset k).
+lb_status enqueue_boxes(lb_handle *h, int src, int k, int S, hipStream_t s) {
+  SweepArgs a = sweep_args(h, h->dblk, 0, h->n_blk, src, k);
+  a.n_wg = h->n_blk;  // one box per workgroup
+  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, h->blk_threads, a, S, s));
+  return LB_OK;
+}
+
 // The observation of the current state: per-row, per-strip partials into
 // part, then the per-channel reduction into prof and scal (and, with
 // update_residual, the residual history in the workspace).
@@ -708,11 +900,14 @@ lb_status capture(lb_handle *h, int src) {
   hipGraph_t g = nullptr;
   HIPCHECK(h, hipStreamBeginCapture(h->cap, hipStreamCaptureModeRelaxed));
   lb_status st = LB_OK;
-  if (h->two_step) {
+  if (h->two_step || h->blk_S) {
+    // the boxes: K / blk_S launches, an even number
+    for (int k = 0, j = 0; k < h->K && st == LB_OK && h->blk_S; k += h->blk_S, ++j)
+      st = enqueue_boxes(h, src ^ (j & 1), k, h->blk_S, h->cap);
     // pairs of steps: one two-step launch for the eligible channels (its
     // j-th launch reads buffer src ^ (j & 1) and writes the other one), and
     // the one-step launches of the others
-    for (int k = 0; k < h->K && st == LB_OK; k += 2) {
+    for (int k = 0; k < h->K && st == LB_OK && !h->blk_only; k += 2) {
       if (h->two_count) {
         SweepArgs a = sweep_args(h, h->dtwo, 0, h->two_count, src ^ ((k / 2) & 1), k);
         a.wall = h->two_wall;
@@ -978,6 +1173,7 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->dbact_rev = reinterpret_cast<Strip *>(h->ws + h->L.off_brstrips);
   h->dtwo = reinterpret_cast<Strip *>(h->ws + h->L.off_tstrips);
   h->btiles = reinterpret_cast<Strip *>(h->ws + h->L.off_btiles);
+  h->dblk = reinterpret_cast<Strip *>(h->ws + h->L.off_blk);
   h->two_step = false;
   for (int i = 0; i < n && two_step_handle(o, h->K); ++i)
     h->two_step = h->two_step || two_step_channel(c[i], h->L.esize) || narrow_two_step_channel(o, c[i], h->L.esize);
@@ -1029,14 +1225,26 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     h->slots = two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED, streamed(h->L), o->viscoelastic) *
                std::max(cus, 1);
     h->simds = 4 * std::max(cus, 1);
+    h->cus = std::max(cus, 1);
     h->n2slots = (long long)narrow_two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED) * std::max(cus, 1);
+  }
+  // channels whose captured steps run in boxes
+  h->blk_ok = block_channels(o, c, n, h->L.esize);
+  {
+    std::vector<lb_channel> chans;
+    for (int i = 0; i < n; ++i)
+      if (h->blk_ok[i]) chans.push_back(c[i]);
+    // (a plan for all is one for those still active later)
+    if (!chans.empty() && plan_boxes(chans, h->K, h->L.esize == 4, h->cus, h->L.max_boxes).S == 0)
+      h->blk_ok.assign(n, 0);
   }
   if (upload_strips(h, true) != LB_OK || upload_strips(h, false) != LB_OK) return bail(LB_EHIP);
   std::vector<Strip> tiles, btiles;  // kept until the synchronisation below
   for (int i = 0; i < n; ++i)
     if (tiled(o, c[i])) {
       add_tiles(i, c[i], tile_shape(o), tiles);
-      if (!h->two_step || !two_step_channel(c[i], h->L.esize)) add_tiles(i, c[i], tile_shape(o), btiles);
+      if (!h->blk_ok[i] && !(h->two_step && two_step_channel(c[i], h->L.esize)))
+        add_tiles(i, c[i], tile_shape(o), btiles);
     }
   if (!tiles.empty() && hipMemcpyAsync(h->tiles, tiles.data(), sizeof(Strip) * tiles.size(),
                                        hipMemcpyHostToDevice, h->stream) != hipSuccess)
@@ -1094,12 +1302,17 @@ lb_status lb_step(lb_handle *h, int64_t n) {
       m = h->K;
     } else {
       m = (int)std::min<int64_t>(left, h->K - h->since_block);
-      for (int k = 0; k < m; ++k) {
-        lb_status st = enqueue_step(h, h->cur ^ (k & 1), k, h->stream);
+      int launches = 0;
+      for (int k = 0; k < m; ++launches) {
+        // boxes hold the halo of up to blk_S steps
+        const int S = h->blk_only ? std::min(h->blk_S, m - k) : 1;
+        lb_status st = h->blk_only ? enqueue_boxes(h, h->cur ^ (launches & 1), k, S, h->stream)
+                                   : enqueue_step(h, h->cur ^ (launches & 1), k, h->stream);
         if (st != LB_OK) return st;
+        k += S;
       }
       HIPCHECK(h, launch_advance(h->dch, h->n_ch, m, h->stream));
-      h->cur ^= (m & 1);
+      h->cur ^= (launches & 1);
     }
     for (int i = 0; i < h->n_ch; ++i)
       if (h->active[i]) h->t[i] += m;

@@ -1,0 +1,106 @@
+"""Many steps per launch on boxes of nodes (small lattices) against one step
+per pass, bit for bit: every node update is the same arithmetic, so the box a
+node falls in, the steps a launch takes and the halo around it must not show.
+
+Shapes: one node, channels shorter and narrower than a halo, whole channels in
+one workgroup and just too large for one (1024 nodes), boxes cut by rows, by
+columns and both ways, the periodic wrap of a cut row, ragged last boxes, and
+every width class. The two-step kernels of the aligned widths, which larger
+lattices keep, are compared with one step per pass at sizes above the boxes'
+limits."""
+import numpy as np
+import pytest
+
+from paper_1310_7450_amd import workloads
+from paper_1310_7450_amd.lbnlm import ChannelSpec
+
+pytestmark = pytest.mark.gpu
+
+
+def spec(nx, ny, **kw):
+    base = dict(force=3e-6, tau_lb=0.8, G=2e-4, tau0=500.0, gamma_c=0.1, eps=0.01, visc_split=0.3, t_startup=13)
+    base.update(kw)
+    return ChannelSpec(nx=nx, ny=ny, **base)
+
+
+def run(chans, precision, obs_every, steps, steps_per_sweep, viscoelastic=False):
+    """States (and stresses) of every channel after the steps, from seeded
+    random states."""
+    from paper_1310_7450_amd import Solver
+    with Solver(chans, precision=precision, obs_every=obs_every, viscoelastic=viscoelastic,
+                steps_per_sweep=steps_per_sweep) as s:
+        for i, c in enumerate(chans):
+            s.set_state(i, *workloads.random_state(c.nx, c.ny, seed=31 * c.nx + c.ny + i), 0)
+            if viscoelastic:
+                s.set_stress(i, workloads.random_stress(c.nx, c.ny, seed=7 + i))
+        for n in steps:
+            s.step(n)
+        out = [s.get_state(i) + ((s.get_stress(i),) if viscoelastic else ()) for i in range(len(chans))]
+        assert all(s.observe(i, "step") == sum(steps) for i in range(len(chans)))
+    return out
+
+
+def assert_same(a, b, what):
+    for i, (x, y) in enumerate(zip(a, b)):
+        for p, q in zip(x, y):
+            assert np.isfinite(q).all() and np.array_equal(p, q), (what, i, np.abs(p - q).max())
+
+
+SHAPES = [(1, 1), (2, 3), (1, 1024), (1, 1025), (8, 128), (8, 129), (16, 7), (64, 16), (64, 90), (33, 31), (65, 2),
+          (100, 20), (128, 9), (200, 20), (203, 61), (256, 37), (320, 5), (1000, 30), (1024, 33)]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("nx,ny", SHAPES)
+def test_boxes_equal_one_step(precision, nx, ny):
+    """Whole blocks (K = 20: boxes of 1, 2, 5 or 10 steps; the force ends
+    inside one) and odd counts of steps off the block boundaries."""
+    for steps in ([40], [7, 13, 20, 3]):
+        a, b = (run([spec(nx, ny)], precision, 20, steps, sps) for sps in (0, 1))
+        assert_same(a, b, (precision, nx, ny, steps))
+
+
+@pytest.mark.parametrize("obs_every", [2, 6, 14, 100])
+def test_boxes_of_every_block_length(obs_every):
+    """Block lengths whose half has few divisors, or many."""
+    c = [spec(24, 40), spec(8, 50)]
+    a, b = (run(c, "fp64", obs_every, [2 * obs_every + 1], sps) for sps in (0, 1))
+    assert_same(a, b, obs_every)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("wall", [dict(wall_velocity=1e-3), dict(top_wall="zou_he", wall_velocity=1e-3,
+                                                                 nn_pressure=False)])
+@pytest.mark.parametrize("viscoelastic", [False, True])
+def test_boxes_walls_and_models(precision, wall, viscoelastic):
+    """Moving half-way and Zou-He tops (stopping inside a launch), with both
+    stress models, in a handle of ragged channels of several widths."""
+    c = [spec(8, 64, **wall), spec(200, 20, **wall), spec(1, 9), spec(256, 18, **wall), spec(130, 2, **wall)]
+    a, b = (run(c, precision, 20, [40, 9], sps, viscoelastic) for sps in (0, 1))
+    assert_same(a, b, (precision, wall, viscoelastic))
+
+
+def test_boxes_beside_other_channels():
+    """A handle that also holds a pressure-driven channel (one step per
+    pass inside the same blocks)."""
+    c = [spec(8, 40), spec(64, 12, force=0.0, pressure_gradient=1e-6, nn_pressure=False), spec(300, 11)]
+    a, b = (run(c, "fp64", 20, [40, 3], sps) for sps in (0, 1))
+    assert_same(a, b, "mixed")
+
+
+# (width, rows) above the boxes' limits; FP32 results of the two-step sweep
+# are those of one step per pass, FP64 ones agree to round-off amplified over
+# a few steps (2^-52 of the populations' size over a deviation of 1e-3: 1e-11)
+LARGE = {"fp32": [(1280, 1050), (256, 5203), (8192, 161)], "fp64": [(1024, 800), (64 * 13, 1001), (8192, 101)]}
+
+
+@pytest.mark.parametrize("viscoelastic", [False, True])
+@pytest.mark.parametrize("precision,nx,ny", [(p, *q) for p in LARGE for q in LARGE[p]])
+def test_large_two_step_equals_one_step(precision, nx, ny, viscoelastic):
+    c = [spec(nx, ny, wall_velocity=1e-3 if ny % 2 else 0.0)]
+    a, b = (run(c, precision, 8, [16, 1], sps, viscoelastic) for sps in (0, 1))
+    for p, q in zip(a[0], b[0]):
+        scale = np.abs(q - (workloads.REST_WEIGHTS[:, None, None] if q.shape[0] == 9 and q.ndim == 3 else 0)).max()
+        err = np.abs(p - q).max() / scale
+        print(f"{precision} {nx}x{ny} viscoelastic {viscoelastic}: {err:.2e}", flush=True)
+        assert err <= (2e-4 if precision == "fp32" else 1e-9 if q.ndim == 2 else 1e-11)
