@@ -49,7 +49,7 @@ struct ChanDev {
   double lgt;           // lambda G_inf tau
   double uw;            // top wall x velocity while t < t_startup
   double pd;            // pressure drive: p+ - p- = (nx + 1) G_p while t < t_startup
-  int gpbc;             // generalised periodic boundaries in x
+  int gpbc;             // generalised periodic boundaries in x: 1 by the column pass, 2 inside the step
   int nnp;              // keep the flow-induced density terms
   int zh;               // top wall: Zou-He velocity boundary on row ny - 1
 };
@@ -181,8 +181,9 @@ hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStre
 // boxes of every block channel in SweepArgs.strips (x0, x1, y0, y1), n_wg =
 // n_strips workgroups of `threads` (256, 512 or 1024) threads; a box and its
 // halo of 2 S nodes hold at most that many nodes. The state goes from A to B
-// over steps k .. k + S - 1.
-hipError_t launch_blocks(bool fp32, int threads, const SweepArgs &a, int S, hipStream_t s);
+// over steps k .. k + S - 1. With gpbc (S = 1), channels with the pressure
+// drive, whose inlet and outlet columns the launch changes too.
+hipError_t launch_blocks(bool fp32, bool gpbc, int threads, const SweepArgs &a, int S, hipStream_t s);
 // workgroups of the narrow two-step kernel one CU holds at once (the fewest
 // over the widths)
 int narrow_two_step_blocks_per_cu(bool fp32);

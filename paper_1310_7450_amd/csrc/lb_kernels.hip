@@ -911,6 +911,64 @@ __global__ void __launch_bounds__(128) sweep_narrow2_kernel(SweepArgs a) {
   }
 }
 
+// Generalised periodic boundaries (Sec. II.B), applied to the state a step
+// writes: a population that the next pull carries across the period (+x out
+// of the outlet column x = nx-1 into the inlet, -x out of the inlet column
+// into the outlet) becomes the equilibrium at the far end's density plus its
+// own non-equilibrium part. With the moments (rho, j) of its source node, a
+// density shift d = p+-/cs2 - mean column density adds
+// a_i [d + (4.5 (c.j)^2 - 1.5 j^2) (1/(rho + d) - 1/rho)]. Diagonal links
+// that meet a wall are reflected, not carried, and stay. f: a node's stored
+// populations (FP32: relative to the equilibrium at density 1 and the row's
+// reference velocity ur, which carries momentum); put(i, v) receives the three
+// that change.
+template <bool SHIFT, typename Put>
+__device__ __forceinline__ void gpbc_change(const double f[9], double ur, double d, bool outlet, int y, int ny,
+                                            Put put) {
+  double s = 0;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) s += f[i];
+  const double rho = SHIFT ? 1.0 + s : s;
+  const double jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]) + (SHIFT ? ur : 0.0);
+  const double jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
+  const double j2 = jx * jx + jy * jy, w = 1.0 / (rho + d) - 1.0 / rho;
+  auto change = [&](int i, double cx, int cy) __attribute__((always_inline)) {
+    if (y + cy < 0 || y + cy >= ny) return;  // met a wall: reflected
+    const double cj = cx * jx + cy * jy;
+    const double a = (i < 5) ? 1.0 / 9.0 : 1.0 / 36.0;
+    put(i, f[i] + a * (d + (4.5 * cj * cj - 1.5 * j2) * w));
+  };
+  if (outlet) {
+    change(1, 1.0, 0);
+    change(5, 1.0, 1);
+    change(8, 1.0, -1);
+  } else {
+    change(3, -1.0, 0);
+    change(6, -1.0, 1);
+    change(7, -1.0, -1);
+  }
+}
+
+// Density of node (x, y) after streaming, in FP64, from the channel's slots C
+// (fixed walls). FP32: stored relative to density 1 and the source rows'
+// references, whose parts of the density vanish: E_2 + E_5 + E_6 = 0 at any
+// reference, and so do the changes of reflected 5 and 6 together.
+template <typename T, bool SHIFT>
+__device__ __forceinline__ double column_density(const T *__restrict__ C, int nx, int ny, int x, int y) {
+  const unsigned row = (unsigned)y * nx;
+  const unsigned xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
+  const bool bot = (y == 0), top = (y == ny - 1);
+  const unsigned dn = row - nx, up = row + nx;
+  const T f0 = C[lslot(0, row + x)], f1 = C[lslot(1, row + xm)], f3 = C[lslot(3, row + xp)];
+  const T f2 = C[bot ? lslot(4, row + x) : lslot(2, dn + x)], f5 = C[bot ? lslot(7, row + x) : lslot(5, dn + xm)],
+          f6 = C[bot ? lslot(8, row + x) : lslot(6, dn + xp)];
+  const T f4 = C[top ? lslot(2, row + x) : lslot(4, up + x)], f7 = C[top ? lslot(5, row + x) : lslot(7, up + xp)],
+          f8 = C[top ? lslot(6, row + x) : lslot(8, up + xm)];
+  const double s = ((double)f0 + (double)f1 + (double)f3) + ((double)f2 + (double)f5 + (double)f6) +
+                   ((double)f4 + (double)f7 + (double)f8);
+  return SHIFT ? 1.0 + s : s;
+}
+
 // Many steps per launch for small lattices: one workgroup takes a box of
 // nodes [x0, x1) x [y0, y1) of one channel through S steps with the state in
 // LDS. It loads the box and a halo of 2 S nodes around it (clipped at the
@@ -932,7 +990,13 @@ __global__ void __launch_bounds__(128) sweep_narrow2_kernel(SweepArgs a) {
 // 4.7 at two steps per launch. With every CU full (256 ragged channels, 80
 // VGPRs, six wavefronts per SIMD in FP32) it issues VALU work about two
 // thirds of the time: 5.3 us per step against 13.2.
-template <typename T, bool VE, int TH>
+//
+// GP: one step (S = 1) of channels with the pressure drive, the generalised
+// periodic boundaries (gpbc_change) in the same launch: a workgroup whose box
+// stores inlet or outlet nodes sums that column's density over all rows of
+// the state it reads (a collision keeps every node's density), while its
+// region loads. A step then is one launch instead of two.
+template <typename T, bool VE, bool GP, int TH>
 __global__ void __launch_bounds__(TH, sizeof(T) == 4 ? 6 : 4) sweep_block_kernel(SweepArgs a, int S) {
   constexpr bool SHIFT = sizeof(T) == 4;
   // planes of TH values: the populations at P(i), u~ at U and V, placed so
@@ -1001,6 +1065,29 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 ? 6 : 4) sweep_block_kernel
   const int ylo = st.y0 - y, yhi = y - (st.y1 - 1);              // > 0 outside the box
   const int xlo = whole ? 0 : halo - cc, xhi = whole ? 0 : cc - (cw - 1 - halo);
   const int out_by = max(max(ylo, yhi), max(xlo, xhi));          // distance outside the box (<= 0: inside)
+  double dcol = 0;  // GP: density shift of the links leaving this thread's column
+  if constexpr (GP) {
+    __shared__ double colsum[2][TH / 64];
+    const bool stores[2] = {st.x0 == 0, st.x1 >= nx};
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      double sum = 0;
+      if (stores[side])
+        for (int yy = threadIdx.x; yy < ny; yy += TH)
+          sum += column_density<T, SHIFT>(static_cast<const T *>(a.A) + c.off * kPlanes, nx, ny,
+                                          side ? nx - 1 : 0, yy);
+      sum = group_sum<64>(sum);
+      if ((threadIdx.x & 63) == 0) colsum[side][threadIdx.x >> 6] = sum;
+    }
+    __syncthreads();
+    double in_sum = 0, out_sum = 0;
+    for (int w = 0; w < TH / 64; ++w) {
+      in_sum += colsum[0][w];
+      out_sum += colsum[1][w];
+    }
+    const double dp = (c.t + a.k < c.t_startup) ? c.pd : 0.0;
+    dcol = x == 0 ? 1.0 - 1.5 * dp - in_sum / ny : 1.0 + 1.5 * dp - out_sum / ny;
+  }
   __syncthreads();
 #pragma unroll 1
   for (int s = 0; s < S; ++s) {
@@ -1058,6 +1145,14 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 ? 6 : 4) sweep_block_kernel
       if constexpr (VE) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) sg[p] = sn[p];
+      }
+      if constexpr (GP) {
+        if (x == 0 || x == nx - 1) {
+          double g[9];
+#pragma unroll
+          for (int i = 0; i < 9; ++i) g[i] = (double)out[i];
+          gpbc_change<SHIFT>(g, (double)urc, dcol, x != 0, y, ny, [&](int i, double v) { out[i] = (T)v; });
+        }
       }
       if (s < S - 1) {
 #pragma unroll
@@ -2472,76 +2567,68 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const do
   }
 }
 
-// Generalised periodic boundaries (Sec. II.B), applied to the state a step
-// has just written: a population that the next pull carries across the
-// period (+x out of the outlet column x = nx-1 into the inlet, -x out of the
-// inlet column into the outlet) becomes the equilibrium at the far end's
-// density plus its own non-equilibrium part. With the moments (rho, j) of its
-// source node, a density shift d = p+-/cs2 - mean column density adds
-// a_i [d + (4.5 (c.j)^2 - 1.5 j^2) (1/(rho + d) - 1/rho)]. Diagonal links
-// that meet a wall are reflected, not carried, and stay. One workgroup per
-// channel; the column means are taken before anything is changed.
+// The generalised periodic boundaries (gpbc_change) as a pass over the state
+// a step has just written, for the channels that do not step in boxes
+// (ChanDev.gpbc == 1). One workgroup per channel; the column means are taken
+// before anything is changed.
+//
+// Bound by latency: one row of a column per thread, the inlet column in the
+// first 256 threads and the outlet column in the others, so that all loads of
+// both columns are in flight together and a row's populations stay in
+// registers for the change (columns of up to 256 rows read memory once).
+constexpr int kGpbcRows = 256;  // rows of a column taken at once
 template <typename T, bool SHIFT>
-__global__ void __launch_bounds__(256) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref) {
+__global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref) {
   const ChanDev c = ch[blockIdx.x];
-  if (!c.gpbc || !c.active) return;
+  if (c.gpbc != 1 || !c.active) return;
   const long long t = c.t + k;
   const double dp = (t < c.t_startup) ? c.pd : 0.0;
   const int nx = c.nx, ny = c.ny;
-  auto node = [&](int x, int y) -> long long { return c.off + (long long)y * nx + x; };
-  // density and momentum of a node (FP32: stored relative to the equilibrium
-  // at density 1 and the row's reference velocity, which carries momentum ur)
-  auto load9 = [&](long long n, int y, double f[9], double &rho, double &jx, double &jy) {
-    double s = 0;
-    jx = jy = 0;
-    for (int i = 0; i < 9; ++i) {
-      f[i] = (double)B[slot(i, n)];
-      s += f[i];
-    }
-    jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
-    jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
-    if (SHIFT) jx += (double)uref[c.row_off + y];
-    rho = SHIFT ? 1.0 + s : s;
+  const int l = threadIdx.x & (kGpbcRows - 1);
+  const bool outlet = __builtin_amdgcn_readfirstlane(threadIdx.x / kGpbcRows) != 0;
+  struct Node {
+    double f[9], rho;
   };
-  __shared__ double red[2][256];
-  double si = 0, so = 0;
-  for (int y = threadIdx.x; y < ny; y += blockDim.x) {
-    double f[9], r, jx, jy;
-    load9(node(0, y), y, f, r, jx, jy);
-    si += r;
-    load9(node(nx - 1, y), y, f, r, jx, jy);
-    so += r;
+  auto node = [&](int y) { return B + slot(0, c.off + (long long)y * nx + (outlet ? nx - 1 : 0)); };
+  auto load9 = [&](int y, Node &q) {
+    const T *b = node(y);
+    double s = 0;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) q.f[i] = (double)b[i * kTile];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) s += q.f[i];
+    q.rho = SHIFT ? 1.0 + s : s;
+  };
+  __shared__ double red[2][kGpbcRows];
+  Node first;
+  double sum = 0;
+  if (l < ny) {
+    load9(l, first);
+    sum = first.rho;
   }
-  red[0][threadIdx.x] = si;
-  red[1][threadIdx.x] = so;
+  for (int y = l + kGpbcRows; y < ny; y += kGpbcRows) {
+    Node q;
+    load9(y, q);
+    sum += q.rho;
+  }
+  red[outlet][l] = sum;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + st];
-      red[1][threadIdx.x] += red[1][threadIdx.x + st];
-    }
+  for (int st = kGpbcRows / 2; st > 0; st >>= 1) {
+    if (l < st) red[outlet][l] += red[outlet][l + st];
     __syncthreads();
   }
-  const double d_in = 1.0 + 1.5 * dp - red[1][0] / ny;   // links entering the inlet
-  const double d_out = 1.0 - 1.5 * dp - red[0][0] / ny;  // links entering the outlet
-  auto fix = [&](long long n, double d, int i0, int i1, int i2, int y) {
-    double f[9], r, jx, jy;
-    load9(n, y, f, r, jx, jy);
-    const double j2 = jx * jx + jy * jy, w = 1.0 / (r + d) - 1.0 / r;
-    const int ids[3] = {i0, i1, i2};
-    for (int q = 0; q < 3; ++q) {
-      const int i = ids[q];
-      const int cy = (i == 5 || i == 6) ? 1 : ((i == 7 || i == 8) ? -1 : 0);
-      if (y + cy < 0 || y + cy >= ny) continue;  // met a wall: reflected
-      const double cx = (i == 1 || i == 5 || i == 8) ? 1.0 : -1.0;
-      const double cj = cx * jx + cy * jy;
-      const double a = (i < 5) ? 1.0 / 9.0 : 1.0 / 36.0;
-      B[slot(i, n)] = (T)(f[i] + a * (d + (4.5 * cj * cj - 1.5 * j2) * w));
-    }
+  // links leaving the outlet enter the inlet, and the other way round
+  const double d = outlet ? 1.0 + 1.5 * dp - red[1][0] / ny : 1.0 - 1.5 * dp - red[0][0] / ny;
+  auto fix = [&](int y, const Node &q) {
+    T *b = node(y);
+    gpbc_change<SHIFT>(q.f, SHIFT ? (double)uref[c.row_off + y] : 0.0, d, outlet, y, ny,
+                       [&](int i, double v) { b[i * kTile] = (T)v; });
   };
-  for (int y = threadIdx.x; y < ny; y += blockDim.x) {
-    fix(node(nx - 1, y), d_in, 1, 5, 8, y);
-    fix(node(0, y), d_out, 3, 6, 7, y);
+  if (l < ny) fix(l, first);
+  for (int y = l + kGpbcRows; y < ny; y += kGpbcRows) {
+    Node q;
+    load9(y, q);
+    fix(y, q);
   }
 }
 
@@ -3013,23 +3100,26 @@ hipError_t launch_tiles(const SweepArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, bool VE>
+template <typename T, bool VE, bool GP>
 hipError_t launch_block_t(int threads, const SweepArgs &a, int S, hipStream_t s) {
   const dim3 grid(a.n_wg), block(threads);
   switch (threads) {
-    case 256: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 256>), grid, block, 0, s, a, S); break;
-    case 512: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 512>), grid, block, 0, s, a, S); break;
-    case 1024: hipLaunchKernelGGL((sweep_block_kernel<T, VE, 1024>), grid, block, 0, s, a, S); break;
+    case 256: hipLaunchKernelGGL((sweep_block_kernel<T, VE, GP, 256>), grid, block, 0, s, a, S); break;
+    case 512: hipLaunchKernelGGL((sweep_block_kernel<T, VE, GP, 512>), grid, block, 0, s, a, S); break;
+    case 1024: hipLaunchKernelGGL((sweep_block_kernel<T, VE, GP, 1024>), grid, block, 0, s, a, S); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_blocks(bool fp32, int threads, const SweepArgs &a, int S, hipStream_t s) {
+hipError_t launch_blocks(bool fp32, bool gpbc, int threads, const SweepArgs &a, int S, hipStream_t s) {
   if (a.n_strips == 0) return hipSuccess;
-  if (a.ve && (!a.SA || !a.SB)) return hipErrorInvalidValue;
-  if (fp32) return a.ve ? launch_block_t<float, true>(threads, a, S, s) : launch_block_t<float, false>(threads, a, S, s);
-  return a.ve ? launch_block_t<double, true>(threads, a, S, s) : launch_block_t<double, false>(threads, a, S, s);
+  if ((a.ve && (!a.SA || !a.SB)) || (gpbc && S != 1)) return hipErrorInvalidValue;
+#define LB_BLOCKS(VE, GP) \
+  (fp32 ? launch_block_t<float, VE, GP>(threads, a, S, s) : launch_block_t<double, VE, GP>(threads, a, S, s))
+  if (gpbc) return a.ve ? LB_BLOCKS(true, true) : LB_BLOCKS(false, true);
+  return a.ve ? LB_BLOCKS(true, false) : LB_BLOCKS(false, false);
+#undef LB_BLOCKS
 }
 
 hipError_t launch_reduce(const ChanDev *ch, int n_ch, const double *part, double *prof,
@@ -3044,11 +3134,11 @@ hipError_t launch_reduce(const ChanDev *ch, int n_ch, const double *part, double
 hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, const float *uref, hipStream_t s) {
   if (n_ch == 0) return hipSuccess;
   if (fp32)
-    hipLaunchKernelGGL((gpbc_kernel<float, true>), dim3(n_ch), dim3(256), 0, s, static_cast<float *>(B), ch, k,
-                       uref);
+    hipLaunchKernelGGL((gpbc_kernel<float, true>), dim3(n_ch), dim3(2 * kGpbcRows), 0, s, static_cast<float *>(B),
+                       ch, k, uref);
   else
-    hipLaunchKernelGGL((gpbc_kernel<double, false>), dim3(n_ch), dim3(256), 0, s, static_cast<double *>(B), ch,
-                       k, uref);
+    hipLaunchKernelGGL((gpbc_kernel<double, false>), dim3(n_ch), dim3(2 * kGpbcRows), 0, s,
+                       static_cast<double *>(B), ch, k, uref);
   return hipGetLastError();
 }
 

@@ -58,6 +58,7 @@ struct Layout {
   // (and their reverse), and the two-step strips
   size_t off_bstrips = 0, off_brstrips = 0, off_tstrips = 0;
   size_t off_blk = 0;     // boxes of the channels that run many steps per launch
+  size_t off_gpb = 0;     // boxes of the pressure-driven channels
   size_t off_btiles = 0;  // tiles of the tiled channels without two-step strips
   int strip_cap = 0;      // entries of each one-step strip list
   int max_two = 0;
@@ -222,8 +223,8 @@ bool two_step_channel(const lb_channel &c, int esize) {
 bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize) {
   return !o->viscoelastic && !is_strip_class(width_class(c.nx, esize)) && c.pressure_gradient == 0;
 }
-// Channels whose steps run in boxes, many per launch (sweep_block_kernel):
-// without the pressure drive, with either stress model and any top wall,
+// Channels whose steps run in boxes (sweep_block_kernel), many per launch or,
+// with the pressure drive, one: with either stress model and any top wall,
 // while the handle's channels of the same kind hold few enough nodes. A small
 // lattice is bound by the latency of its launches, which boxes take once for
 // several steps; a large one by instruction issue, of which the boxes' halos
@@ -237,28 +238,35 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize
 //    1000 x 300 8.8 / 21.3, 4000 x 2000 180 / 210; FP64 (tiles) 200 x 20
 //    1.9 / 6.2, 1000 x 300 11.4 / 12.2, 1000 x 500 18.0 / 16.6, but
 //    time-integrated 4000 x 2000 278 / 309;
+//  * the pressure drive, one step per launch with the boundary columns in it
+//    (FP64): 64 x 32 6.1 / 45 (a strip march and a
+//    column pass), 1000 x 320 19.4 / 26.9, 1000 x 1000 48.5 / 65.4;
 //  * narrow widths, whose boxes need no columns beside them: 8 x 64 1.1 / 4.7
 //    (FP64 1.4 / 3.9), 256 ragged channels of 8 columns 5.3 / 13.2 (8.5 /
 //    22.1), 8 x 262144 27.7 / 48.1; from 32 columns on a box holds few rows:
 //    64 x 8192 12.8 / 15.7 (FP64 17.3 / 15.2), 64 x 65536 92 / 80.
+// values of block_channels: not in boxes; many steps per launch; pressure drive
+enum { kNoBoxes = 0, kBoxes = 1, kPressureBoxes = 2 };
 std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize) {
-  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, KINDS };
+  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, KINDS };
   const bool fp32 = esize == 4, ve = o->viscoelastic;
   const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
   const long long limit[KINDS] = {fp32 ? M + M / 4 : (ve ? 5 * M / 8 : 3 * M / 4), (fp32 || ve) ? 8 * M : 3 * M / 10,
-                                  always, ve ? always : (fp32 ? M : M / 4)};
+                                  always, ve ? always : (fp32 ? M : M / 4), M};
   std::vector<int> kind(n, -1);
   long long nodes[KINDS] = {};
   for (int i = 0; i < n; ++i) {
-    if (o->steps_per_sweep == 1 || o->stress_force || c[i].pressure_gradient != 0) continue;
+    const bool gp = c[i].pressure_gradient != 0;  // one step per launch in either setting
+    if ((o->steps_per_sweep == 1 && !gp) || o->stress_force) continue;
     const size_t N = (size_t)c[i].nx * c[i].ny;
     if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
     const int cls = width_class(c[i].nx, esize);
-    kind[i] = cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
+    kind[i] = gp ? PRESSURE : cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
     nodes[kind[i]] += (long long)N;
   }
   std::vector<char> ok(n, 0);
-  for (int i = 0; i < n; ++i) ok[i] = kind[i] >= 0 && nodes[kind[i]] <= limit[kind[i]];
+  for (int i = 0; i < n; ++i)
+    if (kind[i] >= 0 && nodes[kind[i]] <= limit[kind[i]]) ok[i] = kind[i] == PRESSURE ? kPressureBoxes : kBoxes;
   return ok;
 }
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
@@ -553,6 +561,7 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
   // boxes of 64 nodes, or 4096 boxes and two per channel
   L.max_boxes = std::max<long long>(4096 + 2ll * n, L.plane / 64);
   L.off_blk = take(sizeof(Strip) * L.max_boxes);
+  L.off_gpb = take(sizeof(Strip) * L.max_boxes);
   L.off_tstrips = take(sizeof(Strip) * std::max(L.max_two, 1));
   L.bytes = at;
   return L;
@@ -586,8 +595,12 @@ struct lb_handle {
   // captured blocks: the boxes of the channels that run blk_S steps per launch
   Strip *dblk = nullptr;
   int n_blk = 0, blk_S = 0, blk_threads = 0;
+  // every step: the boxes of the pressure-driven channels that step in them
+  Strip *dgpb = nullptr;
+  int n_gpb = 0, gpb_threads = 0;
+  int n_tiles = 0;           // tiles of the one-step tile list
   bool blk_only = false;       // every active channel runs in boxes
-  std::vector<char> blk_ok;    // channels whose captured steps run in boxes
+  std::vector<char> blk_ok;    // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
   int cus = 256;
   // captured blocks: the narrow two-step strips of each width, after the
   // others in dbact
@@ -610,7 +623,7 @@ struct lb_handle {
   std::vector<int> active;
   int n_checks = 0;
   int since_block = 0;       // steps since the last block boundary (handle clock)
-  bool any_gpbc = false;     // some channel has the pressure drive
+  bool any_gpbc = false;     // some channel's pressure drive takes the column pass
   bool any_zh = false;       // some channel has a Zou-He top wall
   int device = -1;           // the GPU current at lb_create
   double *noalloc = nullptr; // that GPU's copy of `scratch` (device address)
@@ -670,7 +683,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
     auto count = [&]() {
       long long S = 0;
       for (int i = 0; i < h->n_ch; ++i) {
-        if (!h->active[i] || tiled(&h->opt, h->in[i])) continue;
+        if (!h->active[i] || h->blk_ok[i] == kPressureBoxes || tiled(&h->opt, h->in[i])) continue;
         const ChanDev &d = h->L.ch[i];
         const int cls = width_class(d.nx, h->L.esize);
         const int w = strip_cols(cls, h->L.esize);
@@ -681,7 +694,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
     for (long long S = count(); S > 0 && S < h->simds && div < 64;) {
       div *= 2;
       const long long S2 = count();
-      if (S2 == S || S2 > h->L.strip_cap) {  // every channel at its smallest height, or no room
+      if (S2 > h->L.strip_cap) {  // no room
         div /= 2;
         break;
       }
@@ -689,7 +702,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
     }
   }
   for (int i = 0; i < h->n_ch; ++i) {
-    if (!all && (!h->active[i] || tiled(&h->opt, h->in[i]))) continue;
+    if (!all && (!h->active[i] || h->blk_ok[i] == kPressureBoxes || tiled(&h->opt, h->in[i]))) continue;
     const ChanDev &d = h->L.ch[i];
     add_strips(i, d, h->L.esize,
                all ? strip_rows_for(width_class(d.nx, h->L.esize), d.nx, d.ny, h->opt.strip_rows) : rows_of(i),
@@ -715,32 +728,35 @@ lb_status upload_strips(lb_handle *h, bool all) {
     // one-step strips of the others
     std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped, boxes;
     bool wall = false;
-    h->blk_S = h->n_blk = 0;
-    h->blk_only = false;
-    {
+    // boxes of the channels that step in them: many steps per launch, and
+    // (at S = 1) those with the pressure drive
+    h->blk_S = h->n_blk = h->n_gpb = 0;
+    h->blk_only = true;
+    for (int i = 0; i < h->n_ch; ++i) h->blk_only = h->blk_only && (!h->active[i] || h->blk_ok[i] == kBoxes);
+    std::vector<Strip> gboxes;
+    for (const char kind : {kBoxes, kPressureBoxes}) {
       std::vector<lb_channel> chans;
       std::vector<int> ids;
-      bool others = false;
-      for (int i = 0; i < h->n_ch; ++i) {
-        if (!h->active[i]) continue;
-        if (h->blk_ok[i]) {
+      for (int i = 0; i < h->n_ch; ++i)
+        if (h->active[i] && h->blk_ok[i] == kind) {
           chans.push_back(h->in[i]);
           ids.push_back(i);
-        } else {
-          others = true;
         }
-      }
-      if (!ids.empty()) {
-        BoxPlan p = plan_boxes(chans, h->K, h->L.esize == 4, h->cus, h->L.max_boxes);
-        if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
-        for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], boxes);
-        if ((long long)boxes.size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
+      if (ids.empty()) continue;
+      const BoxPlan p = plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
+      if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
+      std::vector<Strip> &list = kind == kBoxes ? boxes : gboxes;
+      for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], list);
+      if ((long long)list.size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
+      HIPCHECK(h, hipMemcpyAsync(kind == kBoxes ? h->dblk : h->dgpb, list.data(), list.size() * sizeof(Strip),
+                                 hipMemcpyHostToDevice, h->stream));
+      if (kind == kBoxes) {
         h->blk_S = p.S;
         h->blk_threads = p.threads;
-        h->n_blk = (int)boxes.size();
-        h->blk_only = !others;
-        HIPCHECK(h, hipMemcpyAsync(h->dblk, boxes.data(), boxes.size() * sizeof(Strip), hipMemcpyHostToDevice,
-                                   h->stream));
+        h->n_blk = (int)list.size();
+      } else {
+        h->gpb_threads = p.threads;
+        h->n_gpb = (int)list.size();
       }
     }
     if (h->two_step || h->blk_S) {
@@ -830,7 +846,7 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     return LB_OK;
   }
   Strip *tl = block ? h->btiles : h->tiles;
-  const int ntl = block ? h->n_btiles : h->L.n_tiles;
+  const int ntl = block ? h->n_btiles : h->n_tiles;
   if (ntl) HIPCHECK(h, launch_tiles(sweep_args(h, tl, 0, ntl, src, k), s));
   const int *begin = block ? h->bact_begin : h->act_begin, *count = block ? h->bact_count : h->act_count;
   Strip *fwd = block ? h->dbact : h->dact, *rev = block ? h->dbact_rev : h->dact_rev;
@@ -845,8 +861,13 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     a.down = (src == 1);
     HIPCHECK(h, launch_sweep(h->opt.precision == LB_FP32_SHIFTED, c, false, a, s));
   }
-  // generalised periodic boundaries: the inlet/outlet column pass on the
-  // state just written
+  if (h->n_gpb) {
+    SweepArgs a = sweep_args(h, h->dgpb, 0, h->n_gpb, src, k);
+    a.n_wg = h->n_gpb;  // one box per workgroup
+    HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, true, h->gpb_threads, a, 1, s));
+  }
+  // generalised periodic boundaries of the others: the inlet/outlet column
+  // pass on the state just written
   if (h->any_gpbc)
     HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
                             s));
@@ -858,7 +879,7 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
 lb_status enqueue_boxes(lb_handle *h, int src, int k, int S, hipStream_t s) {
   SweepArgs a = sweep_args(h, h->dblk, 0, h->n_blk, src, k);
   a.n_wg = h->n_blk;  // one box per workgroup
-  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, h->blk_threads, a, S, s));
+  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, false, h->blk_threads, a, S, s));
   return LB_OK;
 }
 
@@ -1156,7 +1177,6 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->opt = *o;
   h->n_ch = n;
   for (int i = 0; i < n; ++i) {
-    h->any_gpbc = h->any_gpbc || h->L.ch[i].gpbc;
     h->any_zh = h->any_zh || h->L.ch[i].zh;
   }
   h->K = o->obs_every > 0 ? o->obs_every : kDefaultK;
@@ -1174,6 +1194,7 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->dtwo = reinterpret_cast<Strip *>(h->ws + h->L.off_tstrips);
   h->btiles = reinterpret_cast<Strip *>(h->ws + h->L.off_btiles);
   h->dblk = reinterpret_cast<Strip *>(h->ws + h->L.off_blk);
+  h->dgpb = reinterpret_cast<Strip *>(h->ws + h->L.off_gpb);
   h->two_step = false;
   for (int i = 0; i < n && two_step_handle(o, h->K); ++i)
     h->two_step = h->two_step || two_step_channel(c[i], h->L.esize) || narrow_two_step_channel(o, c[i], h->L.esize);
@@ -1205,17 +1226,6 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     h->own_stream = true;
   }
   if (hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking) != hipSuccess) return bail(LB_EHIP);
-  if (hipMemcpyAsync(h->dch, h->L.ch.data(), sizeof(ChanDev) * n, hipMemcpyHostToDevice, h->stream) !=
-      hipSuccess)
-    return bail(LB_EHIP);
-  std::vector<double> nanrows(std::max(1, h->L.total_rows), std::numeric_limits<double>::quiet_NaN());
-  if (hipMemcpyAsync(h->dprev, nanrows.data(), sizeof(double) * h->L.total_rows, hipMemcpyHostToDevice,
-                     h->stream) != hipSuccess)
-    return bail(LB_EHIP);
-  std::vector<float> zrows(std::max(1, h->L.total_rows), 0.0f);
-  if (hipMemcpyAsync(h->duref, zrows.data(), sizeof(float) * h->L.total_rows, hipMemcpyHostToDevice, h->stream) !=
-      hipSuccess)
-    return bail(LB_EHIP);
   {
     // strips of the two-step sweep resident at once
     int dev = 0, cus = 0;
@@ -1228,20 +1238,38 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     h->cus = std::max(cus, 1);
     h->n2slots = (long long)narrow_two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED) * std::max(cus, 1);
   }
-  // channels whose captured steps run in boxes
+  // channels that step in boxes
   h->blk_ok = block_channels(o, c, n, h->L.esize);
-  {
+  for (const char kind : {kBoxes, kPressureBoxes}) {
     std::vector<lb_channel> chans;
     for (int i = 0; i < n; ++i)
-      if (h->blk_ok[i]) chans.push_back(c[i]);
+      if (h->blk_ok[i] == kind) chans.push_back(c[i]);
     // (a plan for all is one for those still active later)
-    if (!chans.empty() && plan_boxes(chans, h->K, h->L.esize == 4, h->cus, h->L.max_boxes).S == 0)
-      h->blk_ok.assign(n, 0);
+    if (!chans.empty() &&
+        plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes).S == 0)
+      for (char &k : h->blk_ok)
+        if (k == kind) k = kNoBoxes;
   }
+  for (int i = 0; i < n; ++i) {
+    ChanDev &d = h->L.ch[i];
+    if (d.gpbc && h->blk_ok[i] == kPressureBoxes) d.gpbc = 2;
+    h->any_gpbc = h->any_gpbc || d.gpbc == 1;
+  }
+  if (hipMemcpyAsync(h->dch, h->L.ch.data(), sizeof(ChanDev) * n, hipMemcpyHostToDevice, h->stream) !=
+      hipSuccess)
+    return bail(LB_EHIP);
+  std::vector<double> nanrows(std::max(1, h->L.total_rows), std::numeric_limits<double>::quiet_NaN());
+  if (hipMemcpyAsync(h->dprev, nanrows.data(), sizeof(double) * h->L.total_rows, hipMemcpyHostToDevice,
+                     h->stream) != hipSuccess)
+    return bail(LB_EHIP);
+  std::vector<float> zrows(std::max(1, h->L.total_rows), 0.0f);
+  if (hipMemcpyAsync(h->duref, zrows.data(), sizeof(float) * h->L.total_rows, hipMemcpyHostToDevice, h->stream) !=
+      hipSuccess)
+    return bail(LB_EHIP);
   if (upload_strips(h, true) != LB_OK || upload_strips(h, false) != LB_OK) return bail(LB_EHIP);
   std::vector<Strip> tiles, btiles;  // kept until the synchronisation below
   for (int i = 0; i < n; ++i)
-    if (tiled(o, c[i])) {
+    if (tiled(o, c[i]) && h->blk_ok[i] != kPressureBoxes) {
       add_tiles(i, c[i], tile_shape(o), tiles);
       if (!h->blk_ok[i] && !(h->two_step && two_step_channel(c[i], h->L.esize)))
         add_tiles(i, c[i], tile_shape(o), btiles);
@@ -1249,6 +1277,7 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   if (!tiles.empty() && hipMemcpyAsync(h->tiles, tiles.data(), sizeof(Strip) * tiles.size(),
                                        hipMemcpyHostToDevice, h->stream) != hipSuccess)
     return bail(LB_EHIP);
+  h->n_tiles = (int)tiles.size();
   h->n_btiles = (int)btiles.size();
   if (!btiles.empty() && hipMemcpyAsync(h->btiles, btiles.data(), sizeof(Strip) * btiles.size(),
                                         hipMemcpyHostToDevice, h->stream) != hipSuccess)

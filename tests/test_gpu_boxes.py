@@ -104,3 +104,31 @@ def test_large_two_step_equals_one_step(precision, nx, ny, viscoelastic):
         err = np.abs(p - q).max() / scale
         print(f"{precision} {nx}x{ny} viscoelastic {viscoelastic}: {err:.2e}", flush=True)
         assert err <= (2e-4 if precision == "fp32" else 1e-9 if q.ndim == 2 else 1e-11)
+
+
+# bounds of the pressure-drive state parity (50 x 1e-12 and 50 x 2e-6 of the
+# state's deviation from rest after some tens of steps)
+@pytest.mark.parametrize("precision,tol", [("fp32", 1e-4), ("fp64", 5e-11)])
+@pytest.mark.parametrize("nx,ny,steps", [(2, 3, 30), (16, 64, 30), (64, 32, 30), (33, 1100, 20), (700, 5, 30),
+                                         (1030, 1030, 6)])
+def test_pressure_boxes_match_oracle(orc, precision, tol, nx, ny, steps):
+    """The boundary columns inside the box launch: a channel of one box, boxes
+    that store one of the two columns or neither, columns taller than a
+    workgroup; and (1030 x 1030, above the boxes' limit) the column pass over
+    more rows than it takes at once. The drive ends inside the run, which is
+    split off the block boundaries."""
+    from paper_1310_7450_amd import Solver
+    c = spec(nx, ny, force=0.0, pressure_gradient=1e-6, nn_pressure=False, t_startup=steps - 3)
+    pops, P = workloads.random_state(nx, ny, seed=nx + 5 * ny)
+    o = orc.Channel(nx, ny, 0.0, tau_lb=c.tau_lb, G=c.G, tau0=c.tau0, gamma_c=c.gamma_c, eps=c.eps,
+                    visc_split=c.visc_split, t_startup=c.t_startup, nn_pressure=False,
+                    pressure_gradient=c.pressure_gradient)
+    o.set_state(pops, P, t=0)
+    with Solver([c], precision=precision, obs_every=4) as s:
+        s.set_state(0, pops, P, 0)
+        for n in (steps - 5, 5):
+            s.step(n)
+        o.run(steps)
+        err = np.abs(s.get_state(0)[0] - o.n).max() / np.abs(o.n - workloads.REST_WEIGHTS[:, None, None]).max()
+    print(f"{precision} {nx}x{ny}: {err:.2e}", flush=True)
+    assert err < tol
