@@ -15,6 +15,15 @@
 // hundred rows and columns wide: the operands sit in L2, and the kernels are
 // bound by latency, so the tile keeps many wavefronts busy instead of staging
 // through LDS.
+//
+// Networks whose layers are at most 256 wide run fused instead: everything
+// that is local to a row of the batch (the forward pass, the loss gradient, the
+// chain of dZ) is one launch (rows_kernel), everything that sums over the rows
+// (dW, db, and the Adam update of what they belong to) a second one
+// (weights_kernel). A GEMM per launch cost about 6.5 us each in a training step
+// of 20 of them (batch 512, 5-256-256-256-192: 126 us), of which the products
+// are under 1 us. The products' order of accumulation is that of the GEMM per
+// launch, so results do not depend on which path ran.
 #include "lbml.h"
 
 #include <hip/hip_runtime.h>
@@ -33,14 +42,9 @@ typedef unsigned short bf16_t;
 constexpr int kPad = 32;  // operand padding (rows and columns)
 constexpr int kMaxLayers = 16;
 
-// FP32 -> BF16 with round to nearest even (NaN kept quiet).
-__host__ __device__ inline bf16_t to_bf16(float f) {
-  unsigned int u;
-  memcpy(&u, &f, 4);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (bf16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
-}
+// FP32 -> BF16 with round to nearest even (NaN kept quiet): gfx950's
+// conversion instruction.
+__device__ inline bf16_t to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 
 __device__ inline float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
 
@@ -190,6 +194,14 @@ __global__ void __launch_bounds__(64) sum_kernel(const double *part, int n, doub
   if (threadIdx.x == 0) *out = s * scale;
 }
 
+// Operands of the fused passes lie in the order of the MFMA fragments: element
+// (row, k) of a matrix of kp columns (a multiple of 32) is element k % 8 of
+// lane (row % 16) + 16 ((k % 32) / 8) of the fragment of rows row / 16 and
+// columns k / 32, so that a wavefront's load of a fragment is 1 KB in a row.
+__device__ inline long long frag(int row, int k, int kp) {
+  return (((long long)(row >> 4) * (kp >> 5) + (k >> 5)) * 64 + (row & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+
 // The weights' BF16 operands of every layer: W[out][in] and W^T, padded.
 struct WeightMap {
   int nl;
@@ -197,6 +209,7 @@ struct WeightMap {
   long long boff[kMaxLayers];        // offset of b_l (the end of W_l)
   int din[kMaxLayers], dout[kMaxLayers];
   long long wb[kMaxLayers], wt[kMaxLayers];  // element offsets of the BF16 copies
+  int fused;                         // the copies lie in fragment order (frag) of so many columns, 0: row by row
 };
 
 __device__ inline void store_weight(const WeightMap &w, bf16_t *pb, long long i, float v) {
@@ -206,28 +219,287 @@ __device__ inline void store_weight(const WeightMap &w, bf16_t *pb, long long i,
     const int o = (int)(j / w.din[l]), in = (int)(j - (long long)o * w.din[l]);
     const int pin = (w.din[l] + kPad - 1) / kPad * kPad, pout = (w.dout[l] + kPad - 1) / kPad * kPad;
     const bf16_t b = to_bf16(v);
-    pb[w.wb[l] + (long long)o * pin + in] = b;
-    pb[w.wt[l] + (long long)in * pout + o] = b;
+    pb[w.wb[l] + (w.fused ? frag(o, in, w.fused) : (long long)o * pin + in)] = b;
+    pb[w.wt[l] + (w.fused ? frag(in, o, w.fused) : (long long)in * pout + o)] = b;
   }
 }
 
-__global__ void adam_kernel(float *p, const float *g, float *m, float *v, bf16_t *pb, WeightMap w, long long n,
-                            float lr, float b1, float b2, float eps, float c1, float c2) {
+// Adam update of parameter i with gradient gi; returns the new value.
+struct AdamArgs {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+__device__ inline float adam_element(const AdamArgs &a, long long i, float gi) {
+  // (explicit fused operations: the same rounding in every kernel)
+  const float mi = fmaf(1.0f - a.b1, gi, __fmul_rn(a.b1, a.m[i]));
+  const float vi = fmaf(__fmul_rn(1.0f - a.b2, gi), gi, __fmul_rn(a.b2, a.v[i]));
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float wv = a.p[i] - __fmul_rn(a.lr, mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  a.p[i] = wv;
+  return wv;
+}
+
+__global__ void adam_kernel(AdamArgs a, const float *g, bf16_t *pb, WeightMap w, long long n) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float wv = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  p[i] = wv;
-  store_weight(w, pb, i, wv);
+  store_weight(w, pb, i, adam_element(a, i, g[i]));
 }
 
 __global__ void refresh_kernel(const float *p, bf16_t *pb, WeightMap w, long long n) {
   const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i < n) store_weight(w, pb, i, p[i]);
+}
+
+// The fused passes: at most kFusedLayers layers, each at most kFusedWidth wide
+// (16 column tiles of 16, one per wavefront of a workgroup). Their operands
+// are zero-padded to kFusedWidth rows and columns, so that a stage is the
+// same straight-line code whatever its layer's shape.
+constexpr int kFusedWidth = 256, kFusedLayers = 4;
+constexpr int kFusedRows = 16;  // batch rows of a workgroup
+constexpr int kFusedK = kFusedWidth / 32;
+struct RowsArgs {
+  int batch, bp;                  // rows, padded rows of the largest batch
+  int dims[kFusedLayers + 1];
+  long long boff[kFusedLayers];   // biases in the parameters
+  const float *p;                 // parameters
+  const bf16_t *wb, *wt;          // W and W^T of layer l at l kFusedWidth^2
+  const float *x;                 // FWD: input rows
+  const int32_t *idx;             // rows of x (and t) to take, or NULL
+  float *y;                       // FWD: output, or NULL
+  const float *t;                 // LOSS: targets
+  float scale;                    // LOSS: dy = scale (y - t)
+  const float *dy;                // BWD alone: the gradient of the output
+  // per layer, kFusedWidth columns (rows) each: pre-activations Z[m][n],
+  // dZ[m][n] in FP32, and the operands of dW, BF16 in fragment order: the
+  // layer's input transposed (l = 0: x) and dZ transposed
+  float *z, *dz;
+  bf16_t *ht, *dzt;
+};
+
+// One workgroup takes kFusedRows rows of the batch through all NL layers and
+// back. A stage is one product [rows x K] [K x N], each wavefront one 16 x 16
+// tile of it; the rows' operand lies in LDS (one barrier per stage, two
+// buffers), the weights come from L2 straight into registers, where the next
+// stage's load while this stage computes; the stages are unrolled, so that
+// waits count the loads they need. 16 rows are the least an MFMA tile takes:
+// a batch of 512 then fills 32 CUs, and more rows per workgroup would only
+// lengthen the chain of stages, which is what the launch costs. Measured
+// (batch 512, 5-256-256-256-192, forward, loss and backward chain): 15.8 us,
+// about 2 us a stage, of which the activations' exponentials and divisions
+// are near half. Two tiles per wavefront took 17.7 us, with the weights of two
+// stages ahead 18.7; touching all weights' lines first, 17.7.
+template <int NL, bool FWD, bool LOSS, bool BWD>
+__global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a) {
+  __shared__ __align__(16) bf16_t act[2][kFusedRows][kFusedWidth + 8];
+  constexpr int kMat = kFusedWidth * kFusedWidth;
+  constexpr int NST = (FWD ? NL : 0) + (BWD ? NL - 1 : 0);  // stages: layers 0 .. NL-1, then the chain through NL-1 .. 1
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, kg = 8 * (lane >> 4);
+  const int m0 = blockIdx.x * kFusedRows, n = 16 * wv + r, mq = m0 + 4 * (lane >> 4);
+  const int nout = a.dims[NL];
+  const size_t zl = (size_t)a.bp * kFusedWidth;  // per layer of z, dz, ht and dzt
+  struct Weights {
+    bf16x8 w[kFusedK];  // this wavefront's rows
+  };
+  auto fetch = [&](int s, Weights &q) __attribute__((always_inline)) {
+    const bool fwd = FWD && s < NL;
+    const int l = fwd ? s : NL - 1 - (s - (FWD ? NL : 0));
+    const bf16_t *b = (fwd ? a.wb : a.wt) + (size_t)l * kMat + wv * 16 * kFusedWidth + 8 * lane;
+#pragma unroll
+    for (int j = 0; j < kFusedK; ++j) q.w[j] = *reinterpret_cast<const bf16x8 *>(b + 512 * j);
+  };
+  Weights q[2];
+  if (NST > 0) fetch(0, q[0]);
+  // biases, and the targets of this lane's outputs
+  float bias[NL], tgt[4] = {0.f, 0.f, 0.f, 0.f}, z[NL][4], sg[NL][4];
+  if constexpr (FWD) {
+#pragma unroll
+    for (int l = 0; l < NL; ++l) bias[l] = n < a.dims[l + 1] ? a.p[a.boff[l] + n] : 0.f;
+  } else {
+#pragma unroll
+    for (int l = 0; l < NL - 1; ++l)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z[l][i] = a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n];
+  }
+  if constexpr (LOSS) {
+    int row[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = mq + i < a.batch ? mq + i : 0;
+      row[i] = a.idx ? a.idx[m] : m;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tgt[i] = a.t[(long long)row[i] * nout + (n < nout ? n : 0)];
+  }
+  {
+    // the first operand: the input rows, or (BWD alone) the given dy, zero
+    // beyond their columns and the batch
+    const int cols = FWD ? a.dims[0] : nout;
+    const float *src = FWD ? a.x : a.dy;
+    bf16_t *tr = FWD ? a.ht : a.dzt + (NL - 1) * zl;
+    constexpr int per = kFusedRows * kFusedWidth / (64 * kFusedWidth / 16);  // 4 per thread
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      const int at = threadIdx.x + e * (64 * kFusedWidth / 16);
+      const int mm = at / kFusedWidth, c = at % kFusedWidth, m = m0 + mm;
+      bf16_t b = 0;
+      if (m < a.batch && c < cols) {
+        const long long row = (FWD && a.idx) ? (long long)a.idx[m] : (long long)m;
+        b = to_bf16(src[row * cols + c]);
+      }
+      act[0][mm][c] = b;
+      if (c < cols) tr[frag(c, m, a.bp)] = b;
+    }
+  }
+  // the lines of the later stages' weights, for this XCD's L2 (the update
+  // wrote them from other XCDs, and each stage's loads alone would wait for
+  // such a miss): workgroups w, w + 8, ... run on one XCD and share them
+  unsigned touched = 0;
+  // this lane's four entries of a column to the next stage's operand and to
+  // the transposed copy
+  auto store_operand = [&](const float v[4], bf16_t (*to)[kFusedWidth + 8], bf16_t *tr) __attribute__((always_inline)) {
+    bf16_t b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      b[i] = mq + i < a.batch ? to_bf16(v[i]) : (bf16_t)0;
+      to[mq - m0 + i][n] = b[i];
+    }
+    uint2 u;
+    u.x = b[0] | (unsigned)b[1] << 16;
+    u.y = b[2] | (unsigned)b[3] << 16;
+    *reinterpret_cast<uint2 *>(tr + frag(n, mq, a.bp)) = u;
+  };
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < NST; ++s) {
+    const bool fwd = FWD && s < NL;
+    const int l = fwd ? s : NL - 1 - (s - (FWD ? NL : 0));
+    if (s + 1 < NST) fetch(s + 1, q[(s + 1) & 1]);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bf16_t *ar = &act[s & 1][r][kg];
+#pragma unroll
+    for (int j = 0; j < kFusedK; ++j)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(ar + 32 * j), q[s & 1].w[j], acc,
+                                                    0, 0, 0);
+    float v[4];
+    if (fwd && l < NL - 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = acc[i] + bias[l];
+        z[l][i] = v[i];
+        sg[l][i] = sigmoid(v[i]);
+        a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
+        v[i] = v[i] * sg[l][i];
+      }
+      store_operand(v, act[(s + 1) & 1], a.ht + (l + 1) * zl);
+    } else if (fwd) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int m = mq + i;
+        const bool in = m < a.batch && n < nout;
+        v[i] = acc[i] + bias[l];
+        if (in && a.y) a.y[(long long)m * nout + n] = v[i];
+        if constexpr (LOSS) {
+          v[i] = in ? a.scale * (v[i] - tgt[i]) : 0.f;
+          a.dz[l * zl + (size_t)m * kFusedWidth + n] = v[i];
+        }
+      }
+      if constexpr (LOSS) store_operand(v, act[(s + 1) & 1], a.dzt + l * zl);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float zz = z[l - 1][i], s1 = FWD ? sg[l - 1][i] : sigmoid(zz);
+        v[i] = acc[i] * (s1 * (1.0f + zz * (1.0f - s1)));
+        a.dz[(l - 1) * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
+      }
+      store_operand(v, act[(s + 1) & 1], a.dzt + (l - 1) * zl);
+    }
+    if (s + 1 < NST) __syncthreads();
+  }
+  asm volatile("" ::"v"(touched));  // (keeps the loads above)
+}
+
+// dW and db of every layer in one launch, and with ADAM the update of each
+// parameter by the lane that holds its gradient. A wavefront takes one 16 x 16
+// tile of a dW (K runs over the batch; eight steps' operands, 64 VGPRs, are
+// in flight at a time), a workgroup four of them, or 16 columns of a db
+// (sixteen partial sums per column, rows q, q + 16, ..., then a fixed tree).
+// 720 tiles keep the loads of all CUs busy; the launch is one chain of
+// K / 256 loads and the update's. Measured (batch 512, the same network): 6.8 us.
+struct WeightsArgs {
+  WeightMap w;
+  int batch, kb, bp;              // rows, padded rows, stride of the operands
+  int block0[kFusedLayers + 1];   // first workgroup of each layer
+  const bf16_t *dzt, *ht;         // (as in RowsArgs)
+  const float *dz, *dz_last;      // dz_last: the output's dZ, of ld_last columns
+  int ld_last;
+  float *g;
+  bf16_t *pb;
+  AdamArgs adam;
+};
+template <bool ADAM>
+__global__ void __launch_bounds__(256) weights_kernel(WeightsArgs a) {
+  __shared__ float part[16][16];
+  int l = 0;
+  while (l + 1 < a.w.nl && (int)blockIdx.x >= a.block0[l + 1]) ++l;
+  const int blk = blockIdx.x - a.block0[l], din = a.w.din[l], dout = a.w.dout[l];
+  const int tiles_i = (din + 15) / 16, tiles = tiles_i * ((dout + 15) / 16), wblocks = (tiles + 3) / 4;
+  if (blk >= wblocks) {
+    const int c = threadIdx.x & 15, q = threadIdx.x >> 4, n = (blk - wblocks) * 16 + c;
+    const float *dz = l == a.w.nl - 1 ? a.dz_last : a.dz + (size_t)l * a.bp * kFusedWidth;
+    const int ld = l == a.w.nl - 1 ? a.ld_last : kFusedWidth;
+    float s = 0.f;
+    if (n < dout) {
+#pragma unroll 8
+      for (int m = q; m < a.batch; m += 16) s += dz[(long long)m * ld + n];
+    }
+    part[q][c] = s;
+    __syncthreads();
+    for (int w = 8; w > 0; w >>= 1) {
+      if (q < w) part[q][c] += part[q + w][c];
+      __syncthreads();
+    }
+    if (q == 0 && n < dout) {
+      const long long i = a.w.boff[l] + n;
+      a.g[i] = part[0][c];
+      if constexpr (ADAM) adam_element(a.adam, i, part[0][c]);
+    }
+    return;
+  }
+  const int tile = blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (tile >= tiles) return;
+  const int to = tile / tiles_i, ti = tile - to * tiles_i;
+  const int lane = threadIdx.x & 63, r = lane & 15;
+  const bf16_t *A = a.dzt + ((size_t)l * kFusedWidth + 16 * to) * a.bp + 8 * lane;
+  const bf16_t *B = a.ht + ((size_t)l * kFusedWidth + 16 * ti) * a.bp + 8 * lane;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 8;
+  for (int k0 = 0; k0 < a.kb; k0 += 32 * U) {
+    bf16x8 fa[U], fb[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (k0 + 32 * j < a.kb) {
+        fa[j] = *reinterpret_cast<const bf16x8 *>(A + (k0 / 32 + j) * 512);
+        fb[j] = *reinterpret_cast<const bf16x8 *>(B + (k0 / 32 + j) * 512);
+      }
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (k0 + 32 * j < a.kb) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[j], fb[j], acc, 0, 0, 0);
+  }
+  const int i = 16 * ti + r;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int o = 16 * to + 4 * (lane >> 4) + q;
+    if (o >= dout || i >= din) continue;
+    const long long id = a.w.woff[l] + (long long)o * din + i;
+    a.g[id] = acc[q];
+    if constexpr (ADAM) {
+      const bf16_t b = to_bf16(adam_element(a.adam, id, acc[q]));
+      a.pb[a.w.wb[l] + frag(o, i, kFusedWidth)] = b;
+      a.pb[a.w.wt[l] + frag(i, o, kFusedWidth)] = b;
+    }
+  }
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -246,6 +518,9 @@ struct Plan {
   size_t off_xb = 0, off_xt = 0;    // BF16 input and its transpose
   size_t off_y = 0, off_dy = 0;     // lbml_train_step: output and its gradient
   std::vector<size_t> off_z, off_hb, off_ht;  // per hidden layer: FP32 Z, BF16 H and H^T
+  // fused passes (RowsArgs): at most kFusedLayers layers of kFusedWidth
+  bool fused = false;
+  size_t off_fz = 0, off_fdz = 0, off_fht = 0, off_fdt = 0;
   size_t bytes = 0;
 };
 constexpr int kMsePart = 64;  // workgroups of the loss reduction
@@ -268,17 +543,20 @@ bool make_plan(int nl, const int32_t *dims, int max_batch, Plan &P) {
     P.max_pw = std::max(P.max_pw, padded(d));
   }
   P.bp = padded(max_batch);
+  P.fused = nl <= kFusedLayers && P.max_pw <= kFusedWidth;
   P.wm.nl = nl;
+  P.wm.fused = P.fused ? kFusedWidth : 0;
   size_t e = 0;
   for (int l = 0; l < nl; ++l) {
     P.wm.woff[l] = (long long)P.woff[l];
     P.wm.boff[l] = (long long)P.boff[l];
     P.wm.din[l] = P.dims[l];
     P.wm.dout[l] = P.dims[l + 1];
-    P.wm.wb[l] = (long long)e;
-    e += (size_t)padded(P.dims[l + 1]) * padded(P.dims[l]);
-    P.wm.wt[l] = (long long)e;
-    e += (size_t)padded(P.dims[l]) * padded(P.dims[l + 1]);
+    const size_t mat = P.fused ? (size_t)kFusedWidth * kFusedWidth
+                               : (size_t)padded(P.dims[l + 1]) * padded(P.dims[l]);
+    P.wm.wb[l] = P.fused ? (long long)(l * mat) : (long long)e;
+    P.wm.wt[l] = P.fused ? (long long)((nl + l) * mat) : (long long)(e + mat);
+    e += 2 * mat;
   }
   P.bf16_weights = e;
   size_t at = 0;
@@ -295,19 +573,28 @@ bool make_plan(int nl, const int32_t *dims, int max_batch, Plan &P) {
   P.off_loss = take(8);
   P.off_part = take(8 * kMsePart);
   const size_t opnd = 2 * (size_t)P.bp * P.max_pw;
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < 2 && !P.fused; ++i) {
     P.off_dz[i] = take(4 * (size_t)max_batch * P.max_width);
     P.off_db[i] = take(opnd);
     P.off_dt[i] = take(opnd);
   }
   P.off_y = take(4 * (size_t)max_batch * P.dims[nl]);
-  P.off_dy = take(4 * (size_t)max_batch * P.dims[nl]);
-  P.off_xb = take(2 * (size_t)P.bp * padded(P.dims[0]));
-  P.off_xt = take(2 * (size_t)P.bp * padded(P.dims[0]));
-  for (int l = 0; l < nl; ++l) {
+  if (!P.fused) P.off_dy = take(4 * (size_t)max_batch * P.dims[nl]);
+  for (int l = 0; l < nl && !P.fused; ++l) {
+    if (l == 0) {
+      P.off_xb = take(2 * (size_t)P.bp * padded(P.dims[0]));
+      P.off_xt = take(2 * (size_t)P.bp * padded(P.dims[0]));
+    }
     P.off_z.push_back(take(4 * (size_t)max_batch * P.dims[l + 1]));
     P.off_hb.push_back(take(2 * (size_t)P.bp * padded(P.dims[l + 1])));
     P.off_ht.push_back(take(2 * (size_t)P.bp * padded(P.dims[l + 1])));
+  }
+  if (P.fused) {
+    const size_t per = (size_t)nl * P.bp * kFusedWidth;
+    P.off_fz = take(4 * (per - (size_t)P.bp * kFusedWidth));  // the hidden layers'
+    P.off_fdz = take(4 * per);
+    P.off_fht = take(2 * per);
+    P.off_fdt = take(2 * per);
   }
   P.bytes = at;
   return true;
@@ -437,8 +724,79 @@ lbml_status lbml_get_grads(lbml_net *h, float *g, size_t n) {
 
 namespace {
 
+// The launches of the fused passes.
+RowsArgs rows_args(lbml_net *h, int32_t batch) {
+  const Plan &P = h->P;
+  RowsArgs a{};
+  a.batch = batch;
+  a.bp = P.bp;
+  for (int l = 0; l <= h->nl; ++l) a.dims[l] = P.dims[l];
+  for (int l = 0; l < h->nl; ++l) a.boff[l] = (long long)P.boff[l];
+  a.p = h->f(P.off_p);
+  a.wb = h->pb() + P.wm.wb[0];
+  a.wt = h->pb() + P.wm.wt[0];
+  a.z = h->f(P.off_fz);
+  a.dz = h->f(P.off_fdz);
+  a.ht = h->b(P.off_fht);
+  a.dzt = h->b(P.off_fdt);
+  return a;
+}
+template <bool FWD, bool LOSS, bool BWD>
+lbml_status launch_rows(lbml_net *h, const RowsArgs &a) {
+  const dim3 grid(padded(a.batch) / kFusedRows), block(64 * kFusedWidth / 16);
+  switch (h->nl) {
+    case 1: hipLaunchKernelGGL((rows_kernel<1, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 2: hipLaunchKernelGGL((rows_kernel<2, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 3: hipLaunchKernelGGL((rows_kernel<3, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 4: hipLaunchKernelGGL((rows_kernel<4, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    default: return fail(h, -5, "no fused pass for this depth");
+  }
+  MLCHECK(h, hipGetLastError());
+  return 0;
+}
+// dW and db from the dZ that launch_rows wrote, the last layer's from dz_last
+// (ld_last columns); with adam also the update.
+lbml_status launch_weights(lbml_net *h, const float *dz_last, int ld_last, int32_t batch, const AdamArgs *adam) {
+  const Plan &P = h->P;
+  WeightsArgs a{};
+  a.w = P.wm;
+  a.batch = batch;
+  a.kb = padded(batch);
+  a.bp = P.bp;
+  a.g = h->f(P.off_g);
+  a.pb = h->pb();
+  a.dzt = h->b(P.off_fdt);
+  a.ht = h->b(P.off_fht);
+  a.dz = h->f(P.off_fdz);
+  a.dz_last = dz_last;
+  a.ld_last = ld_last;
+  int blocks = 0;
+  for (int l = 0; l < h->nl; ++l) {
+    const int ti = (P.dims[l] + 15) / 16, to = (P.dims[l + 1] + 15) / 16;
+    a.block0[l] = blocks;
+    blocks += (ti * to + 3) / 4 + to;
+  }
+  a.block0[h->nl] = blocks;
+  if (adam) {
+    a.adam = *adam;
+    hipLaunchKernelGGL(weights_kernel<true>, dim3(blocks), dim3(256), 0, h->stream, a);
+  } else {
+    hipLaunchKernelGGL(weights_kernel<false>, dim3(blocks), dim3(256), 0, h->stream, a);
+  }
+  MLCHECK(h, hipGetLastError());
+  return 0;
+}
+
 lbml_status forward_impl(lbml_net *h, const float *x, const int32_t *idx, int32_t batch, float *y) {
   const Plan &P = h->P;
+  if (P.fused) {
+    RowsArgs a = rows_args(h, batch);
+    a.x = x;
+    a.idx = idx;
+    a.y = y;
+    h->last_batch = batch;
+    return launch_rows<true, false, false>(h, a);
+  }
   // the input as BF16 operands: [batch][in] for this GEMM, transposed for dW
   MLCHECK(h, to_operands(h->stream, x, idx, batch, P.dims[0], h->b(P.off_xb), padded(P.dims[0]), h->b(P.off_xt),
                          P.bp));
@@ -492,6 +850,12 @@ lbml_status mse_impl(lbml_net *h, const float *y, const float *t, const int32_t 
 
 lbml_status backward_impl(lbml_net *h, const float *dy, int32_t batch) {
   const Plan &P = h->P;
+  if (P.fused) {
+    RowsArgs a = rows_args(h, batch);
+    a.dy = dy;
+    const lbml_status st = launch_rows<false, false, true>(h, a);
+    return st != 0 ? st : launch_weights(h, dy, P.dims[h->nl], batch, nullptr);
+  }
   const int kb = padded(batch);
   int ping = 0;
   // dZ of the last layer: the caller's FP32 dy (bias gradient) and its BF16
@@ -546,12 +910,15 @@ bool adam_args_ok(float lr, float b1, float b2, float eps, int32_t t) {
   return t >= 1 && lr > 0 && b1 >= 0 && b1 < 1 && b2 >= 0 && b2 < 1 && eps > 0;
 }
 
+AdamArgs adam_args(lbml_net *h, float lr, float b1, float b2, float eps, int32_t t) {
+  return AdamArgs{h->f(h->P.off_p), h->f(h->P.off_m), h->f(h->P.off_v), lr, b1, b2, eps, 1.0f - powf(b1, (float)t),
+                  1.0f - powf(b2, (float)t)};
+}
+
 lbml_status adam_impl(lbml_net *h, float lr, float b1, float b2, float eps, int32_t t) {
   const long long n = (long long)h->P.params;
-  const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, h->stream, h->f(h->P.off_p),
-                     h->f(h->P.off_g), h->f(h->P.off_m), h->f(h->P.off_v), h->pb(), h->P.wm, n, lr, b1, b2, eps,
-                     c1, c2);
+  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, h->stream, adam_args(h, lr, b1, b2, eps, t),
+                     h->f(h->P.off_g), h->pb(), h->P.wm, n);
   MLCHECK(h, hipGetLastError());
   return 0;
 }
@@ -589,8 +956,27 @@ lbml_status lbml_train_step(lbml_net *h, const float *X, const float *Y, const i
   if (!h) return -1;
   if (!X || !Y || !idx || batch < 1 || batch > h->max_batch) return fail(h, -1, "bad train_step arguments");
   if (!adam_args_ok(lr, b1, b2, eps, t)) return fail(h, -1, "bad Adam arguments");
-  float *y = h->f(h->P.off_y), *dy = h->f(h->P.off_dy);
-  lbml_status st = forward_impl(h, X, idx, batch, y);
+  float *y = h->f(h->P.off_y);
+  lbml_status st = 0;
+  if (h->P.fused) {
+    RowsArgs a = rows_args(h, batch);
+    a.x = X;
+    a.idx = idx;
+    a.t = Y;
+    a.scale = 2.0f / (float)((long long)batch * h->P.dims[h->nl]);
+    a.y = host_loss ? y : nullptr;
+    h->last_batch = batch;
+    st = launch_rows<true, true, true>(h, a);
+    const AdamArgs ad = adam_args(h, lr, b1, b2, eps, t);
+    float *dz_last = h->f(h->P.off_fdz) + (size_t)(h->nl - 1) * h->P.bp * kFusedWidth;
+    if (st == 0) st = launch_weights(h, dz_last, kFusedWidth, batch, &ad);
+    // the loss from the outputs kept (its dy goes where the last dZ no longer
+    // is needed)
+    if (st == 0 && host_loss) st = mse_impl(h, y, Y, idx, batch, dz_last, host_loss);
+    return st;
+  }
+  float *dy = h->f(h->P.off_dy);
+  st = forward_impl(h, X, idx, batch, y);
   if (st == 0) st = mse_impl(h, y, Y, idx, batch, dy, host_loss);
   if (st == 0) st = backward_impl(h, dy, batch);
   if (st == 0) st = adam_impl(h, lr, b1, b2, eps, t);

@@ -257,3 +257,52 @@ def test_train_step_equals_separate_calls():
         assert la == lb
         assert np.array_equal(a.get_grads(), b.get_grads())
         assert np.array_equal(a.get_params(), b.get_params())
+
+
+# The fused passes (up to four layers of at most 256) and the GEMM per launch
+# (deeper or wider networks): every depth, widths of one, of no multiple of a
+# tile and of the limit, batches around the 16 rows of a workgroup.
+@pytest.mark.parametrize("dims", [[3, 7], [5, 64, 48], [1, 100, 192, 96], [256, 256, 17, 256, 256], [5, 33, 1, 65],
+                                  [4, 32, 32, 32, 32, 8], [5, 300, 20]])
+@pytest.mark.parametrize("batch", [1, 16, 17, 95])
+def test_network_shapes(dims, batch):
+    """Forward within 2^-8 of the last layer's absolute product sums of the
+    oracle at BF16 operands; gradients of the mean squared error within 2e-2
+    (relative L2) of the oracle's at BF16 operands; one training step equal,
+    bit for bit, to the separate calls, after a larger batch left its data in
+    the workspace."""
+    import torch
+    from paper_1310_7450_amd import mlp
+    rng = np.random.default_rng(sum(dims) + batch)
+    p = mlp.init_params(dims, seed=3)
+    p = (p + rng.uniform(-0.1, 0.1, p.size)).astype(np.float32)
+    X = rng.standard_normal((120, dims[0])).astype(np.float32)
+    T = (0.3 * rng.standard_normal((120, dims[-1]))).astype(np.float32)
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    a, b = mlp.Net(dims, max_batch=120), mlp.Net(dims, max_batch=120)
+    for net in (a, b):
+        net.set_params(p)
+        net.forward(Xd)  # the whole batch first
+    x, t = Xd[:batch].contiguous(), Td[:batch].contiguous()
+    y = a.forward(x)
+    dy = torch.empty_like(y)
+    a.mse(y, t, dy)
+    a.backward(dy)
+    p64 = p.astype(np.float64)
+    yb, cache = omlp.forward(p64, dims, X[:batch].astype(np.float64), operand=bf16)
+    absum = np.abs(bf16(cache[-1][0])) @ np.abs(bf16(omlp.unpack(p64, dims)[-1][0])).T
+    assert np.all(np.abs(y.cpu().numpy() - yb) <= TOL_ABS_SUM * absum + 2.0 ** -20)
+    _, dyo = omlp.mse(yb, T[:batch].astype(np.float64))
+    g = omlp.backward(p64, dims, cache, dyo, operand=bf16)
+    assert rel(a.get_grads().astype(np.float64), g) < 2e-2
+    a.adam_step(lr=1e-3)
+    idx = torch.arange(batch, dtype=torch.int32, device="cuda")
+    b.train_step(Xd, Td, idx, lr=1e-3, want_loss=False)
+    torch.cuda.synchronize()
+    assert np.array_equal(a.get_grads(), b.get_grads())
+    assert np.array_equal(a.get_params(), b.get_params())
+    # a training step keeps its forward pass for another backward
+    a.backward(dy)
+    b.backward(dy)
+    assert np.array_equal(a.get_grads(), b.get_grads())
+    assert np.array_equal(a.forward(x).cpu().numpy(), b.forward(x).cpu().numpy())
