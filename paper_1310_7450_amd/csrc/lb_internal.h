@@ -154,7 +154,7 @@ hipError_t launch_tiles(const SweepArgs &a, hipStream_t s);
 #endif
 constexpr int kSafTileX = LB_SAF_TX, kSafTileY = LB_SAF_TY, kSafThreads = LB_SAF_THREADS;
 hipError_t launch_saf_fused(const double *A, double *B, const ChanDev *ch, const Strip *tiles, int n_tiles, int k,
-                            int nt, hipStream_t s);
+                            int nt, int down, hipStream_t s);
 hipError_t launch_saf_observe(const double *A, const ChanDev *ch, int n_ch, long long plane, int total_rows,
                               double *U, double *Tn, double *part, hipStream_t s);
 hipError_t launch_rereference(float *A, const ChanDev *ch, int n_ch, int total_rows, const double *prof,
@@ -169,7 +169,19 @@ hipError_t launch_rereference(float *A, const ChanDev *ch, int n_ch, int total_r
 // the viscoelastic model also the stress) goes from A to B over steps k and
 // k+1.
 inline int two_step_npl(bool fp32, bool nt, bool ve) { return (fp32 && nt && !ve) ? 4 : 2; }
-inline int two_step_cols(int npl) { return 64 * npl - 2 * npl * ((2 + npl - 1) / npl); }
+// Columns on a window's either side that it does not store (step t+1 is valid
+// four columns inside the window), and the multiple of columns strips are cut
+// at. In FP64 a strip stores whole 128-byte lines (16 columns; a line
+// two strips share is written twice: 4096 x 1024 77.7 us per step at
+// multiples of 2 columns, 71.7 at 8, 70.6 at 16), in FP32 whole 32-byte
+// sectors (16 columns would leave only 112 of 128: 41.8 us against 41.0).
+constexpr int kTwoStepMargin = 4;
+inline int two_step_unit(bool fp32) { return fp32 ? 8 : 16; }
+inline int two_step_cols(int npl, bool fp32) {
+  return (64 * npl - 2 * kTwoStepMargin) / two_step_unit(fp32) * two_step_unit(fp32);
+}
+// wavefronts per SIMD the two-step kernel is compiled for
+constexpr int two_step_waves_per_simd(bool fp32, int npl, bool ve) { return fp32 && npl == 2 ? 3 : 2; }
 // wavefronts per strip (one per stage) and the most rows a strip may have
 constexpr int kTwoStepWaves = 2, kTwoStepMaxRows = 56;
 hipError_t launch_two_step(bool fp32, const SweepArgs &a, hipStream_t s);

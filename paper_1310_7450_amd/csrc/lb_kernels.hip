@@ -101,6 +101,32 @@ __device__ __forceinline__ T shift_down(T edge, T v) {
     return __builtin_bit_cast(T, ((long long)hi << 32) | (unsigned int)lo);
   }
 }
+// The same with zero in the end lane (no register to keep for it).
+__device__ __forceinline__ int dpp_shr0(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int dpp_shl0(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
+template <typename T>
+__device__ __forceinline__ T shift_in_up(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, dpp_shr0(__builtin_bit_cast(int, v)));
+  } else {
+    const long long x = __builtin_bit_cast(long long, v);
+    return __builtin_bit_cast(T, ((long long)dpp_shr0((int)(x >> 32)) << 32) | (unsigned int)dpp_shr0((int)x));
+  }
+}
+template <typename T>
+__device__ __forceinline__ T shift_in_down(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, dpp_shl0(__builtin_bit_cast(int, v)));
+  } else {
+    const long long x = __builtin_bit_cast(long long, v);
+    return __builtin_bit_cast(T, ((long long)dpp_shl0((int)(x >> 32)) << 32) | (unsigned int)dpp_shl0((int)x));
+  }
+}
+// A value that is the same in every lane, kept in scalar registers.
+__device__ __forceinline__ float uniform(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform(double v) { return v; }
 template <typename T>
 __device__ __forceinline__ T lane_value(T v, int l) {
   if constexpr (sizeof(T) == 4) {
@@ -283,8 +309,8 @@ struct Coef {
   T om, kf, sp, G, inv_tau, inv_gc, lgt;
   bool stress_on;
   __device__ explicit Coef(const ChanDev &c)
-      : om(T(c.omega)), kf(T(c.kf)), sp(T(c.sp)), G(T(c.G)), inv_tau(T(c.inv_tau)),
-        inv_gc(T(c.inv_gc)), lgt(T(c.lgt)), stress_on(c.G > 0.0) {}
+      : om(uniform(T(c.omega))), kf(uniform(T(c.kf))), sp(uniform(T(c.sp))), G(uniform(T(c.G))),
+        inv_tau(uniform(T(c.inv_tau))), inv_gc(uniform(T(c.inv_gc))), lgt(uniform(T(c.lgt))), stress_on(c.G > 0.0) {}
 };
 
 // Instantaneous stress (Eqs. (nlmaxwell), (sigtsum)) for the velocity
@@ -1188,7 +1214,9 @@ static_assert(kMainRing <= kMainThreads, "at most one ring node per thread");
 template <bool VE, bool NT>
 __global__ void __launch_bounds__(kMainThreads) sweep_tile_kernel(SweepArgs a) {
   __shared__ double su[2][kMainUY][kMainUX];
-  const Strip tl = a.strips[xcd_item(blockIdx.x, gridDim.x)];
+  int item = xcd_item(blockIdx.x, gridDim.x);
+  if (a.down) item = gridDim.x - 1 - item;
+  const Strip tl = a.strips[item];
   const ChanDev c = a.ch[tl.ch];
   if (!c.active) return;  // frozen channel (uniform over the workgroup)
   const int nx = c.nx, ny = c.ny;
@@ -1989,11 +2017,12 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_vec_kernel(SweepArgs a
 // row references or plain FP64). One workgroup of two wavefronts takes an
 // output strip of columns [x0, x1) and rows [y0, y1) through steps t and
 // t+1 without writing step t to memory; each lane holds NPL adjacent nodes
-// of a row (two, or four for streamed FP32 states of the instantaneous
-// model):
+// of a row:
 //  * the window is the 64 NPL columns starting HL NPL columns left of x0
-//    (HL = ceil(2 / NPL) lanes, wrapped periodically), with one column
-//    beside it on either side as the vector sweep has;
+//    (HL = ceil(4 / NPL) lanes, wrapped periodically). A step's pull and its
+//    stencil each need one more column on either side, so the window loses
+//    two columns per step and the HL outermost lanes store nothing; no
+//    columns beside the window are read;
 //  * wavefront 0 runs stage A (step t): the vector sweep's row machine over
 //    the window for rows max(y0-2, 0) .. min(y1+2, ny)-1, read from the
 //    state; each row's post-collision populations and trace (and with the
@@ -2002,178 +2031,150 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_vec_kernel(SweepArgs a
 //  * wavefront 1 runs stage B (step t+1): the same machine reading its rows
 //    from that ring, three rows behind stage A, and stores rows y0 .. y1-1
 //    of lanes HL .. 63-HL to the other buffer.
-// The two stages share one loop with one barrier per row. Splitting them
-// over two wavefronts halves what each keeps in registers, so that two or
-// three wavefronts fit a SIMD and one's arithmetic covers the other's waits.
-// After step t the window's two outermost columns on each side lack valid
-// neighbours for step t+1; the lanes holding them store nothing, so every
-// stored node saw only values of the exact step-t state. Per node the
-// arithmetic is the vector sweep's (same helpers, same pull, reference
-// shifts and collision), so the result equals two one-step sweeps to the
-// rounding of the operations. A moving top wall takes each stage's own
-// step's velocity.
+// Each wavefront runs its own loop with one barrier per row, the same number
+// in both. Splitting the stages over two wavefronts halves what each keeps in
+// registers, so that more wavefronts fit a SIMD and one's arithmetic covers
+// the other's waits. What a row's reference adds to its pulled populations
+// (FP32) is formed once per launch, a lane per row, and read from LDS.
+// Every stored node saw only values of the exact step-t state, and per node
+// the arithmetic is the vector sweep's (same helpers, same pull, reference
+// shifts and collision). A moving top wall takes each stage's own step's
+// velocity.
+//
+// Bound by the memory path. On 4096 x 1024 (us per step; in brackets the same
+// kernel with the node update left out): FP32 41.0 (39.2), time-integrated
+// FP32 52.0 (52.6), FP64 70.4 (68.9 to 75 with the alignment of its stores),
+// time-integrated FP64 91.8; 16 x 8192 x 2048 FP32 2580 (2510). Before, with
+// the columns beside the window read for stage A, row references formed per
+// row and stage A's loads issued at the end of an iteration: 50.3, 60.7, 77.3,
+// 108.5, 2790. What moved it: no side columns (the FP32 kernel 150 -> 130
+// VGPRs, 22% fewer vector instructions), loads issued before the update
+// (44.5 -> 42.6), every other launch marching downwards, so that it starts on
+// the rows written last, the likeliest to sit in the last-level cache (42.6
+// -> 41.4, time-integrated 62.7 -> 56.1), and strips that end on whole lines
+// (two_step_unit). Not kept: loads two rows ahead (spills), one node per lane
+// in FP64 (86), touching lines some rows ahead (47), four wavefronts per SIMD
+// in FP32 (42.9), four nodes per lane for cached FP32 states (43.2).
 constexpr int kV2Ring = 4;
+// The row table (FP32): shifts of the pulled populations 2, 5, 6, 4, 7, 8,
+// the row's reference, its share of d_y u_x (a fixed wall behind wall rows),
+// and the reference below (mirrored at the bottom wall).
+constexpr int kV2Tab = 9;
 
-// Side values of stage A's rows, by lane i < 24: (row offset, column offset
-// from the window start, field), with the wall rows' bounce-back sources;
-// the same meaning as kSideIn/kSideBot/kSideTop for the columns beside a
-// window that need not start on a tile. The table is written for a window
-// of 256 columns (offsets 255..257 on the right); v2_side<W> moves the
-// right side to a window of W columns. Lanes 24..26 carry the row
-// references (FP32 storage).
-struct SideEntry {
-  int dy, dc, p;
-};
-// interior rows, packed as (dy + 1) | (dc + 2) << 2 | p << 12
-#define V2SIDE(dy, dc, p) ((dy) + 1 | ((dc) + 2) << 2 | (p) << 12)
-constexpr int kV2Side[24] = {
-    V2SIDE(0, -1, 1),   V2SIDE(0, 256, 3),  V2SIDE(-1, -1, 5), V2SIDE(-1, 256, 6), V2SIDE(1, 256, 7),
-    V2SIDE(1, -1, 8),   V2SIDE(0, -1, 0),   V2SIDE(0, -2, 1),  V2SIDE(0, 0, 3),    V2SIDE(-1, -1, 2),
-    V2SIDE(-1, -2, 5),  V2SIDE(-1, 0, 6),   V2SIDE(1, -1, 4),  V2SIDE(1, 0, 7),    V2SIDE(1, -2, 8),
-    V2SIDE(0, 256, 0),  V2SIDE(0, 255, 1),  V2SIDE(0, 257, 3), V2SIDE(-1, 256, 2), V2SIDE(-1, 255, 5),
-    V2SIDE(-1, 257, 6), V2SIDE(1, 256, 4),  V2SIDE(1, 257, 7), V2SIDE(1, 255, 8)};
-#undef V2SIDE
-template <int W>
-__device__ __forceinline__ SideEntry v2_side(int i, bool bot, bool top) {
-  const int code = kV2Side[i];
-  SideEntry e{(code & 3) - 1, ((code >> 2) & 1023) - 2, code >> 12};
-  if (e.dc >= 255) e.dc += W - 256;
-  if (bot && e.dy < 0) {
-    // entries 2, 3: edge values of pulls the wall row takes from its own
-    // node (unused); the side columns' pops 2, 5, 6 bounce back from 4, 7, 8
-    const bool edge = (i == 2 || i == 3);
-    const int col = (i < 15) ? -1 : W;
-    const int back = e.p == 2 ? 4 : (e.p == 5 ? 7 : 8);
-    e = edge ? SideEntry{0, 0, 0} : SideEntry{0, col, back};
-  }
-  if (top && e.dy > 0) {
-    const bool edge = (i == 4 || i == 5);
-    const int col = (i < 15) ? -1 : W;
-    const int back = e.p == 4 ? 2 : (e.p == 7 ? 5 : 6);
-    e = edge ? SideEntry{0, 0, 0} : SideEntry{0, col, back};
-  }
-  return e;
-}
-
-template <typename T, int NPL, bool NT, bool VE, bool WALL>
-__global__ void __launch_bounds__(64 * kTwoStepWaves, VE ? 1 : kTwoStepWaves) sweep_vec2_kernel(SweepArgs a) {
+template <typename T, int NPL, bool NT, bool VE, bool WALL, bool DOWN>
+__global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(sizeof(T) == 4, NPL, VE))
+    sweep_vec2_kernel(SweepArgs a) {
   // FP32: storage relative to the row references; FP64: plain storage
   constexpr bool SHIFT = sizeof(T) == 4;
-  constexpr int W = 64 * NPL;                 // window columns
-  constexpr int HL = (2 + NPL - 1) / NPL;     // lanes per side without valid step t+1
+  constexpr int HL = (kTwoStepMargin + NPL - 1) / NPL;  // lanes per side that store nothing
   typedef typename Vec<T, NPL>::type V;
   // the ring of step-t rows: populations and trace, and with VE the stress
-  // sigma(t) (sizeof(T) x NPL x 5 KB per workgroup, x 6.5 KB with VE)
+  // sigma(t) (sizeof(T) x NPL x 2.5 KB per workgroup, x 3.25 KB with VE)
   constexpr int RP = kPlanes + (VE ? kStressPlanes : 0);
   __shared__ V ring[kV2Ring][RP][64];
+  __shared__ T rtab[SHIFT ? 64 : 1][kV2Tab];
   const int lane = threadIdx.x & 63;
   // wave 0 runs stage A, wave 1 stage B of the same strip
   const bool isA = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
-  const int sidx = xcd_item(blockIdx.x, a.n_wg);
+  int sidx = xcd_item(blockIdx.x, a.n_wg);
   if (sidx >= a.n_strips) return;  // the whole workgroup, before any barrier
+  if (DOWN) sidx = a.n_strips - 1 - sidx;
   const Strip st = a.strips[sidx];
   const ChanDev c = a.ch[st.ch];
   const T *__restrict__ A = static_cast<const T *>(a.A);
   T *__restrict__ B = static_cast<T *>(a.B);
   const int nx = c.nx, ny = c.ny;
-  const long long t = c.t + a.k;
-  const T fxA = (t < c.t_startup) ? T(c.g) : T(0);
-  const T fxB = (t + 1 < c.t_startup) ? T(c.g) : T(0);
-  const T fx = isA ? fxA : fxB;
-  // WALL: a moving top wall at this stage's step ts: its velocity (stencil
+  const long long ts = c.t + a.k + (isA ? 0 : 1);  // this stage's step
+  const T fx = uniform((ts < c.t_startup) ? T(c.g) : T(0));
+  // WALL: a moving top wall at this stage's step: its velocity (stencil
   // ghost) and, for the half-way wall, u_w/6 of step ts - 1, whose reflected
   // links step ts pulls; or the Zou-He completion of the top row
-  const long long ts = isA ? t : t + 1;
-  const T uwg = (WALL && ts < c.t_startup) ? T(c.uw) : T(0);
-  const T uw6 = (WALL && !c.zh && ts >= 1 && ts - 1 < c.t_startup) ? T(c.uw / 6.0) : T(0);
+  const T uwg = uniform((WALL && ts < c.t_startup) ? T(c.uw) : T(0));
+  const T uw6 = uniform((WALL && !c.zh && ts >= 1 && ts - 1 < c.t_startup) ? T(c.uw / 6.0) : T(0));
   const Coef<T> q(c);
   constexpr int F = kTile;
-  const long long tile00 = c.off >> 6;
   const int tiles_row = nx >> 6;
-  const long long row_stride = (long long)tiles_row * kPlanes * F;
-  auto rowbase = [&](int y) __attribute__((always_inline)) { return (tile00 + (long long)y * tiles_row) * (kPlanes * F); };
-  // column of window offset dc, wrapped, as an element offset inside a row
-  const int w0 = st.x0 - HL * NPL;
-  auto colpart = [&](int dc) __attribute__((always_inline)) -> long long {
-    int col = w0 + dc;
-    col += (col < 0) ? nx : 0;
-    col -= (col >= nx) ? nx : 0;
-    return (long long)(col >> 6) * (kPlanes * F) + (col & 63);
-  };
-  const long long lcol = colpart(NPL * lane);
-  // VE: the stress fields, three planes per tile of 64 nodes
-  const T *__restrict__ SA = static_cast<const T *>(a.SA);
-  T *__restrict__ SB = static_cast<T *>(a.SB);
-  auto srow = [&](int y) __attribute__((always_inline)) {
-    return (tile00 + (long long)y * tiles_row) * (kStressPlanes * F);
-  };
-  const long long scol = (long long)(((w0 + NPL * lane + nx) % nx) >> 6) * (kStressPlanes * F) +
-                         ((w0 + NPL * lane + nx) % nx & 63);
+  const long long row_stride = (long long)tiles_row * kPlanes * F, srow_stride = (long long)tiles_row * kStressPlanes * F;
+  const T *const A0p = A + c.off * kPlanes;
+  // this lane's first column, wrapped, as an element offset inside a row
+  int col = st.x0 - HL * NPL + NPL * lane;
+  col += (col < 0) ? nx : 0;
+  col -= (col >= nx) ? nx : 0;
+  const unsigned lcol = (unsigned)(col >> 6) * (kPlanes * F) + (col & 63);
+  const unsigned scol = (unsigned)(col >> 6) * (kStressPlanes * F) + (col & 63);
   auto clampy = [&](int y) __attribute__((always_inline)) { return y < 0 ? 0 : (y >= ny ? ny - 1 : y); };
 
   // ---- rows of the two stages
   const int A0 = st.y0 - 2 < 0 ? 0 : st.y0 - 2, A1 = st.y1 + 2 > ny ? ny : st.y1 + 2;
-  const int R0 = st.y0 - 1 < 0 ? 0 : st.y0 - 1, R1 = st.y1 + 1 > ny ? ny : st.y1 + 1;
-  const int iend = st.y1 + 3;  // iterations [A0, iend): stage B updates row i - 3
+  // the march: rows first, first + step, ...; stage A's nA rows, stage B's
+  // start from the row before its first (or its first, at the wall); the
+  // iterations whose barriers both stages pass
+  constexpr int step = DOWN ? -1 : 1;
+  const int firstA = DOWN ? A1 - 1 : A0, nA = A1 - A0;
+  const int firstB = DOWN ? st.y1 - 1 : st.y0, nB = st.y1 - st.y0;
+  const int nIter = (DOWN ? A1 - 1 - st.y0 : st.y1 - 1 - A0) + 4;
   // stage B's stores: lanes whose columns lie in [x0, x1)
   const bool store_lane = lane >= HL && NPL * (lane - HL) < st.x1 - st.x0;
-  // FP32: row references of rows A0-1 .. A0+62 (clamped), lane j holding
-  // row A0-1+j: stage B reads those of its rows from here (strips have at
-  // most 56 rows, so rows A0-1 .. A1 fit)
-  T uall = T(0);
-  if constexpr (SHIFT) uall = a.uref[c.row_off + clampy(A0 - 1 + lane)];
-  auto ref = [&](int y) __attribute__((always_inline)) {
-    return SHIFT ? lane_value(uall, clampy(y) - (A0 - 1)) : T(0);
-  };
+  // FP32: the table of rows A0-1 .. A0+62 (clamped; strips have at most 56
+  // rows, so rows A0-1 .. A1 fit)
+  if constexpr (SHIFT) {
+    if (isA) {
+      const int y = clampy(A0 - 1 + lane);
+      const float *ur = a.uref + c.row_off;
+      const bool bot = y == 0, top = y == ny - 1;
+      const T urc = ur[y], urd = ur[bot ? y : y - 1], uru = ur[top ? y : y + 1];
+      T sh[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
+      to_row_reference(sh, urd, urc, uru, bot, top);
+      T *w = rtab[lane];
+      w[0] = sh[2];
+      w[1] = sh[5];
+      w[2] = sh[6];
+      w[3] = sh[4];
+      w[4] = sh[7];
+      w[5] = sh[8];
+      w[6] = urc;
+      const T d = bot ? -urc : urd;
+      w[7] = T(0.5) * ((top ? -urc : uru) - d);
+      w[8] = d;
+    }
+    __syncthreads();
+  }
 
-  // ---- stage A: raw loads of a row of the state (window and side values)
+  // a row's values: pulled populations, P and the previous stress, moments
+  // and u~ of the window's columns, and the row's reference
+  struct Row {
+    T f[9][NPL], P[NPL], sd[NPL], mx[NPL], my[NPL], sg[VE ? 3 : 1][NPL];
+    T urc;
+  };
   struct Raw {
     V r[10];
-    V sg[VE ? 3 : 1];  // VE: the stress of the previous step at the row's own nodes
-    T side;
+    V sg[VE ? 3 : 1];
   };
-  const int li = lane < 24 ? lane : 0;
-  // element offset of this lane's side value relative to the row (decoded
-  // again on wall rows: a choice between precomputed offsets would keep them
-  // in scratch memory)
-  auto side_offset = [&](bool bot, bool top) __attribute__((always_inline)) -> long long {
-    const SideEntry e = v2_side<W>(li, bot, top);
-    return (lane < 24) ? (long long)e.dy * row_stride + colpart(e.dc) + (long long)e.p * F : lcol;
-  };
-  const long long o_in = side_offset(false, false);
+  // stage A: a row of the state (its pull's source rows, unshifted)
   auto load_raw = [&](int y, Raw &R) __attribute__((always_inline)) {
     const bool bot = (y == 0), top = (y == ny - 1);
-    const long long rb = rowbase(y);
-    const long long rd = bot ? rb : rb - row_stride, ru = top ? rb : rb + row_stride;
-    auto run = [&](long long base, int p) __attribute__((always_inline)) {
-      return *reinterpret_cast<const V *>(A + base + lcol + (long long)p * F);
+    const T *rc = A0p + (long long)y * row_stride;
+    const T *rd = bot ? rc : rc - row_stride, *ru = top ? rc : rc + row_stride;
+    auto run = [&](const T *base, int p) __attribute__((always_inline)) {
+      return *reinterpret_cast<const V *>(base + p * F + lcol);
     };
-    R.r[0] = run(rb, 0);
-    R.r[1] = run(rb, 1);
-    R.r[3] = run(rb, 3);
-    R.r[9] = run(rb, 9);
+    R.r[0] = run(rc, 0);
+    R.r[1] = run(rc, 1);
+    R.r[3] = run(rc, 3);
+    R.r[9] = run(rc, 9);
     R.r[2] = run(rd, bot ? 4 : 2);
     R.r[5] = run(rd, bot ? 7 : 5);
     R.r[6] = run(rd, bot ? 8 : 6);
     R.r[4] = run(ru, top ? 2 : 4);
     R.r[7] = run(ru, top ? 5 : 7);
     R.r[8] = run(ru, top ? 6 : 8);
-    long long o = o_in;
-    if (bot || top) o = side_offset(bot, top);  // wall rows only
-    const T *ps = A + rb + o;
     if constexpr (VE) {
+      const T *sr = static_cast<const T *>(a.SA) + c.off * kStressPlanes + (long long)y * srow_stride;
 #pragma unroll
-      for (int p = 0; p < 3; ++p) R.sg[p] = *reinterpret_cast<const V *>(SA + srow(y) + scol + (long long)p * F);
+      for (int p = 0; p < 3; ++p) R.sg[p] = *reinterpret_cast<const V *>(sr + p * F + scol);
     }
-    if constexpr (SHIFT) {
-      const int yr = y + lane - 25;
-      const T *pu = a.uref + c.row_off + (yr < 0 ? 0 : (yr >= ny ? ny - 1 : yr));
-      ps = (lane >= 24 && lane <= 26) ? pu : ps;
-    }
-    R.side = *ps;
   };
-  // ---- stage B: the same row from the LDS ring of step-t rows (no side
-  // values: lanes 0 and 63, which would use them, store nothing)
+  // stage B: the same row from the LDS ring of step-t rows
   auto load_lds = [&](int y, Raw &R) __attribute__((always_inline)) {
     const bool bot = (y == 0), top = (y == ny - 1);
     const int sc = y & (kV2Ring - 1), sd = bot ? sc : ((y - 1) & (kV2Ring - 1)), su = top ? sc : ((y + 1) & (kV2Ring - 1));
@@ -2191,133 +2192,108 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, VE ? 1 : kTwoStepWaves) sw
 #pragma unroll
       for (int p = 0; p < 3; ++p) R.sg[p] = ring[sc][kPlanes + p][lane];
     }
-    R.side = T(0);
   };
 
-  // Pulled populations, P, moments and u~ of the window's columns of row y,
-  // and (stage A) u~ of the two columns beside it (the vector sweep's
-  // assembly, fixed walls), with the row references urd, urc, uru.
-  auto assemble = [&](int y, const Raw &R, T urd, T urc, T uru, T f[9][NPL], T P[NPL], T sd[NPL], T mx[NPL],
-                      T my[NPL], U2<T> u[NPL], U2<T> &uL, U2<T> &uR) __attribute__((always_inline)) {
+  // Row y from its raw values.
+  auto assemble = [&](int y, const Raw &R, Row &w, U2<T> u[NPL]) __attribute__((always_inline)) {
     const bool bot = (y == 0), top = (y == ny - 1);
-    auto from_left = [&](const V &r, T edge, T out[NPL]) __attribute__((always_inline)) {
-      out[0] = shift_up(edge, r[NPL - 1]);
+    auto from_left = [&](const V &r, T out[NPL]) __attribute__((always_inline)) {
+      out[0] = shift_in_up(r[NPL - 1]);
 #pragma unroll
       for (int k = 1; k < NPL; ++k) out[k] = r[k - 1];
     };
-    auto from_right = [&](const V &r, T edge, T out[NPL]) __attribute__((always_inline)) {
+    auto from_right = [&](const V &r, T out[NPL]) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = 0; k < NPL - 1; ++k) out[k] = r[k + 1];
-      out[NPL - 1] = shift_down(edge, r[0]);
+      out[NPL - 1] = shift_in_down(r[0]);
     };
     auto split = [&](const V &r, T out[NPL]) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = 0; k < NPL; ++k) out[k] = r[k];
     };
-    split(R.r[0], f[0]);
-    from_left(R.r[1], lane_value(R.side, 0), f[1]);
-    from_right(R.r[3], lane_value(R.side, 1), f[3]);
-    split(R.r[9], P);
-    split(R.r[2], f[2]);
-    split(R.r[4], f[4]);
+    T sh[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+    w.urc = T(0);
+    if constexpr (SHIFT) {
+      const T *tab = rtab[y - (A0 - 1)];
+#pragma unroll
+      for (int j = 0; j < 6; ++j) sh[j] = tab[j];
+      w.urc = tab[6];
+    }
+    split(R.r[0], w.f[0]);
+    from_left(R.r[1], w.f[1]);
+    from_right(R.r[3], w.f[3]);
+    split(R.r[9], w.P);
+    split(R.r[2], w.f[2]);
+    split(R.r[4], w.f[4]);
     if (bot) {
-      split(R.r[5], f[5]);
-      split(R.r[6], f[6]);
+      split(R.r[5], w.f[5]);
+      split(R.r[6], w.f[6]);
     } else {
-      from_left(R.r[5], lane_value(R.side, 2), f[5]);
-      from_right(R.r[6], lane_value(R.side, 3), f[6]);
+      from_left(R.r[5], w.f[5]);
+      from_right(R.r[6], w.f[6]);
     }
     if (top) {
-      split(R.r[7], f[7]);
-      split(R.r[8], f[8]);
+      split(R.r[7], w.f[7]);
+      split(R.r[8], w.f[8]);
       if constexpr (WALL) {
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-          f[7][k] -= uw6;
-          f[8][k] += uw6;
+          w.f[7][k] -= uw6;
+          w.f[8][k] += uw6;
         }
       }
     } else {
-      from_right(R.r[7], lane_value(R.side, 4), f[7]);
-      from_left(R.r[8], lane_value(R.side, 5), f[8]);
+      from_right(R.r[7], w.f[7]);
+      from_left(R.r[8], w.f[8]);
     }
     const bool zhtop = WALL && top && c.zh;
 #pragma unroll
     for (int k = 0; k < NPL; ++k) {
       T g[9];
 #pragma unroll
-      for (int i = 0; i < 9; ++i) g[i] = f[i][k];
-      if constexpr (SHIFT) to_row_reference(g, urd, urc, uru, bot, top);
-      if (zhtop) zou_he_top<T, SHIFT>(g, uwg, urc, fx);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) f[i][k] = g[i];
-      moments<T>(g, sd[k], mx[k], my[k]);
-      u[k] = u_tilde<T, SHIFT>(sd[k], mx[k], my[k], fx, urc);
-    }
-    uL = uR = U2<T>{T(0), T(0)};
-    if (isA) {
-      T l[9], r[9];
-      l[0] = lane_value(R.side, 6);
-      l[1] = lane_value(R.side, 7);
-      l[3] = lane_value(R.side, 8);
-      l[2] = lane_value(R.side, 9);
-      l[5] = lane_value(R.side, 10);
-      l[6] = lane_value(R.side, 11);
-      l[4] = lane_value(R.side, 12);
-      l[7] = lane_value(R.side, 13);
-      l[8] = lane_value(R.side, 14);
-      r[0] = lane_value(R.side, 15);
-      r[1] = lane_value(R.side, 16);
-      r[3] = lane_value(R.side, 17);
-      r[2] = lane_value(R.side, 18);
-      r[5] = lane_value(R.side, 19);
-      r[6] = lane_value(R.side, 20);
-      r[4] = lane_value(R.side, 21);
-      r[7] = lane_value(R.side, 22);
-      r[8] = lane_value(R.side, 23);
-      if constexpr (WALL) {
-        const T wc = top ? uw6 : T(0);
-        l[7] -= wc;
-        l[8] += wc;
-        r[7] -= wc;
-        r[8] += wc;
-      }
+      for (int i = 0; i < 9; ++i) g[i] = w.f[i][k];
       if constexpr (SHIFT) {
-        to_row_reference(l, urd, urc, uru, bot, top);
-        to_row_reference(r, urd, urc, uru, bot, top);
+#pragma clang fp contract(off)
+        g[2] += sh[0];
+        g[5] += sh[1];
+        g[6] += sh[2];
+        g[4] += sh[3];
+        g[7] += sh[4];
+        g[8] += sh[5];
       }
-      if (zhtop) {
-        zou_he_top<T, SHIFT>(l, uwg, urc, fx);
-        zou_he_top<T, SHIFT>(r, uwg, urc, fx);
-      }
-      T s0, m0, n0;
-      moments<T>(l, s0, m0, n0);
-      uL = u_tilde<T, SHIFT>(s0, m0, n0, fx, urc);
-      moments<T>(r, s0, m0, n0);
-      uR = u_tilde<T, SHIFT>(s0, m0, n0, fx, urc);
+      if (zhtop) zou_he_top<T, SHIFT>(g, uwg, w.urc, fx);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) w.f[i][k] = g[i];
+      moments<T>(g, w.sd[k], w.mx[k], w.my[k]);
+      u[k] = u_tilde<T, SHIFT>(w.sd[k], w.mx[k], w.my[k], fx, w.urc);
     }
+#pragma unroll
+    for (int p = 0; p < (VE ? 3 : 1); ++p)
+#pragma unroll
+      for (int k = 0; k < NPL; ++k) w.sg[p][k] = VE ? R.sg[p][k] : T(0);
   };
 
-  // Update of row y from its assembled state (fc ..., uCur, side u~, the
-  // references) and u~ of the rows below and above; out and trT receive
-  // the new populations and trace.
-  auto update = [&](int y, T fc[9][NPL], const T Pc[NPL], const T sdc[NPL], const T mxc[NPL], const T myc[NPL],
-                    const U2<T> uPrev[NPL], const U2<T> uCur[NPL], const U2<T> uNext[NPL], U2<T> uLc, U2<T> uRc,
-                    const T urC[3], const T sgc[VE ? 3 : 1][NPL], V out[RP]) __attribute__((always_inline)) {
-    const T urc = urC[1];
-    const T urd = (y == 0) ? -urc : urC[0];
-    const T uru = (y == ny - 1) ? T(2) * uwg - (WALL && c.zh ? urd : urc) : urC[2];
-    // FP32: the references' share of d_y u_x (ghost rows mirrored); FP64
-    // stores plain populations and has none
-    const T kref = SHIFT ? T(0.5) * (uru - urd) : T(0);
+  // Update of row y from its assembled values and u~ of the rows below, at
+  // and above it; out receives the new populations, trace (and stress).
+  auto update = [&](int y, const Row &w, const U2<T> uPrev[NPL], const U2<T> uCur[NPL], const U2<T> uNext[NPL],
+                    V out[RP]) __attribute__((always_inline)) {
+    T kref = T(0);
+    if constexpr (SHIFT) {
+      const T *tab = rtab[y - (A0 - 1)];
+      kref = tab[7];
+      if (WALL && y == ny - 1) {
+        const T urd = tab[8];
+        kref = T(0.5) * ((T(2) * uwg - (c.zh ? urd : w.urc)) - urd);
+      }
+    }
 #pragma unroll
     for (int k = 0; k < NPL; ++k) {
       U2<T> lf, rt;
-      if (k == 0) lf = U2<T>{shift_up(uLc.x, uCur[NPL - 1].x), shift_up(uLc.y, uCur[NPL - 1].y)};
+      if (k == 0) lf = U2<T>{shift_in_up(uCur[NPL - 1].x), shift_in_up(uCur[NPL - 1].y)};
       else lf = uCur[k - 1];
-      if (k == NPL - 1) rt = U2<T>{shift_down(uRc.x, uCur[0].x), shift_down(uRc.y, uCur[0].y)};
+      if (k == NPL - 1) rt = U2<T>{shift_in_down(uCur[0].x), shift_in_down(uCur[0].y)};
       else rt = uCur[k + 1];
-      U2<T> dn = uPrev[k], up = uNext[k];
+      U2<T> dn = DOWN ? uNext[k] : uPrev[k], up = DOWN ? uPrev[k] : uNext[k];
       if (y == 0) dn = U2<T>{-uCur[k].x, -uCur[k].y};
       // no-slip ghosts behind the half-way walls (moving at u_w above), or
       // behind a Zou-He node wall mirrored through the wall row
@@ -2327,11 +2303,11 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, VE ? 1 : kTwoStepWaves) sw
       }
       T g[9], o[9], tr, sn[3];
 #pragma unroll
-      for (int i = 0; i < 9; ++i) g[i] = fc[i][k];
-      const T sp[3] = {VE ? sgc[0][k] : T(0), VE ? sgc[VE ? 1 : 0][k] : T(0), VE ? sgc[VE ? 2 : 0][k] : T(0)};
+      for (int i = 0; i < 9; ++i) g[i] = w.f[i][k];
+      const T sp[3] = {VE ? w.sg[0][k] : T(0), VE ? w.sg[VE ? 1 : 0][k] : T(0), VE ? w.sg[VE ? 2 : 0][k] : T(0)};
       double ob[OF_COUNT];
-      node_update<T, SHIFT, false, VE>(g, sdc[k], mxc[k], myc[k], Pc[k], fx, lf, rt, dn, up, urc, kref, q, c.nnp, sp,
-                                       sn, o, tr, ob);
+      node_update<T, SHIFT, false, VE>(g, w.sd[k], w.mx[k], w.my[k], w.P[k], fx, lf, rt, dn, up, w.urc, kref, q, c.nnp,
+                                       sp, sn, o, tr, ob);
 #pragma unroll
       for (int i = 0; i < 9; ++i) out[i][k] = o[i];
       out[9][k] = tr;
@@ -2341,148 +2317,99 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, VE ? 1 : kTwoStepWaves) sw
       }
     }
   };
-
-  // The state each wave carries from one iteration to the next: its
-  // assembled current row and u~ of the rows below and at it (stage A: row
-  // i and the raw loads of row i+1; stage B: row i-3).
-  T fc[9][NPL], Pc[NPL], sdc[NPL], mxc[NPL], myc[NPL], urC[3], sgc[VE ? 3 : 1][NPL];
-  U2<T> uPrev[NPL], uCur[NPL], uLc, uRc;
-  Raw R;
-  // VE: the stress of the previous step at a row's nodes, from its loads
-  auto take_sigma = [&](const Raw &Q, T sg[VE ? 3 : 1][NPL]) __attribute__((always_inline)) {
+  auto copy_u = [&](U2<T> to[NPL], const U2<T> from[NPL]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < (VE ? 3 : 1); ++p)
-#pragma unroll
-      for (int k = 0; k < NPL; ++k) sg[p][k] = VE ? Q.sg[p][k] : T(0);
+    for (int k = 0; k < NPL; ++k) to[k] = from[k];
   };
-  if (isA) {
-    Raw Rp;
-    const int yp = clampy(A0 - 1);
-    load_raw(yp, Rp);
-    load_raw(A0, R);
-    T ftmp[9][NPL], Ptmp[NPL], s0[NPL], m0[NPL], n0[NPL];
-    U2<T> hl, hr;
-    // row references (FP32; zero in FP64, which stores plain populations)
-    auto refs = [&](const Raw &Q, T u[3]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) u[j] = SHIFT ? lane_value(Q.side, 24 + j) : T(0);
-    };
-    T urp[3];
-    refs(Rp, urp);
-    assemble(yp, Rp, urp[0], urp[1], urp[2], ftmp, Ptmp, s0, m0, n0, uPrev, hl, hr);
-    refs(R, urC);
-    assemble(A0, R, urC[0], urC[1], urC[2], fc, Pc, sdc, mxc, myc, uCur, uLc, uRc);
-    take_sigma(R, sgc);
-    load_raw(clampy(A0 + 1), R);
-  } else {
-#pragma unroll
-    for (int k = 0; k < NPL; ++k) {
-      uPrev[k] = uCur[k] = U2<T>{T(0), T(0)};
-      Pc[k] = sdc[k] = mxc[k] = myc[k] = T(0);
-#pragma unroll
-      for (int j = 0; j < 9; ++j) fc[j][k] = T(0);
-    }
-    uLc = uRc = U2<T>{T(0), T(0)};
-    urC[0] = urC[1] = urC[2] = T(0);
-#pragma unroll
-    for (int j = 0; j < 10; ++j) R.r[j] = V{};
-#pragma unroll
-    for (int j = 0; j < (VE ? 3 : 1); ++j) R.sg[j] = V{};
-    R.side = T(0);
-    take_sigma(R, sgc);
-  }
 
-  // Iteration i. Stage A (rows [A0, A1)): assembles row i+1 from the loads
-  // issued in the previous iteration, updates row i into ring slot i mod 4,
-  // then issues the loads of row i+2. Stage B: assembles row i-2 from the
-  // ring (rows [R0, R1)), updates row i-3 and stores it (rows [y0, y1)).
-  // One barrier per iteration orders stage A's ring writes before stage B's
-  // reads three iterations later, and stage B's reads before the slot is
-  // written again; both waves run every iteration.
-  auto iteration = [&](int i) __attribute__((always_inline)) {
-    const int r = isA ? i + 1 : i - 2, y = isA ? i : i - 3;
-    const bool do_asm = isA ? (i < A1) : (r >= R0 && r < R1);
-    const bool do_upd = isA ? (i < A1) : (y >= st.y0 && y < st.y1);
-    T fn[9][NPL], Pn[NPL], sdn[NPL], mxn[NPL], myn[NPL], urN[3], sgn[VE ? 3 : 1][NPL];
-    U2<T> uNext[NPL], uLn, uRn;
-    if (do_asm) {
-      if (!isA) load_lds(r, R);
-      const int rr = clampy(r);
-#pragma unroll
-      for (int j = 0; j < 3; ++j) urN[j] = !SHIFT ? T(0) : (isA ? lane_value(R.side, 24 + j) : ref(rr - 1 + j));
-      assemble(rr, R, urN[0], urN[1], urN[2], fn, Pn, sdn, mxn, myn, uNext, uLn, uRn);
-      take_sigma(R, sgn);
-    } else {
-#pragma unroll
-      for (int p = 0; p < (VE ? 3 : 1); ++p)
-#pragma unroll
-        for (int k = 0; k < NPL; ++k) sgn[p][k] = T(0);
-#pragma unroll
-      for (int k = 0; k < NPL; ++k) {
-        uNext[k] = U2<T>{T(0), T(0)};
-        Pn[k] = sdn[k] = mxn[k] = myn[k] = T(0);
-#pragma unroll
-        for (int j = 0; j < 9; ++j) fn[j][k] = T(0);
-      }
-      uLn = uRn = U2<T>{T(0), T(0)};
-      urN[0] = urN[1] = urN[2] = T(0);
+  Row wa, wb;
+  U2<T> uPrev[NPL], uCur[NPL], uNext[NPL];
+  Raw R;
+  if (isA) {
+    // Iteration j, row y: assembles the next row from the loads issued in the
+    // previous iteration, issues those of the row after it (rows clamped to
+    // the lattice), in flight during the update and across the barrier, and
+    // updates row y into ring slot y mod 4.
+    {
+      Raw Rp;
+      const int yp = clampy(firstA - step);
+      load_raw(yp, Rp);
+      load_raw(firstA, R);
+      assemble(yp, Rp, wb, uPrev);
+      assemble(firstA, R, wa, uCur);
+      load_raw(clampy(firstA + step), R);
     }
-    if (do_upd) {
+    auto iteration = [&](int y, const Row &cur, Row &next) __attribute__((always_inline)) {
+      assemble(clampy(y + step), R, next, uNext);
+      load_raw(clampy(y + 2 * step), R);
       V out[RP];
-      update(y, fc, Pc, sdc, mxc, myc, uPrev, uCur, uNext, uLc, uRc, urC, sgc, out);
-      if (isA) {
-        const int slot = y & (kV2Ring - 1);
+      update(y, cur, uPrev, uCur, uNext, out);
+      const int slot = y & (kV2Ring - 1);
 #pragma unroll
-        for (int p = 0; p < RP; ++p) ring[slot][p][lane] = out[p];
-      } else if (store_lane) {
-        T *w = B + rowbase(y) + lcol;
+      for (int p = 0; p < RP; ++p) ring[slot][p][lane] = out[p];
+      copy_u(uPrev, uCur);
+      copy_u(uCur, uNext);
+      __syncthreads();
+    };
+#pragma unroll 1
+    for (int j = 0; j < nA; j += 2) {
+      iteration(firstA + step * j, wa, wb);
+      if (j + 1 >= nA) break;
+      iteration(firstA + step * (j + 1), wb, wa);
+    }
+    for (int j = nA; j < nIter; ++j) __syncthreads();
+  } else {
+    // Three iterations behind stage A: in iteration j it assembles the row two
+    // before stage A's row from the ring and updates the one before that.
+    // Stage A writes its row meanwhile, so the barriers order its writes
+    // before these reads and these before a slot is written again.
+    const int start = clampy(firstB - step);
+    for (int j = (start - firstA) * step + 2; j > 0; --j) __syncthreads();
+    load_lds(start, R);
+    assemble(start, R, wa, uCur);
+    __syncthreads();
+    if (start != firstB) {
+      copy_u(uPrev, uCur);
+      load_lds(firstB, R);
+      assemble(firstB, R, wa, uCur);
+      __syncthreads();
+    }
+    T *w = B + c.off * kPlanes + (long long)firstB * row_stride;
+    T *ws = VE ? static_cast<T *>(a.SB) + c.off * kStressPlanes + (long long)firstB * srow_stride : nullptr;
+    auto iteration = [&](int y, const Row &cur, Row &next) __attribute__((always_inline)) {
+      const int yn = clampy(y + step);
+      load_lds(yn, R);
+      assemble(yn, R, next, uNext);
+      V out[RP];
+      update(y, cur, uPrev, uCur, uNext, out);
+      if (store_lane) {
 #pragma unroll
         for (int p = 0; p < kPlanes; ++p) {
-          if constexpr (NT) __builtin_nontemporal_store(out[p], reinterpret_cast<V *>(w + (long long)p * F));
-          else *reinterpret_cast<V *>(w + (long long)p * F) = out[p];
+          V *d = reinterpret_cast<V *>(w + p * F + lcol);
+          if constexpr (NT) __builtin_nontemporal_store(out[p], d);
+          else *d = out[p];
         }
         if constexpr (VE) {
-          T *ws = SB + srow(y) + scol;
 #pragma unroll
           for (int p = 0; p < 3; ++p) {
-            if constexpr (NT) __builtin_nontemporal_store(out[kPlanes + p], reinterpret_cast<V *>(ws + (long long)p * F));
-            else *reinterpret_cast<V *>(ws + (long long)p * F) = out[kPlanes + p];
+            V *d = reinterpret_cast<V *>(ws + p * F + scol);
+            if constexpr (NT) __builtin_nontemporal_store(out[kPlanes + p], d);
+            else *d = out[kPlanes + p];
           }
         }
       }
-    }
-    uLc = uLn;
-    uRc = uRn;
-    urC[0] = urN[0];
-    urC[1] = urN[1];
-    urC[2] = urN[2];
-#pragma unroll
-    for (int p = 0; p < (VE ? 3 : 1); ++p)
-#pragma unroll
-      for (int k = 0; k < NPL; ++k) sgc[p][k] = sgn[p][k];
-#pragma unroll
-    for (int k = 0; k < NPL; ++k) {
-      uPrev[k] = uCur[k];
-      uCur[k] = uNext[k];
-      Pc[k] = Pn[k];
-      sdc[k] = sdn[k];
-      mxc[k] = mxn[k];
-      myc[k] = myn[k];
-#pragma unroll
-      for (int j = 0; j < 9; ++j) fc[j][k] = fn[j][k];
-    }
-    // the loads of row i+2 (clamped to the lattice), in flight across the
-    // barrier
-    if (isA && i + 1 < A1) load_raw(clampy(i + 2), R);
-    __syncthreads();
-  };
-  // unrolled twice: the two-deep state swaps stay in fixed registers (the
-  // trip count is the same for both wavefronts, so they pass the same
-  // barriers)
+      w += step * row_stride;
+      if constexpr (VE) ws += step * srow_stride;
+      copy_u(uPrev, uCur);
+      copy_u(uCur, uNext);
+      __syncthreads();
+    };
 #pragma unroll 1
-  for (int i = A0; i < iend; i += 2) {
-    iteration(i);
-    if (i + 1 < iend) iteration(i + 1);
+    for (int j = 0; j < nB; j += 2) {
+      iteration(firstB + step * j, wa, wb);
+      if (j + 1 >= nB) break;
+      iteration(firstB + step * (j + 1), wb, wa);
+    }
   }
 }
 
@@ -2813,12 +2740,14 @@ static_assert(kSafRing <= kSafThreads, "at most one ring node per thread");
 template <bool NT>
 __global__ void __launch_bounds__(kSafThreads) saf_fused_kernel(const double *__restrict__ A,
                                                                 double *__restrict__ B, const ChanDev *ch,
-                                                                const Strip *tiles, int k) {
+                                                                const Strip *tiles, int k, int down) {
   __shared__ double su[2][kSafUY][kSafUX];
   __shared__ double sT[3][kSafSY][kSafSX];
   constexpr int cx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
   constexpr int cy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
-  const Strip tl = tiles[xcd_item(blockIdx.x, gridDim.x)];
+  int item = xcd_item(blockIdx.x, gridDim.x);
+  if (down) item = gridDim.x - 1 - item;
+  const Strip tl = tiles[item];
   const ChanDev c = ch[tl.ch];
   if (!c.active) return;  // frozen channel (uniform over the workgroup)
   const int nx = c.nx, ny = c.ny;
@@ -3142,15 +3071,20 @@ hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, co
   return hipGetLastError();
 }
 
+template <typename T, int NPL, bool VE, bool WALL, bool DOWN>
+void launch_two_step_d(const SweepArgs &a, hipStream_t s) {
+  const dim3 grid(a.n_wg), block(64 * kTwoStepWaves);
+  if (a.nt) hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, true, VE, WALL, DOWN>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, false, VE, WALL, DOWN>), grid, block, 0, s, a);
+}
 template <typename T, int NPL, bool VE>
 void launch_two_step_t(const SweepArgs &a, hipStream_t s) {
-  const dim3 grid(a.n_wg), block(64 * kTwoStepWaves);
   if (a.wall) {
-    if (a.nt) hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, true, VE, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, false, VE, true>), grid, block, 0, s, a);
+    if (a.down) launch_two_step_d<T, NPL, VE, true, true>(a, s);
+    else launch_two_step_d<T, NPL, VE, true, false>(a, s);
   } else {
-    if (a.nt) hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, true, VE, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, false, VE, false>), grid, block, 0, s, a);
+    if (a.down) launch_two_step_d<T, NPL, VE, false, true>(a, s);
+    else launch_two_step_d<T, NPL, VE, false, false>(a, s);
   }
 }
 
@@ -3221,13 +3155,13 @@ int two_step_blocks_per_cu(bool fp32, bool nt, bool ve) {
   constexpr int b = 64 * kTwoStepWaves;
   hipError_t e;
   if (fp32 && two_step_npl(fp32, nt, ve) == 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 4, true, false, false>, b, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 4, true, false, false, false>, b, 0);
   else if (fp32)
-    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, true, false>, b, 0)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, false, false>, b, 0);
+    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, true, false, false>, b, 0)
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, false, false, false>, b, 0);
   else
-    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, true, false>, b, 0)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, false, false>, b, 0);
+    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, true, false, false>, b, 0)
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, false, false, false>, b, 0);
   return (e == hipSuccess && n > 0) ? n : 1;
 }
 
@@ -3244,10 +3178,11 @@ static int saf_blocks(long long plane) {
 }
 
 hipError_t launch_saf_fused(const double *A, double *B, const ChanDev *ch, const Strip *tiles, int n_tiles, int k,
-                            int nt, hipStream_t s) {
+                            int nt, int down, hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
-  if (nt) hipLaunchKernelGGL(saf_fused_kernel<true>, dim3(n_tiles), dim3(kSafThreads), 0, s, A, B, ch, tiles, k);
-  else hipLaunchKernelGGL(saf_fused_kernel<false>, dim3(n_tiles), dim3(kSafThreads), 0, s, A, B, ch, tiles, k);
+  if (nt) hipLaunchKernelGGL(saf_fused_kernel<true>, dim3(n_tiles), dim3(kSafThreads), 0, s, A, B, ch, tiles, k,
+                             down);
+  else hipLaunchKernelGGL(saf_fused_kernel<false>, dim3(n_tiles), dim3(kSafThreads), 0, s, A, B, ch, tiles, k, down);
   return hipGetLastError();
 }
 

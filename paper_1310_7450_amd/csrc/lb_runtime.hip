@@ -231,9 +231,9 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize
 // cost more than the halos of strips. Measured, us per step, boxes against
 // the path they replace:
 //  * aligned widths (vector class; two steps per launch): FP32 512 x 512 7.3
-//    against 20.2, 1024 x 1024 21.3 / 27.0, 2048 x 1024 41.1 / 34.4; FP64
-//    1536 x 512 27.2 / 31.7, 1024 x 1024 34.2 / 32.1; FP64 time-integrated
-//    1024 x 512 19.4 / 23.7, 1536 x 512 29.3 / 24.1;
+//    against 20.2, 1024 x 768 16.0 / 17.9, 1024 x 1024 20.2 / 18.6; FP64
+//    1024 x 512 18.1 / 23.8, 1024 x 768 26.4 / 24.1, and about the same with
+//    the time-integrated stress;
 //  * other widths above 64: FP32 (one step per launch) 200 x 20 1.9 / 14.3,
 //    1000 x 300 8.8 / 21.3, 4000 x 2000 180 / 210; FP64 (tiles) 200 x 20
 //    1.9 / 6.2, 1000 x 300 11.4 / 12.2, 1000 x 500 18.0 / 16.6, but
@@ -251,7 +251,7 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
   enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, KINDS };
   const bool fp32 = esize == 4, ve = o->viscoelastic;
   const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
-  const long long limit[KINDS] = {fp32 ? M + M / 4 : (ve ? 5 * M / 8 : 3 * M / 4), (fp32 || ve) ? 8 * M : 3 * M / 10,
+  const long long limit[KINDS] = {fp32 ? 7 * M / 8 : 5 * M / 8, (fp32 || ve) ? 8 * M : 3 * M / 10,
                                   always, ve ? always : (fp32 ? M : M / 4), M};
   std::vector<int> kind(n, -1);
   long long nodes[KINDS] = {};
@@ -270,14 +270,13 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
   return ok;
 }
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
-// Stored columns of the two-step strips of a width at npl nodes per lane:
-// at most two_step_cols(npl) (248 at four, 124 at two), in multiples of
-// npl, as even as possible.
-std::vector<int> two_step_cuts(int nx, int npl) {
-  const int cols = two_step_cols(npl);
-  const int units = nx / npl, m = (nx + cols - 1) / cols;
+// Stored columns of the two-step strips of a width: at most two_step_cols,
+// in multiples of two_step_unit columns, as even as possible.
+std::vector<int> two_step_cuts(int nx, int npl, bool fp32) {
+  const int U = two_step_unit(fp32), cols = two_step_cols(npl, fp32);
+  const int units = nx / U, m = (nx + cols - 1) / cols;
   std::vector<int> x(1, 0);
-  for (int i = 0; i < m; ++i) x.push_back(x.back() + npl * (units / m + (i < units % m)));
+  for (int i = 0; i < m; ++i) x.push_back(x.back() + U * (units / m + (i < units % m)));
   return x;
 }
 // Rows per two-step strip: whole rounds of resident strips cost each
@@ -287,13 +286,13 @@ std::vector<int> two_step_cuts(int nx, int npl) {
 // start, so the cost is the strips' rows (each plus 6) over the slots (the
 // tallest strips then win: 16 x 8192 x 2048 at 56 rows 108.7-108.9k MLUPS,
 // at 50 rows, the whole-round choice, 107.3k).
-int two_step_rows(const std::vector<lb_channel> &chans, int npl, int slots) {
+int two_step_rows(const std::vector<lb_channel> &chans, int npl, bool fp32, int slots) {
   int best = 16;
   double best_cost = 1e300;
   for (int H = 16; H <= kTwoStepMaxRows; ++H) {
     long long S = 0, work = 0;
     for (const lb_channel &c : chans) {
-      const long long cuts = (long long)(two_step_cuts(c.nx, npl).size() - 1), full = c.ny / H, rem = c.ny % H;
+      const long long cuts = (long long)(two_step_cuts(c.nx, npl, fp32).size() - 1), full = c.ny / H, rem = c.ny % H;
       S += cuts * (full + (rem > 0));
       work += cuts * (full * (H + 6) + (rem > 0 ? rem + 6 : 0));
     }
@@ -450,8 +449,8 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
   }
   return best;
 }
-void add_two_step_strips(int ci, const lb_channel &c, int npl, int H, std::vector<Strip> &out) {
-  const std::vector<int> x = two_step_cuts(c.nx, npl);
+void add_two_step_strips(int ci, const lb_channel &c, int npl, bool fp32, int H, std::vector<Strip> &out) {
+  const std::vector<int> x = two_step_cuts(c.nx, npl, fp32);
   for (int y0 = 0; y0 < c.ny; y0 += H)
     for (size_t s = 0; s + 1 < x.size(); ++s)
       out.push_back(Strip{ci, x[s], y0, std::min(y0 + H, c.ny), 0, x[s + 1]});
@@ -556,7 +555,7 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
   const int npl = two_step_npl(L.esize == 4, streamed(L), o->viscoelastic);
   for (int i = 0; i < n && two_step_handle(o, o->obs_every > 0 ? o->obs_every : kDefaultK); ++i)
     if (two_step_channel(c[i], L.esize))
-      L.max_two += (int)(two_step_cuts(c[i].nx, npl).size() - 1) * ((c[i].ny + min_rows - 1) / min_rows);
+      L.max_two += (int)(two_step_cuts(c[i].nx, npl, L.esize == 4).size() - 1) * ((c[i].ny + min_rows - 1) / min_rows);
   L.off_btiles = take(sizeof(Strip) * std::max(L.n_tiles, 1));
   // boxes of 64 nodes, or 4096 boxes and two per channel
   L.max_boxes = std::max<long long>(4096 + 2ll * n, L.plane / 64);
@@ -769,11 +768,11 @@ lb_status upload_strips(lb_handle *h, bool all) {
       }
       const int npl = two_step_npl(es == 4, streamed(h->L), h->opt.viscoelastic);
       const int H = h->opt.strip_rows > 0 ? std::min(h->opt.strip_rows, kTwoStepMaxRows)
-                                          : two_step_rows(elig, npl, h->slots);
+                                          : two_step_rows(elig, npl, es == 4, h->slots);
       for (int i = 0; i < h->n_ch; ++i) {
         if (!h->active[i] || h->blk_ok[i]) continue;
         if (h->two_step && two_step_channel(h->in[i], es)) {
-          add_two_step_strips(i, h->in[i], npl, H, two);
+          add_two_step_strips(i, h->in[i], npl, es == 4, H, two);
           wall = wall || two_step_wall(h->in[i]);
         } else if (!(h->two_step && narrow_two_step_channel(&h->opt, h->in[i], es)) && !tiled(&h->opt, h->in[i])) {
           add_strips(i, h->L.ch[i], es, rows_of(i), stack, braw);
@@ -842,12 +841,16 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
   if (h->opt.stress_force) {
     HIPCHECK(h, launch_saf_fused(static_cast<const double *>(h->buf[src]), static_cast<double *>(h->buf[src ^ 1]),
                                  h->dch, h->tiles, h->L.n_tiles, k,
-                                 streamed(h->L), s));
+                                 streamed(h->L), src == 1, s));
     return LB_OK;
   }
   Strip *tl = block ? h->btiles : h->tiles;
   const int ntl = block ? h->n_btiles : h->n_tiles;
-  if (ntl) HIPCHECK(h, launch_tiles(sweep_args(h, tl, 0, ntl, src, k), s));
+  if (ntl) {
+    SweepArgs a = sweep_args(h, tl, 0, ntl, src, k);
+    a.down = (src == 1);
+    HIPCHECK(h, launch_tiles(a, s));
+  }
   const int *begin = block ? h->bact_begin : h->act_begin, *count = block ? h->bact_count : h->act_count;
   Strip *fwd = block ? h->dbact : h->dact, *rev = block ? h->dbact_rev : h->dact_rev;
   for (int c = 0; c < kClasses; ++c) {
@@ -932,6 +935,7 @@ lb_status capture(lb_handle *h, int src) {
       if (h->two_count) {
         SweepArgs a = sweep_args(h, h->dtwo, 0, h->two_count, src ^ ((k / 2) & 1), k);
         a.wall = h->two_wall;
+        a.down = (src ^ ((k / 2) & 1)) == 1;
         a.n_wg = h->two_count;  // one strip per workgroup (a wavefront per stage)
         hipError_t e = launch_two_step(h->opt.precision == LB_FP32_SHIFTED, a, h->cap);
         if (e != hipSuccess) st = hipfail(h, e, "launch_two_step");
@@ -1232,8 +1236,12 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       return bail(LB_EHIP);
-    h->slots = two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED, streamed(h->L), o->viscoelastic) *
-               std::max(cus, 1);
+    // four and more strips on a CU in even numbers: each is two wavefronts, and
+    // an odd one leaves two SIMDs with a wavefront more than the others
+    // (time-integrated FP32, 4096 x 1024: five strips 54.5 us, four 52.0)
+    int per_cu = two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED, streamed(h->L), o->viscoelastic);
+    if (per_cu >= 4) per_cu &= ~1;
+    h->slots = per_cu * std::max(cus, 1);
     h->simds = 4 * std::max(cus, 1);
     h->cus = std::max(cus, 1);
     h->n2slots = (long long)narrow_two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED) * std::max(cus, 1);
