@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <limits>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -28,6 +29,7 @@ namespace {
 
 constexpr int kDefaultK = 1000;
 constexpr size_t kAlign = 256;
+constexpr size_t kStageNodes = 4096;  // 320 KB
 #ifndef LB_WG_WAVES
 #define LB_WG_WAVES 4
 #endif
@@ -59,10 +61,14 @@ struct Layout {
   size_t off_bstrips = 0, off_brstrips = 0, off_tstrips = 0;
   size_t off_blk = 0;     // boxes of the channels that run many steps per launch
   size_t off_gpb = 0;     // boxes of the pressure-driven channels
+  // FP32: staging of a state where the other buffer holds too few rows of it
+  // (see store_state), and of every state of at most kStageNodes
+  size_t off_stage = 0, stage = 0;
   size_t off_btiles = 0;  // tiles of the tiled channels without two-step strips
   int strip_cap = 0;      // entries of each one-step strip list
   int max_two = 0;
   long long max_boxes = 0;
+  std::vector<char> blk_ok;  // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
   std::vector<ChanDev> ch;
 };
 
@@ -147,25 +153,6 @@ double wall_pull_term(const lb_channel &q, int i, long long t) {
   const double uw = (q.top_wall == LB_WALL_HALFWAY && t >= 1 && t - 1 < q.t_startup) ? q.wall_velocity : 0.0;
   const int o = HOPP[i];
   return -6.0 * hweight(o) * HCX[o] * uw;
-}
-
-// Zou-He completion (the kernels' zou_he_top) of the top row's populations
-// entering from above, on a host copy of a channel's state at step t:
-// no flow through the wall, n4 = n2, and the diagonals such that
-// (m + f/2)/s is the wall velocity of step t.
-void host_zou_he_top(const lb_channel &q, long long t, double *pops) {
-  const size_t N = (size_t)q.nx * q.ny;
-  const double uw = t < q.t_startup ? q.wall_velocity : 0.0, fx = t < q.t_startup ? q.force : 0.0;
-  for (int x = 0; x < q.nx; ++x) {
-    const size_t id = (size_t)(q.ny - 1) * q.nx + x;
-    double f[9];
-    for (int i = 0; i < 9; ++i) f[i] = pops[(size_t)i * N + id];
-    const double s = (f[0] + f[1] + f[3]) + 2.0 * (f[2] + f[5] + f[6]);
-    const double d87 = (s * uw - 0.5 * fx) - ((f[1] - f[3]) + (f[5] - f[6]));
-    pops[4 * N + id] = f[2];
-    pops[8 * N + id] = 0.5 * ((f[5] + f[6]) + d87);
-    pops[7 * N + id] = 0.5 * ((f[5] + f[6]) - d87);
-  }
 }
 
 int strip_rows_for(int cls, int nx, int ny, int requested) {
@@ -415,6 +402,7 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
                wave = fp32 ? 0.29 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
   for (int S = 1; S <= K / 2 && S <= 64; ++S) {  // (beyond 64 a launch's own time no longer counts)
     if ((K / 2) % S) continue;
+    std::map<int, std::vector<BoxShape>> shapes;  // by largest region (empty: not every channel has one)
     for (int th = 256; th <= 1024; th *= 2) {
       const int resident = (fp32 ? 24 : 16) * 64 / th;  // workgroups of a CU, by registers
       for (int part : {8, 6, 4, 3, 2}) {
@@ -422,11 +410,20 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
         p.S = S;
         p.threads = th;
         double W = 0, R = 0, V = 0, vmax = 0;
-        bool ok = true;
-        for (const lb_channel &c : chans) {
+        const auto [it, added] = shapes.try_emplace(th * part / 8);
+        for (size_t i = 0; added && i < chans.size(); ++i) {
           BoxShape b;
-          if (!(ok = box_shape(c, S, th * part / 8, b))) break;
-          p.shape.push_back(b);
+          if (!box_shape(chans[i], S, th * part / 8, b)) {
+            it->second.clear();
+            break;
+          }
+          it->second.push_back(b);
+        }
+        if (it->second.empty()) continue;
+        p.shape = it->second;
+        for (size_t i = 0; i < chans.size(); ++i) {
+          const lb_channel &c = chans[i];
+          const BoxShape b = p.shape[i];
           const double w = (double)box_count(c, b);
           const int v0 = box_waves(c, b, S, 0);
           const double v = 0.5 * (v0 + box_waves(c, b, S, S - 1));
@@ -435,7 +432,7 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
           V += w * v;
           vmax = std::max(vmax, v);
         }
-        if (!ok || W > (double)room) continue;
+        if (W > (double)room) continue;
         const double slots = (double)resident * cus, rounds = std::ceil(W / slots);
         const double m = W <= slots ? std::ceil(W / cus) : 1.3;
         const double us =
@@ -557,11 +554,22 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
     if (two_step_channel(c[i], L.esize))
       L.max_two += (int)(two_step_cuts(c[i].nx, npl, L.esize == 4).size() - 1) * ((c[i].ny + min_rows - 1) / min_rows);
   L.off_btiles = take(sizeof(Strip) * std::max(L.n_tiles, 1));
-  // boxes of 64 nodes, or 4096 boxes and two per channel
+  // boxes of 64 nodes, or 4096 boxes and two per channel, in handles with
+  // channels that step in them
+  L.blk_ok = block_channels(o, c, n, L.esize);
   L.max_boxes = std::max<long long>(4096 + 2ll * n, L.plane / 64);
-  L.off_blk = take(sizeof(Strip) * L.max_boxes);
-  L.off_gpb = take(sizeof(Strip) * L.max_boxes);
+  auto boxes = [&](char kind) {
+    return std::count(L.blk_ok.begin(), L.blk_ok.end(), kind) ? sizeof(Strip) * L.max_boxes : 0;
+  };
+  L.off_blk = take(boxes(kBoxes));
+  L.off_gpb = take(boxes(kPressureBoxes));
   L.off_tstrips = take(sizeof(Strip) * std::max(L.max_two, 1));
+  for (int i = 0; i < n && L.esize == 4; ++i) {
+    const size_t N = (size_t)c[i].nx * c[i].ny;
+    const size_t nodes = N <= kStageNodes ? N : (c[i].ny < 6 ? (size_t)c[i].nx * std::min(c[i].ny, 3) : 0);
+    L.stage = std::max(L.stage, sizeof(double) * kPlanes * nodes);
+  }
+  L.off_stage = take(L.stage);
   L.bytes = at;
   return L;
 }
@@ -600,6 +608,7 @@ struct lb_handle {
   int n_tiles = 0;           // tiles of the one-step tile list
   bool blk_only = false;       // every active channel runs in boxes
   std::vector<char> blk_ok;    // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
+  BoxPlan plan[2];             // of all kBoxes and all kPressureBoxes channels
   int cus = 256;
   // captured blocks: the narrow two-step strips of each width, after the
   // others in dbact
@@ -742,7 +751,9 @@ lb_status upload_strips(lb_handle *h, bool all) {
           ids.push_back(i);
         }
       if (ids.empty()) continue;
-      const BoxPlan p = plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
+      const BoxPlan &all_of = h->plan[kind == kPressureBoxes];
+      const BoxPlan p = all_of.shape.size() == ids.size() ? all_of
+                        : plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
       if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
       std::vector<Strip> &list = kind == kBoxes ? boxes : gboxes;
       for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], list);
@@ -1068,11 +1079,225 @@ lb_status rereference(lb_handle *h, bool observed) {
   return LB_OK;
 }
 
+// ---- state and stress between the storage and the layout of the C ABI -----
+//
+// lb_get_state, lb_set_state, lb_set_profile and the stress calls convert on
+// the GPU; what crosses the host link is the caller's FP64 array, staged in
+// the other state (stress) buffer, which mirror_channel then makes equal to
+// the current one again. The link bounds it: the copies of the 24 MB of
+// 1000 x 300 nodes take 0.7 ms in and 1.4 ms out (pageable memory). Set, 200
+// FP32 steps and read take 5.4 ms there, with host loops over the nodes 24.1.
+// Every value is formed by the operations, in the order, of the definition in
+// FP64 (no contraction).
+
+__device__ __forceinline__ double weight(int i) { return i == 0 ? 4.0 / 9.0 : (i < 5 ? 1.0 / 9.0 : 1.0 / 36.0); }
 // E_i(u) of the FP32 storage: the velocity part of the equilibrium at
 // density 1, a_i (3 c_ix u + (9/2 c_ix^2 - 3/2) u^2).
-double href_eq(int i, double u) {
+__device__ __forceinline__ double ref_eq(int i, double u) {
+#pragma clang fp contract(off)
   const double cx = HCX[i];
-  return hweight(i) * (3.0 * cx * u + (4.5 * cx * cx - 1.5) * u * u);
+  return weight(i) * (3.0 * cx * u + (4.5 * cx * cx - 1.5) * u * u);
+}
+// What a layout conversion has to know of its channel.
+struct StateArgs {
+  int nx, ny;
+  int zh;                // top wall: Zou-He, with the wall velocity and force of the step
+  double uw, fx;
+  double wall[3];        // what the pull adds to a top-row node's populations 4, 7 and 8
+};
+__device__ __forceinline__ double wall_term(const StateArgs &a, int i) { return a.wall[i == 4 ? 0 : i - 6]; }
+// Zou-He completion (the steps' zou_he_top) of a top-row node: no flow
+// through the wall, n4 = n2, and the diagonals such that (m + f/2)/s is the
+// wall velocity.
+__device__ __forceinline__ void complete_top(const StateArgs &a, double f[9]) {
+#pragma clang fp contract(off)
+  const double s = (f[0] + f[1] + f[3]) + 2.0 * (f[2] + f[5] + f[6]);
+  const double d87 = (s * a.uw - 0.5 * a.fx) - ((f[1] - f[3]) + (f[5] - f[6]));
+  f[4] = f[2];
+  f[8] = 0.5 * ((f[5] + f[6]) + d87);
+  f[7] = 0.5 * ((f[5] + f[6]) - d87);
+}
+
+// Planes [p0, p1) of the state (populations after the pull; 9 is the previous
+// trace), FP64, plane by plane at out, one node per thread. src: the
+// channel's first slot; uref: the reference velocity of its rows (FP32).
+template <typename T>
+__global__ void unpack_state_kernel(const T *__restrict__ src, const float *__restrict__ uref,
+                                    double *__restrict__ out, StateArgs a, int p0, int p1) {
+#pragma clang fp contract(off)
+  const long long N = (long long)a.nx * a.ny, id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= N) return;
+  const int y = (int)(id / a.nx), x = (int)(id - (long long)y * a.nx);
+  // FP32 slots hold n - a_i - E_i(u_ref) of the row the slot belongs to
+  auto at = [&](int p, int xs, int ys) -> double {
+    const double v = src[slot(p, (long long)ys * a.nx + xs)];
+    return sizeof(T) == 4 ? v + weight(p) + ref_eq(p, uref[ys]) : v;
+  };
+  const bool top = a.zh && y == a.ny - 1;
+  double f[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    f[i] = 0;
+    if (!top && (i < p0 || i >= p1)) continue;
+    const int ys = y - HCY[i];
+    int xs = x - HCX[i];
+    xs = xs < 0 ? a.nx - 1 : (xs >= a.nx ? 0 : xs);
+    if (ys < 0)
+      f[i] = at(HOPP[i], x, y);
+    else if (ys >= a.ny)
+      f[i] = at(HOPP[i], x, y) + wall_term(a, i);
+    else
+      f[i] = at(i, xs, ys);
+  }
+  if (top) complete_top(a, f);
+#pragma unroll
+  for (int i = 0; i < 9; ++i)
+    if (i >= p0 && i < p1) out[(i - p0) * N + id] = f[i];
+  if (p1 == 10) out[(9 - p0) * N + id] = src[slot(9, id)];
+}
+
+// Stores rows [r0, r1) of a state, a row at a time per workgroup: every slot
+// from the (node, population) it feeds (the inverse of the pull). src: rows
+// [s0, s0 + srows) of the ten planes, plane by plane; one column stands for
+// all if !cols. A Zou-He top wall replaces what enters its row from above.
+// FP32: the row's reference velocity becomes the row mean of u_x (0 where
+// that is not a finite velocity), summed from x = 0 on. Starts the channel's
+// residual history anew and sets its step counter.
+template <typename T>
+__global__ void pack_state_kernel(T *__restrict__ dst, const double *__restrict__ src, StateArgs a, int r0, int r1,
+                                  int s0, int srows, int cols, float *__restrict__ uref, double *__restrict__ prev,
+                                  long long *__restrict__ step, long long t) {
+#pragma clang fp contract(off)
+  __shared__ double su[256];
+  const long long width = cols ? a.nx : 1, plane = width * srows;
+  auto at = [&](int p, int x, int ys) { return src[p * plane + (ys - s0) * width + (cols ? x : 0)]; };
+  for (int y = r0 + (int)blockIdx.x; y < r1; y += gridDim.x) {
+    const bool top = y == a.ny - 1;
+    auto node = [&](int x, double f[9]) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) f[i] = at(i, x, y);
+      if (a.zh && top) complete_top(a, f);
+    };
+    float ur = 0.0f;
+    if constexpr (sizeof(T) == 4) {
+      double sum = 0;
+      for (int x0 = 0; x0 < a.nx; x0 += blockDim.x) {
+        const int x = x0 + (int)threadIdx.x;
+        if (x < a.nx) {
+          double f[9], rho = 0, jx = 0;
+          node(x, f);
+#pragma unroll
+          for (int i = 0; i < 9; ++i) {
+            rho += f[i];
+            jx += HCX[i] * f[i];
+          }
+          su[threadIdx.x] = jx / rho;
+        }
+        __syncthreads();
+        const int n = min((int)blockDim.x, a.nx - x0);
+        for (int k = 0; k < n; ++k) sum += su[k];
+        __syncthreads();
+      }
+      const double u = sum / a.nx;
+      if (isfinite(u) && fabs(u) <= 1.0) ur = (float)u;
+      if (threadIdx.x == 0) uref[y] = ur;
+    }
+    if (threadIdx.x == 0) {
+      prev[y] = __longlong_as_double(0x7ff8000000000000ll);
+      if (y == 0) *step = t;
+    }
+    for (int x = threadIdx.x; x < a.nx; x += blockDim.x) {
+      const long long id = (long long)y * a.nx + x;
+      double f[9];
+      node(x, f);
+#pragma unroll
+      for (int j = 0; j < 9; ++j) {
+        const int yd = y + HCY[j];
+        int xd = x + HCX[j];
+        xd = xd < 0 ? a.nx - 1 : (xd >= a.nx ? 0 : xd);
+        double v;
+        if (yd < 0)
+          v = f[HOPP[j]];
+        else if (yd >= a.ny)
+          v = f[HOPP[j]] - wall_term(a, HOPP[j]);
+        else
+          v = at(j, xd, yd);
+        dst[slot(j, id)] = sizeof(T) == 4 ? (T)(v - weight(j) - ref_eq(j, ur)) : (T)v;
+      }
+      dst[slot(9, id)] = (T)at(9, x, y);
+    }
+  }
+}
+
+// The stored stress to and from planes [p0, p1) of the C ABI's layout.
+template <typename T>
+__global__ void unpack_stress_kernel(const T *__restrict__ src, double *__restrict__ out, long long N, int p0, int p1) {
+  const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= N) return;
+  for (int p = p0; p < p1; ++p) out[(p - p0) * N + id] = src[sslot(p, id)];
+}
+template <typename T>
+__global__ void pack_stress_kernel(T *__restrict__ dst, const double *__restrict__ in, long long N, int p0, int p1) {
+  const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (id >= N) return;
+  for (int p = p0; p < p1; ++p) dst[sslot(p, id)] = (T)in[(p - p0) * N + id];
+}
+
+StateArgs state_args(const lb_handle *h, int ch, long long t) {
+  const ChanDev &d = h->L.ch[ch];
+  const lb_channel &q = h->in[ch];
+  return StateArgs{d.nx, d.ny, d.zh, t < q.t_startup ? q.wall_velocity : 0.0, t < q.t_startup ? q.force : 0.0,
+                   {wall_pull_term(q, 4, t), wall_pull_term(q, 7, t), wall_pull_term(q, 8, t)}};
+}
+
+// lb_set_state from pops[9][ny][width] and P[ny][width], where one column
+// (width 1) stands for all. As many rows at a time as the staging holds, with
+// the rows next to them.
+lb_status store_state(lb_handle *h, int ch, const double *pops, const double *P, bool cols, long long t) {
+  const ChanDev &d = h->L.ch[ch];
+  const int es = h->L.esize;
+  const size_t width = cols ? d.nx : 1, N = width * d.ny, Npad = align_up((size_t)d.nx * d.ny, kTile);
+  char *dst = static_cast<char *>(h->buf[h->cur]) + (size_t)slot(0, d.off) * es;
+  char *other = static_cast<char *>(h->buf[h->cur ^ 1]) + (size_t)slot(0, d.off) * es;
+  const size_t row = sizeof(double) * kPlanes * width, other_rows = kPlanes * Npad * es / row,
+               stage_rows = h->L.stage / row;
+  double *stage = reinterpret_cast<double *>(other_rows >= (size_t)d.ny || other_rows >= stage_rows
+                                                 ? other : h->ws + h->L.off_stage);
+  const int cap = (int)std::min<size_t>(std::max(other_rows, stage_rows), d.ny);
+  if (cap < d.ny && cap < 3) return fail(h, LB_ENOMEM, "no room to stage a row of the state");
+  const int step = cap == d.ny ? d.ny : cap - 2;
+  const StateArgs a = state_args(h, ch, t);
+  const unsigned threads = (unsigned)std::min<size_t>(256, align_up(d.nx, 64));
+  for (int r0 = 0; r0 < d.ny; r0 += step) {
+    const int r1 = std::min(r0 + step, d.ny), s0 = std::max(r0 - 1, 0), srows = std::min(r1 + 1, d.ny) - s0;
+    const size_t plane = width * srows;
+    if (srows == d.ny) {
+      HIPCHECK(h, hipMemcpyAsync(stage, pops, sizeof(double) * 9 * N, hipMemcpyHostToDevice, h->stream));
+    } else {
+      for (int i = 0; i < 9; ++i)
+        HIPCHECK(h, hipMemcpyAsync(stage + i * plane, pops + i * N + s0 * width, sizeof(double) * plane,
+                                   hipMemcpyHostToDevice, h->stream));
+    }
+    HIPCHECK(h, hipMemcpyAsync(stage + 9 * plane, P + s0 * width, sizeof(double) * plane, hipMemcpyHostToDevice,
+                               h->stream));
+    auto pack = [&](auto *to) {
+      hipLaunchKernelGGL(pack_state_kernel, dim3(std::min(r1 - r0, 1 << 20)), dim3(threads), 0, h->stream, to,
+                         static_cast<const double *>(stage), a, r0, r1, s0, srows, (int)cols, h->duref + d.row_off,
+                         h->dprev + d.row_off, &h->dch[ch].t, t);
+    };
+    if (es == 8)
+      pack(reinterpret_cast<double *>(dst));
+    else
+      pack(reinterpret_cast<float *>(dst));
+    HIPCHECK(h, hipGetLastError());
+  }
+  // both buffers: a frozen channel is read from whichever is current later
+  const lb_status m = mirror_channel(h, ch);
+  if (m != LB_OK) return m;
+  HIPCHECK(h, hipStreamSynchronize(h->stream));
+  h->t[ch] = t;
+  h->obs_valid = false;
+  return LB_OK;
 }
 
 lb_status fill_rest(lb_handle *h, int which);
@@ -1247,14 +1472,15 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     h->n2slots = (long long)narrow_two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED) * std::max(cus, 1);
   }
   // channels that step in boxes
-  h->blk_ok = block_channels(o, c, n, h->L.esize);
+  h->blk_ok = h->L.blk_ok;
   for (const char kind : {kBoxes, kPressureBoxes}) {
     std::vector<lb_channel> chans;
     for (int i = 0; i < n; ++i)
       if (h->blk_ok[i] == kind) chans.push_back(c[i]);
     // (a plan for all is one for those still active later)
-    if (!chans.empty() &&
-        plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes).S == 0)
+    BoxPlan &p = h->plan[kind == kPressureBoxes];
+    if (!chans.empty()) p = plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
+    if (!chans.empty() && p.S == 0)
       for (char &k : h->blk_ok)
         if (k == kind) k = kNoBoxes;
   }
@@ -1487,136 +1713,38 @@ lb_status lb_get_state(lb_handle *h, int32_t ch, double *pops, double *P) {
   if (ch < 0 || ch >= h->n_ch || !pops || !P) return fail(h, LB_EINVAL, "bad channel or output");
   const ChanDev &d = h->L.ch[ch];
   const size_t N = (size_t)d.nx * d.ny;
-  const size_t Npad = align_up(N, kTile);
   const int es = h->L.esize;
-  // the channel's tiles are one contiguous block of the state buffer
-  std::vector<char> raw((size_t)kPlanes * Npad * es);
-  const char *src = static_cast<const char *>(h->buf[h->cur]);
-  HIPCHECK(h, hipMemcpyAsync(raw.data(), src + (size_t)slot(0, d.off) * es, raw.size(),
-                             hipMemcpyDeviceToHost, h->stream));
-  std::vector<float> ur(d.ny, 0.0f);
-  if (es == 4)
-    HIPCHECK(h, hipMemcpyAsync(ur.data(), h->duref + d.row_off, sizeof(float) * d.ny, hipMemcpyDeviceToHost,
-                               h->stream));
+  // the channel's tiles are one contiguous block of each state buffer; that
+  // of the other one holds 10 planes in FP64, or 5 where slots are FP32
+  const char *src = static_cast<const char *>(h->buf[h->cur]) + (size_t)slot(0, d.off) * es;
+  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->buf[h->cur ^ 1]) + (size_t)slot(0, d.off) * es);
+  const StateArgs a = state_args(h, ch, h->t[ch]);
+  const dim3 grid((unsigned)((N + 255) / 256));
+  const int per = es == 8 ? kPlanes : kPlanes / 2;
+  for (int p0 = 0; p0 < kPlanes; p0 += per) {
+    const int p1 = p0 + per;
+    if (es == 8)
+      hipLaunchKernelGGL(unpack_state_kernel<double>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const double *>(src), h->duref + d.row_off, stage, a, p0, p1);
+    else
+      hipLaunchKernelGGL(unpack_state_kernel<float>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const float *>(src), h->duref + d.row_off, stage, a, p0, p1);
+    HIPCHECK(h, hipGetLastError());
+    const int np = std::min(p1, 9) - p0;
+    HIPCHECK(h, hipMemcpyAsync(pops + p0 * N, stage, sizeof(double) * np * N, hipMemcpyDeviceToHost, h->stream));
+    if (p1 == kPlanes)
+      HIPCHECK(h, hipMemcpyAsync(P, stage + np * N, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream));
+  }
+  const lb_status m = mirror_channel(h, ch);
+  if (m != LB_OK) return m;
   HIPCHECK(h, hipStreamSynchronize(h->stream));
-  // FP32 slots hold n - a_i - E_i(u_ref) of the row the slot belongs to
-  auto at = [&](int p, size_t id) -> double {
-    const size_t k = (size_t)slot(p, (long long)id);
-    if (es == 8) return reinterpret_cast<const double *>(raw.data())[k];
-    const double v = reinterpret_cast<const float *>(raw.data())[k];
-    return p < 9 ? v + hweight(p) + href_eq(p, ur[id / d.nx]) : v;
-  };
-  // the pull: stored slot (plane i, source node) -> n_i at the destination
-  for (int y = 0; y < d.ny; ++y)
-    for (int x = 0; x < d.nx; ++x) {
-      const size_t id = (size_t)y * d.nx + x;
-      for (int i = 0; i < 9; ++i) {
-        const int ys = y - HCY[i];
-        const int xs = ((x - HCX[i]) % d.nx + d.nx) % d.nx;
-        double v;
-        if (ys < 0)
-          v = at(HOPP[i], id);
-        else if (ys >= d.ny)
-          v = at(HOPP[i], id) + wall_pull_term(h->in[ch], i, h->t[ch]);
-        else
-          v = at(i, (size_t)ys * d.nx + xs);
-        pops[(size_t)i * N + id] = v;
-      }
-      P[id] = at(9, id);
-    }
-  if (d.zh) host_zou_he_top(h->in[ch], h->t[ch], pops);
   return LB_OK;
 }
 
 lb_status lb_set_state(lb_handle *h, int32_t ch, const double *pops_in, const double *P, int64_t t) {
   if (!h) return LB_EINVAL;
   if (ch < 0 || ch >= h->n_ch || !pops_in || !P || t < 0) return fail(h, LB_EINVAL, "bad arguments");
-  const ChanDev &d = h->L.ch[ch];
-  const size_t N = (size_t)d.nx * d.ny;
-  // a Zou-He top wall replaces what enters its row from above (the next step
-  // completes it; completing it here keeps the FP32 row reference consistent)
-  std::vector<double> zcopy;
-  const double *pops = pops_in;
-  if (d.zh) {
-    zcopy.assign(pops_in, pops_in + 9 * N);
-    host_zou_he_top(h->in[ch], t, zcopy.data());
-    pops = zcopy.data();
-  }
-  const size_t Npad = align_up(N, kTile);
-  const int es = h->L.esize;
-  // start from the device copy so the padding slots of the last tile keep
-  // their values
-  std::vector<char> raw((size_t)kPlanes * Npad * es);
-  char *dst = static_cast<char *>(h->buf[h->cur]);
-  HIPCHECK(h, hipMemcpyAsync(raw.data(), dst + (size_t)slot(0, d.off) * es, raw.size(),
-                             hipMemcpyDeviceToHost, h->stream));
-  HIPCHECK(h, hipStreamSynchronize(h->stream));
-  // FP32: every row's reference velocity becomes the row mean of u_x of the
-  // new state (0 where that is not a finite velocity)
-  std::vector<float> ur(d.ny, 0.0f);
-  if (es == 4)
-    for (int y = 0; y < d.ny; ++y) {
-      double su = 0;
-      for (int x = 0; x < d.nx; ++x) {
-        const size_t id = (size_t)y * d.nx + x;
-        double rho = 0, jx = 0;
-        for (int i = 0; i < 9; ++i) {
-          const double v = pops[(size_t)i * N + id];
-          rho += v;
-          jx += HCX[i] * v;
-        }
-        su += jx / rho;
-      }
-      const double u = su / d.nx;
-      ur[y] = (std::isfinite(u) && std::fabs(u) <= 1.0) ? (float)u : 0.0f;
-    }
-  auto put = [&](int p, size_t id, double v) {
-    const size_t k = (size_t)slot(p, (long long)id);
-    if (es == 8)
-      reinterpret_cast<double *>(raw.data())[k] = v;
-    else
-      reinterpret_cast<float *>(raw.data())[k] = (float)(p < 9 ? v - hweight(p) - href_eq(p, ur[id / d.nx]) : v);
-  };
-  // inverse of the pull: every stored slot feeds exactly one (node, i)
-  for (int y = 0; y < d.ny; ++y)
-    for (int x = 0; x < d.nx; ++x) {
-      const size_t id = (size_t)y * d.nx + x;
-      for (int i = 0; i < 9; ++i) {
-        const int ys = y - HCY[i];
-        const int xs = ((x - HCX[i]) % d.nx + d.nx) % d.nx;
-        const double v = pops[(size_t)i * N + id];
-        if (ys < 0)
-          put(HOPP[i], id, v);
-        else if (ys >= d.ny)
-          put(HOPP[i], id, v - wall_pull_term(h->in[ch], i, t));
-        else
-          put(i, (size_t)ys * d.nx + xs, v);
-      }
-      put(9, id, P[id]);
-    }
-  HIPCHECK(h, hipMemcpyAsync(dst + (size_t)slot(0, d.off) * es, raw.data(), raw.size(),
-                             hipMemcpyHostToDevice, h->stream));
-  if (es == 4)
-    HIPCHECK(h, hipMemcpyAsync(h->duref + d.row_off, ur.data(), sizeof(float) * d.ny, hipMemcpyHostToDevice,
-                               h->stream));
-  // both buffers: a frozen channel is read from whichever is current later
-  {
-    lb_status m = mirror_channel(h, ch);
-    if (m != LB_OK) return m;
-  }
-  // step counter and residual history of this channel
-  std::vector<ChanDev> cur(h->n_ch);
-  HIPCHECK(h, hipMemcpyAsync(cur.data(), h->dch, sizeof(ChanDev) * h->n_ch, hipMemcpyDeviceToHost, h->stream));
-  HIPCHECK(h, hipStreamSynchronize(h->stream));
-  cur[ch].t = t;
-  HIPCHECK(h, hipMemcpyAsync(h->dch, cur.data(), sizeof(ChanDev) * h->n_ch, hipMemcpyHostToDevice, h->stream));
-  std::vector<double> nanrows(d.ny, std::numeric_limits<double>::quiet_NaN());
-  HIPCHECK(h, hipMemcpyAsync(h->dprev + d.row_off, nanrows.data(), sizeof(double) * d.ny,
-                             hipMemcpyHostToDevice, h->stream));
-  HIPCHECK(h, hipStreamSynchronize(h->stream));
-  h->t[ch] = t;
-  h->obs_valid = false;
-  return LB_OK;
+  return store_state(h, ch, pops_in, P, true, t);
 }
 
 lb_status lb_get_stress(lb_handle *h, int32_t ch, double *sigma) {
@@ -1625,20 +1753,26 @@ lb_status lb_get_stress(lb_handle *h, int32_t ch, double *sigma) {
   if (!h->opt.viscoelastic) return fail(h, LB_EINVAL, "the handle runs the instantaneous model (no stored stress)");
   const ChanDev &d = h->L.ch[ch];
   const size_t N = (size_t)d.nx * d.ny;
-  const size_t Npad = align_up(N, kTile);
   const int es = h->L.esize;
-  // the channel's stress tiles are one contiguous block of the buffer
-  std::vector<char> raw((size_t)kStressPlanes * Npad * es);
-  const char *src = static_cast<const char *>(h->sbuf[h->cur]);
-  HIPCHECK(h, hipMemcpyAsync(raw.data(), src + (size_t)sslot(0, d.off) * es, raw.size(), hipMemcpyDeviceToHost,
-                             h->stream));
+  // the channel's stress tiles are one contiguous block of each buffer; that
+  // of the other one holds the planes in FP64, or one where slots are FP32
+  const char *src = static_cast<const char *>(h->sbuf[h->cur]) + (size_t)sslot(0, d.off) * es;
+  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->sbuf[h->cur ^ 1]) + (size_t)sslot(0, d.off) * es);
+  const dim3 grid((unsigned)((N + 255) / 256));
+  const int per = es == 8 ? kStressPlanes : 1;
+  for (int p0 = 0; p0 < kStressPlanes; p0 += per) {
+    if (es == 8)
+      hipLaunchKernelGGL(unpack_stress_kernel<double>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const double *>(src), stage, (long long)N, p0, p0 + per);
+    else
+      hipLaunchKernelGGL(unpack_stress_kernel<float>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const float *>(src), stage, (long long)N, p0, p0 + per);
+    HIPCHECK(h, hipGetLastError());
+    HIPCHECK(h, hipMemcpyAsync(sigma + p0 * N, stage, sizeof(double) * per * N, hipMemcpyDeviceToHost, h->stream));
+  }
+  const lb_status m = mirror_channel(h, ch);
+  if (m != LB_OK) return m;
   HIPCHECK(h, hipStreamSynchronize(h->stream));
-  for (int p = 0; p < kStressPlanes; ++p)
-    for (size_t id = 0; id < N; ++id) {
-      const size_t k = (size_t)sslot(p, (long long)id);
-      sigma[(size_t)p * N + id] = es == 8 ? reinterpret_cast<const double *>(raw.data())[k]
-                                          : (double)reinterpret_cast<const float *>(raw.data())[k];
-    }
   return LB_OK;
 }
 
@@ -1648,26 +1782,21 @@ lb_status lb_set_stress(lb_handle *h, int32_t ch, const double *sigma) {
   if (!h->opt.viscoelastic) return fail(h, LB_EINVAL, "the handle runs the instantaneous model (no stored stress)");
   const ChanDev &d = h->L.ch[ch];
   const size_t N = (size_t)d.nx * d.ny;
-  const size_t Npad = align_up(N, kTile);
   const int es = h->L.esize;
-  // start from the device copy so the padding slots of the last tile keep
-  // their values
-  std::vector<char> raw((size_t)kStressPlanes * Npad * es);
-  char *dst = static_cast<char *>(h->sbuf[h->cur]);
-  HIPCHECK(h, hipMemcpyAsync(raw.data(), dst + (size_t)sslot(0, d.off) * es, raw.size(), hipMemcpyDeviceToHost,
-                             h->stream));
-  HIPCHECK(h, hipStreamSynchronize(h->stream));
-  for (int p = 0; p < kStressPlanes; ++p)
-    for (size_t id = 0; id < N; ++id) {
-      const size_t k = (size_t)sslot(p, (long long)id);
-      const double v = sigma[(size_t)p * N + id];
-      if (es == 8)
-        reinterpret_cast<double *>(raw.data())[k] = v;
-      else
-        reinterpret_cast<float *>(raw.data())[k] = (float)v;
-    }
-  HIPCHECK(h, hipMemcpyAsync(dst + (size_t)sslot(0, d.off) * es, raw.data(), raw.size(), hipMemcpyHostToDevice,
-                             h->stream));
+  char *dst = static_cast<char *>(h->sbuf[h->cur]) + (size_t)sslot(0, d.off) * es;
+  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->sbuf[h->cur ^ 1]) + (size_t)sslot(0, d.off) * es);
+  const dim3 grid((unsigned)((N + 255) / 256));
+  const int per = es == 8 ? kStressPlanes : 1;
+  for (int p0 = 0; p0 < kStressPlanes; p0 += per) {
+    HIPCHECK(h, hipMemcpyAsync(stage, sigma + p0 * N, sizeof(double) * per * N, hipMemcpyHostToDevice, h->stream));
+    if (es == 8)
+      hipLaunchKernelGGL(pack_stress_kernel<double>, grid, dim3(256), 0, h->stream, reinterpret_cast<double *>(dst),
+                         stage, (long long)N, p0, p0 + per);
+    else
+      hipLaunchKernelGGL(pack_stress_kernel<float>, grid, dim3(256), 0, h->stream, reinterpret_cast<float *>(dst),
+                         stage, (long long)N, p0, p0 + per);
+    HIPCHECK(h, hipGetLastError());
+  }
   {
     lb_status m = mirror_channel(h, ch);
     if (m != LB_OK) return m;
@@ -1714,23 +1843,19 @@ lb_status lb_set_profile(lb_handle *h, int32_t ch, const double *ux, const doubl
       q[y] = hit >= 0 ? n1[hit] : num_q / den;
     }
   }
-  const size_t N = (size_t)d.nx * d.ny;
-  std::vector<double> pops(9 * N), P(N);
+  // one column: every node of a row starts alike
+  std::vector<double> pops((size_t)9 * d.ny);
   for (int y = 0; y < d.ny; ++y) {
     // with the flow-induced density the conserved mass is sum (s + 3/2 P);
     // without it, sum s
     const double rho = d.nnp ? 1.0 - 1.5 * q[y] : 1.0;
     const double usq = u[y] * u[y];
-    for (int x = 0; x < d.nx; ++x) {
-      const size_t id = (size_t)y * d.nx + x;
-      for (int i = 0; i < 9; ++i) {
-        const double cu = HCX[i] * u[y];
-        pops[(size_t)i * N + id] = hweight(i) * rho * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq);
-      }
-      P[id] = q[y];
+    for (int i = 0; i < 9; ++i) {
+      const double cu = HCX[i] * u[y];
+      pops[(size_t)i * d.ny + y] = hweight(i) * rho * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq);
     }
   }
-  return lb_set_state(h, ch, pops.data(), P.data(), h->t[ch]);
+  return store_state(h, ch, pops.data(), q.data(), false, h->t[ch]);
 }
 
 }  // extern "C"
