@@ -2043,7 +2043,7 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_vec_kernel(SweepArgs a
 //
 // Bound by the memory path. On 4096 x 1024 (us per step; in brackets the same
 // kernel with the node update left out): FP32 41.0 (39.2), time-integrated
-// FP32 52.0 (52.6), FP64 70.4 (68.9 to 75 with the alignment of its stores),
+// FP32 50.0 (52.6 before its bands marched in pairs), FP64 70.4 (68.9 to 75 with the alignment of its stores),
 // time-integrated FP64 91.8; 16 x 8192 x 2048 FP32 2580 (2510). Before, with
 // the columns beside the window read for stage A, row references formed per
 // row and stage A's loads issued at the end of an iteration: 50.3, 60.7, 77.3,
@@ -2051,8 +2051,9 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_vec_kernel(SweepArgs a
 // VGPRs, 22% fewer vector instructions), loads issued before the update
 // (44.5 -> 42.6), every other launch marching downwards, so that it starts on
 // the rows written last, the likeliest to sit in the last-level cache (42.6
-// -> 41.4, time-integrated 62.7 -> 56.1), and strips that end on whole lines
-// (two_step_unit). Not kept: loads two rows ahead (spills), one node per lane
+// -> 41.4, time-integrated 62.7 -> 56.1), strips that end on whole lines
+// (two_step_unit), and neighbouring bands that march against each other
+// (time-integrated 52.0 -> 50.0, see add_two_step_strips). Not kept: loads two rows ahead (spills), one node per lane
 // in FP64 (86), touching lines some rows ahead (47), four wavefronts per SIMD
 // in FP32 (42.9), four nodes per lane for cached FP32 states (43.2).
 constexpr int kV2Ring = 4;
@@ -2061,25 +2062,33 @@ constexpr int kV2Ring = 4;
 // and the reference below (mirrored at the bottom wall).
 constexpr int kV2Tab = 9;
 
+// LDS of a workgroup: the ring of step-t rows, populations and trace, and
+// with VE the stress sigma(t) (sizeof(T) x NPL x 2.5 KB, x 3.25 KB with VE),
+// and the row table.
+template <typename T>
+struct V2Rows {};
+template <>
+struct V2Rows<float> {
+  float rtab[64][kV2Tab];
+};
+template <typename T, int NPL, bool VE>
+struct V2Shared : V2Rows<T> {
+  static constexpr int RP = kPlanes + (VE ? kStressPlanes : 0);
+  typename Vec<T, NPL>::type ring[kV2Ring][RP][64];
+};
+
+// One strip, marched downwards or upwards.
 template <typename T, int NPL, bool NT, bool VE, bool WALL, bool DOWN>
-__global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(sizeof(T) == 4, NPL, VE))
-    sweep_vec2_kernel(SweepArgs a) {
+__device__ __forceinline__ void two_step_strip(const SweepArgs &a, const Strip &st, V2Shared<T, NPL, VE> &shared) {
   // FP32: storage relative to the row references; FP64: plain storage
   constexpr bool SHIFT = sizeof(T) == 4;
   constexpr int HL = (kTwoStepMargin + NPL - 1) / NPL;  // lanes per side that store nothing
   typedef typename Vec<T, NPL>::type V;
-  // the ring of step-t rows: populations and trace, and with VE the stress
-  // sigma(t) (sizeof(T) x NPL x 2.5 KB per workgroup, x 3.25 KB with VE)
-  constexpr int RP = kPlanes + (VE ? kStressPlanes : 0);
-  __shared__ V ring[kV2Ring][RP][64];
-  __shared__ T rtab[SHIFT ? 64 : 1][kV2Tab];
+  constexpr int RP = V2Shared<T, NPL, VE>::RP;
+  auto &ring = shared.ring;
   const int lane = threadIdx.x & 63;
   // wave 0 runs stage A, wave 1 stage B of the same strip
   const bool isA = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
-  int sidx = xcd_item(blockIdx.x, a.n_wg);
-  if (sidx >= a.n_strips) return;  // the whole workgroup, before any barrier
-  if (DOWN) sidx = a.n_strips - 1 - sidx;
-  const Strip st = a.strips[sidx];
   const ChanDev c = a.ch[st.ch];
   const T *__restrict__ A = static_cast<const T *>(a.A);
   T *__restrict__ B = static_cast<T *>(a.B);
@@ -2125,7 +2134,7 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(si
       const T urc = ur[y], urd = ur[bot ? y : y - 1], uru = ur[top ? y : y + 1];
       T sh[9] = {T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0), T(0)};
       to_row_reference(sh, urd, urc, uru, bot, top);
-      T *w = rtab[lane];
+      T *w = shared.rtab[lane];
       w[0] = sh[2];
       w[1] = sh[5];
       w[2] = sh[6];
@@ -2214,7 +2223,7 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(si
     T sh[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
     w.urc = T(0);
     if constexpr (SHIFT) {
-      const T *tab = rtab[y - (A0 - 1)];
+      const T *tab = shared.rtab[y - (A0 - 1)];
 #pragma unroll
       for (int j = 0; j < 6; ++j) sh[j] = tab[j];
       w.urc = tab[6];
@@ -2279,7 +2288,7 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(si
                     V out[RP]) __attribute__((always_inline)) {
     T kref = T(0);
     if constexpr (SHIFT) {
-      const T *tab = rtab[y - (A0 - 1)];
+      const T *tab = shared.rtab[y - (A0 - 1)];
       kref = tab[7];
       if (WALL && y == ny - 1) {
         const T urd = tab[8];
@@ -2411,6 +2420,18 @@ __global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(si
       iteration(firstB + step * (j + 1), wb, wa);
     }
   }
+}
+
+template <typename T, int NPL, bool NT, bool VE, bool WALL>
+__global__ void __launch_bounds__(64 * kTwoStepWaves, two_step_waves_per_simd(sizeof(T) == 4, NPL, VE))
+    sweep_vec2_kernel(SweepArgs a) {
+  __shared__ V2Shared<T, NPL, VE> shared;
+  int sidx = xcd_item(blockIdx.x, a.n_wg);
+  if (sidx >= a.n_strips) return;  // the whole workgroup, before any barrier
+  if (a.down) sidx = a.n_strips - 1 - sidx;
+  const Strip st = a.strips[sidx];
+  if (st.flip != a.down) two_step_strip<T, NPL, NT, VE, WALL, true>(a, st, shared);
+  else two_step_strip<T, NPL, NT, VE, WALL, false>(a, st, shared);
 }
 
 __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const double *part,
@@ -3071,21 +3092,16 @@ hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, co
   return hipGetLastError();
 }
 
-template <typename T, int NPL, bool VE, bool WALL, bool DOWN>
-void launch_two_step_d(const SweepArgs &a, hipStream_t s) {
+template <typename T, int NPL, bool VE, bool WALL>
+void launch_two_step_w(const SweepArgs &a, hipStream_t s) {
   const dim3 grid(a.n_wg), block(64 * kTwoStepWaves);
-  if (a.nt) hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, true, VE, WALL, DOWN>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, false, VE, WALL, DOWN>), grid, block, 0, s, a);
+  if (a.nt) hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, true, VE, WALL>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((sweep_vec2_kernel<T, NPL, false, VE, WALL>), grid, block, 0, s, a);
 }
 template <typename T, int NPL, bool VE>
 void launch_two_step_t(const SweepArgs &a, hipStream_t s) {
-  if (a.wall) {
-    if (a.down) launch_two_step_d<T, NPL, VE, true, true>(a, s);
-    else launch_two_step_d<T, NPL, VE, true, false>(a, s);
-  } else {
-    if (a.down) launch_two_step_d<T, NPL, VE, false, true>(a, s);
-    else launch_two_step_d<T, NPL, VE, false, false>(a, s);
-  }
+  if (a.wall) launch_two_step_w<T, NPL, VE, true>(a, s);
+  else launch_two_step_w<T, NPL, VE, false>(a, s);
 }
 
 hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStream_t s) {
@@ -3155,13 +3171,13 @@ int two_step_blocks_per_cu(bool fp32, bool nt, bool ve) {
   constexpr int b = 64 * kTwoStepWaves;
   hipError_t e;
   if (fp32 && two_step_npl(fp32, nt, ve) == 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 4, true, false, false, false>, b, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 4, true, false, false>, b, 0);
   else if (fp32)
-    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, true, false, false>, b, 0)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, false, false, false>, b, 0);
+    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, true, false>, b, 0)
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<float, 2, false, false, false>, b, 0);
   else
-    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, true, false, false>, b, 0)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, false, false, false>, b, 0);
+    e = ve ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, true, false>, b, 0)
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sweep_vec2_kernel<double, 2, false, false, false>, b, 0);
   return (e == hipSuccess && n > 0) ? n : 1;
 }
 

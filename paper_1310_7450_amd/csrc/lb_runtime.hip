@@ -446,11 +446,17 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
   }
   return best;
 }
-void add_two_step_strips(int ci, const lb_channel &c, int npl, bool fp32, int H, std::vector<Strip> &out) {
+// Strips of one channel, band by band. With flip odd bands march against the
+// others, so that two neighbouring bands are at their common boundary at the
+// same time and read its rows from memory once: for the time-integrated
+// model (4096 x 1024, us per step, without and with: FP32 51.9 / 50.0, FP64
+// 91.6 / 91.6), not for the others (FP32 41.0 / 41.9, FP64 70.8 / 71.4, though
+// 12% and 8% less is read there from beyond the L2).
+void add_two_step_strips(int ci, const lb_channel &c, int npl, bool fp32, int H, bool flip, std::vector<Strip> &out) {
   const std::vector<int> x = two_step_cuts(c.nx, npl, fp32);
   for (int y0 = 0; y0 < c.ny; y0 += H)
     for (size_t s = 0; s + 1 < x.size(); ++s)
-      out.push_back(Strip{ci, x[s], y0, std::min(y0 + H, c.ny), 0, x[s + 1]});
+      out.push_back(Strip{ci, x[s], y0, std::min(y0 + H, c.ny), flip ? (y0 / H) & 1 : 0, x[s + 1]});
 }
 
 // The tiled step: the fused stress-force kernel for every channel of a
@@ -783,7 +789,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
       for (int i = 0; i < h->n_ch; ++i) {
         if (!h->active[i] || h->blk_ok[i]) continue;
         if (h->two_step && two_step_channel(h->in[i], es)) {
-          add_two_step_strips(i, h->in[i], npl, es == 4, H, two);
+          add_two_step_strips(i, h->in[i], npl, es == 4, H, h->opt.viscoelastic, two);
           wall = wall || two_step_wall(h->in[i]);
         } else if (!(h->two_step && narrow_two_step_channel(&h->opt, h->in[i], es)) && !tiled(&h->opt, h->in[i])) {
           add_strips(i, h->L.ch[i], es, rows_of(i), stack, braw);
