@@ -60,7 +60,7 @@ struct Layout {
   // (and their reverse), and the two-step strips
   size_t off_bstrips = 0, off_brstrips = 0, off_tstrips = 0;
   size_t off_blk = 0;     // boxes of the channels that run many steps per launch
-  size_t off_gpb = 0;     // boxes of the pressure-driven channels
+  size_t off_gpb = 0, off_gpm = 0;  // boxes of the pressure-driven channels, one and many steps per launch
   // FP32: staging of a state where the other buffer holds too few rows of it
   // (see store_state), and of every state of at most kStageNodes
   size_t off_stage = 0, stage = 0;
@@ -343,7 +343,13 @@ struct BoxPlan {
 // Largest boxes whose region (box and a halo of 2 S nodes, clipped at the
 // walls; none across a box of the whole width) holds at most cap nodes: the
 // whole width if that fits, all rows, or cut both ways, whichever repeats the
-// fewest halo nodes. False if not even one node fits.
+// fewest halo nodes. False if not even one node fits. With the pressure drive
+// a launch of several steps needs whole columns, whose density it takes every
+// step: boxes of all rows, in channels of at most 48 (above, most of a region
+// is halo) or of one box. Measured with that limit off, FP64 us per step, many
+// steps per launch against one: 64 x 32 3.1 / 5.9, 8000 x 20 5.3 / 13.2, 20000
+// x 30 22.9 / 47.4, 1000 x 48 4.6 / 6.3, 8 x 64 2.4 / 5.1, but 64 x 64 6.4 /
+// 6.8, 500 x 100 8.9 / 7.2, 4000 x 64 20.9 / 15.8.
 bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
   const int h = 4 * S;  // halo nodes in one direction, both sides
   double eff = 0;
@@ -360,9 +366,14 @@ bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
       best = BoxShape{ow, oh};
     }
   };
+  const bool columns = c.pressure_gradient != 0 && S > 1;
   if (c.nx <= cap) {
     if ((long long)c.nx * c.ny <= cap) offer(c.nx, c.ny);
-    offer(c.nx, cap / c.nx - h);
+    if (!columns) offer(c.nx, cap / c.nx - h);
+  }
+  if (columns) {
+    if (c.ny <= 48) offer(cap / c.ny - h, c.ny);
+    return eff > 0;
   }
   if (c.nx <= 64) return eff > 0;  // cutting such a row only adds halo
   if (c.ny <= cap) offer(cap / c.ny - h, c.ny);
@@ -400,11 +411,13 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
   double best_us = 1e300;
   const double launch = fp32 ? 2.7 : 2.0, start = fp32 ? 0.13 : 0.63, step = fp32 ? 0.38 : 0.59,
                wave = fp32 ? 0.29 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
+  bool pressure = false;
+  for (const lb_channel &c : chans) pressure = pressure || c.pressure_gradient != 0;
   for (int S = 1; S <= K / 2 && S <= 64; ++S) {  // (beyond 64 a launch's own time no longer counts)
     if ((K / 2) % S) continue;
     std::map<int, std::vector<BoxShape>> shapes;  // by largest region (empty: not every channel has one)
     for (int th = 256; th <= 1024; th *= 2) {
-      const int resident = (fp32 ? 24 : 16) * 64 / th;  // workgroups of a CU, by registers
+      const int resident = (fp32 && !pressure ? 24 : 16) * 64 / th;  // workgroups of a CU, by registers
       for (int part : {8, 6, 4, 3, 2}) {
         BoxPlan p;
         p.S = S;
@@ -569,6 +582,7 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
   };
   L.off_blk = take(boxes(kBoxes));
   L.off_gpb = take(boxes(kPressureBoxes));
+  L.off_gpm = take(boxes(kPressureBoxes));
   L.off_tstrips = take(sizeof(Strip) * std::max(L.max_two, 1));
   for (int i = 0; i < n && L.esize == 4; ++i) {
     const size_t N = (size_t)c[i].nx * c[i].ny;
@@ -605,16 +619,18 @@ struct lb_handle {
   Strip *dbact = nullptr, *dbact_rev = nullptr;  // captured blocks: active channels without two-step strips
   Strip *dtwo = nullptr;                        // two-step strips of the active channels
   int bact_begin[kClasses] = {0}, bact_count[kClasses] = {0};
-  // captured blocks: the boxes of the channels that run blk_S steps per launch
-  Strip *dblk = nullptr;
-  int n_blk = 0, blk_S = 0, blk_threads = 0;
-  // every step: the boxes of the pressure-driven channels that step in them
-  Strip *dgpb = nullptr;
-  int n_gpb = 0, gpb_threads = 0;
+  // the active channels that step in boxes
+  enum { kMany, kPressure, kPressureMany, kBoxLists };
+  struct BoxList {
+    Strip *d = nullptr;
+    int n = 0, S = 0, threads = 0;  // boxes, steps per launch (0: no list), threads
+    BoxPlan all;                    // the plan of all channels of the kind
+  };
+  BoxList boxes[kBoxLists];  // captured blocks; every other step with the pressure drive; captured blocks with it
   int n_tiles = 0;           // tiles of the one-step tile list
-  bool blk_only = false;       // every active channel runs in boxes
+  bool blk_only = false;       // every active channel runs in boxes, none with the pressure drive
+  bool blk_all = false;        // every active channel runs many steps per launch in boxes
   std::vector<char> blk_ok;    // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
-  BoxPlan plan[2];             // of all kBoxes and all kPressureBoxes channels
   int cus = 256;
   // captured blocks: the narrow two-step strips of each width, after the
   // others in dbact
@@ -671,6 +687,17 @@ void group_strips(const std::vector<Strip> &s, const std::vector<ChanDev> &ch, i
       if (width_class(ch[x.ch].nx, esize) == c) out.push_back(x);
     count[c] = (int)out.size() - begin[c];
   }
+}
+
+// captured blocks run some channels many steps per launch
+bool many_steps(const lb_handle *h) {
+  return h->boxes[lb_handle::kMany].S || h->boxes[lb_handle::kPressureMany].S;
+}
+// Plan of a box list. With the pressure drive: one step per launch, and as
+// many as pay in captured blocks.
+BoxPlan box_list_plan(const lb_handle *h, int list, const std::vector<lb_channel> &chans) {
+  const bool one = list == lb_handle::kPressure || h->opt.steps_per_sweep == 1;
+  return plan_boxes(chans, one ? 2 : h->K, h->L.esize == 4, h->cus, h->L.max_boxes);
 }
 
 lb_status upload_strips(lb_handle *h, bool all) {
@@ -740,42 +767,38 @@ lb_status upload_strips(lb_handle *h, bool all) {
     }
     // captured blocks: two-step strips for the eligible active channels, the
     // one-step strips of the others
-    std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped, boxes;
+    std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped, lists[lb_handle::kBoxLists];
     bool wall = false;
-    // boxes of the channels that step in them: many steps per launch, and
-    // (at S = 1) those with the pressure drive
-    h->blk_S = h->n_blk = h->n_gpb = 0;
+    // boxes of the channels that step in them
     h->blk_only = true;
     for (int i = 0; i < h->n_ch; ++i) h->blk_only = h->blk_only && (!h->active[i] || h->blk_ok[i] == kBoxes);
-    std::vector<Strip> gboxes;
-    for (const char kind : {kBoxes, kPressureBoxes}) {
+    for (int l = 0; l < lb_handle::kBoxLists; ++l) {
+      lb_handle::BoxList &list = h->boxes[l];
+      list.n = list.S = 0;
       std::vector<lb_channel> chans;
       std::vector<int> ids;
       for (int i = 0; i < h->n_ch; ++i)
-        if (h->active[i] && h->blk_ok[i] == kind) {
+        if (h->active[i] && h->blk_ok[i] == (l == lb_handle::kMany ? kBoxes : kPressureBoxes)) {
           chans.push_back(h->in[i]);
           ids.push_back(i);
         }
       if (ids.empty()) continue;
-      const BoxPlan &all_of = h->plan[kind == kPressureBoxes];
-      const BoxPlan p = all_of.shape.size() == ids.size() ? all_of
-                        : plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
+      const BoxPlan p = list.all.shape.size() == ids.size() ? list.all : box_list_plan(h, l, chans);
+      if (l == lb_handle::kPressureMany && p.S <= 1) continue;
       if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
-      std::vector<Strip> &list = kind == kBoxes ? boxes : gboxes;
-      for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], list);
-      if ((long long)list.size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
-      HIPCHECK(h, hipMemcpyAsync(kind == kBoxes ? h->dblk : h->dgpb, list.data(), list.size() * sizeof(Strip),
-                                 hipMemcpyHostToDevice, h->stream));
-      if (kind == kBoxes) {
-        h->blk_S = p.S;
-        h->blk_threads = p.threads;
-        h->n_blk = (int)list.size();
-      } else {
-        h->gpb_threads = p.threads;
-        h->n_gpb = (int)list.size();
-      }
+      for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], lists[l]);
+      if ((long long)lists[l].size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
+      HIPCHECK(h, hipMemcpyAsync(list.d, lists[l].data(), lists[l].size() * sizeof(Strip), hipMemcpyHostToDevice,
+                                 h->stream));
+      list.S = p.S;
+      list.threads = p.threads;
+      list.n = (int)lists[l].size();
     }
-    if (h->two_step || h->blk_S) {
+    h->blk_all = true;
+    for (int i = 0; i < h->n_ch; ++i)
+      h->blk_all = h->blk_all && (!h->active[i] || h->blk_ok[i] == kBoxes ||
+                                  (h->blk_ok[i] == kPressureBoxes && h->boxes[lb_handle::kPressureMany].S));
+    if (h->two_step || many_steps(h)) {
       const int es = h->L.esize;
       std::vector<lb_channel> elig, nelig;
       for (int i = 0; i < h->n_ch; ++i) {
@@ -852,6 +875,17 @@ SweepArgs sweep_args(lb_handle *h, const Strip *strips, int begin, int count, in
   return a;
 }
 
+// Enqueues S steps of the channels of a box list, if there are any (from
+// buffer src, step offset k).
+lb_status enqueue_boxes(lb_handle *h, int which, int src, int k, int S, hipStream_t s) {
+  const lb_handle::BoxList &l = h->boxes[which];
+  if (!l.n) return LB_OK;
+  SweepArgs a = sweep_args(h, l.d, 0, l.n, src, k);
+  a.n_wg = l.n;  // one box per workgroup
+  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, which != lb_handle::kMany, l.threads, a, S, s));
+  return LB_OK;
+}
+
 // Enqueues the sweeps of one step (source buffer src, step offset k), over
 // every active channel or (block) over those without two-step strips.
 lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block = false) {
@@ -881,25 +915,15 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     a.down = (src == 1);
     HIPCHECK(h, launch_sweep(h->opt.precision == LB_FP32_SHIFTED, c, false, a, s));
   }
-  if (h->n_gpb) {
-    SweepArgs a = sweep_args(h, h->dgpb, 0, h->n_gpb, src, k);
-    a.n_wg = h->n_gpb;  // one box per workgroup
-    HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, true, h->gpb_threads, a, 1, s));
+  if (!(block && h->boxes[lb_handle::kPressureMany].S)) {
+    const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
+    if (st != LB_OK) return st;
   }
   // generalised periodic boundaries of the others: the inlet/outlet column
   // pass on the state just written
   if (h->any_gpbc)
     HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
                             s));
-  return LB_OK;
-}
-
-// Enqueues S steps of every channel that runs in boxes (from buffer src, step
-// offset k).
-lb_status enqueue_boxes(lb_handle *h, int src, int k, int S, hipStream_t s) {
-  SweepArgs a = sweep_args(h, h->dblk, 0, h->n_blk, src, k);
-  a.n_wg = h->n_blk;  // one box per workgroup
-  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, false, h->blk_threads, a, S, s));
   return LB_OK;
 }
 
@@ -941,14 +965,17 @@ lb_status capture(lb_handle *h, int src) {
   hipGraph_t g = nullptr;
   HIPCHECK(h, hipStreamBeginCapture(h->cap, hipStreamCaptureModeRelaxed));
   lb_status st = LB_OK;
-  if (h->two_step || h->blk_S) {
-    // the boxes: K / blk_S launches, an even number
-    for (int k = 0, j = 0; k < h->K && st == LB_OK && h->blk_S; k += h->blk_S, ++j)
-      st = enqueue_boxes(h, src ^ (j & 1), k, h->blk_S, h->cap);
+  if (h->two_step || many_steps(h)) {
+    // the boxes: K / S launches, an even number
+    for (int l : {lb_handle::kMany, lb_handle::kPressureMany}) {
+      const int S = h->boxes[l].S;
+      for (int k = 0, j = 0; S && k < h->K && st == LB_OK; k += S, ++j)
+        st = enqueue_boxes(h, l, src ^ (j & 1), k, S, h->cap);
+    }
     // pairs of steps: one two-step launch for the eligible channels (its
     // j-th launch reads buffer src ^ (j & 1) and writes the other one), and
     // the one-step launches of the others
-    for (int k = 0; k < h->K && st == LB_OK && !h->blk_only; k += 2) {
+    for (int k = 0; k < h->K && st == LB_OK && !h->blk_all; k += 2) {
       if (h->two_count) {
         SweepArgs a = sweep_args(h, h->dtwo, 0, h->two_count, src ^ ((k / 2) & 1), k);
         a.wall = h->two_wall;
@@ -1428,8 +1455,9 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->dbact_rev = reinterpret_cast<Strip *>(h->ws + h->L.off_brstrips);
   h->dtwo = reinterpret_cast<Strip *>(h->ws + h->L.off_tstrips);
   h->btiles = reinterpret_cast<Strip *>(h->ws + h->L.off_btiles);
-  h->dblk = reinterpret_cast<Strip *>(h->ws + h->L.off_blk);
-  h->dgpb = reinterpret_cast<Strip *>(h->ws + h->L.off_gpb);
+  h->boxes[lb_handle::kMany].d = reinterpret_cast<Strip *>(h->ws + h->L.off_blk);
+  h->boxes[lb_handle::kPressure].d = reinterpret_cast<Strip *>(h->ws + h->L.off_gpb);
+  h->boxes[lb_handle::kPressureMany].d = reinterpret_cast<Strip *>(h->ws + h->L.off_gpm);
   h->two_step = false;
   for (int i = 0; i < n && two_step_handle(o, h->K); ++i)
     h->two_step = h->two_step || two_step_channel(c[i], h->L.esize) || narrow_two_step_channel(o, c[i], h->L.esize);
@@ -1479,14 +1507,16 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   }
   // channels that step in boxes
   h->blk_ok = h->L.blk_ok;
-  for (const char kind : {kBoxes, kPressureBoxes}) {
+  for (int l = 0; l < lb_handle::kBoxLists; ++l) {
+    const char kind = l == lb_handle::kMany ? kBoxes : kPressureBoxes;
     std::vector<lb_channel> chans;
     for (int i = 0; i < n; ++i)
       if (h->blk_ok[i] == kind) chans.push_back(c[i]);
+    if (chans.empty()) continue;
     // (a plan for all is one for those still active later)
-    BoxPlan &p = h->plan[kind == kPressureBoxes];
-    if (!chans.empty()) p = plan_boxes(chans, kind == kBoxes ? h->K : 2, h->L.esize == 4, h->cus, h->L.max_boxes);
-    if (!chans.empty() && p.S == 0)
+    BoxPlan &p = h->boxes[l].all;
+    p = box_list_plan(h, l, chans);
+    if (p.S == 0 && l != lb_handle::kPressureMany)
       for (char &k : h->blk_ok)
         if (k == kind) k = kNoBoxes;
   }
@@ -1573,9 +1603,9 @@ lb_status lb_step(lb_handle *h, int64_t n) {
       m = (int)std::min<int64_t>(left, h->K - h->since_block);
       int launches = 0;
       for (int k = 0; k < m; ++launches) {
-        // boxes hold the halo of up to blk_S steps
-        const int S = h->blk_only ? std::min(h->blk_S, m - k) : 1;
-        lb_status st = h->blk_only ? enqueue_boxes(h, h->cur ^ (launches & 1), k, S, h->stream)
+        // boxes hold the halo of up to S steps
+        const int S = h->blk_only ? std::min(h->boxes[lb_handle::kMany].S, m - k) : 1;
+        lb_status st = h->blk_only ? enqueue_boxes(h, lb_handle::kMany, h->cur ^ (launches & 1), k, S, h->stream)
                                    : enqueue_step(h, h->cur ^ (launches & 1), k, h->stream);
         if (st != LB_OK) return st;
         k += S;

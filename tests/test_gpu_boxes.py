@@ -88,6 +88,23 @@ def test_boxes_beside_other_channels():
     assert_same(a, b, "mixed")
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("viscoelastic", [False, True])
+def test_pressure_many_steps_per_launch(precision, viscoelastic):
+    """Boxes of whole columns, whose density every step of a launch takes: one
+    and two columns' period, a channel of one box, boxes cut into columns
+    (several periods wide with their halo), 64, 65 and more rows of density,
+    heights with and without a plan; alone and beside other channels. The
+    drive ends inside a launch."""
+    kw = dict(force=0.0, pressure_gradient=1e-6, nn_pressure=False, t_startup=31)
+    shapes = [(2, 5), (3, 64), (5, 65), (64, 32), (200, 20), (1000, 12), (33, 112), (21, 190), (600, 300), (24, 1)]
+    cases = [[spec(nx, ny, **kw)] for nx, ny in shapes]
+    cases.append([spec(64, 32, **kw), spec(16, 9, **kw), spec(300, 11), spec(8, 40)])
+    for c in cases:
+        a, b = (run(c, precision, 40, [80, 7], sps, viscoelastic) for sps in (0, 1))
+        assert_same(a, b, (precision, [(q.nx, q.ny) for q in c], viscoelastic))
+
+
 # (width, rows) above the boxes' limits; FP32 results of the two-step sweep
 # are those of one step per pass, FP64 ones agree to round-off amplified over
 # a few steps (2^-52 of the populations' size over a deviation of 1e-3: 1e-11)
