@@ -1019,6 +1019,34 @@ __device__ __forceinline__ double column_density(const T *__restrict__ C, int nx
   return SHIFT ? 1.0 + s : s;
 }
 
+// Sum of a column of n densities (stride s apart) over a wavefront, all lanes
+// active: 64 rows after 64, or (TREE) in the order of gpbc_kernel.
+template <bool TREE>
+__device__ __forceinline__ double column_sum(const double *col, int s, int n) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (!TREE) {
+    double sum = 0;
+    for (int k = 0; k < n; k += 64) sum += group_sum<64>(k + lane < n ? col[(k + lane) * s] : 0.0);
+    return sum;
+  } else {
+    double part[4] = {0, 0, 0, 0};
+    for (int k = 0; k < n; k += 256) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (k + 64 * j < n) part[j] += k + 64 * j + lane < n ? col[(k + 64 * j + lane) * s] : 0.0;
+    }
+    double v = (part[0] + part[2]) + (part[1] + part[3]);
+    v += __shfl_xor(v, 32, 64);
+    v += __shfl_xor(v, 16, 64);
+    // rows of 16 lanes hold the same now: rotations fetch what xor would
+    v += dpp_move<0x128>(v);  // row_ror 8
+    v += dpp_move<0x124>(v);
+    v += dpp_move<0x122>(v);
+    v += dpp_move<0x121>(v);
+    return v;
+  }
+}
+
 // Many steps per launch for small lattices: one workgroup takes a box of
 // nodes [x0, x1) x [y0, y1) of one channel through S steps with the state in
 // LDS. It loads the box and a halo of 2 S nodes around it (clipped at the
@@ -1043,12 +1071,15 @@ __device__ __forceinline__ double column_density(const T *__restrict__ C, int nx
 //
 // GP: channels with the pressure drive, the generalised periodic boundaries
 // (gpbc_change) in the same launch. A step needs the density of the inlet and
-// outlet columns, summed over all rows of what it pulls (a collision keeps
-// every node's density). With S = 1 a workgroup whose box stores inlet or
-// outlet nodes sums it from the state it reads, while its region loads. With
-// S > 1 the region holds all rows, and the wavefronts with inlet or outlet
-// nodes sum it every step from LDS, chunk by chunk of 64 rows in the same
-// order: 64 x 32 FP64 3.1 us per step against 5.9 with S = 1.
+// outlet columns, summed over all rows. FP64 takes it from what the step pulls
+// (a collision keeps every node's density): with S = 1 a workgroup whose box
+// stores inlet or outlet nodes sums it from the state it reads, while its
+// region loads; with S > 1 the region holds all rows, and the wavefronts with
+// inlet or outlet nodes sum it every step from LDS, in the same order. 64 x 32
+// FP64 takes 3.2 us per step against 5.9 with S = 1. FP32 rounding does not
+// keep the density exactly, and the boundary acts on that of the stored
+// values: S > 1 sums it after the update, behind a third barrier, in the order
+// of gpbc_kernel, which with S = 1 follows every step.
 template <typename T, bool VE, bool GP, int TH>
 __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block_kernel(SweepArgs a, int S) {
   constexpr bool SHIFT = sizeof(T) == 4;
@@ -1120,10 +1151,11 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
   const int out_by = max(max(ylo, yhi), max(xlo, xhi));          // distance outside the box (<= 0: inside)
   double dcol = 0;  // GP: density shift of the links leaving this thread's column
   __shared__ double dens[GP ? TH : 1];
+  const bool edge_column = GP && (x == 0 || x == nx - 1);
   // first inlet and outlet columns of the region (it may be several periods wide)
   const int inlet = !GP || cx0 == 0 ? 0 : (cx0 < 0 ? -cx0 % nx : nx - cx0);
   const int outlet = inlet == 0 ? nx - 1 : inlet - 1;
-  if (GP && S == 1) {
+  if (GP && !SHIFT && S == 1) {
     __shared__ double colsum[2][TH / 64];
     const bool stores[2] = {st.x0 == 0, st.x1 >= nx};
 #pragma unroll
@@ -1165,10 +1197,10 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
       f[4] = l[i4];
       f[7] = l[i7] - (top ? uw6 : T(0));
       f[8] = l[i8] + (top ? uw6 : T(0));
-      if (GP && S > 1 && (x == 0 || x == nx - 1)) {  // as column_density
+      if (GP && !SHIFT && S > 1 && edge_column) {  // as column_density
         const double d = ((double)f[0] + (double)f[1] + (double)f[3]) + ((double)f[2] + (double)f[5] + (double)f[6]) +
                          ((double)f[4] + (double)f[7] + (double)f[8]);
-        dens[n] = SHIFT ? 1.0 + d : d;
+        dens[n] = d;
       }
       if constexpr (SHIFT) {
 #pragma clang fp contract(off)
@@ -1186,29 +1218,25 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
       l[V + n] = uc.y;
     }
     __syncthreads();
-    if (GP && S > 1) {
-      const bool edge = in && out_by <= reach && (x == 0 || x == nx - 1);
-      if (__builtin_amdgcn_ballot_w64(edge)) {
-        const int lane = threadIdx.x & 63;
-        double mine = 0;
+    const bool update = in && out_by <= reach;
+    // the shift dcol of the wavefronts with inlet or outlet nodes to update
+    const bool edge = update && edge_column;
+    auto column_shift = [&]() __attribute__((always_inline)) {
+      if (!__builtin_amdgcn_ballot_w64(edge)) return;
+      double mine = 0;
 #pragma unroll 1
-        for (int i = inlet, o = outlet; i < cw || o < cw; i += nx, o += nx) {
-          double sum[2] = {0, 0};
-          for (int k = 0; k < ny; k += 64) {
-            const bool row = k + lane < ny;
-            const int at = (k + lane) * sy;
-            const double vi = row && i < cw ? dens[i * sx + at] : 0.0, vo = row && o < cw ? dens[o * sx + at] : 0.0;
-            sum[0] += group_sum<64>(vi);
-            sum[1] += group_sum<64>(vo);
-          }
-          if (cc == i) mine = sum[0];
-          if (cc == o) mine = sum[1];
-        }
-        const double dp = (t < c.t_startup) ? c.pd : 0.0;
-        dcol = (x == 0 ? 1.0 - 1.5 * dp : 1.0 + 1.5 * dp) - mine / ny;
+      for (int i = inlet, o = outlet; i < cw || o < cw; i += nx, o += nx) {
+        const double si = i < cw ? column_sum<SHIFT>(dens + i * sx, sy, ny) : 0.0;
+        const double so = o < cw ? column_sum<SHIFT>(dens + o * sx, sy, ny) : 0.0;
+        if (cc == i) mine = si;
+        if (cc == o) mine = so;
       }
-    }
-    if (in && out_by <= reach) {
+      const double dp = (t < c.t_startup) ? c.pd : 0.0;
+      dcol = (x == 0 ? 1.0 - 1.5 * dp : 1.0 + 1.5 * dp) - mine / ny;
+    };
+    if (GP && !SHIFT && S > 1) column_shift();
+    T out[9], trT, sn[3];
+    if (update) {
       const U2<T> lf{l[U + il], l[V + il]}, rt{l[U + ir], l[V + ir]};
       U2<T> dn{l[U - P(2) + i2], l[V - P(2) + i2]}, up{l[U - P(4) + i4], l[V - P(4) + i4]};
       if (bot) dn = U2<T>{-uc.x, -uc.y};
@@ -1221,7 +1249,6 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
         const T urt = top ? T(2) * uwg - (c.zh ? urd : urc) : uru;
         kref = T(0.5) * (urt - urd);
       }
-      T out[9], trT, sn[3];
       double obs[OF_COUNT];
       node_update<T, SHIFT, false, VE>(f, sd, mx, my, Pc, fx, lf, rt, dn, up, urc, kref, q, c.nnp, sg, sn, out, trT,
                                        obs);
@@ -1230,14 +1257,26 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
 #pragma unroll
         for (int p = 0; p < 3; ++p) sg[p] = sn[p];
       }
-      if constexpr (GP) {
-        if (x == 0 || x == nx - 1) {
-          double g[9];
+    }
+    if constexpr (GP) {
+      double g[9];
+      if (edge) {
 #pragma unroll
-          for (int i = 0; i < 9; ++i) g[i] = (double)out[i];
-          gpbc_change<SHIFT>(g, (double)urc, dcol, x != 0, y, ny, [&](int i, double v) { out[i] = (T)v; });
-        }
+        for (int i = 0; i < 9; ++i) g[i] = (double)out[i];
       }
+      if (SHIFT) {
+        if (edge) {
+          double d = 0;
+#pragma unroll
+          for (int i = 0; i < 9; ++i) d += g[i];
+          dens[n] = 1.0 + d;
+        }
+        __syncthreads();
+      }
+      if (SHIFT) column_shift();
+      if (edge) gpbc_change<SHIFT>(g, (double)urc, dcol, x != 0, y, ny, [&](int i, double v) { out[i] = (T)v; });
+    }
+    if (update) {
       if (s < S - 1) {
 #pragma unroll
         for (int i = 0; i < 9; ++i) l[P(i) + n] = out[i];

@@ -347,7 +347,7 @@ struct BoxPlan {
 // a launch of several steps needs whole columns, whose density it takes every
 // step: boxes of all rows, in channels of at most 48 (above, most of a region
 // is halo) or of one box. Measured with that limit off, FP64 us per step, many
-// steps per launch against one: 64 x 32 3.1 / 5.9, 8000 x 20 5.3 / 13.2, 20000
+// steps per launch against one: 64 x 32 3.2 / 5.9, 8000 x 20 5.3 / 13.2, 20000
 // x 30 22.9 / 47.4, 1000 x 48 4.6 / 6.3, 8 x 64 2.4 / 5.1, but 64 x 64 6.4 /
 // 6.8, 500 x 100 8.9 / 7.2, 4000 x 64 20.9 / 15.8.
 bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
@@ -628,7 +628,7 @@ struct lb_handle {
   };
   BoxList boxes[kBoxLists];  // captured blocks; every other step with the pressure drive; captured blocks with it
   int n_tiles = 0;           // tiles of the one-step tile list
-  bool blk_only = false;       // every active channel runs in boxes, none with the pressure drive
+  int only = -1;               // the box list that holds every active channel, if one does
   bool blk_all = false;        // every active channel runs many steps per launch in boxes
   std::vector<char> blk_ok;    // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
   int cus = 256;
@@ -770,8 +770,6 @@ lb_status upload_strips(lb_handle *h, bool all) {
     std::vector<Strip> braw, bgrouped, two, n2raw, n2grouped, lists[lb_handle::kBoxLists];
     bool wall = false;
     // boxes of the channels that step in them
-    h->blk_only = true;
-    for (int i = 0; i < h->n_ch; ++i) h->blk_only = h->blk_only && (!h->active[i] || h->blk_ok[i] == kBoxes);
     for (int l = 0; l < lb_handle::kBoxLists; ++l) {
       lb_handle::BoxList &list = h->boxes[l];
       list.n = list.S = 0;
@@ -795,9 +793,14 @@ lb_status upload_strips(lb_handle *h, bool all) {
       list.n = (int)lists[l].size();
     }
     h->blk_all = true;
-    for (int i = 0; i < h->n_ch; ++i)
-      h->blk_all = h->blk_all && (!h->active[i] || h->blk_ok[i] == kBoxes ||
-                                  (h->blk_ok[i] == kPressureBoxes && h->boxes[lb_handle::kPressureMany].S));
+    h->only = -1;
+    for (int i = 0; i < h->n_ch; ++i) {
+      if (!h->active[i]) continue;
+      const int l = h->blk_ok[i] == kBoxes ? lb_handle::kMany : lb_handle::kPressureMany;
+      if (h->blk_ok[i] == kNoBoxes || !h->boxes[l].S) h->blk_all = false;
+      h->only = h->only < 0 || h->only == l ? l : lb_handle::kBoxLists;
+    }
+    if (!h->blk_all || h->only == lb_handle::kBoxLists) h->only = -1;
     if (h->two_step || many_steps(h)) {
       const int es = h->L.esize;
       std::vector<lb_channel> elig, nelig;
@@ -882,7 +885,9 @@ lb_status enqueue_boxes(lb_handle *h, int which, int src, int k, int S, hipStrea
   if (!l.n) return LB_OK;
   SweepArgs a = sweep_args(h, l.d, 0, l.n, src, k);
   a.n_wg = l.n;  // one box per workgroup
-  HIPCHECK(h, launch_blocks(h->opt.precision == LB_FP32_SHIFTED, which != lb_handle::kMany, l.threads, a, S, s));
+  const bool fp32 = h->opt.precision == LB_FP32_SHIFTED;
+  const bool gpbc = which == lb_handle::kPressureMany || (which == lb_handle::kPressure && !fp32);
+  HIPCHECK(h, launch_blocks(fp32, gpbc, l.threads, a, S, s));
   return LB_OK;
 }
 
@@ -915,12 +920,12 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     a.down = (src == 1);
     HIPCHECK(h, launch_sweep(h->opt.precision == LB_FP32_SHIFTED, c, false, a, s));
   }
-  if (!(block && h->boxes[lb_handle::kPressureMany].S)) {
-    const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
-    if (st != LB_OK) return st;
-  }
-  // generalised periodic boundaries of the others: the inlet/outlet column
-  // pass on the state just written
+  // pressure-driven channels, unless the block takes them many steps at once
+  if (block && h->boxes[lb_handle::kPressureMany].S) return LB_OK;
+  const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
+  if (st != LB_OK) return st;
+  // generalised periodic boundaries where the step leaves them: the
+  // inlet/outlet column pass on the state just written
   if (h->any_gpbc)
     HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
                             s));
@@ -1522,7 +1527,7 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   }
   for (int i = 0; i < n; ++i) {
     ChanDev &d = h->L.ch[i];
-    if (d.gpbc && h->blk_ok[i] == kPressureBoxes) d.gpbc = 2;
+    if (d.gpbc && h->blk_ok[i] == kPressureBoxes && h->L.esize == 8) d.gpbc = 2;
     h->any_gpbc = h->any_gpbc || d.gpbc == 1;
   }
   if (hipMemcpyAsync(h->dch, h->L.ch.data(), sizeof(ChanDev) * n, hipMemcpyHostToDevice, h->stream) !=
@@ -1604,9 +1609,9 @@ lb_status lb_step(lb_handle *h, int64_t n) {
       int launches = 0;
       for (int k = 0; k < m; ++launches) {
         // boxes hold the halo of up to S steps
-        const int S = h->blk_only ? std::min(h->boxes[lb_handle::kMany].S, m - k) : 1;
-        lb_status st = h->blk_only ? enqueue_boxes(h, lb_handle::kMany, h->cur ^ (launches & 1), k, S, h->stream)
-                                   : enqueue_step(h, h->cur ^ (launches & 1), k, h->stream);
+        const int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : 1;
+        lb_status st = h->only >= 0 ? enqueue_boxes(h, h->only, h->cur ^ (launches & 1), k, S, h->stream)
+                                    : enqueue_step(h, h->cur ^ (launches & 1), k, h->stream);
         if (st != LB_OK) return st;
         k += S;
       }

@@ -101,7 +101,7 @@ def test_pressure_many_steps_per_launch(precision, viscoelastic):
     cases = [[spec(nx, ny, **kw)] for nx, ny in shapes]
     cases.append([spec(64, 32, **kw), spec(16, 9, **kw), spec(300, 11), spec(8, 40)])
     for c in cases:
-        a, b = (run(c, precision, 40, [80, 7], sps, viscoelastic) for sps in (0, 1))
+        a, b = (run(c, precision, 40, [80, 7, 1, 4], sps, viscoelastic) for sps in (0, 1))
         assert_same(a, b, (precision, [(q.nx, q.ny) for q in c], viscoelastic))
 
 
