@@ -256,7 +256,7 @@ __global__ void refresh_kernel(const float *p, bf16_t *pb, WeightMap w, long lon
 // are zero-padded to kFusedWidth rows and columns, so that a stage is the
 // same straight-line code whatever its layer's shape.
 constexpr int kFusedWidth = 256, kFusedLayers = 4;
-constexpr int kFusedRows = 16;  // batch rows of a workgroup
+constexpr int kCUs = 256;  // of an MI355X
 constexpr int kFusedK = kFusedWidth / 32;
 struct RowsArgs {
   int batch, bp;                  // rows, padded rows of the largest batch
@@ -277,26 +277,32 @@ struct RowsArgs {
   bf16_t *ht, *dzt;
 };
 
-// One workgroup takes kFusedRows rows of the batch through all NL layers and
-// back. A stage is one product [rows x K] [K x N], each wavefront one 16 x 16
-// tile of it; the rows' operand lies in LDS (one barrier per stage, two
-// buffers), the weights come from L2 straight into registers, where the next
-// stage's load while this stage computes; the stages are unrolled, so that
-// waits count the loads they need. 16 rows are the least an MFMA tile takes:
-// a batch of 512 then fills 32 CUs, and more rows per workgroup would only
-// lengthen the chain of stages, which is what the launch costs. Measured
-// (batch 512, 5-256-256-256-192, forward, loss and backward chain): 15.8 us,
-// about 2 us a stage, of which the activations' exponentials and divisions
-// are near half. Two tiles per wavefront took 17.7 us, with the weights of two
-// stages ahead 18.7; touching all weights' lines first, 17.7.
-template <int NL, bool FWD, bool LOSS, bool BWD>
+// One workgroup takes 4 RPL rows of the batch through all NL layers and back.
+// A stage is one product [rows x K] [K x N], each wavefront one 16 x 16 tile of
+// it; the rows' operand lies in LDS (one barrier per stage, two buffers), the
+// weights come from L2 straight into registers, where the next stage's load
+// while this stage computes; the stages are unrolled, so that waits count the
+// loads they need. An MFMA tile has 16 rows, four per lane. Fewer (RPL = 1 or
+// 2) leave matrix rows unused, which cost nothing here, and spread
+// the exponentials and divisions of the lanes' entries over more CUs: batch
+// 512, 5-256-256-256-192, forward, loss and backward chain, 17.1, 15.4 and
+// 14.6 us with 4, 2 and 1 rows per lane (32, 64 and 128 workgroups; traced).
+// What is left is the launch, the first loads (about 4 us) and some 1.5 us a
+// stage, in which a CU takes 128 KB of weights from its L2. Two column tiles
+// per wavefront took longer (17.7 against 15.8 with RPL = 4), and so did the
+// weights of two stages ahead (16.1 with RPL = 1).
+template <int NL, int RPL, bool FWD, bool LOSS, bool BWD>
 __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a) {
-  __shared__ __align__(16) bf16_t act[2][kFusedRows][kFusedWidth + 8];
+  constexpr int kRows = 4 * RPL;
+  __shared__ __align__(16) bf16_t act[2][kRows][kFusedWidth + 8];
   constexpr int kMat = kFusedWidth * kFusedWidth;
   constexpr int NST = (FWD ? NL : 0) + (BWD ? NL - 1 : 0);  // stages: layers 0 .. NL-1, then the chain through NL-1 .. 1
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kg = 8 * (lane >> 4);
-  const int m0 = blockIdx.x * kFusedRows, n = 16 * wv + r, mq = m0 + 4 * (lane >> 4);
+  // this lane's column, the first of its RPL rows (matrix rows 4 (lane / 16) +
+  // 0 .. RPL - 1; the tile's other rows repeat the last of them)
+  const int m0 = blockIdx.x * kRows, n = 16 * wv + r, mq = m0 + RPL * (lane >> 4);
+  const int ra = RPL * (r >> 2) + ((r & 3) < RPL ? r & 3 : RPL - 1);
   const int nout = a.dims[NL];
   const size_t zl = (size_t)a.bp * kFusedWidth;  // per layer of z, dz, ht and dzt
   struct Weights {
@@ -312,7 +318,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
   Weights q[2];
   if (NST > 0) fetch(0, q[0]);
   // biases, and the targets of this lane's outputs
-  float bias[NL], tgt[4] = {0.f, 0.f, 0.f, 0.f}, z[NL][4], sg[NL][4];
+  float bias[NL], tgt[RPL] = {}, z[NL][RPL], sg[NL][RPL];
   if constexpr (FWD) {
 #pragma unroll
     for (int l = 0; l < NL; ++l) bias[l] = n < a.dims[l + 1] ? a.p[a.boff[l] + n] : 0.f;
@@ -320,17 +326,17 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
 #pragma unroll
     for (int l = 0; l < NL - 1; ++l)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) z[l][i] = a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n];
+      for (int i = 0; i < RPL; ++i) z[l][i] = a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n];
   }
   if constexpr (LOSS) {
-    int row[4];
+    int row[RPL];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RPL; ++i) {
       const int m = mq + i < a.batch ? mq + i : 0;
       row[i] = a.idx ? a.idx[m] : m;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) tgt[i] = a.t[(long long)row[i] * nout + (n < nout ? n : 0)];
+    for (int i = 0; i < RPL; ++i) tgt[i] = a.t[(long long)row[i] * nout + (n < nout ? n : 0)];
   }
   {
     // the first operand: the input rows, or (BWD alone) the given dy, zero
@@ -338,7 +344,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
     const int cols = FWD ? a.dims[0] : nout;
     const float *src = FWD ? a.x : a.dy;
     bf16_t *tr = FWD ? a.ht : a.dzt + (NL - 1) * zl;
-    constexpr int per = kFusedRows * kFusedWidth / (64 * kFusedWidth / 16);  // 4 per thread
+    constexpr int per = kRows * kFusedWidth / (64 * kFusedWidth / 16);
 #pragma unroll
     for (int e = 0; e < per; ++e) {
       const int at = threadIdx.x + e * (64 * kFusedWidth / 16);
@@ -352,23 +358,26 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
       if (c < cols) tr[frag(c, m, a.bp)] = b;
     }
   }
-  // the lines of the later stages' weights, for this XCD's L2 (the update
-  // wrote them from other XCDs, and each stage's loads alone would wait for
-  // such a miss): workgroups w, w + 8, ... run on one XCD and share them
-  unsigned touched = 0;
-  // this lane's four entries of a column to the next stage's operand and to
+  // this lane's entries of a column to the next stage's operand and to
   // the transposed copy
-  auto store_operand = [&](const float v[4], bf16_t (*to)[kFusedWidth + 8], bf16_t *tr) __attribute__((always_inline)) {
-    bf16_t b[4];
+  auto store_operand = [&](const float v[RPL], bf16_t (*to)[kFusedWidth + 8], bf16_t *tr) __attribute__((always_inline)) {
+    bf16_t b[RPL];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RPL; ++i) {
       b[i] = mq + i < a.batch ? to_bf16(v[i]) : (bf16_t)0;
       to[mq - m0 + i][n] = b[i];
     }
-    uint2 u;
-    u.x = b[0] | (unsigned)b[1] << 16;
-    u.y = b[2] | (unsigned)b[3] << 16;
-    *reinterpret_cast<uint2 *>(tr + frag(n, mq, a.bp)) = u;
+    bf16_t *d = tr + frag(n, mq, a.bp);
+    if constexpr (RPL == 4) {
+      uint2 u;
+      u.x = b[0] | (unsigned)b[1] << 16;
+      u.y = b[2] | (unsigned)b[3] << 16;
+      *reinterpret_cast<uint2 *>(d) = u;
+    } else if constexpr (RPL == 2) {
+      *reinterpret_cast<unsigned *>(d) = b[0] | (unsigned)b[1] << 16;
+    } else {
+      *d = b[0];
+    }
   };
   __syncthreads();
 #pragma unroll
@@ -377,15 +386,15 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
     const int l = fwd ? s : NL - 1 - (s - (FWD ? NL : 0));
     if (s + 1 < NST) fetch(s + 1, q[(s + 1) & 1]);
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16_t *ar = &act[s & 1][r][kg];
+    const bf16_t *ar = &act[s & 1][ra][kg];
 #pragma unroll
     for (int j = 0; j < kFusedK; ++j)
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(ar + 32 * j), q[s & 1].w[j], acc,
                                                     0, 0, 0);
-    float v[4];
+    float v[RPL];
     if (fwd && l < NL - 1) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < RPL; ++i) {
         v[i] = acc[i] + bias[l];
         z[l][i] = v[i];
         sg[l][i] = sigmoid(v[i]);
@@ -395,7 +404,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
       store_operand(v, act[(s + 1) & 1], a.ht + (l + 1) * zl);
     } else if (fwd) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < RPL; ++i) {
         const int m = mq + i;
         const bool in = m < a.batch && n < nout;
         v[i] = acc[i] + bias[l];
@@ -408,7 +417,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
       if constexpr (LOSS) store_operand(v, act[(s + 1) & 1], a.dzt + l * zl);
     } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < RPL; ++i) {
         const float zz = z[l - 1][i], s1 = FWD ? sg[l - 1][i] : sigmoid(zz);
         v[i] = acc[i] * (s1 * (1.0f + zz * (1.0f - s1)));
         a.dz[(l - 1) * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
@@ -417,7 +426,6 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
     }
     if (s + 1 < NST) __syncthreads();
   }
-  asm volatile("" ::"v"(touched));  // (keeps the loads above)
 }
 
 // dW and db of every layer in one launch, and with ADAM the update of each
@@ -741,18 +749,30 @@ RowsArgs rows_args(lbml_net *h, int32_t batch) {
   a.dzt = h->b(P.off_fdt);
   return a;
 }
-template <bool FWD, bool LOSS, bool BWD>
-lbml_status launch_rows(lbml_net *h, const RowsArgs &a) {
-  const dim3 grid(padded(a.batch) / kFusedRows), block(64 * kFusedWidth / 16);
+// As few rows per workgroup as leave at most one workgroup per CU, 16 in larger
+// batches. Training step and forward pass of 5-256-256-256-192, us with 1, 2 and
+// 4 rows per lane: batch 64 18.2 / 7.4, 19.9 / 8.3, 21.2 / 8.9; 1024 25.5 / 8.5,
+// 26.0 / 8.8, 27.5 / 9.6; 2048 39.5 / 13.8, 30.3 / 9.6, 31.6 / 10.4; 3000 51 /
+// 19, 43 / 17, 34 / 11.
+template <int RPL, bool FWD, bool LOSS, bool BWD>
+lbml_status launch_rows_of(lbml_net *h, const RowsArgs &a) {
+  const dim3 grid(padded(a.batch) / (4 * RPL)), block(64 * kFusedWidth / 16);
   switch (h->nl) {
-    case 1: hipLaunchKernelGGL((rows_kernel<1, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 2: hipLaunchKernelGGL((rows_kernel<2, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 3: hipLaunchKernelGGL((rows_kernel<3, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 4: hipLaunchKernelGGL((rows_kernel<4, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 1: hipLaunchKernelGGL((rows_kernel<1, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 2: hipLaunchKernelGGL((rows_kernel<2, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 3: hipLaunchKernelGGL((rows_kernel<3, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 4: hipLaunchKernelGGL((rows_kernel<4, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
     default: return fail(h, -5, "no fused pass for this depth");
   }
   MLCHECK(h, hipGetLastError());
   return 0;
+}
+template <bool FWD, bool LOSS, bool BWD>
+lbml_status launch_rows(lbml_net *h, const RowsArgs &a) {
+  const int rows = padded(a.batch);
+  if (rows <= 4 * kCUs) return launch_rows_of<1, FWD, LOSS, BWD>(h, a);
+  if (rows <= 8 * kCUs) return launch_rows_of<2, FWD, LOSS, BWD>(h, a);
+  return launch_rows_of<4, FWD, LOSS, BWD>(h, a);
 }
 // dW and db from the dZ that launch_rows wrote, the last layer's from dz_last
 // (ld_last columns); with adam also the update.

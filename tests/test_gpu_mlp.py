@@ -306,3 +306,37 @@ def test_network_shapes(dims, batch):
     b.backward(dy)
     assert np.array_equal(a.get_grads(), b.get_grads())
     assert np.array_equal(a.forward(x).cpu().numpy(), b.forward(x).cpu().numpy())
+
+
+# The rows a workgroup takes grow with the batch (4 up to 1024 rows, 8 up to
+# 2048, then 16): both sides of each limit.
+@pytest.mark.parametrize("batch", [1000, 1024, 1025, 2048, 2049])
+def test_rows_per_workgroup(batch):
+    """A row's prediction does not depend on the batch it is in (bit for bit);
+    gradients within 2e-2 (relative L2) of the oracle's at BF16 operands; a
+    training step equals the separate calls."""
+    import torch
+    from paper_1310_7450_amd import mlp
+    dims = [5, 64, 256, 40]
+    rng = np.random.default_rng(batch)
+    p = mlp.init_params(dims, seed=3)
+    X = rng.standard_normal((batch, dims[0])).astype(np.float32)
+    T = (0.3 * rng.standard_normal((batch, dims[-1]))).astype(np.float32)
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    a, b, c = mlp.Net(dims, max_batch=batch), mlp.Net(dims, max_batch=batch), mlp.Net(dims, max_batch=500)
+    for net in (a, b, c):
+        net.set_params(p)
+    y = a.forward(Xd)
+    parts = [c.forward(Xd[k:k + 500].contiguous()).cpu().numpy() for k in range(0, batch, 500)]
+    assert np.array_equal(y.cpu().numpy(), np.concatenate(parts))
+    dy = torch.empty_like(y)
+    a.mse(y, Td, dy)
+    a.backward(dy)
+    p64 = p.astype(np.float64)
+    yb, cache = omlp.forward(p64, dims, X.astype(np.float64), operand=bf16)
+    _, dyo = omlp.mse(yb, T.astype(np.float64))
+    assert rel(a.get_grads().astype(np.float64), omlp.backward(p64, dims, cache, dyo, operand=bf16)) < 2e-2
+    a.adam_step(lr=1e-3)
+    b.train_step(Xd, Td, torch.arange(batch, dtype=torch.int32, device="cuda"), lr=1e-3, want_loss=False)
+    torch.cuda.synchronize()
+    assert np.array_equal(a.get_grads(), b.get_grads()) and np.array_equal(a.get_params(), b.get_params())
