@@ -192,10 +192,11 @@ hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStre
 // S steps per launch on boxes of small lattices (sweep_block_kernel): the
 // boxes of every block channel in SweepArgs.strips (x0, x1, y0, y1), n_wg =
 // n_strips workgroups of `threads` (256, 512 or 1024) threads; a box and its
-// halo of 2 S nodes hold at most that many nodes. The state goes from A to B
+// halo of 2 S nodes (3 S with stress_force) hold at most that many nodes. The state goes from A to B
 // over steps k .. k + S - 1. With gpbc, channels with the pressure drive, whose
 // inlet and outlet columns the launch changes too; boxes of all rows if S > 1.
-hipError_t launch_blocks(bool fp32, bool gpbc, int threads, const SweepArgs &a, int S, hipStream_t s);
+hipError_t launch_blocks(bool fp32, bool gpbc, bool stress_force, int threads, const SweepArgs &a, int S,
+                         hipStream_t s);
 // workgroups of the narrow two-step kernel one CU holds at once (the fewest
 // over the widths)
 int narrow_two_step_blocks_per_cu(bool fp32);

@@ -231,24 +231,27 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize
 //  * narrow widths, whose boxes need no columns beside them: 8 x 64 1.1 / 4.7
 //    (FP64 1.4 / 3.9), 256 ragged channels of 8 columns 5.3 / 13.2 (8.5 /
 //    22.1), 8 x 262144 27.7 / 48.1; from 32 columns on a box holds few rows:
-//    64 x 8192 12.8 / 15.7 (FP64 17.3 / 15.2), 64 x 65536 92 / 80.
+//    64 x 8192 12.8 / 15.7 (FP64 17.3 / 15.2), 64 x 65536 92 / 80;
+//  * the stress as a force (FP64; tiles): 8 x 64 1.9 / 10.3, 143 x 43 3.2 / 7.7,
+//    512 x 64 4.4 / 8.0, 1000 x 100 5.9 / 8.6, 512 x 300 9.0 / 10.4, 500 x 500
+//    14.1 / 12.1.
 // values of block_channels: not in boxes; many steps per launch; pressure drive
 enum { kNoBoxes = 0, kBoxes = 1, kPressureBoxes = 2 };
 std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize) {
-  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, KINDS };
+  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, FORCE, KINDS };
   const bool fp32 = esize == 4, ve = o->viscoelastic;
   const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
   const long long limit[KINDS] = {fp32 ? 7 * M / 8 : 5 * M / 8, (fp32 || ve) ? 8 * M : 3 * M / 10,
-                                  always, ve ? always : (fp32 ? M : M / 4), M};
+                                  always, ve ? always : (fp32 ? M : M / 4), M, 5 * M / 32};
   std::vector<int> kind(n, -1);
   long long nodes[KINDS] = {};
   for (int i = 0; i < n; ++i) {
     const bool gp = c[i].pressure_gradient != 0;  // one step per launch in either setting
-    if ((o->steps_per_sweep == 1 && !gp) || o->stress_force) continue;
+    if (o->steps_per_sweep == 1 && !gp) continue;
     const size_t N = (size_t)c[i].nx * c[i].ny;
     if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
     const int cls = width_class(c[i].nx, esize);
-    kind[i] = gp ? PRESSURE : cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
+    kind[i] = o->stress_force ? FORCE : gp ? PRESSURE : cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
     nodes[kind[i]] += (long long)N;
   }
   std::vector<char> ok(n, 0);
@@ -340,7 +343,7 @@ struct BoxPlan {
   int S = 0, threads = 0;  // S = 0: no plan
   std::vector<BoxShape> shape;
 };
-// Largest boxes whose region (box and a halo of 2 S nodes, clipped at the
+// Largest boxes whose region (box and a halo of reach S nodes, clipped at the
 // walls; none across a box of the whole width) holds at most cap nodes: the
 // whole width if that fits, all rows, or cut both ways, whichever repeats the
 // fewest halo nodes. False if not even one node fits. With the pressure drive
@@ -350,8 +353,8 @@ struct BoxPlan {
 // steps per launch against one: 64 x 32 3.2 / 5.9, 8000 x 20 5.3 / 13.2, 20000
 // x 30 22.9 / 47.4, 1000 x 48 4.6 / 6.3, 8 x 64 2.4 / 5.1, but 64 x 64 6.4 /
 // 6.8, 500 x 100 8.9 / 7.2, 4000 x 64 20.9 / 15.8.
-bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
-  const int h = 4 * S;  // halo nodes in one direction, both sides
+bool box_shape(const lb_channel &c, int S, int reach, int cap, BoxShape &best) {
+  const int h = 2 * reach * S;  // halo nodes in one direction, both sides
   double eff = 0;
   auto even = [](int n, int w) { return (n + (n + w - 1) / w - 1) / ((n + w - 1) / w); };
   auto offer = [&](int ow, int oh) {
@@ -381,12 +384,12 @@ bool box_shape(const lb_channel &c, int S, int cap, BoxShape &best) {
   return eff > 0;
 }
 // wavefronts of a region at work in step s of S (see the kernel's node order)
-int box_waves(const lb_channel &c, BoxShape b, int S, int s) {
-  const int reach = 2 * (S - 1 - s) + 1;
+int box_waves(const lb_channel &c, BoxShape b, int S, int step_reach, int s) {
+  const int reach = step_reach * (S - s) - 1, halo = 2 * step_reach * S;
   const bool whole = b.ow >= c.nx;
-  const int cw = whole ? c.nx : b.ow + 4 * S;
+  const int cw = whole ? c.nx : b.ow + halo;
   const int rows = std::min(b.oh + 2 * reach, c.ny);
-  if (!whole && std::min(b.oh + 4 * S, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
+  if (!whole && std::min(b.oh + halo, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
   return (rows * cw + 63) / 64;
 }
 void add_boxes(int ci, const lb_channel &c, BoxShape b, std::vector<Strip> &out) {
@@ -406,11 +409,12 @@ long long box_count(const lb_channel &c, BoxShape b) {
 // mean error 12% FP32, 9% FP64): the plan picked was within 6% of the best
 // measured one in every case. S divides K / 2, so that a captured block is
 // an even number of launches and leaves the state in its buffer.
-BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int cus, long long room) {
+BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, bool stress_force, int cus, long long room) {
   BoxPlan best;
   double best_us = 1e300;
-  const double launch = fp32 ? 2.7 : 2.0, start = fp32 ? 0.13 : 0.63, step = fp32 ? 0.38 : 0.59,
-               wave = fp32 ? 0.29 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
+  const double launch = fp32 ? 2.7 : 2.0, start = fp32 ? 0.13 : 0.63, step = fp32 ? 0.38 : stress_force ? 0.9 : 0.59,
+               wave = fp32 ? 0.29 : stress_force ? 0.6 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
+  const int reach = stress_force ? 3 : 2;  // nodes a step reaches
   bool pressure = false;
   for (const lb_channel &c : chans) pressure = pressure || c.pressure_gradient != 0;
   for (int S = 1; S <= K / 2 && S <= 64; ++S) {  // (beyond 64 a launch's own time no longer counts)
@@ -426,7 +430,7 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
         const auto [it, added] = shapes.try_emplace(th * part / 8);
         for (size_t i = 0; added && i < chans.size(); ++i) {
           BoxShape b;
-          if (!box_shape(chans[i], S, th * part / 8, b)) {
+          if (!box_shape(chans[i], S, reach, th * part / 8, b)) {
             it->second.clear();
             break;
           }
@@ -438,8 +442,8 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, int c
           const lb_channel &c = chans[i];
           const BoxShape b = p.shape[i];
           const double w = (double)box_count(c, b);
-          const int v0 = box_waves(c, b, S, 0);
-          const double v = 0.5 * (v0 + box_waves(c, b, S, S - 1));
+          const int v0 = box_waves(c, b, S, reach, 0);
+          const double v = 0.5 * (v0 + box_waves(c, b, S, reach, S - 1));
           W += w;
           R += w * v0;
           V += w * v;
@@ -697,7 +701,7 @@ bool many_steps(const lb_handle *h) {
 // many as pay in captured blocks.
 BoxPlan box_list_plan(const lb_handle *h, int list, const std::vector<lb_channel> &chans) {
   const bool one = list == lb_handle::kPressure || h->opt.steps_per_sweep == 1;
-  return plan_boxes(chans, one ? 2 : h->K, h->L.esize == 4, h->cus, h->L.max_boxes);
+  return plan_boxes(chans, one ? 2 : h->K, h->L.esize == 4, h->opt.stress_force, h->cus, h->L.max_boxes);
 }
 
 lb_status upload_strips(lb_handle *h, bool all) {
@@ -887,7 +891,7 @@ lb_status enqueue_boxes(lb_handle *h, int which, int src, int k, int S, hipStrea
   a.n_wg = l.n;  // one box per workgroup
   const bool fp32 = h->opt.precision == LB_FP32_SHIFTED;
   const bool gpbc = which == lb_handle::kPressureMany || (which == lb_handle::kPressure && !fp32);
-  HIPCHECK(h, launch_blocks(fp32, gpbc, l.threads, a, S, s));
+  HIPCHECK(h, launch_blocks(fp32, gpbc, h->opt.stress_force, l.threads, a, S, s));
   return LB_OK;
 }
 
@@ -896,7 +900,7 @@ lb_status enqueue_boxes(lb_handle *h, int which, int src, int k, int S, hipStrea
 lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block = false) {
   if (h->opt.stress_force) {
     HIPCHECK(h, launch_saf_fused(static_cast<const double *>(h->buf[src]), static_cast<double *>(h->buf[src ^ 1]),
-                                 h->dch, h->tiles, h->L.n_tiles, k,
+                                 h->dch, block ? h->btiles : h->tiles, block ? h->n_btiles : h->n_tiles, k,
                                  streamed(h->L), src == 1, s));
     return LB_OK;
   }

@@ -23,12 +23,12 @@ def spec(nx, ny, **kw):
     return ChannelSpec(nx=nx, ny=ny, **base)
 
 
-def run(chans, precision, obs_every, steps, steps_per_sweep, viscoelastic=False):
+def run(chans, precision, obs_every, steps, steps_per_sweep, viscoelastic=False, stress_force=False):
     """States (and stresses) of every channel after the steps, from seeded
     random states."""
     from paper_1310_7450_amd import Solver
     with Solver(chans, precision=precision, obs_every=obs_every, viscoelastic=viscoelastic,
-                steps_per_sweep=steps_per_sweep) as s:
+                stress_force=stress_force, steps_per_sweep=steps_per_sweep) as s:
         for i, c in enumerate(chans):
             s.set_state(i, *workloads.random_state(c.nx, c.ny, seed=31 * c.nx + c.ny + i), 0)
             if viscoelastic:
@@ -103,6 +103,28 @@ def test_pressure_many_steps_per_launch(precision, viscoelastic):
     for c in cases:
         a, b = (run(c, precision, 40, [80, 7, 1, 4], sps, viscoelastic) for sps in (0, 1))
         assert_same(a, b, (precision, [(q.nx, q.ny) for q in c], viscoelastic))
+
+
+# the stress as a force: a step reaches three nodes, and the wall's ghost
+# stress takes two rows; FP64 round-off over a few steps as below
+@pytest.mark.parametrize("wall", [{}, dict(wall_velocity=0.02)])
+def test_stress_force_boxes(wall):
+    """Boxes of several steps against one step per launch: one node, one and two
+    rows, channels of one box, cut by rows, by columns and both ways, ragged;
+    alone and in one handle; on both sides of the limit of their kind."""
+    kw = dict(nn_pressure=False, t_startup=31, **wall)
+    shapes = [(1, 1), (3, 1), (5, 2), (8, 40), (64, 3), (8, 400), (200, 20), (143, 43), (37, 113), (1000, 9)]
+    cases = [[spec(nx, ny, **kw)] for nx, ny in shapes] + [[spec(nx, ny, **kw) for nx, ny in shapes[3:8]]]
+    cases += [[spec(500, 300, **kw)], [spec(600, 300, **kw)]]
+    for c in cases:
+        a, b = (run(c, "fp64", 40, [80, 7, 1], sps, stress_force=True) for sps in (0, 1))
+        for x, y in zip(a, b):
+            for p, q in zip(x, y):
+                scale = max(np.abs(q).max(), 1e-300)
+                err = np.abs(p - q).max() / scale
+                assert err <= 1e-11, ([(s.nx, s.ny) for s in c], err)
+        print([(s.nx, s.ny) for s in c], "same" if all(np.array_equal(p, q) for x, y in zip(a, b) for p, q in zip(x, y))
+              else "to round-off", flush=True)
 
 
 # (width, rows) above the boxes' limits; FP32 results of the two-step sweep
