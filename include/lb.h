@@ -141,9 +141,10 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                the block boundaries; even, >= 2 (default 1000 when 0);
  *   strip_rows   rows per wavefront strip of the sweep, also of the
  *                two-step sweep below (0: tuned default; the two-step
- *                default fills whole rounds of resident strips; not used by the boxes of steps_per_sweep). While
- *                the active channels make fewer one-step strips than the
- *                GPU has SIMDs, their heights are divided alike (down to
+ *                default fills whole rounds of resident strips; not used by
+ *                the boxes of steps_per_sweep). While the active channels
+ *                make fewer one-step strips than the GPU has SIMDs, their
+ *                heights are divided alike (down to
  *                4 rows, or a narrow kernel's row group) to spread them
  *                over the GPU. The narrow widths' two-step strips take
  *                the smallest height among 1, 2, 4, the multiples of 8 up
@@ -179,7 +180,8 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                model and channels with nn_pressure = 0, the half-way top
  *                wall, no pressure_gradient and at most 429,496,704 nodes.
  *                Runs as one fused pass per step (u~, Sigma^nN and the
- *                collide-and-stream of a tile of nodes in one workgroup);
+ *                collide-and-stream of a tile of nodes in one workgroup),
+ *                small lattices in boxes (steps_per_sweep);
  *   steps_per_sweep 0 (default) or 2: with either stress model, no
  *                stress_force and K a multiple of 4, the blocks of K steps
  *                advance the vector-class channels (width a multiple of 256
@@ -190,8 +192,9 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                without the viscoelastic option the narrow channels (width
  *                1, 2, 4, ..., 64) without pressure_gradient do too.
  *                Handles whose channels of a width class hold few nodes
- *                (about a million and less, any K; not with stress_force or
- *                pressure_gradient) advance them more steps per pass
+ *                (about a million and less, with stress_force 163,840 and
+ *                less, any K; with pressure_gradient channels of at most 48
+ *                rows) advance them more steps per pass
  *                instead, in boxes of nodes whose state stays on chip for a
  *                divisor of K / 2 steps, also in the steps outside whole
  *                blocks when every active channel does. Other channels,

