@@ -1062,10 +1062,12 @@ __device__ __forceinline__ double column_sum(const double *col, int s, int n) {
 // Collision of the stress-force step of node n, row y of ny (sd its density,
 // inv 1 / sd): div Sigma^nN by central differences of the neighbours' Sigma^nN (three
 // planes of TH values: l left, r right, n + od below, n + ou above; ghost rows
-// extrapolated linearly), then the forcing of the total force.
+// extrapolated linearly), then the forcing of the total force; put(i, v) takes
+// the populations one by one (an array of them costs the fused kernel 1-2%).
+template <typename Put>
 __device__ __forceinline__ void saf_collide(const double f[9], double sd, double inv, double mx, double my, double g,
                                             double om, double kf, const double *S, int TH, int n, int l, int r, int od, int ou,
-                                            int y, int ny, double out[9]) {
+                                            int y, int ny, Put put) {
   constexpr int cx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
   constexpr int cy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
   double dn[3], up[3];
@@ -1091,7 +1093,7 @@ __device__ __forceinline__ void saf_collide(const double f[9], double sd, double
     const double a = weight<double>(i);
     const double neq = a * sd * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * usq);
     const double F = a * kf * (3.0 * cfo + 9.0 * cu * cfo - 3.0 * uf);
-    out[i] = f[i] - om * (f[i] - neq) + F;
+    put(i, f[i] - om * (f[i] - neq) + F);
   }
 }
 
@@ -1311,7 +1313,9 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
     if (GP && !SHIFT && S > 1) column_shift();
     T out[9], trT, sn[3];
     if constexpr (SAF) {
-      if (update) saf_collide(f, sd, recip<double>(sd), mx, my, fx, c.omega, c.kf, l + Sg, TH, n, il, ir, od, ou, y, ny, out);
+      if (update)
+        saf_collide(f, sd, recip<double>(sd), mx, my, fx, c.omega, c.kf, l + Sg, TH, n, il, ir, od, ou, y, ny,
+                    [&](int i, double v) __attribute__((always_inline)) { out[i] = v; });
       trT = Pc;
     } else if (update) {
       const U2<T> lf{l[U + il], l[V + il]}, rt{l[U + ir], l[V + ir]};
@@ -3038,14 +3042,11 @@ __global__ void __launch_bounds__(kSafThreads) saf_fused_kernel(const double *__
     const int yo = tl.y0 + jo + s * kSafRows;
     if (yo >= tl.y1) continue;
     const int n = (jo + s * kSafRows + 1) * kSafSX + io + 1;
-    double out[9];
     saf_collide(f[s], sd[s], inv[s], mx[s], my[s], g, c.omega, c.kf, &sT[0][0][0], kSafSX * kSafSY, n, n - 1, n + 1,
-                -kSafSX, kSafSX, yo, ny, out);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-      if constexpr (NT) __builtin_nontemporal_store(out[q], &Bc[lslot(q, m[s])]);
-      else Bc[lslot(q, m[s])] = out[q];
-    }
+                -kSafSX, kSafSX, yo, ny, [&](int q, double v) __attribute__((always_inline)) {
+                  if constexpr (NT) __builtin_nontemporal_store(v, &Bc[lslot(q, m[s])]);
+                  else Bc[lslot(q, m[s])] = v;
+                });
     if constexpr (NT) __builtin_nontemporal_store(Pc[s], &Bc[lslot(9, m[s])]);
     else Bc[lslot(9, m[s])] = Pc[s];
   }
