@@ -1012,23 +1012,18 @@ __device__ __forceinline__ void gpbc_change(const double f[9], double ur, double
 }
 
 // Density of node (x, y) after streaming, in FP64, from the channel's slots C
-// (fixed walls). FP32: stored relative to density 1 and the source rows'
-// references, whose parts of the density vanish: E_2 + E_5 + E_6 = 0 at any
-// reference, and so do the changes of reflected 5 and 6 together.
-template <typename T, bool SHIFT>
-__device__ __forceinline__ double column_density(const T *__restrict__ C, int nx, int ny, int x, int y) {
+// (FP64 storage, fixed walls).
+__device__ __forceinline__ double column_density(const double *__restrict__ C, int nx, int ny, int x, int y) {
   const unsigned row = (unsigned)y * nx;
   const unsigned xm = (x == 0) ? nx - 1 : x - 1, xp = (x == nx - 1) ? 0 : x + 1;
   const bool bot = (y == 0), top = (y == ny - 1);
   const unsigned dn = row - nx, up = row + nx;
-  const T f0 = C[lslot(0, row + x)], f1 = C[lslot(1, row + xm)], f3 = C[lslot(3, row + xp)];
-  const T f2 = C[bot ? lslot(4, row + x) : lslot(2, dn + x)], f5 = C[bot ? lslot(7, row + x) : lslot(5, dn + xm)],
+  const double f0 = C[lslot(0, row + x)], f1 = C[lslot(1, row + xm)], f3 = C[lslot(3, row + xp)];
+  const double f2 = C[bot ? lslot(4, row + x) : lslot(2, dn + x)], f5 = C[bot ? lslot(7, row + x) : lslot(5, dn + xm)],
           f6 = C[bot ? lslot(8, row + x) : lslot(6, dn + xp)];
-  const T f4 = C[top ? lslot(2, row + x) : lslot(4, up + x)], f7 = C[top ? lslot(5, row + x) : lslot(7, up + xp)],
+  const double f4 = C[top ? lslot(2, row + x) : lslot(4, up + x)], f7 = C[top ? lslot(5, row + x) : lslot(7, up + xp)],
           f8 = C[top ? lslot(6, row + x) : lslot(8, up + xm)];
-  const double s = ((double)f0 + (double)f1 + (double)f3) + ((double)f2 + (double)f5 + (double)f6) +
-                   ((double)f4 + (double)f7 + (double)f8);
-  return SHIFT ? 1.0 + s : s;
+  return (f0 + f1 + f3) + (f2 + f5 + f6) + (f4 + f7 + f8);
 }
 
 // Sum of a column of n densities (stride s apart) over a wavefront, all lanes
@@ -1221,8 +1216,7 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
       double sum = 0;
       if (stores[side])
         for (int yy = threadIdx.x; yy < ny; yy += TH)
-          sum += column_density<T, SHIFT>(static_cast<const T *>(a.A) + c.off * kPlanes, nx, ny,
-                                          side ? nx - 1 : 0, yy);
+          sum += column_density(static_cast<const double *>(a.A) + c.off * kPlanes, nx, ny, side ? nx - 1 : 0, yy);
       sum = group_sum<64>(sum);
       if ((threadIdx.x & 63) == 0) colsum[side][threadIdx.x >> 6] = sum;
     }
