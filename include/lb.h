@@ -196,10 +196,10 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                less, any K; with pressure_gradient channels of at most 48
  *                rows) advance them more steps per pass
  *                instead, in boxes of nodes whose state stays on chip for a
- *                divisor of K / 2 steps, also in the steps outside whole
- *                blocks when every active channel does. Other channels,
- *                other handles and steps outside whole blocks run one step
- *                per pass. Each node update is the arithmetic of the
+ *                divisor of K / 2 steps. Steps outside whole blocks go two
+ *                or more per pass too when every active channel is of one
+ *                of these kinds (the narrow widths' two-step pass excepted).
+ *                Other channels and other handles run one step per pass. Each node update is the arithmetic of the
  *                one-step pass; states agree with it to round-off; 1: one
  *                step per pass always.
  */

@@ -645,6 +645,7 @@ struct lb_handle {
   // others in dbact
   int n2_begin[kClasses] = {0}, n2_count[kClasses] = {0};
   int two_count = 0;
+  bool two_only = false;  // every active channel has two-step strips
   bool two_wall = false;  // some two-step strip's channel has a moving or Zou-He top wall
   Strip *btiles = nullptr;  // captured blocks: tiles of the tiled channels without two-step strips
   int n_btiles = 0;
@@ -860,6 +861,9 @@ lb_status upload_strips(lb_handle *h, bool all) {
     }
     if ((int)two.size() > h->L.max_two) return fail(h, LB_ENOMEM, "two-step strip list exceeds its workspace");
     h->two_count = (int)two.size();
+    h->two_only = h->two_step;
+    for (int i = 0; i < h->n_ch; ++i)
+      if (h->active[i] && (h->blk_ok[i] || !two_step_channel(h->in[i], h->L.esize))) h->two_only = false;
     h->two_wall = wall;
     if (!two.empty())
       HIPCHECK(h, hipMemcpyAsync(h->dtwo, two.data(), two.size() * sizeof(Strip), hipMemcpyHostToDevice, h->stream));
@@ -901,6 +905,18 @@ lb_status enqueue_boxes(lb_handle *h, int which, int src, int k, int S, hipStrea
   const bool fp32 = h->opt.precision == LB_FP32_SHIFTED;
   const bool gpbc = which == lb_handle::kPressureMany || (which == lb_handle::kPressure && !fp32);
   HIPCHECK(h, launch_blocks(fp32, gpbc, h->opt.stress_force, l.threads, a, S, s));
+  return LB_OK;
+}
+
+// Enqueues two steps of the channels with two-step strips, if there are any
+// (from buffer src, step offset k).
+lb_status enqueue_two_step(lb_handle *h, int src, int k, hipStream_t s) {
+  if (!h->two_count) return LB_OK;
+  SweepArgs a = sweep_args(h, h->dtwo, 0, h->two_count, src, k);
+  a.wall = h->two_wall;
+  a.down = (src == 1);
+  a.n_wg = h->two_count;  // one strip per workgroup (a wavefront per stage)
+  HIPCHECK(h, launch_two_step(h->opt.precision == LB_FP32_SHIFTED, a, s));
   return LB_OK;
 }
 
@@ -994,14 +1010,7 @@ lb_status capture(lb_handle *h, int src) {
     // j-th launch reads buffer src ^ (j & 1) and writes the other one), and
     // the one-step launches of the others
     for (int k = 0; k < h->K && st == LB_OK && !h->blk_all; k += 2) {
-      if (h->two_count) {
-        SweepArgs a = sweep_args(h, h->dtwo, 0, h->two_count, src ^ ((k / 2) & 1), k);
-        a.wall = h->two_wall;
-        a.down = (src ^ ((k / 2) & 1)) == 1;
-        a.n_wg = h->two_count;  // one strip per workgroup (a wavefront per stage)
-        hipError_t e = launch_two_step(h->opt.precision == LB_FP32_SHIFTED, a, h->cap);
-        if (e != hipSuccess) st = hipfail(h, e, "launch_two_step");
-      }
+      st = enqueue_two_step(h, src ^ ((k / 2) & 1), k, h->cap);
       for (int c = 0; c < kClasses && st == LB_OK; ++c) {
         if (!h->n2_count[c]) continue;
         SweepArgs a = sweep_args(h, h->dbact, h->n2_begin[c], h->n2_count[c], src ^ ((k / 2) & 1), k);
@@ -1621,10 +1630,14 @@ lb_status lb_step(lb_handle *h, int64_t n) {
       m = (int)std::min<int64_t>(left, h->K - h->since_block);
       int launches = 0;
       for (int k = 0; k < m; ++launches) {
-        // boxes hold the halo of up to S steps
-        const int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : 1;
-        lb_status st = h->only >= 0 ? enqueue_boxes(h, h->only, h->cur ^ (launches & 1), k, S, h->stream)
-                                    : enqueue_step(h, h->cur ^ (launches & 1), k, h->stream);
+        // boxes hold the halo of up to S steps; two steps per launch where
+        // every channel takes them (the same results: no kernel's rounding
+        // differs from another's)
+        const int src = h->cur ^ (launches & 1);
+        const int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : h->two_only ? std::min(2, m - k) : 1;
+        lb_status st = h->only >= 0 ? enqueue_boxes(h, h->only, src, k, S, h->stream)
+                       : S == 2     ? enqueue_two_step(h, src, k, h->stream)
+                                    : enqueue_step(h, src, k, h->stream);
         if (st != LB_OK) return st;
         k += S;
       }

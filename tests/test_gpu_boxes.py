@@ -145,6 +145,18 @@ def test_large_two_step_equals_one_step(precision, nx, ny, viscoelastic):
         assert err <= (2e-4 if precision == "fp32" else 1e-9 if q.ndim == 2 else 1e-11)
 
 
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("viscoelastic", [False, True])
+@pytest.mark.parametrize("wall", [{}, dict(wall_velocity=1e-2, top_wall="zou_he")])
+def test_large_steps_off_block_boundaries(precision, viscoelastic, wall):
+    """Above the boxes' limits steps outside whole blocks go two per launch, a
+    last odd one alone: the same bits however the steps are split over calls."""
+    c = [spec(1024, 1100, **wall)]
+    a = run(c, precision, 8, [16], 0, viscoelastic)
+    for steps in ([3, 5, 1, 7], [1] * 16):
+        assert_same(a, run(c, precision, 8, steps, 0, viscoelastic), (precision, viscoelastic, steps))
+
+
 # bounds of the pressure-drive state parity (50 x 1e-12 and 50 x 2e-6 of the
 # state's deviation from rest after some tens of steps)
 @pytest.mark.parametrize("precision,tol", [("fp32", 1e-4), ("fp64", 5e-11)])
