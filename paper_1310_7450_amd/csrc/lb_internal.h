@@ -49,10 +49,20 @@ struct ChanDev {
   double lgt;           // lambda G_inf tau
   double uw;            // top wall x velocity while t < t_startup
   double pd;            // pressure drive: p+ - p- = (nx + 1) G_p while t < t_startup
-  int gpbc;             // generalised periodic boundaries in x: 1 by the column pass, 2 inside the step
+  int gpbc;             // generalised periodic boundaries in x (GpbcBy; 0: none)
   int nnp;              // keep the flow-induced density terms
   int zh;               // top wall: Zou-He velocity boundary on row ny - 1
 };
+
+// What applies a channel's generalised periodic boundaries: the column pass
+// after every step; the step itself (FP64 boxes); or the launches of several
+// steps (FP32 boxes), and after a step launched alone the column pass.
+enum GpbcBy { kGpbcPass = 1, kGpbcStep = 2, kGpbcBoxes = 3 };
+// The column pass after one step takes this channel. boxed: the boxes of
+// several steps take theirs.
+__host__ __device__ inline bool column_pass_takes(const ChanDev &c, bool boxed) {
+  return c.active && (c.gpbc == kGpbcPass || (c.gpbc == kGpbcBoxes && !boxed));
+}
 
 // Work unit of one wavefront: rows [y0, y1) of channel ch, starting at
 // column x0 (wide mode: first interior column; narrow mode: 0). flip: the
@@ -126,7 +136,8 @@ hipError_t launch_reduce(const ChanDev *ch, int n_ch, const double *part, double
                          double *prev_ux, double *scal, const float *uref, int update_residual,
                          int steps_since, hipStream_t s);
 hipError_t launch_advance(ChanDev *ch, int n_ch, int steps, hipStream_t s);
-hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, const float *uref, hipStream_t s);
+hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, const float *uref, bool boxed,
+                       hipStream_t s);
 // FP64 step over tiles of kMainTileX x kMainTileY nodes (x0, y0, y1 of a
 // Strip; SweepArgs.strips holds the tiles, n_strips their number).
 #ifndef LB_MAIN_TX

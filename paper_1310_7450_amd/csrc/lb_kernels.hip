@@ -2687,7 +2687,7 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const do
 
 // The generalised periodic boundaries (gpbc_change) as a pass over the state
 // a step has just written, for the channels that do not step in boxes
-// (ChanDev.gpbc == 1). One workgroup per channel; the column means are taken
+// (column_pass_takes). One workgroup per channel; the column means are taken
 // before anything is changed.
 //
 // Bound by latency: one row of a column per thread, the inlet column in the
@@ -2696,9 +2696,10 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const do
 // registers for the change (columns of up to 256 rows read memory once).
 constexpr int kGpbcRows = 256;  // rows of a column taken at once
 template <typename T, bool SHIFT>
-__global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref) {
+__global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref,
+                                                             bool boxed) {
   const ChanDev c = ch[blockIdx.x];
-  if (c.gpbc != 1 || !c.active) return;
+  if (!column_pass_takes(c, boxed)) return;
   const long long t = c.t + k;
   const double dp = (t < c.t_startup) ? c.pd : 0.0;
   const int nx = c.nx, ny = c.ny;
@@ -3231,14 +3232,15 @@ hipError_t launch_reduce(const ChanDev *ch, int n_ch, const double *part, double
   return hipGetLastError();
 }
 
-hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, const float *uref, hipStream_t s) {
+hipError_t launch_gpbc(int fp32, void *B, const ChanDev *ch, int n_ch, int k, const float *uref, bool boxed,
+                       hipStream_t s) {
   if (n_ch == 0) return hipSuccess;
   if (fp32)
     hipLaunchKernelGGL((gpbc_kernel<float, true>), dim3(n_ch), dim3(2 * kGpbcRows), 0, s, static_cast<float *>(B),
-                       ch, k, uref);
+                       ch, k, uref, boxed);
   else
     hipLaunchKernelGGL((gpbc_kernel<double, false>), dim3(n_ch), dim3(2 * kGpbcRows), 0, s,
-                       static_cast<double *>(B), ch, k, uref);
+                       static_cast<double *>(B), ch, k, uref, boxed);
   return hipGetLastError();
 }
 

@@ -139,7 +139,7 @@ void resolve(const lb_channel &q, ChanDev &d) {
   d.inv_gc = 1.0 / q.gamma_c;
   d.lgt = lgt;
   d.uw = q.wall_velocity;
-  d.gpbc = q.pressure_gradient != 0;
+  d.gpbc = q.pressure_gradient != 0 ? kGpbcPass : 0;
   d.pd = (q.nx + 1) * q.pressure_gradient;
   d.nnp = q.nn_pressure;
   d.zh = q.top_wall == LB_WALL_ZOU_HE;
@@ -663,7 +663,8 @@ struct lb_handle {
   std::vector<int> active;
   int n_checks = 0;
   int since_block = 0;       // steps since the last block boundary (handle clock)
-  bool any_gpbc = false;     // some channel's pressure drive takes the column pass
+  bool gpbc_pass = false;    // some channel's pressure drive takes the column pass after every step,
+  bool gpbc_boxes = false;   // or after steps launched alone (column_pass_takes)
   bool any_zh = false;       // some channel has a Zou-He top wall
   int device = -1;           // the GPU current at lb_create
   double *noalloc = nullptr; // that GPU's copy of `scratch` (device address)
@@ -949,15 +950,18 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     a.down = (src == 1);
     HIPCHECK(h, launch_sweep(h->opt.precision == LB_FP32_SHIFTED, c, false, a, s));
   }
-  // pressure-driven channels, unless the block takes them many steps at once
-  if (block && h->boxes[lb_handle::kPressureMany].S) return LB_OK;
-  const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
-  if (st != LB_OK) return st;
+  // boxes of the pressure-driven channels, unless the block takes them many
+  // steps at once
+  const bool boxed = block && h->boxes[lb_handle::kPressureMany].S;
+  if (!boxed) {
+    const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
+    if (st != LB_OK) return st;
+  }
   // generalised periodic boundaries where the step leaves them: the
   // inlet/outlet column pass on the state just written
-  if (h->any_gpbc)
+  if (h->gpbc_pass || (h->gpbc_boxes && !boxed))
     HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
-                            s));
+                            boxed, s));
   return LB_OK;
 }
 
@@ -1549,8 +1553,9 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   }
   for (int i = 0; i < n; ++i) {
     ChanDev &d = h->L.ch[i];
-    if (d.gpbc && h->blk_ok[i] == kPressureBoxes && h->L.esize == 8) d.gpbc = 2;
-    h->any_gpbc = h->any_gpbc || d.gpbc == 1;
+    if (d.gpbc && h->blk_ok[i] == kPressureBoxes) d.gpbc = h->L.esize == 8 ? kGpbcStep : kGpbcBoxes;
+    h->gpbc_pass = h->gpbc_pass || d.gpbc == kGpbcPass;
+    h->gpbc_boxes = h->gpbc_boxes || d.gpbc == kGpbcBoxes;
   }
   if (hipMemcpyAsync(h->dch, h->L.ch.data(), sizeof(ChanDev) * n, hipMemcpyHostToDevice, h->stream) !=
       hipSuccess)

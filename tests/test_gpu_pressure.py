@@ -78,3 +78,22 @@ def test_pressure_channel_steady(orc, precision):
         tot = p[:, x] + n1 / 2
         assert tot.max() - tot.min() < 0.1 * spread / 2
     assert p[:, 0].mean() - p[:, -1].mean() == pytest.approx(spec.pressure_gradient * (spec.nx - 1), rel=1e-2)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_pressure_channel_beyond_the_boxes(precision):
+    """A pressure-driven channel of more nodes than the boxes address (429.9
+    million) beside a short one that takes many steps per launch: a block of
+    steps and the same steps one by one give the same bits, and the flow that
+    only the drive makes (the channels start from rest)."""
+    kw = dict(force=0.0, pressure_gradient=1e-6, nn_pressure=False, tau_lb=0.8, G=2e-4, tau0=500.0, gamma_c=0.1)
+    chans = [ChannelSpec(nx=1 << 20, ny=410, **kw), ChannelSpec(nx=64, ny=32, **kw)]
+    res = []
+    for steps in ([4], [1] * 4):
+        with solver(chans, precision=precision, obs_every=4) as s:
+            for n in steps:
+                s.step(n)
+            res.append([s.observe(i, f) for i in range(2) for f in ("ux", "pressure", "flux")])
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
+    assert res[0][2] > 0 and res[0][5] > 0

@@ -1,0 +1,62 @@
+"""Which launches advance which channels, on the CPU: the host runtime linked
+with stand-ins for HIP and for its launchers (host_routing_driver.cpp), which
+check that every step of every channel is taken once, from the right buffer,
+and with the pressure drive's boundary applied once."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="session")
+def route(tmp_path_factory):
+    """route(precision, K, steps, channels, ...) -> per channel a dict of
+    steps by launcher and "most", the most steps of one launch."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc) and shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    exe = tmp_path_factory.mktemp("routing") / "host_routing"
+    csrc = os.path.join(ROOT, "paper_1310_7450_amd", "csrc")
+    cmd = [hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+           "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "lb_runtime.hip"),
+           os.path.join(ROOT, "tests", "host_routing_driver.cpp"), "-o", str(exe)]
+    build = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert build.returncode == 0, build.stderr[-2000:]
+
+    def run(precision, K, steps, channels, viscoelastic=0, stress_force=0, steps_per_sweep=0):
+        args = [f"{nx},{ny}," + ",".join(str(int(f in flags)) for f in ("pressure", "wall", "zou_he"))
+                for nx, ny, *flags in channels]
+        r = subprocess.run([str(exe), precision, str(K), str(viscoelastic), str(stress_force), str(steps_per_sweep),
+                            ",".join(map(str, steps)), *args], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+        return [{k: int(v) for k, v in (w.split("=") for w in line.split()[2:])}
+                for line in r.stdout.splitlines() if line.startswith("channel")]
+
+    return run
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_pressure_channel_beyond_the_boxes_keeps_its_boundary(route, precision):
+    """A pressure-driven channel too large for the boxes' 32-bit slots beside a
+    short one that takes many steps per launch: the column pass follows each of
+    its steps, in whole blocks too."""
+    large, small = route(precision, 20, [40, 3, 1, 60], [(1 << 20, 410, "pressure"), (64, 32, "pressure")])
+    assert large["column_pass"] == 104 and "boxes" not in large
+    assert small["boxes"] == 104 and small["most"] > 1
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("K,steps", [(20, [40, 3, 1, 60]), (2, [7]), (6, [5, 13]), (100, [250, 1, 49])])
+@pytest.mark.parametrize("viscoelastic", [0, 1])
+def test_every_step_once(route, precision, K, steps, viscoelastic):
+    """Channels of every route in one handle, and each alone: narrow, aligned
+    and other widths below and above the boxes' limits, walls, the pressure
+    drive short, tall and above its limit."""
+    chans = [(8, 40, "wall"), (512, 40), (300, 11), (600, 3000), (1024, 2000, "zou_he"), (64, 20000), (32, 9),
+             (64, 32, "pressure"), (24, 300, "pressure")]
+    for case in [chans, chans + [(1100, 1000, "pressure")], chans[:3] + chans[6:7], chans[7:]] + [[c] for c in chans]:
+        route(precision, K, steps, case, viscoelastic)
+        route(precision, K, steps, case, viscoelastic, steps_per_sweep=1)
