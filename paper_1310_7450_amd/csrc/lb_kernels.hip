@@ -1027,13 +1027,18 @@ __device__ __forceinline__ double column_density(const double *__restrict__ C, i
 }
 
 // Sum of a column of n densities (stride s apart) over a wavefront, all lanes
-// active: 64 rows after 64, or (TREE) in the order of gpbc_kernel.
+// active: the sums of the rows of one residue mod 256, 64 of them after 64, or
+// (TREE) in the order of gpbc_kernel.
 template <bool TREE>
 __device__ __forceinline__ double column_sum(const double *col, int s, int n) {
   const int lane = threadIdx.x & 63;
   if constexpr (!TREE) {
     double sum = 0;
-    for (int k = 0; k < n; k += 64) sum += group_sum<64>(k + lane < n ? col[(k + lane) * s] : 0.0);
+    for (int k = 0; k < min(n, 256); k += 64) {
+      double v = 0;
+      for (int r = k + lane; r < n; r += 256) v += col[r * s];
+      sum += group_sum<64>(v);
+    }
     return sum;
   } else {
     double part[4] = {0, 0, 0, 0};
@@ -1209,20 +1214,24 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
   const int inlet = !GP || cx0 == 0 ? 0 : (cx0 < 0 ? -cx0 % nx : nx - cx0);
   const int outlet = inlet == 0 ? nx - 1 : inlet - 1;
   if (GP && !SHIFT && S == 1) {
-    __shared__ double colsum[2][TH / 64];
+    // 256 threads to a column whatever TH, in the order of column_sum (from
+    // 512 on the outlet's are others than the inlet's)
+    __shared__ double colsum[2][4];
     const bool stores[2] = {st.x0 == 0, st.x1 >= nx};
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
+      if (TH > 256 && (wave >> 2) != side) continue;
       double sum = 0;
       if (stores[side])
-        for (int yy = threadIdx.x; yy < ny; yy += TH)
+        for (int yy = threadIdx.x & 255; yy < ny; yy += 256)
           sum += column_density(static_cast<const double *>(a.A) + c.off * kPlanes, nx, ny, side ? nx - 1 : 0, yy);
       sum = group_sum<64>(sum);
-      if ((threadIdx.x & 63) == 0) colsum[side][threadIdx.x >> 6] = sum;
+      if ((threadIdx.x & 63) == 0) colsum[side][wave & 3] = sum;
     }
     __syncthreads();
     double in_sum = 0, out_sum = 0;
-    for (int w = 0; w < TH / 64; ++w) {
+    for (int w = 0; w < 4; ++w) {
       in_sum += colsum[0][w];
       out_sum += colsum[1][w];
     }

@@ -183,3 +183,18 @@ def test_pressure_boxes_match_oracle(orc, precision, tol, nx, ny, steps):
         err = np.abs(s.get_state(0)[0] - o.n).max() / np.abs(o.n - workloads.REST_WEIGHTS[:, None, None]).max()
     print(f"{precision} {nx}x{ny}: {err:.2e}", flush=True)
     assert err < tol
+
+
+@pytest.mark.parametrize("nx,ny", [(2, 400), (3, 300), (2, 512), (24, 300), (24, 513), (40, 1000), (4, 17000)])
+def test_pressure_column_sum_has_one_order(nx, ny):
+    """FP64 columns of more than 256 rows: the density of an inlet or outlet
+    column is summed in one order, whatever workgroup size the plan of the
+    handle's channels picks and whether a launch takes one step or many."""
+    kw = dict(force=0.0, pressure_gradient=1e-6, nn_pressure=False)
+    c = spec(nx, ny, **kw)
+    others = [[], [spec(300, 11)], [spec(700, 900, **kw)], [spec(64, 32, **kw)] * 40,
+              [spec(16 + i, 260 + 9 * i, **kw) for i in range(30)]]
+    first = run([c], "fp64", 40, [80], 0)
+    for o in others:
+        for steps in ([80], [1] * 45 + [35]):
+            assert_same(first, run([c] + o, "fp64", 40, steps, 0)[:1], (nx, ny, len(o), steps))
