@@ -97,3 +97,23 @@ def test_pressure_channel_beyond_the_boxes(precision):
     for a, b in zip(*res):
         assert np.array_equal(a, b)
     assert res[0][2] > 0 and res[0][5] > 0
+
+
+@pytest.mark.parametrize("precision,nx,ny", [("fp32", 16, 4097), ("fp32", 30, 4100), ("fp32", 15, 4100),
+                                             ("fp32", 16, 4096), ("fp64", 30, 12000)])
+def test_pressure_tall_columns_match_oracle(orc, precision, nx, ny):
+    """The column pass on both sides of the height and width from which one
+    thread takes both nodes of a row (and, FP64, from which a channel leaves
+    the boxes), against the oracle with the bounds of the state parity."""
+    spec = ChannelSpec(nx=nx, ny=ny, force=0.0, tau_lb=0.8, G=2e-4, tau0=500.0, gamma_c=0.1, eps=0.01,
+                       visc_split=0.3, t_startup=6, pressure_gradient=1e-5)
+    pops, P = workloads.random_state(nx, ny, seed=nx + ny)
+    o = oracle_channel(orc, spec)
+    o.set_state(pops, P, t=0)
+    o.run(9)
+    with solver([spec], precision=precision, obs_every=4, nn_pressure=False) as s:
+        s.set_state(0, pops, P, 0)
+        s.step(9)
+        err = np.abs(s.get_state(0)[0] - o.n).max() / np.abs(o.n - workloads.REST_WEIGHTS[:, None, None]).max()
+    print(f"{precision} {nx}x{ny}: {err:.2e}", flush=True)
+    assert err < (1e-12 if precision == "fp64" else 2e-6) * 50
