@@ -235,6 +235,16 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize
 //  * the stress as a force (FP64; tiles): 8 x 64 1.9 / 10.3, 143 x 43 3.2 / 7.7,
 //    512 x 64 4.4 / 8.0, 1000 x 100 5.9 / 8.6, 512 x 300 9.0 / 10.4, 500 x 500
 //    14.1 / 12.1.
+// A tall FP64 channel with the pressure drive keeps the strips and the column
+// pass: every box at a period's end sums whole columns, whose lines are read
+// once for each of them, so that work grows with the height squared. Boxes
+// against strips, us per step: 100 x 5000 174 / 264, 100 x 7500 420 / 353; 16 x
+// 10000 186 / 368, 16 x 15800 1775 / 612; 4 x 31600 154 / 340, 4 x 100000 6800 /
+// 980.
+bool tall_pressure(const lb_channel &c, int esize) {
+  const double boxes = (double)c.ny * std::min(c.nx, 70), lines = (double)c.ny * std::min(c.nx, 16);
+  return esize == 8 && boxes * lines > 4e10;
+}
 // values of block_channels: not in boxes; many steps per launch; pressure drive
 enum { kNoBoxes = 0, kBoxes = 1, kPressureBoxes = 2 };
 std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize) {
@@ -250,6 +260,7 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
     if (o->steps_per_sweep == 1 && !gp) continue;
     const size_t N = (size_t)c[i].nx * c[i].ny;
     if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
+    if (gp && tall_pressure(c[i], esize)) continue;
     const int cls = width_class(c[i].nx, esize);
     kind[i] = o->stress_force         ? FORCE
               : gp                    ? PRESSURE

@@ -60,3 +60,16 @@ def test_every_step_once(route, precision, K, steps, viscoelastic):
     for case in [chans, chans + [(1100, 1000, "pressure")], chans[:3] + chans[6:7], chans[7:]] + [[c] for c in chans]:
         route(precision, K, steps, case, viscoelastic)
         route(precision, K, steps, case, viscoelastic, steps_per_sweep=1)
+
+
+@pytest.mark.parametrize("precision,shape,boxes", [
+    ("fp64", (100, 5000), True), ("fp64", (100, 7500), False), ("fp64", (16, 10000), True),
+    ("fp64", (16, 15800), False), ("fp64", (4, 31600), True), ("fp64", (4, 100000), False),
+    ("fp32", (30, 30000), True), ("fp32", (4, 100000), True)])
+def test_tall_pressure_channels_keep_the_column_pass(route, precision, shape, boxes):
+    """Boxes of a tall channel would each sum whole columns: strips and the
+    column pass take it, also beside a short channel in boxes."""
+    for case in [[(*shape, "pressure")], [(*shape, "pressure"), (64, 32, "pressure")]]:
+        tall, *rest = route(precision, 20, [40, 3], case)
+        assert ("boxes" in tall) == boxes and all(c["boxes"] == 43 for c in rest)
+        assert tall.get("column_pass", 0) == (0 if boxes and precision == "fp64" else 43)
