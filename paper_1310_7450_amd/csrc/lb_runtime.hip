@@ -245,34 +245,79 @@ bool tall_pressure(const lb_channel &c, int esize) {
   const double boxes = (double)c.ny * std::min(c.nx, 70), lines = (double)c.ny * std::min(c.nx, 16);
   return esize == 8 && boxes * lines > 4e10;
 }
+// That holds for launches of several steps. One step per launch leaves a box
+// its halo and its loads: above the further limits the one-step sweeps are
+// faster, and take blocks whose length leaves a plan one step (K / 2 without a
+// divisor that pays) and single steps off the block boundaries. Measured, us
+// per step, boxes against one-step sweeps:
+//  * such blocks (K = 1006): FP32 aligned 1024 x 500 15.6 / 17.1, 1024 x 700
+//    17.4 / 16.5 (time-integrated 1024 x 850 21.6 / 22.6); FP64 aligned 256 x
+//    128 4.2 / 5.0, 384 x 256 6.4 / 5.8, other widths 500 x 100 5.0 / 5.3,
+//    1000 x 100 6.5 / 5.7;
+//  * steps one by one, boxes planned for more: FP32 aligned 1024 x 500 18.9 /
+//    19.2, 1024 x 600 20.9 / 18.3 (time-integrated 21.3 / 22.8, 1024 x 700 23.8
+//    / 23.4), other widths 2000 x 1000 53.9 / 55.7, 3000 x 1000 78.6 / 62.8;
+//    FP64 aligned 256 x 256 7.8 / 8.1, 384 x 256 9.1 / 8.5, other widths 500 x
+//    300 10.1 / 10.4, 500 x 450 14.2 / 11.6;
+//  * short runs of steps off the boundaries, FP32 aligned 1024 x 700 15.7 /
+//    17.3, 1024 x 850 18.2 / 17.6; FP64 512 x 512 10.4 / 11.5, 768 x 512 14.8 /
+//    14.0 (time-integrated 1024 x 512 20.1 / 20.4, 1024 x 600 24.3 / 23.6).
+enum BoxKind { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, FORCE, BOX_KINDS };
+struct BoxLimits {
+  long long steps;      // most nodes of a kind in boxes of several steps,
+  long long one;        // in boxes of one step,
+  long long call_one;   // in boxes for a single step off the block boundaries,
+  long long call;       // or several
+};
+BoxLimits box_limits(const lb_options *o, int kind) {
+  const bool fp32 = o->precision == LB_FP32_SHIFTED, ve = o->viscoelastic;
+  const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
+  auto same = [](long long n) { return BoxLimits{n, n, n, n}; };
+  switch (kind) {
+    case ALIGNED:
+      if (fp32) return ve ? BoxLimits{7 * M / 8, 7 * M / 8, 5 * M / 8, 7 * M / 8}
+                          : BoxLimits{7 * M / 8, M / 2, M / 2, 3 * M / 4};
+      return BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? M / 2 : 5 * M / 16};
+    case OTHER:
+      if (fp32) return BoxLimits{8 * M, 8 * M, 2 * M, 8 * M};
+      return ve ? BoxLimits{8 * M, M / 16, 5 * M / 32, 8 * M}
+                : BoxLimits{3 * M / 10, M / 16, 5 * M / 32, 3 * M / 10};
+    case NARROW_WIDE: return same(ve ? always : fp32 ? M : M / 4);
+    case PRESSURE: return same(M);
+    case FORCE: return same(5 * M / 32);
+    default: return same(always);
+  }
+}
+// The kind of a channel, or -1 if no box takes it.
+int box_kind(const lb_options *o, const lb_channel &c, int esize) {
+  const bool gp = c.pressure_gradient != 0;  // one step per launch in either setting
+  if (o->steps_per_sweep == 1 && !gp) return -1;
+  const size_t N = (size_t)c.nx * c.ny;
+  if (align_up(N, kTile) * kPlanes > 0xffffffffull) return -1;  // 32-bit slots in a channel
+  if (gp && tall_pressure(c, esize)) return -1;
+  const int cls = width_class(c.nx, esize);
+  return o->stress_force         ? FORCE
+         : gp                    ? PRESSURE
+         : cls == kVecClass      ? ALIGNED
+         : is_strip_class(cls)   ? OTHER
+         : c.nx > 16             ? NARROW_WIDE
+                                 : NARROW;
+}
 // values of block_channels: not in boxes; many steps per launch; pressure drive
 enum { kNoBoxes = 0, kBoxes = 1, kPressureBoxes = 2 };
-std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize) {
-  enum { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, FORCE, KINDS };
-  const bool fp32 = esize == 4, ve = o->viscoelastic;
-  const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
-  const long long limit[KINDS] = {fp32 ? 7 * M / 8 : 5 * M / 8, (fp32 || ve) ? 8 * M : 3 * M / 10,
-                                  always, ve ? always : (fp32 ? M : M / 4), M, 5 * M / 32};
-  std::vector<int> kind(n, -1);
-  long long nodes[KINDS] = {};
+// The channels whose kind's nodes in the handle do not exceed this limit.
+std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize,
+                                 long long BoxLimits::*limit) {
+  std::vector<int> kind(n);
+  long long nodes[BOX_KINDS] = {};
   for (int i = 0; i < n; ++i) {
-    const bool gp = c[i].pressure_gradient != 0;  // one step per launch in either setting
-    if (o->steps_per_sweep == 1 && !gp) continue;
-    const size_t N = (size_t)c[i].nx * c[i].ny;
-    if (align_up(N, kTile) * kPlanes > 0xffffffffull) continue;  // 32-bit slots in a channel
-    if (gp && tall_pressure(c[i], esize)) continue;
-    const int cls = width_class(c[i].nx, esize);
-    kind[i] = o->stress_force         ? FORCE
-              : gp                    ? PRESSURE
-              : cls == kVecClass      ? ALIGNED
-              : is_strip_class(cls)   ? OTHER
-              : c[i].nx > 16          ? NARROW_WIDE
-                                      : NARROW;
-    nodes[kind[i]] += (long long)N;
+    kind[i] = box_kind(o, c[i], esize);
+    if (kind[i] >= 0) nodes[kind[i]] += (long long)c[i].nx * c[i].ny;
   }
-  std::vector<char> ok(n, 0);
+  std::vector<char> ok(n, kNoBoxes);
   for (int i = 0; i < n; ++i)
-    if (kind[i] >= 0 && nodes[kind[i]] <= limit[kind[i]]) ok[i] = kind[i] == PRESSURE ? kPressureBoxes : kBoxes;
+    if (kind[i] >= 0 && nodes[kind[i]] <= box_limits(o, kind[i]).*limit)
+      ok[i] = kind[i] == PRESSURE ? kPressureBoxes : kBoxes;
   return ok;
 }
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
@@ -595,7 +640,7 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
   L.off_btiles = take(sizeof(Strip) * std::max(L.n_tiles, 1));
   // boxes of 64 nodes, or 4096 boxes and two per channel, in handles with
   // channels that step in them
-  L.blk_ok = block_channels(o, c, n, L.esize);
+  L.blk_ok = block_channels(o, c, n, L.esize, &BoxLimits::steps);
   L.max_boxes = std::max<long long>(4096 + 2ll * n, L.plane / 64);
   auto boxes = [&](char kind) {
     return std::count(L.blk_ok.begin(), L.blk_ok.end(), kind) ? sizeof(Strip) * L.max_boxes : 0;
@@ -650,6 +695,9 @@ struct lb_handle {
   int n_tiles = 0;           // tiles of the one-step tile list
   int only = -1;               // the box list that holds every active channel, if one does
   bool blk_all = false;        // every active channel runs many steps per launch in boxes
+  // off the block boundaries boxes take single steps, or several at a time, of
+  // the channels that run many steps in them
+  bool box_one = false, box_several = false;
   std::vector<char> blk_ok;    // how each channel uses boxes (kNoBoxes, kBoxes, kPressureBoxes)
   int cus = 256;
   // captured blocks: the narrow two-step strips of each width, after the
@@ -1551,16 +1599,34 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->blk_ok = h->L.blk_ok;
   for (int l = 0; l < lb_handle::kBoxLists; ++l) {
     const char kind = l == lb_handle::kMany ? kBoxes : kPressureBoxes;
-    std::vector<lb_channel> chans;
-    for (int i = 0; i < n; ++i)
-      if (h->blk_ok[i] == kind) chans.push_back(c[i]);
-    if (chans.empty()) continue;
     // (a plan for all is one for those still active later)
     BoxPlan &p = h->boxes[l].all;
-    p = box_list_plan(h, l, chans);
+    auto plan = [&]() {
+      std::vector<lb_channel> chans;
+      for (int i = 0; i < n; ++i)
+        if (h->blk_ok[i] == kind) chans.push_back(c[i]);
+      p = chans.empty() ? BoxPlan() : box_list_plan(h, l, chans);
+    };
+    plan();
+    if (l == lb_handle::kMany && p.S == 1) {
+      const std::vector<char> one = block_channels(o, c, n, h->L.esize, &BoxLimits::one);
+      for (int i = 0; i < n; ++i)
+        if (h->blk_ok[i] == kBoxes) h->blk_ok[i] = one[i];
+      plan();
+    }
     if (p.S == 0 && l != lb_handle::kPressureMany)
       for (char &k : h->blk_ok)
         if (k == kind) k = kNoBoxes;
+  }
+  {
+    const std::vector<char> one = block_channels(o, c, n, h->L.esize, &BoxLimits::call_one),
+                            several = block_channels(o, c, n, h->L.esize, &BoxLimits::call);
+    h->box_one = h->box_several = true;
+    for (int i = 0; i < n; ++i)
+      if (h->blk_ok[i] == kBoxes) {
+        h->box_one = h->box_one && one[i];
+        h->box_several = h->box_several && several[i];
+      }
   }
   for (int i = 0; i < n; ++i) {
     ChanDev &d = h->L.ch[i];
@@ -1650,10 +1716,13 @@ lb_status lb_step(lb_handle *h, int64_t n) {
         // every channel takes them (the same results: no kernel's rounding
         // differs from another's)
         const int src = h->cur ^ (launches & 1);
-        const int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : h->two_only ? std::min(2, m - k) : 1;
-        lb_status st = h->only >= 0 ? enqueue_boxes(h, h->only, src, k, S, h->stream)
-                       : S == 2     ? enqueue_two_step(h, src, k, h->stream)
-                                    : enqueue_step(h, src, k, h->stream);
+        int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : 0;
+        if (h->only == lb_handle::kMany && !(S > 1 ? h->box_several : h->box_one)) S = 0;
+        const bool in_boxes = S > 0;
+        if (!in_boxes) S = h->two_only ? std::min(2, m - k) : 1;
+        lb_status st = in_boxes ? enqueue_boxes(h, h->only, src, k, S, h->stream)
+                       : S == 2 ? enqueue_two_step(h, src, k, h->stream)
+                                : enqueue_step(h, src, k, h->stream);
         if (st != LB_OK) return st;
         k += S;
       }

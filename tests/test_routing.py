@@ -73,3 +73,31 @@ def test_tall_pressure_channels_keep_the_column_pass(route, precision, shape, bo
         tall, *rest = route(precision, 20, [40, 3], case)
         assert ("boxes" in tall) == boxes and all(c["boxes"] == 43 for c in rest)
         assert tall.get("column_pass", 0) == (0 if boxes and precision == "fp64" else 43)
+
+
+@pytest.mark.parametrize("precision,shape,viscoelastic,single", [
+    ("fp32", (512, 512), 0, "boxes"), ("fp32", (1024, 600), 0, "sweep"), ("fp32", (1024, 600), 1, "boxes"),
+    ("fp64", (256, 128), 0, "boxes"), ("fp64", (512, 512), 0, "tiles"), ("fp64", (1000, 100), 0, "tiles"),
+    ("fp64", (300, 100), 0, "boxes"), ("fp64", (4000, 2000), 1, "tiles"), ("fp64", (8, 262144), 0, "boxes")])
+def test_blocks_of_one_step_plans(route, precision, shape, viscoelastic, single):
+    """Half a block without a divisor that pays (1, 503): boxes of one step
+    replace the one-step sweeps only where they are faster; blocks of many
+    divisors keep the boxes."""
+    for K in (2, 1006):
+        c, = route(precision, K, [2 * K], [shape], viscoelastic)
+        assert c[single] == 2 * K and c["most"] == 1
+    c, = route(precision, 1000, [1000], [shape], viscoelastic)
+    assert c["boxes"] == 1000 and c["most"] > 1
+
+
+@pytest.mark.parametrize("precision,shape,single,several", [
+    ("fp32", (512, 512), "boxes", "boxes"), ("fp32", (1024, 700), "sweep", "boxes"),
+    ("fp32", (1024, 850), "sweep", "sweep"), ("fp32", (4000, 1000), "sweep", "boxes"),
+    ("fp64", (256, 256), "boxes", "boxes"), ("fp64", (512, 512), "tiles", "boxes"),
+    ("fp64", (1024, 512), "tiles", "tiles"), ("fp64", (500, 500), "tiles", "boxes")])
+def test_steps_off_the_block_boundaries(route, precision, shape, single, several):
+    """Single steps, and runs of some, by the path that is faster there."""
+    c, = route(precision, 1000, [1] * 10, [shape])
+    assert c[single] == 10
+    c, = route(precision, 1000, [500], [shape])
+    assert c[several] >= 498
