@@ -5,6 +5,7 @@
 #include "lb_internal.h"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -476,52 +477,67 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, bool 
   const double launch = fp32 ? 2.7 : 2.0, start = fp32 ? 0.13 : 0.63, step = fp32 ? 0.38 : stress_force ? 0.9 : 0.59,
                wave = fp32 ? 0.29 : stress_force ? 0.6 : 0.47, busy = fp32 ? 0.032 : 0.0, load = fp32 ? 0.2 : 0.22;
   const int reach = stress_force ? 3 : 2;  // nodes a step reaches
+  // the channels' shapes, each once with its number
+  std::vector<const lb_channel *> shaped;
+  std::vector<double> number;
+  std::vector<int> which;
+  std::map<std::array<int, 3>, int> seen;
   bool pressure = false;
-  for (const lb_channel &c : chans) pressure = pressure || c.pressure_gradient != 0;
+  for (const lb_channel &c : chans) {
+    const bool gp = c.pressure_gradient != 0;
+    pressure = pressure || gp;
+    const auto [it, added] = seen.try_emplace({c.nx, c.ny, gp}, (int)shaped.size());
+    if (added) {
+      shaped.push_back(&c);
+      number.push_back(0);
+    }
+    which.push_back(it->second);
+    number[it->second] += 1;
+  }
+  struct Fit {
+    std::vector<BoxShape> shape;  // by shape of a channel; empty: not every one has a box
+    double W = 0, R = 0, V = 0, vmax = 0;
+  };
+  std::vector<BoxShape> best_shape;
   for (int S = 1; S <= K / 2 && S <= 64; ++S) {  // (beyond 64 a launch's own time no longer counts)
     if ((K / 2) % S) continue;
-    std::map<int, std::vector<BoxShape>> shapes;  // by largest region (empty: not every channel has one)
+    std::map<int, Fit> fits;  // by largest region
     for (int th = 256; th <= 1024; th *= 2) {
       const int resident = (fp32 && !pressure ? 24 : 16) * 64 / th;  // workgroups of a CU, by registers
       for (int part : {8, 6, 4, 3, 2}) {
-        BoxPlan p;
-        p.S = S;
-        p.threads = th;
-        double W = 0, R = 0, V = 0, vmax = 0;
-        const auto [it, added] = shapes.try_emplace(th * part / 8);
-        for (size_t i = 0; added && i < chans.size(); ++i) {
+        const auto [it, added] = fits.try_emplace(th * part / 8);
+        Fit &f = it->second;
+        for (size_t i = 0; added && i < shaped.size(); ++i) {
+          const lb_channel &c = *shaped[i];
           BoxShape b;
-          if (!box_shape(chans[i], S, reach, th * part / 8, b)) {
-            it->second.clear();
+          if (!box_shape(c, S, reach, th * part / 8, b)) {
+            f.shape.clear();
             break;
           }
-          it->second.push_back(b);
-        }
-        if (it->second.empty()) continue;
-        p.shape = it->second;
-        for (size_t i = 0; i < chans.size(); ++i) {
-          const lb_channel &c = chans[i];
-          const BoxShape b = p.shape[i];
-          const double w = (double)box_count(c, b);
+          f.shape.push_back(b);
+          const double w = number[i] * (double)box_count(c, b);
           const int v0 = box_waves(c, b, S, reach, 0);
           const double v = 0.5 * (v0 + box_waves(c, b, S, reach, S - 1));
-          W += w;
-          R += w * v0;
-          V += w * v;
-          vmax = std::max(vmax, v);
+          f.W += w;
+          f.R += w * v0;
+          f.V += w * v;
+          f.vmax = std::max(f.vmax, v);
         }
-        if (W > (double)room) continue;
-        const double slots = (double)resident * cus, rounds = std::ceil(W / slots);
-        const double m = W <= slots ? std::ceil(W / cus) : 1.3;
+        if (f.shape.empty() || f.W > (double)room) continue;
+        const double slots = (double)resident * cus, rounds = std::ceil(f.W / slots);
+        const double m = f.W <= slots ? std::ceil(f.W / cus) : 1.3;
         const double us =
-            (launch + rounds * (start + S * (step + wave * m * vmax / 4)) + (S * busy * V + load * R) / cus) / S;
+            (launch + rounds * (start + S * (step + wave * m * f.vmax / 4)) + (S * busy * f.V + load * f.R) / cus) / S;
         if (us < best_us) {
           best_us = us;
-          best = p;
+          best.S = S;
+          best.threads = th;
+          best_shape = f.shape;
         }
       }
     }
   }
+  for (size_t i = 0; best.S && i < chans.size(); ++i) best.shape.push_back(best_shape[which[i]]);
   return best;
 }
 // Strips of one channel, band by band. With flip odd bands march against the
