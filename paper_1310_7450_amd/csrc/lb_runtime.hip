@@ -31,6 +31,7 @@ namespace {
 constexpr int kDefaultK = 1000;
 constexpr size_t kAlign = 256;
 constexpr size_t kStageNodes = 4096;  // 320 KB
+constexpr size_t kHostStressNodes = 1 << 15;  // converted on the host (8 x 4096 FP32: 68 us, on the GPU 143)
 #ifndef LB_WG_WAVES
 #define LB_WG_WAVES 4
 #endif
@@ -62,8 +63,8 @@ struct Layout {
   size_t off_bstrips = 0, off_brstrips = 0, off_tstrips = 0;
   size_t off_blk = 0;     // boxes of the channels that run many steps per launch
   size_t off_gpb = 0, off_gpm = 0;  // boxes of the pressure-driven channels, one and many steps per launch
-  // FP32: staging of a state where the other buffer holds too few rows of it
-  // (see store_state), and of every state of at most kStageNodes
+  // staging of every state of at most kStageNodes, and (FP32) of one where the
+  // other buffer holds too few rows of it (see store_state)
   size_t off_stage = 0, stage = 0;
   size_t off_btiles = 0;  // tiles of the tiled channels without two-step strips
   int strip_cap = 0;      // entries of each one-step strip list
@@ -665,9 +666,10 @@ Layout make_layout(const lb_channel *c, int n, const lb_options *o) {
   L.off_gpb = take(boxes(kPressureBoxes));
   L.off_gpm = take(boxes(kPressureBoxes));
   L.off_tstrips = take(sizeof(Strip) * std::max(L.max_two, 1));
-  for (int i = 0; i < n && L.esize == 4; ++i) {
+  for (int i = 0; i < n; ++i) {
     const size_t N = (size_t)c[i].nx * c[i].ny;
-    const size_t nodes = N <= kStageNodes ? N : (c[i].ny < 6 ? (size_t)c[i].nx * std::min(c[i].ny, 3) : 0);
+    const size_t nodes = N <= kStageNodes ? N
+                         : L.esize == 4 && c[i].ny < 6 ? (size_t)c[i].nx * std::min(c[i].ny, 3) : 0;
     L.stage = std::max(L.stage, sizeof(double) * kPlanes * nodes);
   }
   L.off_stage = take(L.stage);
@@ -1137,21 +1139,28 @@ lb_status read_observation(lb_handle *h) {
 // Copies channel ch's tiles (and stress tiles) from the current buffer to
 // the other one. A frozen channel is no longer swept, so both buffers must
 // hold its state: later steps of odd length change which buffer is current.
-lb_status mirror_channel(lb_handle *h, int ch) {
+lb_status mirror_state(lb_handle *h, int ch) {
   const ChanDev &d = h->L.ch[ch];
-  const size_t Npad = align_up((size_t)d.nx * d.ny, kTile);
-  const int es = h->L.esize;
-  const size_t off = (size_t)slot(0, d.off) * es, bytes = (size_t)kPlanes * Npad * es;
+  const size_t Npad = align_up((size_t)d.nx * d.ny, kTile), es = h->L.esize;
+  const size_t off = (size_t)slot(0, d.off) * es;
   HIPCHECK(h, hipMemcpyAsync(static_cast<char *>(h->buf[h->cur ^ 1]) + off,
-                             static_cast<const char *>(h->buf[h->cur]) + off, bytes, hipMemcpyDeviceToDevice,
-                             h->stream));
-  if (h->sbuf[0]) {
-    const size_t soff = (size_t)sslot(0, d.off) * es, sbytes = (size_t)kStressPlanes * Npad * es;
-    HIPCHECK(h, hipMemcpyAsync(static_cast<char *>(h->sbuf[h->cur ^ 1]) + soff,
-                               static_cast<const char *>(h->sbuf[h->cur]) + soff, sbytes, hipMemcpyDeviceToDevice,
-                               h->stream));
-  }
+                             static_cast<const char *>(h->buf[h->cur]) + off, kPlanes * Npad * es,
+                             hipMemcpyDeviceToDevice, h->stream));
   return LB_OK;
+}
+lb_status mirror_stress(lb_handle *h, int ch) {
+  if (!h->sbuf[0]) return LB_OK;
+  const ChanDev &d = h->L.ch[ch];
+  const size_t Npad = align_up((size_t)d.nx * d.ny, kTile), es = h->L.esize;
+  const size_t off = (size_t)sslot(0, d.off) * es;
+  HIPCHECK(h, hipMemcpyAsync(static_cast<char *>(h->sbuf[h->cur ^ 1]) + off,
+                             static_cast<const char *>(h->sbuf[h->cur]) + off, kStressPlanes * Npad * es,
+                             hipMemcpyDeviceToDevice, h->stream));
+  return LB_OK;
+}
+lb_status mirror_channel(lb_handle *h, int ch) {
+  const lb_status st = mirror_state(h, ch);
+  return st == LB_OK ? mirror_stress(h, ch) : st;
 }
 
 // Convergence check after a graph: residuals of all channels, freeze the
@@ -1222,8 +1231,9 @@ lb_status rereference(lb_handle *h, bool observed) {
 //
 // lb_get_state, lb_set_state, lb_set_profile and the stress calls convert on
 // the GPU; what crosses the host link is the caller's FP64 array, staged in
-// the other state (stress) buffer, which mirror_channel then makes equal to
-// the current one again. The link bounds it: the copies of the 24 MB of
+// the other state buffer, which mirror_state then makes equal to the current
+// one again (small states in an area of their own; a small stress is read
+// through the host). The link bounds it: the copies of the 24 MB of
 // 1000 x 300 nodes take 0.7 ms in and 1.4 ms out (pageable memory). Set, 200
 // FP32 steps and read take 5.4 ms there, with host loops over the nodes 24.1.
 // Every value is formed by the operations, in the order, of the definition in
@@ -1368,18 +1378,18 @@ __global__ void pack_state_kernel(T *__restrict__ dst, const double *__restrict_
   }
 }
 
-// The stored stress to and from planes [p0, p1) of the C ABI's layout.
+// The stored stress to and from the C ABI's layout.
 template <typename T>
-__global__ void unpack_stress_kernel(const T *__restrict__ src, double *__restrict__ out, long long N, int p0, int p1) {
+__global__ void unpack_stress_kernel(const T *__restrict__ src, double *__restrict__ out, long long N) {
   const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (id >= N) return;
-  for (int p = p0; p < p1; ++p) out[(p - p0) * N + id] = src[sslot(p, id)];
+  for (int p = 0; p < kStressPlanes; ++p) out[p * N + id] = src[sslot(p, id)];
 }
 template <typename T>
-__global__ void pack_stress_kernel(T *__restrict__ dst, const double *__restrict__ in, long long N, int p0, int p1) {
+__global__ void pack_stress_kernel(T *__restrict__ dst, const double *__restrict__ in, long long N) {
   const long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (id >= N) return;
-  for (int p = p0; p < p1; ++p) dst[sslot(p, id)] = (T)in[(p - p0) * N + id];
+  for (int p = 0; p < kStressPlanes; ++p) dst[sslot(p, id)] = (T)in[p * N + id];
 }
 
 StateArgs state_args(const lb_handle *h, int ch, long long t) {
@@ -1888,16 +1898,32 @@ lb_status lb_get_state(lb_handle *h, int32_t ch, double *pops, double *P) {
   double *stage = reinterpret_cast<double *>(static_cast<char *>(h->buf[h->cur ^ 1]) + (size_t)slot(0, d.off) * es);
   const StateArgs a = state_args(h, ch, h->t[ch]);
   const dim3 grid((unsigned)((N + 255) / 256));
+  auto unpack = [&](double *to, int p0, int p1) {
+    if (es == 8)
+      hipLaunchKernelGGL(unpack_state_kernel<double>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const double *>(src), h->duref + d.row_off, to, a, p0, p1);
+    else
+      hipLaunchKernelGGL(unpack_state_kernel<float>, grid, dim3(256), 0, h->stream,
+                         reinterpret_cast<const float *>(src), h->duref + d.row_off, to, a, p0, p1);
+    return hipGetLastError();
+  };
+  if (N <= kStageNodes) {
+    // small: by the staging area in one copy, the other buffer left alone (two
+    // copies and the mirroring after them took 61 us for 64 x 32
+    // FP64, this 41)
+    double *small = reinterpret_cast<double *>(h->ws + h->L.off_stage);
+    std::vector<double> out((size_t)kPlanes * N);
+    HIPCHECK(h, unpack(small, 0, kPlanes));
+    HIPCHECK(h, hipMemcpyAsync(out.data(), small, sizeof(double) * kPlanes * N, hipMemcpyDeviceToHost, h->stream));
+    HIPCHECK(h, hipStreamSynchronize(h->stream));
+    std::copy(out.begin(), out.begin() + 9 * N, pops);
+    std::copy(out.begin() + 9 * N, out.end(), P);
+    return LB_OK;
+  }
   const int per = es == 8 ? kPlanes : kPlanes / 2;
   for (int p0 = 0; p0 < kPlanes; p0 += per) {
     const int p1 = p0 + per;
-    if (es == 8)
-      hipLaunchKernelGGL(unpack_state_kernel<double>, grid, dim3(256), 0, h->stream,
-                         reinterpret_cast<const double *>(src), h->duref + d.row_off, stage, a, p0, p1);
-    else
-      hipLaunchKernelGGL(unpack_state_kernel<float>, grid, dim3(256), 0, h->stream,
-                         reinterpret_cast<const float *>(src), h->duref + d.row_off, stage, a, p0, p1);
-    HIPCHECK(h, hipGetLastError());
+    HIPCHECK(h, unpack(stage, p0, p1));
     const int np = std::min(p1, 9) - p0;
     HIPCHECK(h, hipMemcpyAsync(pops + p0 * N, stage, sizeof(double) * np * N, hipMemcpyDeviceToHost, h->stream));
     if (p1 == kPlanes)
@@ -1920,25 +1946,34 @@ lb_status lb_get_stress(lb_handle *h, int32_t ch, double *sigma) {
   if (ch < 0 || ch >= h->n_ch || !sigma) return fail(h, LB_EINVAL, "bad channel or output");
   if (!h->opt.viscoelastic) return fail(h, LB_EINVAL, "the handle runs the instantaneous model (no stored stress)");
   const ChanDev &d = h->L.ch[ch];
-  const size_t N = (size_t)d.nx * d.ny;
+  const size_t N = (size_t)d.nx * d.ny, Npad = align_up(N, kTile);
   const int es = h->L.esize;
-  // the channel's stress tiles are one contiguous block of each buffer; that
-  // of the other one holds the planes in FP64, or one where slots are FP32
+  // the channel's stress tiles are one contiguous block of each buffer
   const char *src = static_cast<const char *>(h->sbuf[h->cur]) + (size_t)sslot(0, d.off) * es;
-  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->sbuf[h->cur ^ 1]) + (size_t)sslot(0, d.off) * es);
-  const dim3 grid((unsigned)((N + 255) / 256));
-  const int per = es == 8 ? kStressPlanes : 1;
-  for (int p0 = 0; p0 < kStressPlanes; p0 += per) {
-    if (es == 8)
-      hipLaunchKernelGGL(unpack_stress_kernel<double>, grid, dim3(256), 0, h->stream,
-                         reinterpret_cast<const double *>(src), stage, (long long)N, p0, p0 + per);
-    else
-      hipLaunchKernelGGL(unpack_stress_kernel<float>, grid, dim3(256), 0, h->stream,
-                         reinterpret_cast<const float *>(src), stage, (long long)N, p0, p0 + per);
-    HIPCHECK(h, hipGetLastError());
-    HIPCHECK(h, hipMemcpyAsync(sigma + p0 * N, stage, sizeof(double) * per * N, hipMemcpyDeviceToHost, h->stream));
+  if (N <= kHostStressNodes) {
+    std::vector<char> raw(kStressPlanes * Npad * es);
+    HIPCHECK(h, hipMemcpyAsync(raw.data(), src, raw.size(), hipMemcpyDeviceToHost, h->stream));
+    HIPCHECK(h, hipStreamSynchronize(h->stream));
+    for (int p = 0; p < kStressPlanes; ++p)
+      for (size_t id = 0; id < N; ++id) {
+        const size_t k = (size_t)sslot(p, (long long)id);
+        sigma[p * N + id] = es == 8 ? reinterpret_cast<const double *>(raw.data())[k]
+                                    : (double)reinterpret_cast<const float *>(raw.data())[k];
+      }
+    return LB_OK;
   }
-  const lb_status m = mirror_channel(h, ch);
+  // staged where the other buffer holds the channel's state
+  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->buf[h->cur ^ 1]) + (size_t)slot(0, d.off) * es);
+  const dim3 grid((unsigned)((N + 255) / 256));
+  if (es == 8)
+    hipLaunchKernelGGL(unpack_stress_kernel<double>, grid, dim3(256), 0, h->stream,
+                       reinterpret_cast<const double *>(src), stage, (long long)N);
+  else
+    hipLaunchKernelGGL(unpack_stress_kernel<float>, grid, dim3(256), 0, h->stream,
+                       reinterpret_cast<const float *>(src), stage, (long long)N);
+  HIPCHECK(h, hipGetLastError());
+  HIPCHECK(h, hipMemcpyAsync(sigma, stage, sizeof(double) * kStressPlanes * N, hipMemcpyDeviceToHost, h->stream));
+  const lb_status m = mirror_state(h, ch);
   if (m != LB_OK) return m;
   HIPCHECK(h, hipStreamSynchronize(h->stream));
   return LB_OK;
@@ -1952,23 +1987,21 @@ lb_status lb_set_stress(lb_handle *h, int32_t ch, const double *sigma) {
   const size_t N = (size_t)d.nx * d.ny;
   const int es = h->L.esize;
   char *dst = static_cast<char *>(h->sbuf[h->cur]) + (size_t)sslot(0, d.off) * es;
-  double *stage = reinterpret_cast<double *>(static_cast<char *>(h->sbuf[h->cur ^ 1]) + (size_t)sslot(0, d.off) * es);
+  // staged like a small state, or where the other buffer holds the channel's
+  const bool small = N <= kStageNodes;
+  char *other = static_cast<char *>(h->buf[h->cur ^ 1]) + (size_t)slot(0, d.off) * es;
+  double *stage = reinterpret_cast<double *>(small ? h->ws + h->L.off_stage : other);
   const dim3 grid((unsigned)((N + 255) / 256));
-  const int per = es == 8 ? kStressPlanes : 1;
-  for (int p0 = 0; p0 < kStressPlanes; p0 += per) {
-    HIPCHECK(h, hipMemcpyAsync(stage, sigma + p0 * N, sizeof(double) * per * N, hipMemcpyHostToDevice, h->stream));
-    if (es == 8)
-      hipLaunchKernelGGL(pack_stress_kernel<double>, grid, dim3(256), 0, h->stream, reinterpret_cast<double *>(dst),
-                         stage, (long long)N, p0, p0 + per);
-    else
-      hipLaunchKernelGGL(pack_stress_kernel<float>, grid, dim3(256), 0, h->stream, reinterpret_cast<float *>(dst),
-                         stage, (long long)N, p0, p0 + per);
-    HIPCHECK(h, hipGetLastError());
-  }
-  {
-    lb_status m = mirror_channel(h, ch);
-    if (m != LB_OK) return m;
-  }
+  HIPCHECK(h, hipMemcpyAsync(stage, sigma, sizeof(double) * kStressPlanes * N, hipMemcpyHostToDevice, h->stream));
+  if (es == 8)
+    hipLaunchKernelGGL(pack_stress_kernel<double>, grid, dim3(256), 0, h->stream, reinterpret_cast<double *>(dst),
+                       stage, (long long)N);
+  else
+    hipLaunchKernelGGL(pack_stress_kernel<float>, grid, dim3(256), 0, h->stream, reinterpret_cast<float *>(dst),
+                       stage, (long long)N);
+  HIPCHECK(h, hipGetLastError());
+  const lb_status m = small ? mirror_stress(h, ch) : mirror_channel(h, ch);
+  if (m != LB_OK) return m;
   HIPCHECK(h, hipStreamSynchronize(h->stream));
   h->obs_valid = false;
   return LB_OK;

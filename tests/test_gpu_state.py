@@ -138,3 +138,32 @@ def test_stress_in_and_out(shape, precision):
         assert not s.get_stress(0).any() and not s.get_stress(2).any()
         after = s.get_state(1)
         assert np.array_equal(after[0], before[0]) and np.array_equal(after[1], before[1])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", [(64, 64), (241, 17), (128, 256), (331, 99)])
+def test_stress_calls_leave_a_run_alone(shape, precision):
+    """Stress in and out on both sides of the sizes up to which it has staging
+    of its own (4096 nodes) and is read through the host (32,768), also
+    between steps, after which either buffer may be current."""
+    from paper_1310_7450_amd import Solver
+    nx, ny = shape
+    chans = [spec(12, 9), spec(nx, ny), spec(12, 9)]
+    pops, P = workloads.random_state(nx, ny, seed=nx)
+    sigma = workloads.random_stress(nx, ny, seed=ny)
+    runs = []
+    for look in (True, False):
+        with Solver(chans, precision=precision, obs_every=20, viscoelastic=True, steps_per_sweep=1) as s:
+            for n in (3, 1, 2):
+                s.set_state(1, pops, P, 7)
+                s.set_stress(1, sigma)
+                if look:
+                    want = sigma if precision == "fp64" else sigma.astype(np.float32).astype(np.float64)
+                    assert np.array_equal(s.get_stress(1), want)
+                s.step(n)
+                if look:
+                    assert np.array_equal(s.get_stress(1), s.get_stress(1))
+                    s.get_state(1)
+                s.step(2)
+            runs.append([a for ch in range(3) for a in (*s.get_state(ch), s.get_stress(ch))])
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
