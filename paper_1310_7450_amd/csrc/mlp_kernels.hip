@@ -291,6 +291,9 @@ struct RowsArgs {
 // stage, in which a CU takes 128 KB of weights from its L2. Two column tiles
 // per wavefront took longer (17.7 against 15.8 with RPL = 4), and so did the
 // weights of two stages ahead (16.1 with RPL = 1).
+//
+// A stage leaves zeros beyond its layer's columns, where an infinite operand
+// times the padded weights' zeros is NaN and would reach the whole next layer.
 template <int NL, int RPL, bool FWD, bool LOSS, bool BWD>
 __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a) {
   constexpr int kRows = 4 * RPL;
@@ -399,7 +402,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
         z[l][i] = v[i];
         sg[l][i] = sigmoid(v[i]);
         a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
-        v[i] = v[i] * sg[l][i];
+        v[i] = n < a.dims[l + 1] ? v[i] * sg[l][i] : 0.f;
       }
       store_operand(v, act[(s + 1) & 1], a.ht + (l + 1) * zl);
     } else if (fwd) {
@@ -419,7 +422,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
 #pragma unroll
       for (int i = 0; i < RPL; ++i) {
         const float zz = z[l - 1][i], s1 = FWD ? sg[l - 1][i] : sigmoid(zz);
-        v[i] = acc[i] * (s1 * (1.0f + zz * (1.0f - s1)));
+        v[i] = n < a.dims[l] ? acc[i] * (s1 * (1.0f + zz * (1.0f - s1))) : 0.f;
         a.dz[(l - 1) * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
       }
       store_operand(v, act[(s + 1) & 1], a.dzt + (l - 1) * zl);

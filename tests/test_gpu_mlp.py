@@ -340,3 +340,42 @@ def test_rows_per_workgroup(batch):
     b.train_step(Xd, Td, torch.arange(batch, dtype=torch.int32, device="cuda"), lr=1e-3, want_loss=False)
     torch.cuda.synchronize()
     assert np.array_equal(a.get_grads(), b.get_grads()) and np.array_equal(a.get_params(), b.get_params())
+
+
+@pytest.mark.parametrize("dims", [[4, 48, 48, 3], [4, 17, 33, 20, 3], [4, 100, 250, 2], [4, 20, 3]])
+def test_infinities_stay_in_their_rows(dims):
+    """An infinite activation or gradient, with positive weights everywhere,
+    stays an infinity of its sign: no padded column (widths below the kernels'
+    padding) turns it into NaN, and rows of finite ones keep their values."""
+    import torch
+    from paper_1310_7450_amd import mlp
+    nl, B = len(dims) - 1, 37
+    rng = np.random.default_rng(5)
+    p = np.concatenate([np.concatenate([rng.uniform(0.05, 0.1, dims[l] * dims[l + 1]), np.zeros(dims[l + 1])])
+                        for l in range(nl)]).astype(np.float32)
+    x = rng.uniform(0.5, 1.0, (B, dims[0])).astype(np.float32)
+    net = mlp.Net(dims, max_batch=64)
+    net.set_params(p)
+    finite = net.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.isfinite(finite).all() and (finite > 0).all()
+    # forward: z of row 3 overflows in the first layer
+    xi = x.copy()
+    xi[3] = 3e38
+    p2 = p.copy()
+    p2[:dims[0] * dims[1]] = 1.0
+    net.set_params(p2)
+    want = net.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+    got = net.forward(torch.from_numpy(xi).cuda()).cpu().numpy()
+    assert np.isposinf(got[3]).all()
+    assert np.array_equal(np.delete(got, 3, 0), np.delete(want, 3, 0))
+    # backward: an infinite dy in every column of a row, z > 0 throughout
+    net.set_params(p)
+    net.forward(torch.from_numpy(x).cuda())
+    dy = np.full((B, dims[-1]), 1e-3, dtype=np.float32)
+    dy[5] = np.inf
+    net.backward(torch.from_numpy(dy).cuda())
+    assert np.isposinf(net.get_grads()).all()
+    dy[5] = 1e-3
+    net.backward(torch.from_numpy(dy).cuda())
+    assert np.isfinite(net.get_grads()).all()
+    net.close()
