@@ -816,9 +816,16 @@ lbml_status forward_impl(lbml_net *h, const float *x, const int32_t *idx, int32_
     RowsArgs a = rows_args(h, batch);
     a.x = x;
     a.idx = idx;
-    a.y = y;
+    // an output over the input (workgroups take their rows at different times)
+    // goes by the workspace
+    const size_t out = sizeof(float) * (size_t)batch * P.dims[h->nl], in = sizeof(float) * (size_t)batch * P.dims[0];
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+    const bool over = !idx && x0 < y0 + out && y0 < x0 + in;
+    a.y = over ? h->f(P.off_y) : y;
     h->last_batch = batch;
-    return launch_rows<true, false, false>(h, a);
+    const lbml_status st = launch_rows<true, false, false>(h, a);
+    if (st == 0 && over) MLCHECK(h, hipMemcpyAsync(y, a.y, out, hipMemcpyDeviceToDevice, h->stream));
+    return st;
   }
   // the input as BF16 operands: [batch][in] for this GEMM, transposed for dW
   MLCHECK(h, to_operands(h->stream, x, idx, batch, P.dims[0], h->b(P.off_xb), padded(P.dims[0]), h->b(P.off_xt),

@@ -379,3 +379,23 @@ def test_infinities_stay_in_their_rows(dims):
     net.backward(torch.from_numpy(dy).cuda())
     assert np.isfinite(net.get_grads()).all()
     net.close()
+
+
+@pytest.mark.parametrize("dims", [[5, 64, 96], [96, 64, 5], [7, 32, 7]])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_forward_over_its_input(dims, shift):
+    """The output may lie over the input (shift: rows between their starts),
+    with more rows than the GPU takes at once."""
+    import torch
+    from paper_1310_7450_amd import mlp
+    B = 20000
+    net = mlp.Net(dims, max_batch=B)
+    net.set_params(mlp.init_params(dims, seed=2))
+    x = torch.randn(B, dims[0], device="cuda")
+    want = net.forward(x).clone()
+    buf = torch.zeros((B + shift) * max(dims[0], dims[-1]), device="cuda")
+    buf[:B * dims[0]] = x.flatten()
+    at = shift * dims[-1]
+    got = net.forward(buf[:B * dims[0]].view(B, dims[0]), buf[at:at + B * dims[-1]].view(B, dims[-1]))
+    assert torch.equal(got, want)
+    net.close()
