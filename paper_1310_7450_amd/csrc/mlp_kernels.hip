@@ -251,26 +251,27 @@ __global__ void refresh_kernel(const float *p, bf16_t *pb, WeightMap w, long lon
   if (i < n) store_weight(w, pb, i, p[i]);
 }
 
-// The fused passes: at most kFusedLayers layers, each at most kFusedWidth wide
-// (16 column tiles of 16, one per wavefront of a workgroup). Their operands
-// are zero-padded to kFusedWidth rows and columns, so that a stage is the
-// same straight-line code whatever its layer's shape.
+// The fused passes: at most kFusedLayers layers, each at most kFusedWidth wide.
+// Their operands are zero-padded to W rows and columns (column tiles of 16, one
+// per wavefront of a workgroup), so that a stage is the same straight-line code
+// whatever its layer's shape. W is 32, 64, 128 or 256, the least that holds
+// every layer: padded to 256, 5-32-32-32 took 433 us for a forward pass of
+// 262,144 rows, and five times the workspace (W = 32: 32; a launch per GEMM: 117).
 constexpr int kFusedWidth = 256, kFusedLayers = 4;
 constexpr int kCUs = 256;  // of an MI355X
-constexpr int kFusedK = kFusedWidth / 32;
 struct RowsArgs {
   int batch, bp;                  // rows, padded rows of the largest batch
   int dims[kFusedLayers + 1];
   long long boff[kFusedLayers];   // biases in the parameters
   const float *p;                 // parameters
-  const bf16_t *wb, *wt;          // W and W^T of layer l at l kFusedWidth^2
+  const bf16_t *wb, *wt;          // W and W^T of layer l at l times W^2
   const float *x;                 // FWD: input rows
   const int32_t *idx;             // rows of x (and t) to take, or NULL
   float *y;                       // FWD: output, or NULL
   const float *t;                 // LOSS: targets
   float scale;                    // LOSS: dy = scale (y - t)
   const float *dy;                // BWD alone: the gradient of the output
-  // per layer, kFusedWidth columns (rows) each: pre-activations Z[m][n],
+  // per layer, W columns (rows) each: pre-activations Z[m][n],
   // dZ[m][n] in FP32, and the operands of dW, BF16 in fragment order: the
   // layer's input transposed (l = 0: x) and dZ transposed
   float *z, *dz;
@@ -294,11 +295,11 @@ struct RowsArgs {
 //
 // A stage leaves zeros beyond its layer's columns, where an infinite operand
 // times the padded weights' zeros is NaN and would reach the whole next layer.
-template <int NL, int RPL, bool FWD, bool LOSS, bool BWD>
-__global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a) {
+template <int W, int NL, int RPL, bool FWD, bool LOSS, bool BWD>
+__global__ void __launch_bounds__(4 * W) rows_kernel(RowsArgs a) {
   constexpr int kRows = 4 * RPL;
-  __shared__ __align__(16) bf16_t act[2][kRows][kFusedWidth + 8];
-  constexpr int kMat = kFusedWidth * kFusedWidth;
+  __shared__ __align__(16) bf16_t act[2][kRows][W + 8];
+  constexpr int kMat = W * W, kSteps = W / 32;
   constexpr int NST = (FWD ? NL : 0) + (BWD ? NL - 1 : 0);  // stages: layers 0 .. NL-1, then the chain through NL-1 .. 1
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kg = 8 * (lane >> 4);
@@ -307,16 +308,16 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
   const int m0 = blockIdx.x * kRows, n = 16 * wv + r, mq = m0 + RPL * (lane >> 4);
   const int ra = RPL * (r >> 2) + ((r & 3) < RPL ? r & 3 : RPL - 1);
   const int nout = a.dims[NL];
-  const size_t zl = (size_t)a.bp * kFusedWidth;  // per layer of z, dz, ht and dzt
+  const size_t zl = (size_t)a.bp * W;  // per layer of z, dz, ht and dzt
   struct Weights {
-    bf16x8 w[kFusedK];  // this wavefront's rows
+    bf16x8 w[kSteps];  // this wavefront's rows
   };
   auto fetch = [&](int s, Weights &q) __attribute__((always_inline)) {
     const bool fwd = FWD && s < NL;
     const int l = fwd ? s : NL - 1 - (s - (FWD ? NL : 0));
-    const bf16_t *b = (fwd ? a.wb : a.wt) + (size_t)l * kMat + wv * 16 * kFusedWidth + 8 * lane;
+    const bf16_t *b = (fwd ? a.wb : a.wt) + (size_t)l * kMat + wv * 16 * W + 8 * lane;
 #pragma unroll
-    for (int j = 0; j < kFusedK; ++j) q.w[j] = *reinterpret_cast<const bf16x8 *>(b + 512 * j);
+    for (int j = 0; j < kSteps; ++j) q.w[j] = *reinterpret_cast<const bf16x8 *>(b + 512 * j);
   };
   Weights q[2];
   if (NST > 0) fetch(0, q[0]);
@@ -329,7 +330,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
 #pragma unroll
     for (int l = 0; l < NL - 1; ++l)
 #pragma unroll
-      for (int i = 0; i < RPL; ++i) z[l][i] = a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n];
+      for (int i = 0; i < RPL; ++i) z[l][i] = a.z[l * zl + (size_t)(mq + i) * W + n];
   }
   if constexpr (LOSS) {
     int row[RPL];
@@ -347,11 +348,11 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
     const int cols = FWD ? a.dims[0] : nout;
     const float *src = FWD ? a.x : a.dy;
     bf16_t *tr = FWD ? a.ht : a.dzt + (NL - 1) * zl;
-    constexpr int per = kRows * kFusedWidth / (64 * kFusedWidth / 16);
+    constexpr int per = kRows * W / (4 * W);
 #pragma unroll
     for (int e = 0; e < per; ++e) {
-      const int at = threadIdx.x + e * (64 * kFusedWidth / 16);
-      const int mm = at / kFusedWidth, c = at % kFusedWidth, m = m0 + mm;
+      const int at = threadIdx.x + e * (4 * W);
+      const int mm = at / W, c = at % W, m = m0 + mm;
       bf16_t b = 0;
       if (m < a.batch && c < cols) {
         const long long row = (FWD && a.idx) ? (long long)a.idx[m] : (long long)m;
@@ -363,7 +364,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
   }
   // this lane's entries of a column to the next stage's operand and to
   // the transposed copy
-  auto store_operand = [&](const float v[RPL], bf16_t (*to)[kFusedWidth + 8], bf16_t *tr) __attribute__((always_inline)) {
+  auto store_operand = [&](const float v[RPL], bf16_t (*to)[W + 8], bf16_t *tr) __attribute__((always_inline)) {
     bf16_t b[RPL];
 #pragma unroll
     for (int i = 0; i < RPL; ++i) {
@@ -391,7 +392,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     const bf16_t *ar = &act[s & 1][ra][kg];
 #pragma unroll
-    for (int j = 0; j < kFusedK; ++j)
+    for (int j = 0; j < kSteps; ++j)
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(ar + 32 * j), q[s & 1].w[j], acc,
                                                     0, 0, 0);
     float v[RPL];
@@ -401,7 +402,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
         v[i] = acc[i] + bias[l];
         z[l][i] = v[i];
         sg[l][i] = sigmoid(v[i]);
-        a.z[l * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
+        a.z[l * zl + (size_t)(mq + i) * W + n] = v[i];
         v[i] = n < a.dims[l + 1] ? v[i] * sg[l][i] : 0.f;
       }
       store_operand(v, act[(s + 1) & 1], a.ht + (l + 1) * zl);
@@ -414,7 +415,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
         if (in && a.y) a.y[(long long)m * nout + n] = v[i];
         if constexpr (LOSS) {
           v[i] = in ? a.scale * (v[i] - tgt[i]) : 0.f;
-          a.dz[l * zl + (size_t)m * kFusedWidth + n] = v[i];
+          a.dz[l * zl + (size_t)m * W + n] = v[i];
         }
       }
       if constexpr (LOSS) store_operand(v, act[(s + 1) & 1], a.dzt + l * zl);
@@ -423,7 +424,7 @@ __global__ void __launch_bounds__(64 * kFusedWidth / 16) rows_kernel(RowsArgs a)
       for (int i = 0; i < RPL; ++i) {
         const float zz = z[l - 1][i], s1 = FWD ? sg[l - 1][i] : sigmoid(zz);
         v[i] = n < a.dims[l] ? acc[i] * (s1 * (1.0f + zz * (1.0f - s1))) : 0.f;
-        a.dz[(l - 1) * zl + (size_t)(mq + i) * kFusedWidth + n] = v[i];
+        a.dz[(l - 1) * zl + (size_t)(mq + i) * W + n] = v[i];
       }
       store_operand(v, act[(s + 1) & 1], a.dzt + (l - 1) * zl);
     }
@@ -452,14 +453,15 @@ struct WeightsArgs {
 template <bool ADAM>
 __global__ void __launch_bounds__(256) weights_kernel(WeightsArgs a) {
   __shared__ float part[16][16];
+  const int W = a.w.fused;
   int l = 0;
   while (l + 1 < a.w.nl && (int)blockIdx.x >= a.block0[l + 1]) ++l;
   const int blk = blockIdx.x - a.block0[l], din = a.w.din[l], dout = a.w.dout[l];
   const int tiles_i = (din + 15) / 16, tiles = tiles_i * ((dout + 15) / 16), wblocks = (tiles + 3) / 4;
   if (blk >= wblocks) {
     const int c = threadIdx.x & 15, q = threadIdx.x >> 4, n = (blk - wblocks) * 16 + c;
-    const float *dz = l == a.w.nl - 1 ? a.dz_last : a.dz + (size_t)l * a.bp * kFusedWidth;
-    const int ld = l == a.w.nl - 1 ? a.ld_last : kFusedWidth;
+    const float *dz = l == a.w.nl - 1 ? a.dz_last : a.dz + (size_t)l * a.bp * W;
+    const int ld = l == a.w.nl - 1 ? a.ld_last : W;
     float s = 0.f;
     if (n < dout) {
 #pragma unroll 8
@@ -482,8 +484,8 @@ __global__ void __launch_bounds__(256) weights_kernel(WeightsArgs a) {
   if (tile >= tiles) return;
   const int to = tile / tiles_i, ti = tile - to * tiles_i;
   const int lane = threadIdx.x & 63, r = lane & 15;
-  const bf16_t *A = a.dzt + ((size_t)l * kFusedWidth + 16 * to) * a.bp + 8 * lane;
-  const bf16_t *B = a.ht + ((size_t)l * kFusedWidth + 16 * ti) * a.bp + 8 * lane;
+  const bf16_t *A = a.dzt + ((size_t)l * W + 16 * to) * a.bp + 8 * lane;
+  const bf16_t *B = a.ht + ((size_t)l * W + 16 * ti) * a.bp + 8 * lane;
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int U = 8;
   for (int k0 = 0; k0 < a.kb; k0 += 32 * U) {
@@ -507,8 +509,8 @@ __global__ void __launch_bounds__(256) weights_kernel(WeightsArgs a) {
     a.g[id] = acc[q];
     if constexpr (ADAM) {
       const bf16_t b = to_bf16(adam_element(a.adam, id, acc[q]));
-      a.pb[a.w.wb[l] + frag(o, i, kFusedWidth)] = b;
-      a.pb[a.w.wt[l] + frag(i, o, kFusedWidth)] = b;
+      a.pb[a.w.wb[l] + frag(o, i, W)] = b;
+      a.pb[a.w.wt[l] + frag(i, o, W)] = b;
     }
   }
 }
@@ -529,7 +531,8 @@ struct Plan {
   size_t off_xb = 0, off_xt = 0;    // BF16 input and its transpose
   size_t off_y = 0, off_dy = 0;     // lbml_train_step: output and its gradient
   std::vector<size_t> off_z, off_hb, off_ht;  // per hidden layer: FP32 Z, BF16 H and H^T
-  // fused passes (RowsArgs): at most kFusedLayers layers of kFusedWidth
+  // fused passes (RowsArgs): at most kFusedLayers layers of kFusedWidth,
+  // padded to wm.fused
   bool fused = false;
   size_t off_fz = 0, off_fdz = 0, off_fht = 0, off_fdt = 0;
   size_t bytes = 0;
@@ -556,14 +559,15 @@ bool make_plan(int nl, const int32_t *dims, int max_batch, Plan &P) {
   P.bp = padded(max_batch);
   P.fused = nl <= kFusedLayers && P.max_pw <= kFusedWidth;
   P.wm.nl = nl;
-  P.wm.fused = P.fused ? kFusedWidth : 0;
+  for (int w = 32; P.fused && P.wm.fused < P.max_pw; w *= 2) P.wm.fused = w;
+  const size_t width = P.wm.fused;
   size_t e = 0;
   for (int l = 0; l < nl; ++l) {
     P.wm.woff[l] = (long long)P.woff[l];
     P.wm.boff[l] = (long long)P.boff[l];
     P.wm.din[l] = P.dims[l];
     P.wm.dout[l] = P.dims[l + 1];
-    const size_t mat = P.fused ? (size_t)kFusedWidth * kFusedWidth
+    const size_t mat = P.fused ? width * width
                                : (size_t)padded(P.dims[l + 1]) * padded(P.dims[l]);
     P.wm.wb[l] = P.fused ? (long long)(l * mat) : (long long)e;
     P.wm.wt[l] = P.fused ? (long long)((nl + l) * mat) : (long long)(e + mat);
@@ -601,8 +605,8 @@ bool make_plan(int nl, const int32_t *dims, int max_batch, Plan &P) {
     P.off_ht.push_back(take(2 * (size_t)P.bp * padded(P.dims[l + 1])));
   }
   if (P.fused) {
-    const size_t per = (size_t)nl * P.bp * kFusedWidth;
-    P.off_fz = take(4 * (per - (size_t)P.bp * kFusedWidth));  // the hidden layers'
+    const size_t per = (size_t)nl * P.bp * width;
+    P.off_fz = take(4 * (per - (size_t)P.bp * width));  // the hidden layers'
     P.off_fdz = take(4 * per);
     P.off_fht = take(2 * per);
     P.off_fdt = take(2 * per);
@@ -757,25 +761,34 @@ RowsArgs rows_args(lbml_net *h, int32_t batch) {
 // 4 rows per lane: batch 64 18.2 / 7.4, 19.9 / 8.3, 21.2 / 8.9; 1024 25.5 / 8.5,
 // 26.0 / 8.8, 27.5 / 9.6; 2048 39.5 / 13.8, 30.3 / 9.6, 31.6 / 10.4; 3000 51 /
 // 19, 43 / 17, 34 / 11.
-template <int RPL, bool FWD, bool LOSS, bool BWD>
+template <int W, int RPL, bool FWD, bool LOSS, bool BWD>
 lbml_status launch_rows_of(lbml_net *h, const RowsArgs &a) {
-  const dim3 grid(padded(a.batch) / (4 * RPL)), block(64 * kFusedWidth / 16);
+  const dim3 grid(padded(a.batch) / (4 * RPL)), block(4 * W);
   switch (h->nl) {
-    case 1: hipLaunchKernelGGL((rows_kernel<1, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 2: hipLaunchKernelGGL((rows_kernel<2, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 3: hipLaunchKernelGGL((rows_kernel<3, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
-    case 4: hipLaunchKernelGGL((rows_kernel<4, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 1: hipLaunchKernelGGL((rows_kernel<W, 1, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 2: hipLaunchKernelGGL((rows_kernel<W, 2, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 3: hipLaunchKernelGGL((rows_kernel<W, 3, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
+    case 4: hipLaunchKernelGGL((rows_kernel<W, 4, RPL, FWD, LOSS, BWD>), grid, block, 0, h->stream, a); break;
     default: return fail(h, -5, "no fused pass for this depth");
   }
   MLCHECK(h, hipGetLastError());
   return 0;
 }
+template <int W, bool FWD, bool LOSS, bool BWD>
+lbml_status launch_rows_wide(lbml_net *h, const RowsArgs &a) {
+  const int rows = padded(a.batch);
+  if (rows <= 4 * kCUs) return launch_rows_of<W, 1, FWD, LOSS, BWD>(h, a);
+  if (rows <= 8 * kCUs) return launch_rows_of<W, 2, FWD, LOSS, BWD>(h, a);
+  return launch_rows_of<W, 4, FWD, LOSS, BWD>(h, a);
+}
 template <bool FWD, bool LOSS, bool BWD>
 lbml_status launch_rows(lbml_net *h, const RowsArgs &a) {
-  const int rows = padded(a.batch);
-  if (rows <= 4 * kCUs) return launch_rows_of<1, FWD, LOSS, BWD>(h, a);
-  if (rows <= 8 * kCUs) return launch_rows_of<2, FWD, LOSS, BWD>(h, a);
-  return launch_rows_of<4, FWD, LOSS, BWD>(h, a);
+  switch (h->P.wm.fused) {
+    case 32: return launch_rows_wide<32, FWD, LOSS, BWD>(h, a);
+    case 64: return launch_rows_wide<64, FWD, LOSS, BWD>(h, a);
+    case 128: return launch_rows_wide<128, FWD, LOSS, BWD>(h, a);
+    default: return launch_rows_wide<256, FWD, LOSS, BWD>(h, a);
+  }
 }
 // dW and db from the dZ that launch_rows wrote, the last layer's from dz_last
 // (ld_last columns); with adam also the update.
@@ -998,8 +1011,9 @@ lbml_status lbml_train_step(lbml_net *h, const float *X, const float *Y, const i
     h->last_batch = batch;
     st = launch_rows<true, true, true>(h, a);
     const AdamArgs ad = adam_args(h, lr, b1, b2, eps, t);
-    float *dz_last = h->f(h->P.off_fdz) + (size_t)(h->nl - 1) * h->P.bp * kFusedWidth;
-    if (st == 0) st = launch_weights(h, dz_last, kFusedWidth, batch, &ad);
+    const int width = h->P.wm.fused;
+    float *dz_last = h->f(h->P.off_fdz) + (size_t)(h->nl - 1) * h->P.bp * width;
+    if (st == 0) st = launch_weights(h, dz_last, width, batch, &ad);
     // the loss from the outputs kept (its dy goes where the last dZ no longer
     // is needed)
     if (st == 0 && host_loss) st = mse_impl(h, y, Y, idx, batch, dz_last, host_loss);

@@ -399,3 +399,43 @@ def test_forward_over_its_input(dims, shift):
     got = net.forward(buf[:B * dims[0]].view(B, dims[0]), buf[at:at + B * dims[-1]].view(B, dims[-1]))
     assert torch.equal(got, want)
     net.close()
+
+
+# The least of 32, 64, 128 and 256 columns that holds every layer pads them:
+# both sides of each limit, every depth, every number of rows per workgroup.
+@pytest.mark.parametrize("batch", [30, 1025, 2049])
+@pytest.mark.parametrize("dims", [[5, 32, 7], [32, 8, 30, 1], [5, 33, 7], [5, 17, 9, 64, 31], [5, 65, 7],
+                                  [60, 128, 2, 90], [5, 129, 7]])
+def test_padded_widths(dims, batch):
+    """The same network with its hidden layers widened to 250 by units of
+    zero weights (padded to 256) gives the same outputs and gradients, bit for
+    bit."""
+    import torch
+    from paper_1310_7450_amd import mlp
+    wide = [dims[0]] + [250] * (len(dims) - 2) + [dims[-1]]
+    rng = np.random.default_rng(sum(dims))
+    at = 0
+    own = []  # positions of the narrow network's parameters in the wide one's
+    for l in range(len(dims) - 1):
+        ids = at + np.arange(wide[l + 1] * wide[l]).reshape(wide[l + 1], wide[l])
+        own.append(ids[:dims[l + 1], :dims[l]].ravel())
+        at += ids.size
+        own.append(at + np.arange(dims[l + 1]))
+        at += wide[l + 1]
+    own = np.concatenate(own)
+    p = rng.uniform(-0.5, 0.5, own.size).astype(np.float32)
+    pw = np.zeros(at, dtype=np.float32)
+    pw[own] = p
+    x = torch.from_numpy(rng.standard_normal((batch, dims[0])).astype(np.float32)).cuda()
+    t = torch.from_numpy(rng.standard_normal((batch, dims[-1])).astype(np.float32)).cuda()
+    idx = torch.arange(batch, dtype=torch.int32, device="cuda")
+    res = []
+    for d, q, pick in ((dims, p, slice(None)), (wide, pw, own)):
+        net = mlp.Net(d, max_batch=batch)
+        net.set_params(q)
+        y = net.forward(x).cpu().numpy()
+        loss = net.train_step(x, t, idx, lr=1e-3, want_loss=True)
+        res.append((y, net.get_grads()[pick], loss))
+        net.close()
+    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1]) and res[0][2] == res[1][2]
+    assert np.abs(res[0][1]).max() > 0
