@@ -198,3 +198,39 @@ def test_pressure_column_sum_has_one_order(nx, ny):
     for o in others:
         for steps in ([80], [1] * 45 + [35]):
             assert_same(first, run([c] + o, "fp64", 40, steps, 0)[:1], (nx, ny, len(o), steps))
+
+
+@pytest.mark.parametrize("viscoelastic", [False, True])
+@pytest.mark.parametrize("precision,nx,ny", [(p, *q) for p in LARGE for q in LARGE[p]])
+def test_large_two_step_same_bits(precision, nx, ny, viscoelastic):
+    """What lets steps be split over calls in any way: two steps of a launch
+    round as two launches do, blocks and pairs off their boundaries alike."""
+    c = [spec(nx, ny, wall_velocity=1e-3 if ny % 2 else 0.0)]
+    a, b = (run(c, precision, 8, [16, 1, 6], sps, viscoelastic) for sps in (0, 1))
+    assert_same(a, b, (precision, nx, ny, viscoelastic))
+
+
+@pytest.mark.parametrize("wall", [{}, dict(wall_velocity=0.02)])
+def test_stress_force_boxes_same_bits(wall):
+    kw = dict(nn_pressure=False, t_startup=31, **wall)
+    shapes = [(1, 1), (3, 1), (5, 2), (8, 40), (64, 3), (8, 400), (200, 20), (143, 43), (37, 113), (1000, 9),
+              (500, 300), (600, 300)]
+    for case in [[q] for q in shapes] + [shapes[3:8]]:
+        c = [spec(nx, ny, **kw) for nx, ny in case]
+        a, b = (run(c, "fp64", 40, [80, 7, 1], sps, stress_force=True) for sps in (0, 1))
+        assert_same(a, b, case)
+
+
+# channels whose single steps, or all off the block boundaries, leave the boxes
+# that take their blocks
+SPLIT = [("fp32", 1024, 600), ("fp32", 1024, 850), ("fp32", 3000, 750), ("fp64", 512, 512), ("fp64", 1024, 512),
+         ("fp64", 500, 500), ("fp64", 300, 700)]
+
+
+@pytest.mark.parametrize("viscoelastic", [False, True])
+@pytest.mark.parametrize("precision,nx,ny", SPLIT)
+def test_steps_split_over_calls_in_any_way(precision, nx, ny, viscoelastic):
+    c = [spec(nx, ny, wall_velocity=1e-3, t_startup=11)]
+    a = run(c, precision, 12, [24], 0, viscoelastic)
+    for steps in ([1] * 24, [5, 7, 1, 11], [13, 11], [12, 3, 9]):
+        assert_same(a, run(c, precision, 12, steps, 0, viscoelastic), (precision, nx, ny, viscoelastic, steps))
