@@ -254,3 +254,95 @@ def test_two_step_walls_match_one_step_and_oracle(orc, precision, nx, wall):
     print(f"{precision} {wall} {nx}: two-step vs one-step {e:.2e} (P {ep:.2e}), vs oracle {eo:.2e}", flush=True)
     assert e < TOL[precision][0] and ep < TOL[precision][1]
     assert eo < ORACLE_TOL[precision][0]
+
+
+# ---- above the boxes' limits. Small channels step in boxes unless the handle
+# holds more nodes of their kind than boxes take, so each handle here has one
+# channel that lifts its kind over the limit (the CPU test of the routing holds
+# these lists to it), and beside it small ones: windows that are the whole
+# period (FP64 128 wide), one to three rows, ragged bands and row groups.
+# (streamed: above 256 MB per state buffer, FP32 at four nodes per lane)
+ABOVE = {
+    ("fp32", "two_step"): [(1024, 1000), (256, 1), (256, 2), (512, 3), (256, 37), (768, 58), (2048, 16), (512, 113)],
+    ("fp64", "two_step"): [(1024, 700), (128, 1), (128, 2), (192, 3), (128, 19), (320, 37), (192, 58), (1088, 5)],
+    ("fp32", "streamed"): [(1024, 6600), (256, 1), (256, 2), (512, 3), (256, 59), (1024, 21)],
+    ("fp64", "streamed"): [(1024, 3300), (128, 1), (192, 2), (128, 61), (448, 3)],
+    ("fp32", "narrow_two_step"): [(64, 20001), (64, 1), (64, 2), (64, 5), (64, 130), (32, 1), (32, 3), (32, 70),
+                                  (32, 999)],
+    ("fp64", "narrow_two_step"): [(64, 5003), (64, 1), (64, 2), (64, 5), (64, 130), (32, 1), (32, 3), (32, 70),
+                                  (32, 999)],
+}
+WALLS = [{}, dict(wall_velocity=1e-3), dict(wall_velocity=1e-3, top_wall="zou_he", nn_pressure=False)]
+
+
+def above(key):
+    """The channels of a handle, every wall in turn (a Zou-He top needs two
+    rows)."""
+    return [spec(nx, ny, t_startup=19, **(WALLS[i % 3] if ny > 1 else {})) for i, (nx, ny) in enumerate(ABOVE[key])]
+
+
+@pytest.mark.parametrize("key,viscoelastic", [(k, ve) for k in ABOVE for ve in (False, True)
+                                              if not (ve and "narrow" in k[1])])
+def test_two_step_kernels_equal_one_step_above_the_boxes(key, viscoelastic):
+    """Blocks of 8 steps and runs of steps off their boundaries (two per launch
+    where every channel takes them, a last odd one alone), the walls stopping
+    inside a launch, against one step per launch: the same bits."""
+    from paper_1310_7450_amd import Solver
+    chans, res = above(key), []
+    for sps in (0, 1):
+        with Solver(chans, precision=key[0], obs_every=8, steps_per_sweep=sps, viscoelastic=viscoelastic) as s:
+            for i, c in enumerate(chans):
+                s.set_state(i, *workloads.random_state(c.nx, c.ny, seed=c.nx + c.ny + i), 0)
+                if viscoelastic:
+                    s.set_stress(i, workloads.random_stress(c.nx, c.ny, seed=i))
+            for n in (16, 3, 5, 1, 2):
+                s.step(n)
+            res.append([s.get_state(i) + ((s.get_stress(i),) if viscoelastic else ()) for i in range(len(chans))])
+    for i, (a, b) in enumerate(zip(*res)):
+        for p, q in zip(a, b):
+            assert np.isfinite(p).all() and np.array_equal(p, q), (key, i, ABOVE[key][i], np.abs(p - q).max())
+
+
+@pytest.mark.parametrize("key", [k for k in ABOVE if k[1] != "streamed"])
+def test_two_step_kernels_match_oracle_above_the_boxes(orc, key):
+    """The same handles against the FP64 oracle, node by node."""
+    from paper_1310_7450_amd import Solver
+    chans = above(key)
+    states = [workloads.random_state(c.nx, c.ny, seed=3 * c.nx + c.ny + i) for i, c in enumerate(chans)]
+    with Solver(chans, precision=key[0], obs_every=8) as s:
+        for i, st in enumerate(states):
+            s.set_state(i, *st, 0)
+        s.step(24)
+        for i, c in enumerate(chans):
+            o = orc.Channel(c.nx, c.ny, c.force, tau_lb=c.tau_lb, G=c.G, tau0=c.tau0, gamma_c=c.gamma_c, eps=c.eps,
+                            visc_split=c.visc_split, t_startup=c.t_startup,
+                            nn_pressure=c.resolved_nn_pressure(True), wall_velocity=c.wall_velocity,
+                            top_wall=c.top_wall)
+            o.set_state(*states[i], t=0)
+            o.run(24)
+            err = np.abs(s.get_state(i)[0] - o.n).max() / np.abs(o.n - workloads.REST_WEIGHTS[:, None, None]).max()
+            print(f"{key} {c.nx}x{c.ny}: {err:.2e}", flush=True)
+            assert err < ORACLE_TOL[key[0]][0]
+
+
+# every route in one block: boxes (narrow, ragged, pressure-driven), two-step
+# strips, narrow two-step strips, one-step sweeps or tiles, the column pass
+MIXED = {
+    "fp32": [(8, 40), (300, 11), (1024, 1000), (256, 7), (64, 20000), (32, 9), (64, 32, "pressure"),
+             (24, 300, "pressure")],
+    "fp64": [(8, 40), (300, 11), (700, 500), (1024, 700), (128, 7), (64, 5000), (32, 9), (64, 32, "pressure"),
+             (100, 7600, "pressure")],
+}
+
+
+@pytest.mark.parametrize("more", [[], [(1100, 1000, "pressure")]])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_every_route_in_one_handle(precision, more):
+    """Whole blocks and odd runs of steps equal one step per launch, bit for
+    bit; with a pressure-driven channel above its limit too."""
+    chans = [spec(nx, ny, **(dict(force=0.0, pressure_gradient=1e-6, nn_pressure=False) if p else {}))
+             for nx, ny, *p in MIXED[precision] + more]
+    pairs, _ = run_pair(chans, [8, 16, 3, 5, 7], obs_every=8, seed=5, precision=precision)
+    for c, (a, b) in zip(chans, pairs):
+        for p, q in zip(a, b):
+            assert np.isfinite(p).all() and np.array_equal(p, q), (precision, c.nx, c.ny, np.abs(p - q).max())

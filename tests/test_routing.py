@@ -101,3 +101,21 @@ def test_steps_off_the_block_boundaries(route, precision, shape, single, several
     assert c[single] == 10
     c, = route(precision, 1000, [500], [shape])
     assert c[several] >= 498
+
+
+def test_gpu_tests_reach_the_routes_they_name(route):
+    """The handles of the two-step tests above the boxes' limits take the
+    kernels those tests are about, the mixed ones every route."""
+    from test_gpu_two_step import ABOVE, MIXED
+    for (precision, kind), shapes in ABOVE.items():
+        name = "two_step" if kind == "streamed" else kind
+        for ve in (0,) if kind == "narrow_two_step" else (0, 1):
+            chans = [(nx, ny, *(("wall",), ("wall", "zou_he"))[i % 2]) if ny > 1 else (nx, ny)
+                     for i, (nx, ny) in enumerate(shapes)]
+            for c in route(precision, 8, [16, 3, 5, 1, 2], chans, ve):
+                assert c[name] >= 16 and "boxes" not in c
+    for precision, shapes in MIXED.items():
+        for more in ([], [(1100, 1000, "pressure")]):
+            taken = set().union(*route(precision, 8, [8, 16, 3, 5, 7], shapes + more))
+            assert {"boxes", "two_step", "narrow_two_step", "column_pass"} <= taken
+            assert ("tiles" if precision == "fp64" else "sweep") in taken
