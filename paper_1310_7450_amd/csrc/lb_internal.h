@@ -196,8 +196,8 @@ constexpr int two_step_waves_per_simd(bool fp32, int npl, bool ve) { return fp32
 // wavefronts per strip (one per stage) and the most rows a strip may have
 constexpr int kTwoStepWaves = 2, kTwoStepMaxRows = 56;
 hipError_t launch_two_step(bool fp32, const SweepArgs &a, hipStream_t s);
-// Two steps per launch for the narrow widths (nx a power of two up to 64,
-// the instantaneous model): one workgroup of two wavefronts per strip of
+// Two steps per launch for the widths of 32 and 64 columns (the
+// instantaneous model): one workgroup of two wavefronts per strip of
 // rows, the strips of one width in SweepArgs.strips, n_wg = n_strips.
 hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStream_t s);
 // S steps per launch on boxes of small lattices (sweep_block_kernel): the

@@ -768,8 +768,8 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_kernel(SweepArgs a) {
   }
 }
 
-// Two steps per launch for the narrow widths (nx = 1, 2, ..., 64: a row
-// fits TXW = nx lanes and a wavefront holds TYW = 64 / nx rows), for the
+// Two steps per launch for the narrow widths of 32 and 64 columns (a row fits
+// TXW = nx lanes and a wavefront holds TYW = 64 / nx rows), for the
 // instantaneous model. A workgroup of two wavefronts takes the strip of rows
 // [y0, y1) of one channel through steps t and t+1 with the narrow sweep's
 // row machine in both:
@@ -780,13 +780,15 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_kernel(SweepArgs a) {
 //  * wavefront 1 (stage B, step t+1) marches the groups of [y0, y1), pulling
 //    from the ring (any row of the last few groups, by index), and stores.
 // A row of the channel is whole in one group, so no column beyond it is
-// needed. Stage B runs L iterations behind stage A (L = 3, or 4 and 5 when
-// a group holds 2 and 1 rows), or sooner at the end of the strip, so that
+// needed. Stage B runs L iterations behind stage A (4 and 5 where a group
+// holds 2 and 1 rows), or sooner at the end of the strip, so that
 // every group it reads is in the ring; one barrier per iteration orders the
 // ring's writes and reads. Per node the arithmetic is the narrow sweep's.
 //
-// For the lattices that do not step in boxes (sweep_block_kernel): widths of 32
-// and 64 beyond about a million nodes, 64 x 65536 80 us per step against 92.
+// For the lattices that do not step in boxes (sweep_block_kernel): FP32 beyond
+// about a million nodes (64 x 65536 80 us per step against 92), FP64 beyond a
+// quarter of that. Narrower channels always step in boxes (or, beyond the nodes
+// boxes address, one step per launch).
 constexpr int kN2Ring = 8;  // groups in the ring
 template <typename T, bool SHIFT, int TXW>
 __global__ void __launch_bounds__(128) sweep_narrow2_kernel(SweepArgs a) {
@@ -3303,11 +3305,6 @@ hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStre
 #define LB_N2(TT, SH, W) hipLaunchKernelGGL((sweep_narrow2_kernel<TT, SH, W>), grid, block, 0, s, a)
 #define LB_N2_ALL(TT, SH)  \
   switch (nx) {            \
-    case 1: LB_N2(TT, SH, 1); break;   \
-    case 2: LB_N2(TT, SH, 2); break;   \
-    case 4: LB_N2(TT, SH, 4); break;   \
-    case 8: LB_N2(TT, SH, 8); break;   \
-    case 16: LB_N2(TT, SH, 16); break; \
     case 32: LB_N2(TT, SH, 32); break; \
     case 64: LB_N2(TT, SH, 64); break; \
     default: return hipErrorInvalidValue; \
@@ -3329,11 +3326,6 @@ int narrow2_blocks_per_cu() {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 128, 0) == hipSuccess && n > 0) lo = std::min(lo, n);
   };
-  q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 1>));
-  q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 2>));
-  q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 4>));
-  q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 8>));
-  q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 16>));
   q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 32>));
   q(reinterpret_cast<const void *>(sweep_narrow2_kernel<T, SH, 64>));
   return lo == (1 << 30) ? 1 : lo;

@@ -207,10 +207,10 @@ bool two_step_handle(const lb_options *o, int K) {
 bool two_step_channel(const lb_channel &c, int esize) {
   return width_class(c.nx, esize) == kVecClass && c.pressure_gradient == 0;
 }
-// The narrow widths (nx = 1, 2, ..., 64) of the instantaneous model take
-// two steps per launch too (sweep_narrow2_kernel), without the pressure drive.
-bool narrow_two_step_channel(const lb_options *o, const lb_channel &c, int esize) {
-  return !o->viscoelastic && !is_strip_class(width_class(c.nx, esize)) && c.pressure_gradient == 0;
+// The widths of 32 and 64 columns of the instantaneous model take two steps per
+// launch too (sweep_narrow2_kernel), without the pressure drive.
+bool narrow_two_step_channel(const lb_options *o, const lb_channel &c) {
+  return !o->viscoelastic && (c.nx == 32 || c.nx == 64) && c.pressure_gradient == 0;
 }
 // Channels whose steps run in boxes (sweep_block_kernel), many per launch or,
 // with the pressure drive, one: with either stress model and any top wall,
@@ -899,7 +899,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
       for (int i = 0; i < h->n_ch; ++i) {
         if (!h->active[i] || h->blk_ok[i] || !h->two_step) continue;
         if (two_step_channel(h->in[i], es)) elig.push_back(h->in[i]);
-        else if (narrow_two_step_channel(&h->opt, h->in[i], es)) nelig.push_back(h->in[i]);
+        else if (narrow_two_step_channel(&h->opt, h->in[i])) nelig.push_back(h->in[i]);
       }
       const int npl = two_step_npl(es == 4, streamed(h->L), h->opt.viscoelastic);
       const int H = h->opt.strip_rows > 0 ? std::min(h->opt.strip_rows, kTwoStepMaxRows)
@@ -909,7 +909,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
         if (h->two_step && two_step_channel(h->in[i], es)) {
           add_two_step_strips(i, h->in[i], npl, es == 4, H, h->opt.viscoelastic, two);
           wall = wall || two_step_wall(h->in[i]);
-        } else if (!(h->two_step && narrow_two_step_channel(&h->opt, h->in[i], es)) && !tiled(&h->opt, h->in[i])) {
+        } else if (!(h->two_step && narrow_two_step_channel(&h->opt, h->in[i])) && !tiled(&h->opt, h->in[i])) {
           add_strips(i, h->L.ch[i], es, rows_of(i), stack, braw);
         }
       }
@@ -918,7 +918,7 @@ lb_status upload_strips(lb_handle *h, bool all) {
         const int R2 = narrow_two_step_rows(nelig, h->n2slots, h->opt.strip_rows,
                                             h->L.strip_cap - (long long)braw.size());
         for (int i = 0; i < h->n_ch; ++i)
-          if (h->active[i] && !h->blk_ok[i] && narrow_two_step_channel(&h->opt, h->in[i], es))
+          if (h->active[i] && !h->blk_ok[i] && narrow_two_step_channel(&h->opt, h->in[i]))
             add_strips(i, h->L.ch[i], es, narrow_rows(R2, h->in[i].nx), stack, n2raw);
       }
     }
@@ -1576,7 +1576,7 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   h->boxes[lb_handle::kPressureMany].d = reinterpret_cast<Strip *>(h->ws + h->L.off_gpm);
   h->two_step = false;
   for (int i = 0; i < n && two_step_handle(o, h->K); ++i)
-    h->two_step = h->two_step || two_step_channel(c[i], h->L.esize) || narrow_two_step_channel(o, c[i], h->L.esize);
+    h->two_step = h->two_step || two_step_channel(c[i], h->L.esize) || narrow_two_step_channel(o, c[i]);
   h->dpart = reinterpret_cast<double *>(h->ws + h->L.off_part);
   h->dprof = reinterpret_cast<double *>(h->ws + h->L.off_prof);
   h->dprev = reinterpret_cast<double *>(h->ws + h->L.off_prev);

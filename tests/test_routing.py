@@ -119,3 +119,8 @@ def test_gpu_tests_reach_the_routes_they_name(route):
             taken = set().union(*route(precision, 8, [8, 16, 3, 5, 7], shapes + more))
             assert {"boxes", "two_step", "narrow_two_step", "column_pass"} <= taken
             assert ("tiles" if precision == "fp64" else "sweep") in taken
+
+
+def test_narrow_channels_beyond_the_boxes_step_singly(route):
+    c, = route("fp32", 8, [8, 3], [(16, 27_000_000)])
+    assert c["sweep"] == 11
