@@ -205,7 +205,9 @@ bool two_step_handle(const lb_options *o, int K) {
   return o->steps_per_sweep != 1 && !o->stress_force && K % 4 == 0;
 }
 bool two_step_channel(const lb_channel &c, int esize) {
-  return width_class(c.nx, esize) == kVecClass && c.pressure_gradient == 0;
+  // (a row's slots in 32 bits)
+  return width_class(c.nx, esize) == kVecClass && c.pressure_gradient == 0 &&
+         align_up((size_t)c.nx, kTile) * kPlanes <= 0xffffffffull;
 }
 // The widths of 32 and 64 columns of the instantaneous model take two steps per
 // launch too (sweep_narrow2_kernel), without the pressure drive.

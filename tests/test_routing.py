@@ -124,3 +124,14 @@ def test_gpu_tests_reach_the_routes_they_name(route):
 def test_narrow_channels_beyond_the_boxes_step_singly(route):
     c, = route("fp32", 8, [8, 3], [(16, 27_000_000)])
     assert c["sweep"] == 11
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_rows_beyond_32_bit_slots_step_singly(route, precision):
+    """The two-step strips address a row's slots by 32 bits: up to 429,496,729
+    columns."""
+    widest = (2 ** 32 // 10) // 256 * 256
+    c, = route(precision, 8, [8, 3], [(widest, 1)])
+    assert c["two_step"] == 10
+    c, = route(precision, 8, [8, 3], [(widest + 256, 1)])
+    assert c["sweep"] == 11
