@@ -6,6 +6,9 @@ stream, keeps the fastest, and caches the choice in a JSON file keyed by the
 device name, the precision and the shape of the batch (the width classes,
 the node count and the row-count range).
 
+A batch whose channels all step in boxes of nodes has no strips: the times of
+its candidates differ by noise alone, and the first candidate stays.
+
 For a batch run to steady state (``to_steady``) the time per step of the
 whole batch alone is the wrong target. A channel relaxes over ~H^2/nu steps,
 so the widest channels converge last and spend much of the run alone: with
@@ -51,6 +54,12 @@ def time_candidate(channels, precision, strip_rows, steps, nn_pressure=True):
         return e0.elapsed_time(e1) / steps
 
 
+def has_strips(channels):
+    """False if every channel is of a width that always steps in boxes (1, 2,
+    4, 8 or 16 columns)."""
+    return any(c.nx not in (1, 2, 4, 8, 16) for c in channels)
+
+
 def widest(channels, fraction):
     """The widest ceil(fraction * n) channels (at least one)."""
     order = sorted(channels, key=lambda c: c.ny, reverse=True)
@@ -82,7 +91,7 @@ def tune_strip_rows(channels: Sequence[ChannelSpec], precision: str = "fp32",
             times[sr] = time_candidate(channels, precision, sr, steps, nn_pressure)
         if verbose:
             print(f"autotune {key}: strip_rows={sr} {times[sr] * 1e3:.1f} us/step", file=sys.stderr, flush=True)
-    best = min(times, key=times.get)
+    best = min(times, key=times.get) if has_strips(channels) else next(iter(times))
     cache[key] = {"strip_rows": best, "ms_per_step": times}
     if cache_path:
         try:

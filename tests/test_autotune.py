@@ -37,3 +37,16 @@ def test_tune_returns_a_candidate_and_caches(tmp_path):
     cache.write_text(json.dumps({key: val}))
     assert autotune.tune_strip_rows(chans, "fp32", candidates=(8, 16), steps=20, cache_path=str(cache),
                                     to_steady=True) == 24
+
+
+def test_batches_without_strips_keep_the_first_candidate(monkeypatch):
+    """The batched sweep's channels (8 wide) step in boxes, which strip_rows
+    does not reach: the noise of the timings does not choose one."""
+    times = {0: 4.78, 4: 4.75, 32: 4.72}
+    monkeypatch.setattr(autotune, "time_candidate", lambda c, p, sr, *a: times[sr])
+    monkeypatch.setattr(autotune, "shape_key", lambda c, p: "key")
+    batch = workloads.batched_sweep()["channels"]
+    assert not autotune.has_strips(batch)
+    assert autotune.tune_strip_rows(batch, candidates=times, cache_path=None, to_steady=True) == 0
+    wide = [ChannelSpec(nx=4096, ny=1024, force=1e-6)]
+    assert autotune.has_strips(wide) and autotune.tune_strip_rows(wide, candidates=times, cache_path=None) == 32
