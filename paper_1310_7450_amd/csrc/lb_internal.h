@@ -200,6 +200,13 @@ hipError_t launch_two_step(bool fp32, const SweepArgs &a, hipStream_t s);
 // instantaneous model): one workgroup of two wavefronts per strip of
 // rows, the strips of one width in SweepArgs.strips, n_wg = n_strips.
 hipError_t launch_narrow_two_step(bool fp32, int nx, const SweepArgs &a, hipStream_t s);
+// Most boxes of a launch that orders its nodes by columns, about one per CU.
+// Wavefronts then drop out of the later steps, but a row's nodes lie in
+// different ones, each line of them loaded and stored by many. us per step, by
+// columns and by rows: FP64 64 x 32 with the pressure drive 3.3 / 4.1, 1000 x 48
+// 4.6 / 5.1; but 16384 x 40 FP32 28.5 / 13.7 (two steps per launch in strips
+// 24.9), time-integrated 25000 x 40 FP64 56.0 / 31.3 (tiles 34.4).
+constexpr int kColumnOrderBoxes = 256;
 // S steps per launch on boxes of small lattices (sweep_block_kernel): the
 // boxes of every block channel in SweepArgs.strips (x0, x1, y0, y1), n_wg =
 // n_strips workgroups of `threads` (256, 512 or 1024) threads; a box and its

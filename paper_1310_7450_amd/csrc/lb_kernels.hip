@@ -1160,10 +1160,10 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
   const int rows = ry1 - ry0;
   const bool in = (int)threadIdx.x < rows * cw;  // (the host keeps rows * cw <= TH)
   const int n = in ? threadIdx.x : 0;
-  // nodes row by row, or column by column where only columns are cut: the
-  // halo is then at both ends of the node order, and whole wavefronts drop
-  // out of the later steps
-  const bool by_col = !whole && rows == ny;
+  // nodes row by row, or column by column where only columns are cut and the
+  // boxes are few: the halo is then at both ends of the node order, and whole
+  // wavefronts drop out of the later steps (see kColumnOrderBoxes)
+  const bool by_col = S > 1 && !whole && rows == ny && a.n_wg <= kColumnOrderBoxes;
   const int sx = by_col ? rows : 1, sy = by_col ? 1 : cw;
   const int major = n / (by_col ? rows : cw), minor = n - major * (by_col ? rows : cw);
   const int r = by_col ? minor : major, cc = by_col ? major : minor, y = ry0 + r;

@@ -448,13 +448,14 @@ bool box_shape(const lb_channel &c, int S, int reach, int cap, BoxShape &best) {
   for (int ow = 4; ow + h <= cap; ow += (ow < 32 ? 4 : 16)) offer(ow, cap / (ow + h) - h);
   return eff > 0;
 }
-// wavefronts of a region at work in step s of S (see the kernel's node order)
-int box_waves(const lb_channel &c, BoxShape b, int S, int step_reach, int s) {
+// wavefronts of a region at work in step s of S (see the kernel's node order;
+// columns: boxes cut by columns alone are in column order)
+int box_waves(const lb_channel &c, BoxShape b, int S, int step_reach, int s, bool columns) {
   const int reach = step_reach * (S - s) - 1, halo = 2 * step_reach * S;
   const bool whole = b.ow >= c.nx;
   const int cw = whole ? c.nx : b.ow + halo;
   const int rows = std::min(b.oh + 2 * reach, c.ny);
-  if (!whole && std::min(b.oh + halo, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
+  if (columns && !whole && std::min(b.oh + halo, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
   return (rows * cw + 63) / 64;
 }
 void add_boxes(int ci, const lb_channel &c, BoxShape b, std::vector<Strip> &out) {
@@ -518,10 +519,15 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, bool 
             break;
           }
           f.shape.push_back(b);
+          f.W += number[i] * (double)box_count(c, b);
+        }
+        const bool columns = S > 1 && f.W <= kColumnOrderBoxes;
+        for (size_t i = 0; added && i < f.shape.size(); ++i) {
+          const lb_channel &c = *shaped[i];
+          const BoxShape b = f.shape[i];
           const double w = number[i] * (double)box_count(c, b);
-          const int v0 = box_waves(c, b, S, reach, 0);
-          const double v = 0.5 * (v0 + box_waves(c, b, S, reach, S - 1));
-          f.W += w;
+          const int v0 = box_waves(c, b, S, reach, 0, columns);
+          const double v = 0.5 * (v0 + box_waves(c, b, S, reach, S - 1, columns));
           f.R += w * v0;
           f.V += w * v;
           f.vmax = std::max(f.vmax, v);
