@@ -266,14 +266,30 @@ bool tall_pressure(const lb_channel &c, int esize) {
 //  * short runs of steps off the boundaries, FP32 aligned 1024 x 700 15.7 /
 //    17.3, 1024 x 850 18.2 / 17.6; FP64 512 x 512 10.4 / 11.5, 768 x 512 14.8 /
 //    14.0 (time-integrated 1024 x 512 20.1 / 20.4, 1024 x 600 24.3 / 23.6).
-enum BoxKind { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, FORCE, BOX_KINDS };
+//  * 64 x 16000 FP32 25.9 / 23.0, 64 x 8192 14.9 / 21.3; 66 x 4000 FP64 12.6 / 16.2.
+// The pressure drive, where a channel's height keeps it to one step per launch:
+// the sweeps it competes with are faster on wide channels, the column pass
+// slower on tall ones. FP64, all such channels together: 2000 x 64 8.3 / 10.7,
+// 4000 x 64 15.5 / 14.6, 2000 x 128 16.7 / 16.8, 8000 x 128 40.3 / 35.0, 4000 x
+// 256 40.1 / 39.4, 1000 x 1000 45 / 67, 100 of 64 x 64 26.1 / 23.2; FP32 aligned
+// 512 x 512 27.0 / 39.0, 4096 x 200 27.5 / 26.3, 1024 x 1000 65 / 60. Blocks
+// that leave short channels one step (FP64, K = 1006): 8000 x 40 16.0 / 16.6,
+// 16000 x 40 28.0 / 23.7, 40000 x 24 32.7 / 31.4.
+enum BoxKind { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, PRESSURE_SHORT, FORCE, BOX_KINDS };
 struct BoxLimits {
   long long steps;      // most nodes of a kind in boxes of several steps,
   long long one;        // in boxes of one step,
   long long call_one;   // in boxes for a single step off the block boundaries,
   long long call;       // or several
 };
-BoxLimits box_limits(const lb_options *o, int kind) {
+// The nodes of a kind in a handle, its tallest and widest channel, and whether
+// any is of the vector class.
+struct BoxNodes {
+  long long nodes = 0;
+  int tallest = 0, widest = 0;
+  bool aligned = false;
+};
+BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
   const bool fp32 = o->precision == LB_FP32_SHIFTED, ve = o->viscoelastic;
   const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
   auto same = [](long long n) { return BoxLimits{n, n, n, n}; };
@@ -284,14 +300,21 @@ BoxLimits box_limits(const lb_options *o, int kind) {
       return BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? M / 2 : 5 * M / 16};
     case OTHER:
       if (fp32) return BoxLimits{8 * M, 8 * M, 2 * M, 8 * M};
+      if (all.widest <= 96) return same(ve ? 8 * M : 3 * M / 10);  // whole rows to a box
       return ve ? BoxLimits{8 * M, M / 16, 5 * M / 32, 8 * M}
                 : BoxLimits{3 * M / 10, M / 16, 5 * M / 32, 3 * M / 10};
-    case NARROW_WIDE: return same(ve ? always : fp32 ? M : M / 4);
-    case PRESSURE: return same(M);
+    case NARROW_WIDE:
+      if (fp32 && !ve) return BoxLimits{M, 15 * M / 16, 15 * M / 16, M};
+      return same(ve ? always : M / 4);
+    case PRESSURE: return same(fp32 ? (all.aligned ? 3 * M / 4 : M) : std::min(M, 2000ll * all.tallest));
+    case PRESSURE_SHORT: return BoxLimits{M, fp32 ? M : std::min(M, 10000ll * all.tallest), M, M};
     case FORCE: return same(5 * M / 32);
     default: return same(always);
   }
 }
+// A channel with the pressure drive of few enough rows, or small enough for one
+// box, for boxes of whole columns.
+bool short_pressure(const lb_channel &c) { return c.ny <= 48 || (long long)c.nx * c.ny <= 1024; }
 // The kind of a channel, or -1 if no box takes it.
 int box_kind(const lb_options *o, const lb_channel &c, int esize) {
   const bool gp = c.pressure_gradient != 0;  // one step per launch in either setting
@@ -301,7 +324,7 @@ int box_kind(const lb_options *o, const lb_channel &c, int esize) {
   if (gp && tall_pressure(c, esize)) return -1;
   const int cls = width_class(c.nx, esize);
   return o->stress_force         ? FORCE
-         : gp                    ? PRESSURE
+         : gp                    ? (short_pressure(c) ? PRESSURE_SHORT : PRESSURE)
          : cls == kVecClass      ? ALIGNED
          : is_strip_class(cls)   ? OTHER
          : c.nx > 16             ? NARROW_WIDE
@@ -313,15 +336,20 @@ enum { kNoBoxes = 0, kBoxes = 1, kPressureBoxes = 2 };
 std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n, int esize,
                                  long long BoxLimits::*limit) {
   std::vector<int> kind(n);
-  long long nodes[BOX_KINDS] = {};
+  BoxNodes all[BOX_KINDS];
   for (int i = 0; i < n; ++i) {
     kind[i] = box_kind(o, c[i], esize);
-    if (kind[i] >= 0) nodes[kind[i]] += (long long)c[i].nx * c[i].ny;
+    if (kind[i] < 0) continue;
+    BoxNodes &k = all[kind[i]];
+    k.nodes += (long long)c[i].nx * c[i].ny;
+    k.tallest = std::max(k.tallest, c[i].ny);
+    k.widest = std::max(k.widest, c[i].nx);
+    k.aligned = k.aligned || width_class(c[i].nx, esize) == kVecClass;
   }
   std::vector<char> ok(n, kNoBoxes);
   for (int i = 0; i < n; ++i)
-    if (kind[i] >= 0 && nodes[kind[i]] <= box_limits(o, kind[i]).*limit)
-      ok[i] = kind[i] == PRESSURE ? kPressureBoxes : kBoxes;
+    if (kind[i] >= 0 && all[kind[i]].nodes <= box_limits(o, kind[i], all[kind[i]]).*limit)
+      ok[i] = c[i].pressure_gradient != 0 ? kPressureBoxes : kBoxes;
   return ok;
 }
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
@@ -1629,36 +1657,39 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
     h->cus = std::max(cus, 1);
     h->n2slots = (long long)narrow_two_step_blocks_per_cu(o->precision == LB_FP32_SHIFTED) * std::max(cus, 1);
   }
-  // channels that step in boxes
+  // channels that step in boxes; where blocks leave a kind's plan one step,
+  // those within its limit
   h->blk_ok = h->L.blk_ok;
-  for (int l = 0; l < lb_handle::kBoxLists; ++l) {
+  const std::vector<char> one = block_channels(o, c, n, h->L.esize, &BoxLimits::one);
+  auto plan = [&](int l) -> BoxPlan & {
     const char kind = l == lb_handle::kMany ? kBoxes : kPressureBoxes;
+    std::vector<lb_channel> chans;
+    for (int i = 0; i < n; ++i)
+      if (h->blk_ok[i] == kind) chans.push_back(c[i]);
     // (a plan for all is one for those still active later)
     BoxPlan &p = h->boxes[l].all;
-    auto plan = [&]() {
-      std::vector<lb_channel> chans;
-      for (int i = 0; i < n; ++i)
-        if (h->blk_ok[i] == kind) chans.push_back(c[i]);
-      p = chans.empty() ? BoxPlan() : box_list_plan(h, l, chans);
-    };
-    plan();
-    if (l == lb_handle::kMany && p.S == 1) {
-      const std::vector<char> one = block_channels(o, c, n, h->L.esize, &BoxLimits::one);
-      for (int i = 0; i < n; ++i)
-        if (h->blk_ok[i] == kBoxes) h->blk_ok[i] = one[i];
-      plan();
-    }
-    if (p.S == 0 && l != lb_handle::kPressureMany)
-      for (char &k : h->blk_ok)
-        if (k == kind) k = kNoBoxes;
+    p = chans.empty() ? BoxPlan() : box_list_plan(h, l, chans);
+    return p;
+  };
+  for (int l : {lb_handle::kMany, lb_handle::kPressureMany}) {
+    const char kind = l == lb_handle::kMany ? kBoxes : kPressureBoxes;
+    if (plan(l).S > 1) continue;
+    for (int i = 0; i < n; ++i)
+      if (h->blk_ok[i] == kind) h->blk_ok[i] = one[i];
+    plan(l);
   }
+  plan(lb_handle::kPressure);
+  for (char &k : h->blk_ok)
+    if ((k == kBoxes && !h->boxes[lb_handle::kMany].all.S) ||
+        (k == kPressureBoxes && !h->boxes[lb_handle::kPressure].all.S))
+      k = kNoBoxes;
   {
-    const std::vector<char> one = block_channels(o, c, n, h->L.esize, &BoxLimits::call_one),
+    const std::vector<char> single = block_channels(o, c, n, h->L.esize, &BoxLimits::call_one),
                             several = block_channels(o, c, n, h->L.esize, &BoxLimits::call);
     h->box_one = h->box_several = true;
     for (int i = 0; i < n; ++i)
       if (h->blk_ok[i] == kBoxes) {
-        h->box_one = h->box_one && one[i];
+        h->box_one = h->box_one && single[i];
         h->box_several = h->box_several && several[i];
       }
   }

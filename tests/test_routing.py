@@ -78,7 +78,8 @@ def test_tall_pressure_channels_keep_the_column_pass(route, precision, shape, bo
 @pytest.mark.parametrize("precision,shape,viscoelastic,single", [
     ("fp32", (512, 512), 0, "boxes"), ("fp32", (1024, 600), 0, "sweep"), ("fp32", (1024, 600), 1, "boxes"),
     ("fp64", (256, 128), 0, "boxes"), ("fp64", (512, 512), 0, "tiles"), ("fp64", (1000, 100), 0, "tiles"),
-    ("fp64", (300, 100), 0, "boxes"), ("fp64", (4000, 2000), 1, "tiles"), ("fp64", (8, 262144), 0, "boxes")])
+    ("fp64", (300, 100), 0, "boxes"), ("fp64", (4000, 2000), 1, "tiles"), ("fp64", (8, 262144), 0, "boxes"),
+    ("fp64", (66, 4000), 0, "boxes")])
 def test_blocks_of_one_step_plans(route, precision, shape, viscoelastic, single):
     """Half a block without a divisor that pays (1, 503): boxes of one step
     replace the one-step sweeps only where they are faster; blocks of many
@@ -135,3 +136,18 @@ def test_rows_beyond_32_bit_slots_step_singly(route, precision):
     assert c["two_step"] == 10
     c, = route(precision, 8, [8, 3], [(widest + 256, 1)])
     assert c["sweep"] == 11
+
+
+@pytest.mark.parametrize("precision,shapes,K,boxes", [
+    ("fp64", [(2000, 64)], 1000, True), ("fp64", [(4000, 64)], 1000, False), ("fp64", [(1000, 1000)], 1000, True),
+    ("fp64", [(64, 64)] * 100, 1000, False), ("fp64", [(16000, 40)], 1000, True), ("fp64", [(16000, 40)], 1006, False),
+    ("fp64", [(8, 100)] * 300, 1000, True), ("fp32", [(4000, 64)], 1000, True), ("fp32", [(4096, 200)], 1000, False),
+    ("fp32", [(512, 512)], 1000, True), ("fp32", [(64, 64)] * 100, 1000, True)])
+def test_pressure_boxes_only_where_faster(route, precision, shapes, K, boxes):
+    """Wide channels too tall for many steps per launch keep the sweeps and the
+    column pass; short ones beside them their boxes."""
+    chans = [(*s, "pressure") for s in shapes]
+    for c in route(precision, K, [K, 3], chans):
+        assert ("boxes" in c) == boxes
+    *_, short = route(precision, 1000, [1000, 3], chans + [(64, 32, "pressure")])
+    assert "boxes" in short
