@@ -2707,10 +2707,12 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const do
 // registers for the change (columns of up to 256 rows read memory once). In a
 // tall column the lines count: there one thread takes both nodes of a row, the
 // inlet node of a row lying beside the outlet node of the row before. us per
-// step with the columns apart and together, FP32: 30 x 30000 1382 / 1041, 16 x
-// 10000 241 / 233; but 30 x 3000 84.7 / 88.4, 4 x 30000 260 / 270.
-constexpr int kGpbcRows = 256;   // rows of a column taken at once
-constexpr int kGpbcTall = 4096;  // rows above which a thread takes both nodes
+// step with the columns apart and together, FP32: 30 x 30000 1382 / 1041, 12 x
+// 20000 367 / 319; FP64 12 x 20000 764 / 638, 5 x 50000 815 / 753; but FP32 30 x
+// 3000 84.7 / 88.4, 4 x 30000 260 / 270, FP64 3 x 80000 792 / 865.
+constexpr int kGpbcRows = 256;      // rows of a column taken at once
+constexpr int kGpbcTall = 4096;     // rows above which a thread takes both nodes,
+constexpr int kGpbcRowBytes = 40;   // if a row of a plane has as many bytes
 template <typename T, bool SHIFT>
 __global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref,
                                                              bool boxed) {
@@ -2748,7 +2750,7 @@ __global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev
     gpbc_change<SHIFT>(q.f, SHIFT ? (double)uref[c.row_off + y] : 0.0, d, outlet, y, ny,
                        [&](int i, double v) { b[i * kTile] = (T)v; });
   };
-  if (ny <= kGpbcTall || nx < 16) {
+  if (ny <= kGpbcTall || nx * (int)sizeof(T) < kGpbcRowBytes) {
     const bool outlet = __builtin_amdgcn_readfirstlane(threadIdx.x / kGpbcRows) != 0;
     Node first;
     double sum = 0;

@@ -549,7 +549,8 @@ BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, bool 
           f.shape.push_back(b);
           f.W += number[i] * (double)box_count(c, b);
         }
-        const bool columns = S > 1 && f.W <= kColumnOrderBoxes;
+        // (one step per launch goes by rows, but the estimate was fitted so)
+        const bool columns = S == 1 || f.W <= kColumnOrderBoxes;
         for (size_t i = 0; added && i < f.shape.size(); ++i) {
           const lb_channel &c = *shaped[i];
           const BoxShape b = f.shape[i];
