@@ -266,7 +266,12 @@ bool tall_pressure(const lb_channel &c, int esize) {
 //  * short runs of steps off the boundaries, FP32 aligned 1024 x 700 15.7 /
 //    17.3, 1024 x 850 18.2 / 17.6; FP64 512 x 512 10.4 / 11.5, 768 x 512 14.8 /
 //    14.0 (time-integrated 1024 x 512 20.1 / 20.4, 1024 x 600 24.3 / 23.6).
-//  * 64 x 16000 FP32 25.9 / 23.0, 64 x 8192 14.9 / 21.3; 66 x 4000 FP64 12.6 / 16.2.
+//  * 64 x 16000 FP32 25.9 / 23.0, 64 x 8192 14.9 / 21.3.
+// Strips of 64 columns and tiles of 64 x 8 nodes do more than a narrow ragged
+// channel needs; up to 96 columns such channels have the limits of several
+// steps throughout (66 x 4000 FP64 12.6 / 16.2, 11 x 281389 FP32 79 / 342), and
+// the further limits of the others grow as the sweeps' nodes (63 FP64 channels
+// of 4 to 490 rows, 178,921 nodes, 18.2 / 30.2).
 // The pressure drive, where a channel's height keeps it to one step per launch:
 // the sweeps it competes with are faster on wide channels, the column pass
 // slower on tall ones. FP64, all such channels together: 2000 x 64 8.3 / 10.7,
@@ -275,39 +280,46 @@ bool tall_pressure(const lb_channel &c, int esize) {
 // 512 x 512 27.0 / 39.0, 4096 x 200 27.5 / 26.3, 1024 x 1000 65 / 60. Blocks
 // that leave short channels one step (FP64, K = 1006): 8000 x 40 16.0 / 16.6,
 // 16000 x 40 28.0 / 23.7, 40000 x 24 32.7 / 31.4.
-enum BoxKind { ALIGNED, OTHER, NARROW, NARROW_WIDE, PRESSURE, PRESSURE_SHORT, FORCE, BOX_KINDS };
+enum BoxKind { ALIGNED, OTHER, RAGGED, NARROW, NARROW_WIDE, PRESSURE, PRESSURE_RAGGED, PRESSURE_SHORT, FORCE, BOX_KINDS };
 struct BoxLimits {
   long long steps;      // most nodes of a kind in boxes of several steps,
   long long one;        // in boxes of one step,
   long long call_one;   // in boxes for a single step off the block boundaries,
   long long call;       // or several
 };
-// The nodes of a kind in a handle, its tallest and widest channel, and whether
-// any is of the vector class.
+// The nodes of a kind in a handle, those its sweeps step (whole strips, FP64
+// whole tiles), its tallest channel, and whether any is of the vector class.
 struct BoxNodes {
-  long long nodes = 0;
-  int tallest = 0, widest = 0;
+  long long nodes = 0, swept = 0;
+  int tallest = 0;
   bool aligned = false;
 };
 BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
   const bool fp32 = o->precision == LB_FP32_SHIFTED, ve = o->viscoelastic;
   const long long always = std::numeric_limits<long long>::max(), M = 1 << 20;
   auto same = [](long long n) { return BoxLimits{n, n, n, n}; };
+  // the limits against the one-step sweeps, by what these step
+  auto swept = [&](BoxLimits l) {
+    const double f = all.nodes > 0 ? (double)all.swept / all.nodes : 1.0;
+    return BoxLimits{l.steps, (long long)(l.one * f), (long long)(l.call_one * f), (long long)(l.call * f)};
+  };
   switch (kind) {
     case ALIGNED:
       if (fp32) return ve ? BoxLimits{7 * M / 8, 7 * M / 8, 5 * M / 8, 7 * M / 8}
                           : BoxLimits{7 * M / 8, M / 2, M / 2, 3 * M / 4};
-      return BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? M / 2 : 5 * M / 16};
+      return swept(BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? M / 2 : 5 * M / 16});
     case OTHER:
-      if (fp32) return BoxLimits{8 * M, 8 * M, 2 * M, 8 * M};
-      if (all.widest <= 96) return same(ve ? 8 * M : 3 * M / 10);  // whole rows to a box
-      return ve ? BoxLimits{8 * M, M / 16, 5 * M / 32, 8 * M}
-                : BoxLimits{3 * M / 10, M / 16, 5 * M / 32, 3 * M / 10};
+      if (fp32) return swept(BoxLimits{8 * M, 8 * M, 2 * M, 8 * M});
+      return swept(ve ? BoxLimits{8 * M, M / 16, 5 * M / 32, 8 * M}
+                      : BoxLimits{3 * M / 10, M / 16, 5 * M / 32, 3 * M / 10});
+    case RAGGED: return same(fp32 || ve ? 8 * M : 3 * M / 10);
     case NARROW_WIDE:
       if (fp32 && !ve) return BoxLimits{M, 15 * M / 16, 15 * M / 16, M};
       return same(ve ? always : M / 4);
     case PRESSURE: return same(fp32 ? (all.aligned ? 3 * M / 4 : M) : std::min(M, 2000ll * all.tallest));
-    case PRESSURE_SHORT: return BoxLimits{M, fp32 ? M : std::min(M, 10000ll * all.tallest), M, M};
+    case PRESSURE_RAGGED: return same(M);
+    case PRESSURE_SHORT:
+      return BoxLimits{M, fp32 ? M : std::min(M, std::max(M / 8, 10000ll * all.tallest)), M, M};
     case FORCE: return same(5 * M / 32);
     default: return same(always);
   }
@@ -323,8 +335,10 @@ int box_kind(const lb_options *o, const lb_channel &c, int esize) {
   if (align_up(N, kTile) * kPlanes > 0xffffffffull) return -1;  // 32-bit slots in a channel
   if (gp && tall_pressure(c, esize)) return -1;
   const int cls = width_class(c.nx, esize);
+  const bool ragged = is_strip_class(cls) && c.nx <= 96;
   return o->stress_force         ? FORCE
-         : gp                    ? (short_pressure(c) ? PRESSURE_SHORT : PRESSURE)
+         : gp                    ? (short_pressure(c) ? PRESSURE_SHORT : ragged ? PRESSURE_RAGGED : PRESSURE)
+         : ragged                ? RAGGED
          : cls == kVecClass      ? ALIGNED
          : is_strip_class(cls)   ? OTHER
          : c.nx > 16             ? NARROW_WIDE
@@ -343,7 +357,8 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
     BoxNodes &k = all[kind[i]];
     k.nodes += (long long)c[i].nx * c[i].ny;
     k.tallest = std::max(k.tallest, c[i].ny);
-    k.widest = std::max(k.widest, c[i].nx);
+    const int rows = esize == 8 ? kMainTileY : 1;
+    k.swept += (long long)((c[i].nx + 63) / 64 * 64) * ((c[i].ny + rows - 1) / rows * rows);
     k.aligned = k.aligned || width_class(c[i].nx, esize) == kVecClass;
   }
   std::vector<char> ok(n, kNoBoxes);
@@ -748,7 +763,8 @@ struct lb_handle {
   };
   BoxList boxes[kBoxLists];  // captured blocks; every other step with the pressure drive; captured blocks with it
   int n_tiles = 0;           // tiles of the one-step tile list
-  int only = -1;               // the box list that holds every active channel, if one does
+  int only = -1;               // the box list that holds every active channel, if one does,
+  bool both = false;           // or whether two hold them
   bool blk_all = false;        // every active channel runs many steps per launch in boxes
   // off the block boundaries boxes take single steps, or several at a time, of
   // the channels that run many steps in them
@@ -921,14 +937,16 @@ lb_status upload_strips(lb_handle *h, bool all) {
       list.threads = p.threads;
       list.n = (int)lists[l].size();
     }
-    h->blk_all = true;
+    h->blk_all = h->both = true;
     h->only = -1;
     for (int i = 0; i < h->n_ch; ++i) {
       if (!h->active[i]) continue;
+      if (h->blk_ok[i] == kNoBoxes) h->both = false;
       const int l = h->blk_ok[i] == kBoxes ? lb_handle::kMany : lb_handle::kPressureMany;
       if (h->blk_ok[i] == kNoBoxes || !h->boxes[l].S) h->blk_all = false;
       h->only = h->only < 0 || h->only == l ? l : lb_handle::kBoxLists;
     }
+    if (h->only != lb_handle::kBoxLists) h->both = false;
     if (!h->blk_all || h->only == lb_handle::kBoxLists) h->only = -1;
     if (h->two_step || many_steps(h)) {
       const int es = h->L.esize;
@@ -1035,6 +1053,20 @@ lb_status enqueue_two_step(lb_handle *h, int src, int k, hipStream_t s) {
   return LB_OK;
 }
 
+// Enqueues what a step of the pressure-driven channels needs beside the sweeps:
+// their boxes, unless (boxed) the block takes them many steps at once, and the
+// inlet/outlet column pass on the state just written, where the step leaves it.
+lb_status enqueue_pressure(lb_handle *h, int src, int k, hipStream_t s, bool boxed) {
+  if (!boxed) {
+    const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
+    if (st != LB_OK) return st;
+  }
+  if (h->gpbc_pass || (h->gpbc_boxes && !boxed))
+    HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
+                            boxed, s));
+  return LB_OK;
+}
+
 // Enqueues the sweeps of one step (source buffer src, step offset k), over
 // every active channel or (block) over those without two-step strips.
 lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block = false) {
@@ -1064,19 +1096,7 @@ lb_status enqueue_step(lb_handle *h, int src, int k, hipStream_t s, bool block =
     a.down = (src == 1);
     HIPCHECK(h, launch_sweep(h->opt.precision == LB_FP32_SHIFTED, c, false, a, s));
   }
-  // boxes of the pressure-driven channels, unless the block takes them many
-  // steps at once
-  const bool boxed = block && h->boxes[lb_handle::kPressureMany].S;
-  if (!boxed) {
-    const lb_status st = enqueue_boxes(h, lb_handle::kPressure, src, k, 1, s);
-    if (st != LB_OK) return st;
-  }
-  // generalised periodic boundaries where the step leaves them: the
-  // inlet/outlet column pass on the state just written
-  if (h->gpbc_pass || (h->gpbc_boxes && !boxed))
-    HIPCHECK(h, launch_gpbc(h->opt.precision == LB_FP32_SHIFTED, h->buf[src ^ 1], h->dch, h->n_ch, k, h->duref,
-                            boxed, s));
-  return LB_OK;
+  return enqueue_pressure(h, src, k, s, block && h->boxes[lb_handle::kPressureMany].S);
 }
 
 // The observation of the current state: per-row, per-strip partials into
@@ -1782,13 +1802,22 @@ lb_status lb_step(lb_handle *h, int64_t n) {
         // every channel takes them (the same results: no kernel's rounding
         // differs from another's)
         const int src = h->cur ^ (launches & 1);
-        int S = h->only >= 0 ? std::min(h->boxes[h->only].S, m - k) : 0;
-        if (h->only == lb_handle::kMany && !(S > 1 ? h->box_several : h->box_one)) S = 0;
+        const int many = h->boxes[lb_handle::kMany].S, pressure = std::max(h->boxes[lb_handle::kPressureMany].S, 1);
+        int S = std::min(h->only >= 0 ? h->boxes[h->only].S : h->both ? std::min(many, pressure) : 0, m - k);
+        if ((h->both || h->only == lb_handle::kMany) && !(S > 1 ? h->box_several : h->box_one)) S = 0;
         const bool in_boxes = S > 0;
         if (!in_boxes) S = h->two_only ? std::min(2, m - k) : 1;
-        lb_status st = in_boxes ? enqueue_boxes(h, h->only, src, k, S, h->stream)
-                       : S == 2 ? enqueue_two_step(h, src, k, h->stream)
-                                : enqueue_step(h, src, k, h->stream);
+        lb_status st;
+        if (in_boxes && h->both) {
+          st = enqueue_boxes(h, lb_handle::kMany, src, k, S, h->stream);
+          if (st == LB_OK)
+            st = S > 1 ? enqueue_boxes(h, lb_handle::kPressureMany, src, k, S, h->stream)
+                       : enqueue_pressure(h, src, k, h->stream, false);
+        } else {
+          st = in_boxes ? enqueue_boxes(h, h->only, src, k, S, h->stream)
+               : S == 2 ? enqueue_two_step(h, src, k, h->stream)
+                        : enqueue_step(h, src, k, h->stream);
+        }
         if (st != LB_OK) return st;
         k += S;
       }

@@ -151,3 +151,13 @@ def test_pressure_boxes_only_where_faster(route, precision, shapes, K, boxes):
         assert ("boxes" in c) == boxes
     *_, short = route(precision, 1000, [1000, 3], chans + [(64, 32, "pressure")])
     assert "boxes" in short
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_steps_of_two_box_lists(route, precision):
+    """Off the block boundaries a handle of short pressure-driven and other small
+    channels steps in both kinds of boxes, not in a sweep per width."""
+    chans = [(8, 40), (300, 11), (16, 9), (64, 32, "pressure"), (24, 300, "pressure")]
+    for case in (chans, chans[:4]):
+        for c in route(precision, 1000, [1, 7, 40], case):
+            assert c["boxes"] == 48
