@@ -2709,9 +2709,10 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ChanDev *ch, const do
 // inlet node of a row lying beside the outlet node of the row before. us per
 // step with the columns apart and together, FP32: 30 x 30000 1382 / 1041, 12 x
 // 20000 367 / 319; FP64 12 x 20000 764 / 638, 5 x 50000 815 / 753; but FP32 30 x
-// 3000 84.7 / 88.4, 4 x 30000 260 / 270, FP64 3 x 80000 792 / 865.
+// 3000 84.7 / 88.4, 18 x 5336 105 / 111, 4 x 30000 260 / 270, FP64 3 x 80000 792 /
+// 865.
 constexpr int kGpbcRows = 256;      // rows of a column taken at once
-constexpr int kGpbcTall = 4096;     // rows above which a thread takes both nodes,
+constexpr int kGpbcTall = 8192;     // rows above which a thread takes both nodes,
 constexpr int kGpbcRowBytes = 40;   // if a row of a plane has as many bytes
 template <typename T, bool SHIFT>
 __global__ void __launch_bounds__(2 * kGpbcRows) gpbc_kernel(T *B, const ChanDev *ch, int k, const float *uref,

@@ -239,33 +239,35 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c) {
 //  * the stress as a force (FP64; tiles): 8 x 64 1.9 / 10.3, 143 x 43 3.2 / 7.7,
 //    512 x 64 4.4 / 8.0, 1000 x 100 5.9 / 8.6, 512 x 300 9.0 / 10.4, 500 x 500
 //    14.1 / 12.1.
-// A tall FP64 channel with the pressure drive keeps the strips and the column
-// pass: every box at a period's end sums whole columns, whose lines are read
-// once for each of them, so that work grows with the height squared. Boxes
-// against strips, us per step: 100 x 5000 174 / 264, 100 x 7500 420 / 353; 16 x
-// 10000 186 / 368, 16 x 15800 1775 / 612; 4 x 31600 154 / 340, 4 x 100000 6800 /
-// 980.
-bool tall_pressure(const lb_channel &c, int esize) {
-  const double boxes = (double)c.ny * std::min(c.nx, 70), lines = (double)c.ny * std::min(c.nx, 16);
-  return esize == 8 && boxes * lines > 4e10;
+// FP64 with the pressure drive, one step per launch: every box at a period's end
+// sums whole columns, whose lines are read once for each of them, so that the
+// work grows with the height squared, summed over the channels (column_work); the
+// column pass takes its channels at the same time. Boxes against strips and the
+// pass, us per step: 100 x 5000 174 / 264, 100 x 7500 420 / 353; 16 x 10000 186 /
+// 368, 16 x 15800 1775 / 612; 4 x 31600 154 / 340, 4 x 100000 6800 / 980; 12
+// channels, the tallest 12 x 19529 and 50 x 4963, the others in boxes and these
+// by the pass 904 to 1187, all by the pass @@.
+constexpr double kColumnWork = 4e10;
+double column_work(const lb_channel &c) {
+  return (double)c.ny * std::min(c.nx, 70) * ((double)c.ny * std::min(c.nx, 16));
 }
 // That holds for launches of several steps. One step per launch leaves a box
 // its halo and its loads: above the further limits the one-step sweeps are
 // faster, and take blocks whose length leaves a plan one step (K / 2 without a
 // divisor that pays) and single steps off the block boundaries. Measured, us
 // per step, boxes against one-step sweeps:
-//  * such blocks (K = 1006): FP32 aligned 1024 x 500 15.6 / 17.1, 1024 x 700
-//    17.4 / 16.5 (time-integrated 1024 x 850 21.6 / 22.6); FP64 aligned 256 x
-//    128 4.2 / 5.0, 384 x 256 6.4 / 5.8, other widths 500 x 100 5.0 / 5.3,
-//    1000 x 100 6.5 / 5.7;
-//  * steps one by one, boxes planned for more: FP32 aligned 1024 x 500 18.9 /
-//    19.2, 1024 x 600 20.9 / 18.3 (time-integrated 21.3 / 22.8, 1024 x 700 23.8
-//    / 23.4), other widths 2000 x 1000 53.9 / 55.7, 3000 x 1000 78.6 / 62.8;
-//    FP64 aligned 256 x 256 7.8 / 8.1, 384 x 256 9.1 / 8.5, other widths 500 x
-//    300 10.1 / 10.4, 500 x 450 14.2 / 11.6;
+//  * such blocks (K = 1006): FP32 aligned 1024 x 500 15.6 / 17.3, 1024 x 700
+//    17.4 / 16.5 (time-integrated 1024 x 850 21.7 / 22.6); FP64 aligned 256 x
+//    128 4.2 / 5.0, 384 x 256 6.5 / 5.8, other widths 359 x 381 7.1 / 8.5, 500 x
+//    450 10.8 / 9.8, but 1000 x 100 6.5 / 5.7;
+//  * steps one by one, boxes planned for more: FP32 aligned 1024 x 500 19.0 /
+//    18.8, 1024 x 600 20.8 / 18.4 (time-integrated 21.6 / 22.9, 1024 x 700 24.0
+//    / 23.1), other widths 2000 x 1000 54.2 / 55.6, 3000 x 1000 78.6 / 62.9, 369 x
+//    11206 142 / 149; FP64 aligned 256 x 256 7.6 / 7.8, 384 x 256 8.9 / 8.4, other
+//    widths 500 x 300 9.8 / 10.1, 500 x 450 14.0 / 11.6, 1000 x 100 8.7 / 8.1;
 //  * short runs of steps off the boundaries, FP32 aligned 1024 x 700 15.7 /
-//    17.3, 1024 x 850 18.2 / 17.6; FP64 512 x 512 10.4 / 11.5, 768 x 512 14.8 /
-//    14.0 (time-integrated 1024 x 512 20.1 / 20.4, 1024 x 600 24.3 / 23.6).
+//    17.3, 1024 x 850 18.3 / 17.9; FP64 512 x 512 10.4 / 11.7, 768 x 512 14.8 /
+//    13.8 (time-integrated 15.6 / 16.3, 4096 x 120 22.6 / 18.2);
 //  * 64 x 16000 FP32 25.9 / 23.0, 64 x 8192 14.9 / 21.3.
 // Strips of 64 columns and tiles of 64 x 8 nodes do more than a narrow ragged
 // channel needs; up to 96 columns such channels have the limits of several
@@ -288,10 +290,11 @@ struct BoxLimits {
   long long call;       // or several
 };
 // The nodes of a kind in a handle, those its sweeps step (whole strips, FP64
-// whole tiles), its tallest channel, and whether any is of the vector class.
+// whole tiles), its tallest and widest channel, and whether any is of the vector
+// class.
 struct BoxNodes {
   long long nodes = 0, swept = 0;
-  int tallest = 0;
+  int tallest = 0, widest = 0;
   bool aligned = false;
 };
 BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
@@ -307,11 +310,13 @@ BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
     case ALIGNED:
       if (fp32) return ve ? BoxLimits{7 * M / 8, 7 * M / 8, 5 * M / 8, 7 * M / 8}
                           : BoxLimits{7 * M / 8, M / 2, M / 2, 3 * M / 4};
-      return swept(BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? M / 2 : 5 * M / 16});
-    case OTHER:
-      if (fp32) return swept(BoxLimits{8 * M, 8 * M, 2 * M, 8 * M});
-      return swept(ve ? BoxLimits{8 * M, M / 16, 5 * M / 32, 8 * M}
-                      : BoxLimits{3 * M / 10, M / 16, 5 * M / 32, 3 * M / 10});
+      return swept(BoxLimits{5 * M / 8, 3 * M / 64, 5 * M / 64, ve ? 7 * M / 16 : 5 * M / 16});
+    case OTHER: {
+      const bool wide = all.widest > 512;
+      if (fp32) return swept(BoxLimits{8 * M, 8 * M, wide ? 2 * M : 8 * M, 8 * M});
+      const long long steps = ve ? 8 * M : 3 * M / 10;
+      return swept(wide ? BoxLimits{steps, M / 16, M / 16, steps} : BoxLimits{steps, 9 * M / 64, 5 * M / 32, steps});
+    }
     case RAGGED: return same(fp32 || ve ? 8 * M : 3 * M / 10);
     case NARROW_WIDE:
       if (fp32 && !ve) return BoxLimits{M, 15 * M / 16, 15 * M / 16, M};
@@ -333,7 +338,6 @@ int box_kind(const lb_options *o, const lb_channel &c, int esize) {
   if (o->steps_per_sweep == 1 && !gp) return -1;
   const size_t N = (size_t)c.nx * c.ny;
   if (align_up(N, kTile) * kPlanes > 0xffffffffull) return -1;  // 32-bit slots in a channel
-  if (gp && tall_pressure(c, esize)) return -1;
   const int cls = width_class(c.nx, esize);
   const bool ragged = is_strip_class(cls) && c.nx <= 96;
   return o->stress_force         ? FORCE
@@ -351,12 +355,19 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
                                  long long BoxLimits::*limit) {
   std::vector<int> kind(n);
   BoxNodes all[BOX_KINDS];
+  auto tall = [&](int i) { return kind[i] == PRESSURE || kind[i] == PRESSURE_RAGGED; };
+  double work = 0;
   for (int i = 0; i < n; ++i) {
     kind[i] = box_kind(o, c[i], esize);
+    if (tall(i)) work += column_work(c[i]);
+  }
+  for (int i = 0; i < n; ++i) {
+    if (esize == 8 && work > kColumnWork && tall(i)) kind[i] = -1;
     if (kind[i] < 0) continue;
     BoxNodes &k = all[kind[i]];
     k.nodes += (long long)c[i].nx * c[i].ny;
     k.tallest = std::max(k.tallest, c[i].ny);
+    k.widest = std::max(k.widest, c[i].nx);
     const int rows = esize == 8 ? kMainTileY : 1;
     k.swept += (long long)((c[i].nx + 63) / 64 * 64) * ((c[i].ny + rows - 1) / rows * rows);
     k.aligned = k.aligned || width_class(c[i].nx, esize) == kVecClass;
@@ -994,7 +1005,9 @@ lb_status upload_strips(lb_handle *h, bool all) {
     }
     if ((int)two.size() > h->L.max_two) return fail(h, LB_ENOMEM, "two-step strip list exceeds its workspace");
     h->two_count = (int)two.size();
-    h->two_only = h->two_step;
+    // (an FP64 state of up to 0.8 million nodes goes faster through the tiles:
+    // 1024 x 700 22.2 us per step, two per launch 24.2; 1024 x 900 26.9 / 24.7)
+    h->two_only = h->two_step && (h->L.esize == 4 || h->opt.viscoelastic || h->L.plane >= 3 << 18);
     for (int i = 0; i < h->n_ch; ++i)
       if (h->active[i] && (h->blk_ok[i] || !two_step_channel(h->in[i], h->L.esize))) h->two_only = false;
     h->two_wall = wall;

@@ -99,8 +99,8 @@ def test_pressure_channel_beyond_the_boxes(precision):
     assert res[0][2] > 0 and res[0][5] > 0
 
 
-@pytest.mark.parametrize("precision,nx,ny", [("fp32", 16, 4097), ("fp32", 30, 4100), ("fp32", 15, 4100),
-                                             ("fp32", 16, 4096), ("fp64", 30, 12000)])
+@pytest.mark.parametrize("precision,nx,ny", [("fp32", 10, 8193), ("fp32", 30, 8200), ("fp32", 9, 8200),
+                                             ("fp32", 16, 8192), ("fp64", 30, 12000)])
 def test_pressure_tall_columns_match_oracle(orc, precision, nx, ny):
     """The column pass on both sides of the height and width from which one
     thread takes both nodes of a row (and, FP64, from which a channel leaves

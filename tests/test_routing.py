@@ -161,3 +161,14 @@ def test_steps_of_two_box_lists(route, precision):
     for case in (chans, chans[:4]):
         for c in route(precision, 1000, [1, 7, 40], case):
             assert c["boxes"] == 48
+
+
+def test_tall_pressure_channels_together(route):
+    """What the boxes of several tall FP64 channels would read of their columns
+    adds up: once it is too much, all of them take the column pass."""
+    one = route("fp64", 20, [20], [(100, 5000, "pressure")])
+    assert one[0]["boxes"] == 20
+    for c in route("fp64", 20, [20], [(100, 5000, "pressure"), (80, 5000, "pressure")]):
+        assert c["column_pass"] == 20 and "boxes" not in c
+    *tall, short = route("fp64", 20, [20], [(100, 5000, "pressure"), (80, 5000, "pressure"), (24, 30, "pressure")])
+    assert all("boxes" not in c for c in tall) and short["boxes"] == 20
