@@ -246,7 +246,7 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c) {
 // pass, us per step: 100 x 5000 174 / 264, 100 x 7500 420 / 353; 16 x 10000 186 /
 // 368, 16 x 15800 1775 / 612; 4 x 31600 154 / 340, 4 x 100000 6800 / 980; 12
 // channels, the tallest 12 x 19529 and 50 x 4963, the others in boxes and these
-// by the pass 904 to 1187, all by the pass @@.
+// by the pass 904 to 1187, all by the pass 814.
 constexpr double kColumnWork = 4e10;
 double column_work(const lb_channel &c) {
   return (double)c.ny * std::min(c.nx, 70) * ((double)c.ny * std::min(c.nx, 16));
@@ -270,8 +270,9 @@ double column_work(const lb_channel &c) {
 //    13.8 (time-integrated 15.6 / 16.3, 4096 x 120 22.6 / 18.2);
 //  * 64 x 16000 FP32 25.9 / 23.0, 64 x 8192 14.9 / 21.3.
 // Strips of 64 columns and tiles of 64 x 8 nodes do more than a narrow ragged
-// channel needs; up to 96 columns such channels have the limits of several
-// steps throughout (66 x 4000 FP64 12.6 / 16.2, 11 x 281389 FP32 79 / 342), and
+// channel needs; up to 96 columns, where they do a quarter more, such channels
+// have the limits of several steps throughout (66 x 4000 FP64 12.6 / 16.2, 11 x
+// 281389 FP32 79 / 342; 62 x 6605 FP64 time-integrated 25.8 / 17.6), and
 // the further limits of the others grow as the sweeps' nodes (63 FP64 channels
 // of 4 to 490 rows, 178,921 nodes, 18.2 / 30.2).
 // The pressure drive, where a channel's height keeps it to one step per launch:
@@ -325,7 +326,8 @@ BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
     case PRESSURE_RAGGED: return same(M);
     case PRESSURE_SHORT:
       return BoxLimits{M, fp32 ? M : std::min(M, std::max(M / 8, 10000ll * all.tallest)), M, M};
-    case FORCE: return same(5 * M / 32);
+    case FORCE:  // (one step, 400 x 400 8.8 / 11.2, 1024 x 147 13.5 / 10.3, 1 x 44747 and 2560 x 9 8.6 / 55)
+      return all.widest > 512 && all.swept < 5 * all.nodes / 4 ? BoxLimits{5 * M / 32, M / 16, M / 16, 5 * M / 32} : same(5 * M / 32);
     default: return same(always);
   }
 }
@@ -339,7 +341,7 @@ int box_kind(const lb_options *o, const lb_channel &c, int esize) {
   const size_t N = (size_t)c.nx * c.ny;
   if (align_up(N, kTile) * kPlanes > 0xffffffffull) return -1;  // 32-bit slots in a channel
   const int cls = width_class(c.nx, esize);
-  const bool ragged = is_strip_class(cls) && c.nx <= 96;
+  const bool ragged = is_strip_class(cls) && c.nx <= 96 && (c.nx + 63) / 64 * 64 >= 5 * c.nx / 4;
   return o->stress_force         ? FORCE
          : gp                    ? (short_pressure(c) ? PRESSURE_SHORT : ragged ? PRESSURE_RAGGED : PRESSURE)
          : ragged                ? RAGGED
@@ -368,7 +370,7 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
     k.nodes += (long long)c[i].nx * c[i].ny;
     k.tallest = std::max(k.tallest, c[i].ny);
     k.widest = std::max(k.widest, c[i].nx);
-    const int rows = esize == 8 ? kMainTileY : 1;
+    const int rows = o->stress_force ? kSafTileY : esize == 8 ? kMainTileY : 1;
     k.swept += (long long)((c[i].nx + 63) / 64 * 64) * ((c[i].ny + rows - 1) / rows * rows);
     k.aligned = k.aligned || width_class(c[i].nx, esize) == kVecClass;
   }
@@ -376,6 +378,14 @@ std::vector<char> block_channels(const lb_options *o, const lb_channel *c, int n
   for (int i = 0; i < n; ++i)
     if (kind[i] >= 0 && all[kind[i]].nodes <= box_limits(o, kind[i], all[kind[i]]).*limit)
       ok[i] = c[i].pressure_gradient != 0 ? kPressureBoxes : kBoxes;
+  // with the pressure drive also all kinds together; the short channels stay
+  // (42 FP64 channels of two million nodes 340 us per step in the sweeps, with
+  // those of up to 96 columns in boxes 477)
+  long long pressure = 0;
+  for (int i = 0; i < n; ++i)
+    if (ok[i] == kPressureBoxes) pressure += (long long)c[i].nx * c[i].ny;
+  for (int i = 0; i < n && pressure > 1 << 20; ++i)
+    if (ok[i] == kPressureBoxes && kind[i] != PRESSURE_SHORT) ok[i] = kNoBoxes;
   return ok;
 }
 bool two_step_wall(const lb_channel &c) { return c.top_wall == LB_WALL_ZOU_HE || c.wall_velocity != 0; }
@@ -516,6 +526,19 @@ void add_boxes(int ci, const lb_channel &c, BoxShape b, std::vector<Strip> &out)
   for (int y0 = 0; y0 < c.ny; y0 += b.oh)
     for (int x0 = 0; x0 < c.nx; x0 += b.ow)
       out.push_back(Strip{ci, x0, y0, std::min(y0 + b.oh, c.ny), 0, std::min(x0 + b.ow, c.nx)});
+}
+// Orders a list so that its items run in this order all over the GPU, where the
+// kernels hand every XCD a contiguous part of it: boxes that sum the columns of a
+// tall channel, long next to others, would all share one (28 FP64 channels of 2
+// to 4114 rows 140 us per step, spread 69; with fewer boxes than CUs the
+// neighbours an XCD's L2 holds count more, 14 of 2 to 921 rows 10.9, spread 13.9).
+void spread_over_xcds(std::vector<Strip> &list) {
+  const std::vector<Strip> in(list);
+  const size_t n = in.size(), q = n >> 3, rem = n & 7;
+  for (size_t w = 0; w < n; ++w) {
+    const size_t j = w & 7;
+    list[j * q + std::min(j, rem) + (w >> 3)] = in[w];
+  }
 }
 long long box_count(const lb_channel &c, BoxShape b) {
   return (long long)((c.nx + b.ow - 1) / b.ow) * ((c.ny + b.oh - 1) / b.oh);
@@ -940,7 +963,19 @@ lb_status upload_strips(lb_handle *h, bool all) {
       const BoxPlan p = list.all.shape.size() == ids.size() ? list.all : box_list_plan(h, l, chans);
       if (l == lb_handle::kPressureMany && p.S <= 1) continue;
       if (p.S == 0) return fail(h, LB_ENOMEM, "no box plan fits its workspace");
-      for (size_t j = 0; j < ids.size(); ++j) add_boxes(ids[j], chans[j], p.shape[j], lists[l]);
+      std::vector<size_t> order(ids.size());
+      for (size_t j = 0; j < ids.size(); ++j) order[j] = j;
+      int tallest = 0;
+      long long total = 0;
+      for (size_t j = 0; j < ids.size(); ++j) {
+        tallest = std::max(tallest, chans[j].ny);
+        total += box_count(chans[j], p.shape[j]);
+      }
+      const bool sums = l == lb_handle::kPressure && h->L.esize == 8 && tallest > 256 && ids.size() > 1 && total > h->cus;
+      if (sums)
+        std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return chans[a].ny > chans[b].ny; });
+      for (size_t j : order) add_boxes(ids[j], chans[j], p.shape[j], lists[l]);
+      if (sums) spread_over_xcds(lists[l]);
       if ((long long)lists[l].size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
       HIPCHECK(h, hipMemcpyAsync(list.d, lists[l].data(), lists[l].size() * sizeof(Strip), hipMemcpyHostToDevice,
                                  h->stream));
@@ -1720,12 +1755,19 @@ lb_status lb_create(const lb_channel *c, int32_t n, const lb_options *o, void *w
   {
     const std::vector<char> single = block_channels(o, c, n, h->L.esize, &BoxLimits::call_one),
                             several = block_channels(o, c, n, h->L.esize, &BoxLimits::call);
-    h->box_one = h->box_several = true;
+    // (a handle of several kinds steps in as many sweeps: boxes unless those
+    // within no limit hold three quarters of the nodes. 26 FP64 channels 1 to
+    // 14923 wide, 62%, step by step 53 us, in sweeps 213)
+    double in_boxes = 0, beyond_one = 0, beyond_several = 0;
     for (int i = 0; i < n; ++i)
       if (h->blk_ok[i] == kBoxes) {
-        h->box_one = h->box_one && single[i];
-        h->box_several = h->box_several && several[i];
+        const double nodes = (double)c[i].nx * c[i].ny;
+        in_boxes += nodes;
+        if (!single[i]) beyond_one += nodes;
+        if (!several[i]) beyond_several += nodes;
       }
+    h->box_one = beyond_one < 0.75 * in_boxes;
+    h->box_several = beyond_several < 0.75 * in_boxes;
   }
   for (int i = 0; i < n; ++i) {
     ChanDev &d = h->L.ch[i];
