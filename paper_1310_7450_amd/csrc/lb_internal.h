@@ -66,7 +66,8 @@ __host__ __device__ inline bool column_pass_takes(const ChanDev &c, bool boxed) 
 
 // Work unit of one wavefront: rows [y0, y1) of channel ch, starting at
 // column x0 (wide mode: first interior column; narrow mode: 0). flip: the
-// vector sweep marches this strip against the step's direction (odd bands).
+// vector sweep marches this strip against the step's direction (odd bands); a
+// box cut by columns alone takes its nodes column by column.
 // x1: the two-step sweep stores columns [x0, x1) (at most two_step_cols).
 struct Strip {
   int ch, x0, y0, y1, flip, x1;

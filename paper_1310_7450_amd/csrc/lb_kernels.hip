@@ -1028,17 +1028,18 @@ __device__ __forceinline__ double column_density(const double *__restrict__ C, i
   return (f0 + f1 + f3) + (f2 + f5 + f6) + (f4 + f7 + f8);
 }
 
-// Sum of a column of n densities (stride s apart) over a wavefront, all lanes
-// active: the sums of the rows of one residue mod 256, 64 of them after 64, or
-// (TREE) in the order of gpbc_kernel.
+// Sum of a column of n densities (stride s apart; at most 512, as a box of 1024
+// nodes holds at least two of them) over a wavefront, all lanes active: the
+// sums of the rows of one residue mod 256, 64 of them after 64, or (TREE) in the
+// order of gpbc_kernel.
 template <bool TREE>
 __device__ __forceinline__ double column_sum(const double *col, int s, int n) {
   const int lane = threadIdx.x & 63;
   if constexpr (!TREE) {
     double sum = 0;
     for (int k = 0; k < min(n, 256); k += 64) {
-      double v = 0;
-      for (int r = k + lane; r < n; r += 256) v += col[r * s];
+      double v = k + lane < n ? col[(k + lane) * s] : 0.0;
+      if (n > 256) v += k + 256 + lane < n ? col[(k + 256 + lane) * s] : 0.0;
       sum += group_sum<64>(v);
     }
     return sum;
@@ -1161,9 +1162,9 @@ __global__ void __launch_bounds__(TH, sizeof(T) == 4 && !GP ? 6 : 4) sweep_block
   const bool in = (int)threadIdx.x < rows * cw;  // (the host keeps rows * cw <= TH)
   const int n = in ? threadIdx.x : 0;
   // nodes row by row, or column by column where only columns are cut and the
-  // boxes are few: the halo is then at both ends of the node order, and whole
-  // wavefronts drop out of the later steps (see kColumnOrderBoxes)
-  const bool by_col = S > 1 && !whole && rows == ny && a.n_wg <= kColumnOrderBoxes;
+  // boxes are few (st.flip, see kColumnOrderBoxes): the halo is then at both ends
+  // of the node order, and whole wavefronts drop out of the later steps
+  const bool by_col = st.flip && !whole && rows == ny;
   const int sx = by_col ? rows : 1, sy = by_col ? 1 : cw;
   const int major = n / (by_col ? rows : cw), minor = n - major * (by_col ? rows : cw);
   const int r = by_col ? minor : major, cc = by_col ? major : minor, y = ry0 + r;

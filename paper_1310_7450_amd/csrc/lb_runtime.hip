@@ -522,10 +522,10 @@ int box_waves(const lb_channel &c, BoxShape b, int S, int step_reach, int s, boo
   if (columns && !whole && std::min(b.oh + halo, c.ny) == c.ny) return ((b.ow + 2 * reach) * c.ny + 63) / 64 + 1;
   return (rows * cw + 63) / 64;
 }
-void add_boxes(int ci, const lb_channel &c, BoxShape b, std::vector<Strip> &out) {
+void add_boxes(int ci, const lb_channel &c, BoxShape b, bool columns, std::vector<Strip> &out) {
   for (int y0 = 0; y0 < c.ny; y0 += b.oh)
     for (int x0 = 0; x0 < c.nx; x0 += b.ow)
-      out.push_back(Strip{ci, x0, y0, std::min(y0 + b.oh, c.ny), 0, std::min(x0 + b.ow, c.nx)});
+      out.push_back(Strip{ci, x0, y0, std::min(y0 + b.oh, c.ny), columns, std::min(x0 + b.ow, c.nx)});
 }
 // Orders a list so that its items run in this order all over the GPU, where the
 // kernels hand every XCD a contiguous part of it: boxes that sum the columns of a
@@ -974,7 +974,8 @@ lb_status upload_strips(lb_handle *h, bool all) {
       const bool sums = l == lb_handle::kPressure && h->L.esize == 8 && tallest > 256 && ids.size() > 1 && total > h->cus;
       if (sums)
         std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return chans[a].ny > chans[b].ny; });
-      for (size_t j : order) add_boxes(ids[j], chans[j], p.shape[j], lists[l]);
+      for (size_t j : order)
+        add_boxes(ids[j], chans[j], p.shape[j], p.S > 1 && total <= kColumnOrderBoxes, lists[l]);
       if (sums) spread_over_xcds(lists[l]);
       if ((long long)lists[l].size() > h->L.max_boxes) return fail(h, LB_ENOMEM, "box list exceeds its workspace");
       HIPCHECK(h, hipMemcpyAsync(list.d, lists[l].data(), lists[l].size() * sizeof(Strip), hipMemcpyHostToDevice,
