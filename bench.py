@@ -207,8 +207,9 @@ def two_step_roofline(achieved, nodes, sec_per_step, traffic, precision="fp32", 
     performs two node updates per node, so at B bytes per node update (80 in
     FP32, 160 in FP64) its algorithmic bytes are 2 B per node and launch; the
     state itself is read and written once per launch (B per node), which
-    state_GBs reports beside the counters' traffic per launch. The kernel is
-    limited by instruction issue, not by HBM (state_frac)."""
+    state_GBs reports beside the counters' traffic per launch. frac counts the
+    bytes one step per pass would move, state_frac those of the state: what
+    limits the kernel is the memory path, at about a large copy's rate."""
     bpn = BYTES_PER_NODE[precision] if bpn is None else bpn
     state = bpn * nodes / (2 * sec_per_step) / 1e9
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -146,7 +146,7 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                make fewer one-step strips than the GPU has SIMDs, their
  *                heights are divided alike (down to
  *                4 rows, or a narrow kernel's row group) to spread them
- *                over the GPU. The narrow widths' two-step strips take
+ *                over the GPU. The two-step strips of widths 32 and 64 take
  *                the smallest height among 1, 2, 4, the multiples of 8 up
  *                to 64 and the powers of two beyond (at most strip_rows
  *                when it is set) whose strips the GPU holds all at once.
@@ -182,26 +182,37 @@ enum { LB_WALL_HALFWAY = 0, LB_WALL_ZOU_HE = 1 };
  *                Runs as one fused pass per step (u~, Sigma^nN and the
  *                collide-and-stream of a tile of nodes in one workgroup),
  *                small lattices in boxes (steps_per_sweep);
- *   steps_per_sweep 0 (default) or 2: with either stress model, no
- *                stress_force and K a multiple of 4, the blocks of K steps
- *                advance the vector-class channels (width a multiple of 256
- *                in LB_FP32_SHIFTED, of 64 in LB_FP64, not a power of two up
- *                to 64) without pressure_gradient (any top wall) two
- *                steps per pass over the state (a
- *                strip's rows of step t are kept on chip for step t+1);
- *                without the viscoelastic option the narrow channels (width
- *                1, 2, 4, ..., 64) without pressure_gradient do too.
- *                Handles whose channels of a width class hold few nodes
- *                (about a million and less, with stress_force 163,840 and
- *                less, any K; with pressure_gradient channels of at most 48
- *                rows) advance them more steps per pass
- *                instead, in boxes of nodes whose state stays on chip for a
- *                divisor of K / 2 steps. Steps outside whole blocks go two
- *                or more per pass too when every active channel is of one
- *                of these kinds (the narrow widths' two-step pass excepted).
- *                Other channels and other handles run one step per pass. Each node update is the arithmetic of the
- *                one-step pass; states agree with it to round-off; 1: one
- *                step per pass always.
+ *   steps_per_sweep 0 (default) or 2: small lattices go several steps per
+ *                pass, in boxes of nodes whose state stays on chip for S
+ *                steps, S a divisor of K / 2: the channels of a handle that
+ *                are of one kind, while they hold together at most (M =
+ *                1,048,576 nodes)
+ *                  vector class (width a multiple of 256 in LB_FP32_SHIFTED,
+ *                    of 64 in LB_FP64, no power of two up to 64): 7/8 M in
+ *                    FP32, 5/8 M in FP64;
+ *                  other widths: 8 M in FP32 or with the viscoelastic
+ *                    option, 3/10 M in FP64;
+ *                  widths 32 and 64: M in FP32, M / 4 in FP64, any number
+ *                    with the viscoelastic option;
+ *                  widths 1 to 16 in powers of two: any number;
+ *                  stress_force, any width: 163,840;
+ *                  pressure_gradient, several steps per pass in channels
+ *                    of at most 48 rows or 1,024 nodes: M; one in others: M
+ *                    (FP32 of the vector class 3/4 M; FP64 at most 2,000
+ *                    for each row of the tallest channel), both together M.
+ *                Fewer, where only one step per pass is possible. Larger
+ *                lattices, with K a multiple of 4, no stress_force and no
+ *                pressure_gradient (any top wall): the blocks of K steps
+ *                advance the vector-class channels (either stress model) and,
+ *                without the viscoelastic option, those of width 32 and 64
+ *                two steps per pass over the state (a strip's rows of step t
+ *                are kept on chip for step t+1). Steps outside whole blocks
+ *                go several per pass too where every active channel steps in
+ *                boxes, or every one is of the vector class and beyond them.
+ *                All others run one step per pass. Each node update is the
+ *                arithmetic of the one-step pass; states agree with it to
+ *                round-off and do not depend on how a caller splits the
+ *                steps; 1: one step per pass always.
  */
 typedef struct {
   int32_t precision;

@@ -786,7 +786,7 @@ __global__ void __launch_bounds__(64 * LB_WG_WAVES) sweep_kernel(SweepArgs a) {
 // ring's writes and reads. Per node the arithmetic is the narrow sweep's.
 //
 // For the lattices that do not step in boxes (sweep_block_kernel): FP32 beyond
-// about a million nodes (64 x 65536 80 us per step against 92), FP64 beyond a
+// about a million nodes (64 x 65536 73 us per step against 92), FP64 beyond a
 // quarter of that. Narrower channels always step in boxes (or, beyond the nodes
 // boxes address, one step per launch).
 constexpr int kN2Ring = 8;  // groups in the ring
@@ -1117,10 +1117,10 @@ __device__ __forceinline__ void saf_collide(const double f[9], double sd, double
 // Small lattices are bound by latency: a launch of one or two steps costs
 // 4 to 10 us whatever it computes. Here a step costs its chain of two LDS
 // exchanges and the node update, about 0.9 us at one wavefront per SIMD and
-// 1.05 at two (FP64 1.0 and 1.4): one 8 x 64 channel 1.05 us per step against
+// 1.05 at two (FP64 1.0 and 1.4): one 8 x 64 channel 1.1 us per step against
 // 4.7 at two steps per launch. With every CU full (256 ragged channels, 80
-// VGPRs, six wavefronts per SIMD in FP32) it issues VALU work about two
-// thirds of the time: 5.3 us per step against 13.2.
+// VGPRs, six wavefronts per SIMD in FP32) it issues VALU work about three
+// quarters of the time: 5.3 us per step against 13.2.
 //
 // GP: channels with the pressure drive, the generalised periodic boundaries
 // (gpbc_change) in the same launch. A step needs the density of the inlet and
@@ -1129,7 +1129,7 @@ __device__ __forceinline__ void saf_collide(const double f[9], double sd, double
 // stores inlet or outlet nodes sums it from the state it reads, while its
 // region loads; with S > 1 the region holds all rows, and the wavefronts with
 // inlet or outlet nodes sum it every step from LDS, in the same order. 64 x 32
-// FP64 takes 3.2 us per step against 5.9 with S = 1. FP32 rounding does not
+// FP64 takes 3.3 us per step against 5.9 with S = 1. FP32 rounding does not
 // keep the density exactly, and the boundary acts on that of the stored
 // values: S > 1 sums it after the update, behind a third barrier, in the order
 // of gpbc_kernel, which with S = 1 follows every step.

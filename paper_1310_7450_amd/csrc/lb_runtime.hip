@@ -198,9 +198,9 @@ void add_strips(int ci, const ChanDev &d, int esize, int srows, bool stack, std:
 
 // Two steps per launch (sweep_vec2_kernel) for the blocks of captured steps:
 // vector-class channels without the pressure drive (whose column pass runs
-// between steps), with either stress model and any top wall, with blocks a multiple of four steps (a
-// block is then an even number of two-step launches and returns the state
-// to its buffer, as one-step launches do).
+// between steps), with either stress model and any top wall, with blocks a
+// multiple of four steps (a block is then an even number of two-step launches
+// and returns the state to its buffer, as one-step launches do).
 bool two_step_handle(const lb_options *o, int K) {
   return o->steps_per_sweep != 1 && !o->stress_force && K % 4 == 0;
 }
@@ -221,24 +221,24 @@ bool narrow_two_step_channel(const lb_options *o, const lb_channel &c) {
 // several steps; a large one by instruction issue, of which the boxes' halos
 // cost more than the halos of strips. Measured, us per step, boxes against
 // the path they replace:
-//  * aligned widths (vector class; two steps per launch): FP32 512 x 512 7.3
-//    against 20.2, 1024 x 768 16.0 / 17.9, 1024 x 1024 20.2 / 18.6; FP64
-//    1024 x 512 18.1 / 23.8, 1024 x 768 26.4 / 24.1, and about the same with
+//  * aligned widths (vector class; two steps per launch): FP32 512 x 512 6.4
+//    against 19.4, 1024 x 768 15.8 / 17.9, 1024 x 1024 20.2 / 17.8; FP64
+//    1024 x 512 18.0 / 23.8, 1024 x 768 26.4 / 24.2, and about the same with
 //    the time-integrated stress;
-//  * other widths above 64: FP32 (one step per launch) 200 x 20 1.9 / 14.3,
-//    1000 x 300 8.8 / 21.3, 4000 x 2000 180 / 210; FP64 (tiles) 200 x 20
-//    1.9 / 6.2, 1000 x 300 11.4 / 12.2, 1000 x 500 18.0 / 16.6, but
-//    time-integrated 4000 x 2000 278 / 309;
+//  * other widths above 64: FP32 (one step per launch) 200 x 20 2.0 / 14.4,
+//    1000 x 300 7.6 / 19.8, 4000 x 2000 181 / 211; FP64 (tiles) 200 x 20
+//    2.1 / 6.3, 1000 x 300 11.1 / 12.0, 1000 x 500 18.0 / 16.5, but
+//    time-integrated 4000 x 2000 278 / 308;
 //  * the pressure drive, one step per launch with the boundary columns in it
-//    (FP64): 64 x 32 6.1 / 45 (a strip march and a
-//    column pass), 1000 x 320 19.4 / 26.9, 1000 x 1000 48.5 / 65.4;
+//    (FP64): 64 x 32 5.9 / 45 (a strip march and a column pass), 1000 x 320
+//    18.8 / 26.0, 1000 x 1000 45 / 67;
 //  * narrow widths, whose boxes need no columns beside them: 8 x 64 1.1 / 4.7
-//    (FP64 1.4 / 3.9), 256 ragged channels of 8 columns 5.3 / 13.2 (8.5 /
-//    22.1), 8 x 262144 27.7 / 48.1; from 32 columns on a box holds few rows:
-//    64 x 8192 12.8 / 15.7 (FP64 17.3 / 15.2), 64 x 65536 92 / 80;
-//  * the stress as a force (FP64; tiles): 8 x 64 1.9 / 10.3, 143 x 43 3.2 / 7.7,
-//    512 x 64 4.4 / 8.0, 1000 x 100 5.9 / 8.6, 512 x 300 9.0 / 10.4, 500 x 500
-//    14.1 / 12.1.
+//    (FP64 1.4 / 3.9), 256 ragged channels of 8 columns 5.3 / 13.2 (8.4 /
+//    22.1), 8 x 262144 18.8 / 40.4; from 32 columns on a box holds few rows:
+//    64 x 8192 10.8 / 14.6 (FP64 17.3 / 15.1), 64 x 65536 92 / 73;
+//  * the stress as a force (FP64; tiles): 8 x 64 1.9 / 9.9, 143 x 43 3.2 / 7.6,
+//    512 x 64 4.4 / 7.9, 1000 x 100 5.7 / 8.5, 512 x 300 8.9 / 10.3, 500 x 500
+//    14.1 / 11.8.
 // FP64 with the pressure drive, one step per launch: every box at a period's end
 // sums whole columns, whose lines are read once for each of them, so that the
 // work grows with the height squared, summed over the channels (column_work); the
@@ -283,7 +283,9 @@ double column_work(const lb_channel &c) {
 // 512 x 512 27.0 / 39.0, 4096 x 200 27.5 / 26.3, 1024 x 1000 65 / 60. Blocks
 // that leave short channels one step (FP64, K = 1006): 8000 x 40 16.0 / 16.6,
 // 16000 x 40 28.0 / 23.7, 40000 x 24 32.7 / 31.4.
-enum BoxKind { ALIGNED, OTHER, RAGGED, NARROW, NARROW_WIDE, PRESSURE, PRESSURE_RAGGED, PRESSURE_SHORT, FORCE, BOX_KINDS };
+enum BoxKind {
+  ALIGNED, OTHER, RAGGED, NARROW, NARROW_WIDE, PRESSURE, PRESSURE_RAGGED, PRESSURE_SHORT, FORCE, BOX_KINDS
+};
 struct BoxLimits {
   long long steps;      // most nodes of a kind in boxes of several steps,
   long long one;        // in boxes of one step,
@@ -316,7 +318,8 @@ BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
       const bool wide = all.widest > 512;
       if (fp32) return swept(BoxLimits{8 * M, 8 * M, wide ? 2 * M : 8 * M, 8 * M});
       const long long steps = ve ? 8 * M : 3 * M / 10;
-      return swept(wide ? BoxLimits{steps, M / 16, M / 16, steps} : BoxLimits{steps, 9 * M / 64, 5 * M / 32, steps});
+      return swept(wide ? BoxLimits{steps, M / 16, M / 16, steps}
+                        : BoxLimits{steps, 9 * M / 64, 5 * M / 32, steps});
     }
     case RAGGED: return same(fp32 || ve ? 8 * M : 3 * M / 10);
     case NARROW_WIDE:
@@ -327,7 +330,8 @@ BoxLimits box_limits(const lb_options *o, int kind, const BoxNodes &all) {
     case PRESSURE_SHORT:
       return BoxLimits{M, fp32 ? M : std::min(M, std::max(M / 8, 10000ll * all.tallest)), M, M};
     case FORCE:  // (one step, 400 x 400 8.8 / 11.2, 1024 x 147 13.5 / 10.3, 1 x 44747 and 2560 x 9 8.6 / 55)
-      return all.widest > 512 && all.swept < 5 * all.nodes / 4 ? BoxLimits{5 * M / 32, M / 16, M / 16, 5 * M / 32} : same(5 * M / 32);
+      return all.widest > 512 && all.swept < 5 * all.nodes / 4 ? BoxLimits{5 * M / 32, M / 16, M / 16, 5 * M / 32}
+                                                               : same(5 * M / 32);
     default: return same(always);
   }
 }
@@ -429,12 +433,12 @@ int two_step_rows(const std::vector<lb_channel> &chans, int npl, bool fp32, int 
 // strips take it rounded up to its row group), the smallest whose strips
 // all fit the GPU's resident workgroups at once (slots), so that the strips
 // are as short as one round allows; not above the requested height when
-// one is given; within the room left in the strip list. (Measured on
-// 8-wide channels of 32..512 rows, 16 to 256 of them: among powers of two
-// this height was the fastest in every case, a second round or strips
-// twice as tall costing 10-55% per step; the multiples of 8 gained a
-// further 14% with all 256 channels active, at 48 rows against 64, and
-// lost 2% with 64 active, at 24 rows against 32.)
+// one is given; within the room left in the strip list. (Measured where the
+// kernel took 16 to 256 channels of 8 columns and 32 to 512 rows, which step in
+// boxes now: among powers of two this height was the fastest in every case, a
+// second round or strips twice as tall costing 10-55% per step; the multiples
+// of 8 gained a further 14% with all 256 channels active, at 48 rows against
+// 64, and lost 2% with 64 active, at 24 rows against 32.)
 // a channel's rows per strip for height R: R rounded up to its row group
 int narrow_rows(int R, int nx) {
   const int g = 64 / nx;
@@ -547,11 +551,12 @@ long long box_count(const lb_channel &c, BoxShape b) {
 // launch + rounds (start + S (step + wave v m)) + (S busy V + load R) / CUs
 // for its rounds of resident workgroups, v wavefronts per SIMD of the largest
 // box at work, m boxes sharing a CU, V wavefronts at work and R wavefronts of
-// the regions in all; part/8 of the threads hold the largest region. The constants are fitted to 700 launches (one 8 x 64
-// channel to 1024 x 512 nodes and 256 ragged 8-wide channels, S 1 to 20;
-// mean error 12% FP32, 9% FP64): the plan picked was within 6% of the best
-// measured one in every case. S divides K / 2, so that a captured block is
-// an even number of launches and leaves the state in its buffer.
+// the regions in all; part/8 of the threads hold the largest region. The
+// constants are fitted to 700 launches (one 8 x 64 channel to 1024 x 512 nodes
+// and 256 ragged 8-wide channels, S 1 to 20; mean error 12% FP32, 9% FP64): the
+// plan picked was within 6% of the best measured one in every case. S divides
+// K / 2, so that a captured block is an even number of launches and leaves the
+// state in its buffer.
 BoxPlan plan_boxes(const std::vector<lb_channel> &chans, int K, bool fp32, bool stress_force, int cus, long long room) {
   BoxPlan best;
   double best_us = 1e300;
@@ -1836,8 +1841,9 @@ lb_status lb_step(lb_handle *h, int64_t n) {
   // Every K steps of the handle's clock end a block: the convergence check
   // (if enabled) and, for FP32 storage, the move of the row reference
   // velocities. Whole blocks run as one graph; steps that start or end off
-  // a block boundary are enqueued one by one. The boundaries do not depend
-  // on how the steps are split over calls, so neither does the result.
+  // a block boundary are enqueued launch by launch, several steps each where
+  // a kernel takes them. The boundaries do not depend on how the steps are
+  // split over calls, and all kernels round alike, so neither does the result.
   while (left > 0) {
     bool any = false;
     for (int a : h->active) any |= (a != 0);

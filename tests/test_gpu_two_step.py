@@ -9,20 +9,23 @@ t+1 to them; each node update is the one-step sweep's arithmetic, so the
 states agree with one step per pass to round-off (and, where the compiler
 contracts the same products into the same fused operations, bit for bit).
 Shapes cover one, two, three and many column strips per row (two-step strips
-are at most 124 columns at two nodes per lane and 248 at four, split as
-evenly as the width allows in multiples of the nodes per lane), ragged row
-bands, states of either size, one- and
+are at most 120 columns in FP32 at two nodes per lane and 248 at four, in
+multiples of 8, and 112 in FP64, in multiples of 16, split as evenly as the
+width allows), ragged row bands, states of either size, one- and
 two-row channels, the periodic wrap of the window around the channel, and
 handles that mix eligible channels with others (pressure drive, other
 widths) whose steps still run one per pass inside the same block (in FP64 on
 the tile sweep). Moving half-way walls and Zou-He tops run two steps per pass
 too, with the wall switched off between the two steps of a launch.
 
-The narrow widths (1, 2, 4, ..., 64: a row in nx lanes, 64 / nx rows per
-wavefront) take two steps per pass in their own kernel, which keeps whole
-row groups of step t in a ring; their shapes cover every width, strips of a
-few groups and of one, channels shorter than a group and ragged last
-groups."""
+Lattices of few nodes step in boxes instead, so the small shapes here cover
+those; shapes beyond the boxes' limits follow them.
+
+Of the narrow widths (1, 2, 4, ..., 64: a row in nx lanes, 64 / nx rows per
+wavefront), which step in boxes too, 32 and 64 beyond the boxes' limits take
+two steps per pass in their own kernel, which keeps whole row groups of step t
+in a ring; shapes cover every width, strips of a few groups and of one,
+channels shorter than a group and ragged last groups."""
 import numpy as np
 import pytest
 
