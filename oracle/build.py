@@ -1,7 +1,7 @@
 """Builds the C oracle into ``oracle/liblboracle.so`` with gcc.
 
 TEST INFRASTRUCTURE: the oracle is the independent reference of the test
-suite; building it is part of ``build()`` so the checker exists wherever the
+suite; building it is part of ``build()`` so that it exists wherever the
 library is built.
 """
 import os
